@@ -229,6 +229,105 @@ __global__ void __launch_bounds__(TPB) kv_copy_kernel(CacheGeom g, void* cache, 
     }
 }
 
+// The same copy for bf16 caches whose plain tensor is 16-byte aligned, one workgroup per (layer, kv head,
+// 32-position block).  Bound by memory: every byte is read and written once, in 16-byte lane accesses that
+// cover whole 128-byte lines on both sides.  Keys are a permutation of 16-byte units (8 dims of a position):
+// a wavefront takes 8 positions x 8 units, 128 contiguous bytes either way.  A unit of values holds 8
+// positions of one dim, so values are turned around in LDS.  Element by element (the kernel above) every
+// 2-byte access to the cache touched a line of its own: 699 MB read and written (7B-shape, 1333 positions) took
+// 1039 us in and 935 us out; by blocks 264 us each way (5.3 TB/s; a plain copy reaches 4.8-5.2).
+typedef unsigned int kv_unit __attribute__((ext_vector_type(4)));
+
+template <int HD, bool TO_CACHE>
+__global__ void __launch_bounds__(TPB) kv_block_kernel(CacheGeom g, uint16_t* cache, int slot, int pos0, int n_pos,
+                                                       uint16_t* plain, int blk0, int n_blk)
+{
+    constexpr int GROUPS = HD / 8, UNITS = 32 * GROUPS, PER = UNITS / TPB;   // 16-byte units of a part, per thread
+    constexpr int LD = HD + 8;                                               // LDS row, 16-byte aligned
+    __shared__ __align__(16) uint16_t rows[32 * LD];
+    const int head = blockIdx.x % g.n_kv_heads;
+    const int r = blockIdx.x / g.n_kv_heads;
+    const int blk = blk0 + r % n_blk, layer = r / n_blk;
+    const int base = blk * 32;
+    const int lo = max(pos0 - base, 0), hi = min(pos0 + n_pos - base, 32);   // positions of the block that are copied
+    uint16_t* kc = cache + cache_block_base(g, layer, slot, head, blk);
+    uint16_t* vc = kc + 32 * HD;
+    const ptrdiff_t row0 = (ptrdiff_t)base - pos0;                           // plain row of the block's position 0
+    uint16_t* kp = plain + (((ptrdiff_t)layer * 2 * g.n_kv_heads + head) * n_pos + row0) * HD;
+    uint16_t* vp = kp + (ptrdiff_t)g.n_kv_heads * n_pos * HD;
+    auto unit = [](uint16_t* p) { return reinterpret_cast<kv_unit*>(p); };
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+
+    kv_unit k[PER], v[PER];
+    int kt[PER], kd[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int q = i * 4 + wave;                     // 8 positions x 8 units
+        kt[i] = (q / (GROUPS / 8)) * 8 + (lane & 7);
+        kd[i] = (q % (GROUPS / 8)) * 8 + (lane >> 3);
+    }
+    auto k_cache = [&](int i) { return unit(kc + tiled_k_within(HD, kt[i], 8 * kd[i])); };
+    auto k_plain = [&](int i) { return unit(kp + (ptrdiff_t)kt[i] * HD + 8 * kd[i]); };
+    auto inside = [&](int t) { return t >= lo && t < hi; };
+    // values: thread u takes unit (position u / GROUPS, dims 8 * (u % GROUPS)) of the plain rows and unit
+    // u = 64 * dim tile + lane of the cache
+    auto v_row = [&](int i) { return (i * TPB + (int)threadIdx.x) / GROUPS; };
+    auto v_col = [&](int i) { return (i * TPB + (int)threadIdx.x) % GROUPS * 8; };
+    auto v_cache = [&](int i) { return unit(vc + (size_t)(i * TPB + threadIdx.x) * 8); };
+    auto v_dim = [&](int i) { return ((i * TPB + (int)threadIdx.x) >> 6) * 16 + (lane & 15); };
+    auto v_pos = [&](int e) { return e < 4 ? 4 * (lane >> 4) + e : 12 + 4 * (lane >> 4) + e; };
+
+    if constexpr (TO_CACHE) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (inside(v_row(i))) v[i] = __builtin_nontemporal_load(unit(vp + (ptrdiff_t)v_row(i) * HD + v_col(i)));
+            if (inside(kt[i])) k[i] = __builtin_nontemporal_load(k_plain(i));
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (inside(v_row(i))) *unit(rows + v_row(i) * LD + v_col(i)) = v[i];
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (inside(kt[i])) *k_cache(i) = k[i];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            uint16_t e8[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) e8[e] = rows[v_pos(e) * LD + v_dim(i)];
+            if (lo == 0 && hi == 32) {
+                kv_unit u;
+                __builtin_memcpy(&u, e8, 16);
+                *v_cache(i) = u;
+            } else {   // the block's other positions may hold entries: only these are written
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (inside(v_pos(e))) reinterpret_cast<uint16_t*>(v_cache(i))[e] = e8[e];
+            }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            v[i] = __builtin_nontemporal_load(v_cache(i));
+            k[i] = __builtin_nontemporal_load(k_cache(i));
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            uint16_t e8[8];
+            __builtin_memcpy(e8, &v[i], 16);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) rows[v_pos(e) * LD + v_dim(i)] = e8[e];
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (inside(kt[i])) *k_plain(i) = k[i];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (inside(v_row(i))) *unit(vp + (ptrdiff_t)v_row(i) * HD + v_col(i)) = *unit(rows + v_row(i) * LD + v_col(i));
+    }
+}
+
 unsigned blocks_for(size_t total)
 {
     size_t b = (total + TPB - 1) / TPB;
@@ -380,6 +479,28 @@ int launch_kv_compact(const CacheGeom& g, void* cache, const StepTables& t, int 
 int launch_kv_copy(const CacheGeom& g, void* cache, int slot, int pos0, int n_pos, void* plain, bool to_cache,
                    hipStream_t s)
 {
+    // Whole blocks at a time wherever 16-byte accesses are possible; a tensor at an odd address and fp32 caches
+    // go element by element.
+    if (g.dtype == SPEC_DTYPE_BF16 && (g.head_dim == 64 || g.head_dim == 128) && (((uintptr_t)plain | (uintptr_t)cache) & 15) == 0) {
+        const int blk0 = pos0 >> 5, n_blk = ((pos0 + n_pos - 1) >> 5) - blk0 + 1;
+        const size_t groups = (size_t)g.n_layers * n_blk * g.n_kv_heads;
+        if (groups <= 0x7fffffff) {
+            const dim3 grid((unsigned)groups);
+#define SPECV_KV_BLOCK(HD, IN)                                                                                    \
+    hipLaunchKernelGGL((kv_block_kernel<HD, IN>), grid, dim3(TPB), 0, s, g, (uint16_t*)cache, slot, pos0, n_pos, \
+                       (uint16_t*)plain, blk0, n_blk)
+            if (g.head_dim == 128) {
+                if (to_cache) SPECV_KV_BLOCK(128, true);
+                else SPECV_KV_BLOCK(128, false);
+            } else {
+                if (to_cache) SPECV_KV_BLOCK(64, true);
+                else SPECV_KV_BLOCK(64, false);
+            }
+#undef SPECV_KV_BLOCK
+            SPECV_LAUNCH_CHECK("kv_block_kernel");
+            return SPEC_OK;
+        }
+    }
     const size_t total = (size_t)g.n_layers * 2 * g.n_kv_heads * n_pos * g.head_dim;
     const dim3 grid(blocks_for(total));
     if (g.dtype == SPEC_DTYPE_BF16) {
