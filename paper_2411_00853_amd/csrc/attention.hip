@@ -103,13 +103,19 @@ __global__ void __launch_bounds__(64) attn_merge_kernel(StepTables t, LookaheadP
     store_x_unit(static_cast<uint4*>(xo.frags), xo.mt, xo.planes, m, unit, v);
 }
 
-// Plain fp32 attention for fp32 caches: one workgroup per (row, query head).
-__global__ void __launch_bounds__(256) attn_f32_kernel(StepTables t, CacheGeom g, int n_q_heads, int layer,
+// Plain fp32 attention for fp32 caches: one workgroup per (row, query head).  LP lanes share a position (four
+// dims each), so keys and values are read in contiguous runs, four positions per group in flight; at a
+// hundred or a thousand positions the launch is a few memory round trips.  (A thread per key, and one per dim walking
+// all values, took 9.8 us at 133 positions of 64 dims.)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__global__ void __launch_bounds__(256) attn_f32_kernel(StepTables t, CacheGeom g, int n_q_heads, int layer, int lp,
                                                        const float* __restrict__ cache, const float* __restrict__ q,
                                                        float scale, float* __restrict__ out)
 {
-    extern __shared__ float sh[];   // [hd] query, [n_keys] scores
+    extern __shared__ float4 dyn[];
     __shared__ float red[4];
+    float* osum = reinterpret_cast<float*>(dyn);   // [4][4 * lp] outputs of the wavefronts
+    float* sc = osum + 16 * lp;                    // [n_keys] scores
     const int m = blockIdx.x, hq = blockIdx.y;
     const int hd = g.head_dim;
     const int pos = t.row_pos[m];
@@ -125,18 +131,35 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(StepTables t, CacheGeom g
     const int hkv = hq / (n_q_heads / g.n_kv_heads);
     const float* kbase = cache + cache_head_base(g, layer, slot, hkv) + plain_offset(g, 0, 0, 0);
     const float* vbase = cache + cache_head_base(g, layer, slot, hkv) + plain_offset(g, 1, 0, 0);
-    float* qs = sh;
-    float* sc = sh + hd;
-    for (int i = threadIdx.x; i < hd; i += 256) qs[i] = q[((size_t)m * n_q_heads + hq) * hd + i];
-    __syncthreads();
+    const int sub = threadIdx.x & (lp - 1), grp = threadIdx.x / lp, n_grp = 256 / lp;   // lp: power of two, 4 * lp >= hd
+    const int d0 = 4 * sub;
+    // four dims of a row from d0 on; a head's last lanes may have fewer
+    auto load4 = [&](const float* row) -> float4 {
+        if (d0 + 4 <= hd) {
+            const f32x4u v = *reinterpret_cast<const f32x4u*>(row + d0);
+            return make_float4(v.x, v.y, v.z, v.w);
+        }
+        return make_float4(d0 < hd ? row[d0] : 0.f, d0 + 1 < hd ? row[d0 + 1] : 0.f, d0 + 2 < hd ? row[d0 + 2] : 0.f, 0.f);
+    };
+    const float4 qv = load4(q + ((size_t)m * n_q_heads + hq) * hd);
+    constexpr int U = 4;   // positions per group and trip, requested together (past the end: the last one again)
     float mx = -INFINITY;
-    for (int k = threadIdx.x; k < n_keys; k += 256) {
-        float a = 0.f;
-        for (int e = 0; e < hd; ++e) a = fmaf(qs[e], kbase[(size_t)k * hd + e], a);
-        a *= scale;
-        if (k >= n_cached && !((wmask >> (k - n_cached)) & 1u)) a = -INFINITY;   // window slot not on this row's path
-        sc[k] = a;
-        mx = fmaxf(mx, a);
+    for (int k0 = grp; k0 < n_keys; k0 += U * n_grp) {
+        float4 kv[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) kv[i] = load4(kbase + (size_t)min(k0 + i * n_grp, n_keys - 1) * hd);
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            float a = fmaf(qv.x, kv[i].x, fmaf(qv.y, kv[i].y, fmaf(qv.z, kv[i].z, qv.w * kv[i].w)));
+            for (int o = lp >> 1; o > 0; o >>= 1) a += __shfl_xor(a, o);
+            const int k = k0 + i * n_grp;
+            if (k < n_keys) {
+                a *= scale;
+                if (k >= n_cached && !((wmask >> (k - n_cached)) & 1u)) a = -INFINITY;   // window slot not on this row's path
+                if (sub == 0) sc[k] = a;
+                mx = fmaxf(mx, a);
+            }
+        }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
@@ -155,10 +178,37 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(StepTables t, CacheGeom g
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = z;
     __syncthreads();
     z = (red[0] + red[1]) + (red[2] + red[3]);
-    for (int e = threadIdx.x; e < hd; e += 256) {
-        float a = 0.f;
-        for (int k = 0; k < n_keys; ++k) a = fmaf(sc[k], vbase[(size_t)k * hd + e], a);
-        dst[e] = a / z;
+    float4 o4 = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int k0 = grp; k0 < n_keys; k0 += U * n_grp) {
+        float4 vv[U];
+        float p[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int k = k0 + i * n_grp;
+            vv[i] = load4(vbase + (size_t)min(k, n_keys - 1) * hd);
+            p[i] = k < n_keys ? sc[k] : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            // (a position that takes no part has weight zero; its value, which may be anything, is left out)
+            const bool on = p[i] != 0.f;
+            o4.x = on ? fmaf(p[i], vv[i].x, o4.x) : o4.x;
+            o4.y = on ? fmaf(p[i], vv[i].y, o4.y) : o4.y;
+            o4.z = on ? fmaf(p[i], vv[i].z, o4.z) : o4.z;
+            o4.w = on ? fmaf(p[i], vv[i].w, o4.w) : o4.w;
+        }
+    }
+    for (int o = lp; o < 64; o <<= 1) {
+        o4.x += __shfl_xor(o4.x, o);
+        o4.y += __shfl_xor(o4.y, o);
+        o4.z += __shfl_xor(o4.z, o);
+        o4.w += __shfl_xor(o4.w, o);
+    }
+    if ((threadIdx.x & 63) < lp) *reinterpret_cast<float4*>(osum + (threadIdx.x >> 6) * 4 * lp + d0) = o4;
+    __syncthreads();
+    if ((int)threadIdx.x < hd) {
+        const int e = threadIdx.x;
+        dst[e] = ((osum[e] + osum[4 * lp + e]) + (osum[8 * lp + e] + osum[12 * lp + e])) / z;
     }
 }
 
@@ -353,10 +403,12 @@ int launch_attention(int max_kv_len, int cu_count, const StepTables& t, const Lo
     const float scale = 1.0f / sqrtf((float)hd);
     if (g.dtype != SPEC_DTYPE_BF16) {
         // scores for one row live in LDS: positions * 4 bytes
-        const size_t lds = (size_t)(hd + g.t_pad) * sizeof(float);
-        if (lds > 60 * 1024) return fail(SPEC_ERR_SHAPE, "fp32 attention supports max_kv_len up to ~15000");
+        if ((size_t)(hd + g.t_pad) * sizeof(float) > 60 * 1024) return fail(SPEC_ERR_SHAPE, "fp32 attention supports max_kv_len up to ~15000");
         ProfScope ps(prof, SPEC_PROF_ATTENTION, s);
-        hipLaunchKernelGGL(attn_f32_kernel, dim3(M, n_q_heads), dim3(256), lds, s, t, g, n_q_heads, layer,
+        int lp = 1;   // lanes per position, four dims each
+        while (4 * lp < hd) lp *= 2;
+        const size_t lds = (size_t)(16 * lp + g.t_pad) * sizeof(float);
+        hipLaunchKernelGGL(attn_f32_kernel, dim3(M, n_q_heads), dim3(256), lds, s, t, g, n_q_heads, layer, lp,
                            (const float*)cache, q, scale, xo.plain);
         SPECV_LAUNCH_CHECK("attn_f32_kernel");
         return SPEC_OK;

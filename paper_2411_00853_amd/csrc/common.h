@@ -204,11 +204,8 @@ int launch_embed(int dtype, const void* tok_embed, const int32_t* row_tok, int M
 // x * gain written as the next GEMM's operand
 int launch_resid(const float* partial, int n_split, size_t split_stride, int ld, int M, int d, float* x, float* ssq,
                  const float* gain, const XOut& xo, hipStream_t s);
-// h = x * inv_rms * gain (only the fp32 path materialises normalised activations)
-int launch_rmsnorm_apply(const float* x, const float* ssq, const float* gain, float eps, int M, int d, float* h,
-                         hipStream_t s);
-int launch_silu_mul(const float* partial, int n_split, size_t split_stride, int ld, int M, int F, bool interleaved,
-                    const NormScale& ns, const XOut& xo, hipStream_t s);
+int launch_silu_mul(const float* partial, int n_split, size_t split_stride, int ld, int M, int F, const NormScale& ns,
+                    const XOut& xo, hipStream_t s);
 int launch_rope_append(const float* partial, int n_split, size_t split_stride, int ld, const StepTables& t, int M,
                        const CacheGeom& g, int n_q_heads, int layer, const float* cos_sin, const NormScale& ns,
                        void* cache, float* q_out, hipStream_t s);
@@ -253,7 +250,11 @@ void set_swiglu_min_wgs(int workgroups);
 void set_swiglu_column_groups(int groups);
 int launch_gemm_swiglu(const void* x_frags, int planes, const void* w_gate_up, int M, int F, int K, const float* ssq,
                        int n_ssq, int d, float eps, void* act_frags, int act_mt, int act_planes, int cu_count, hipStream_t s);
-int launch_gemm_f32(const float* x, const float* w, int M, int N, int K, float* y, hipStream_t s);
+// fp32: y = x * W^T (F32_STORE), y += x * W^T (F32_ADD), or y[m][n] = silu(gate) * up with W = N gate rows then N up
+// rows (F32_SWIGLU).  gain != NULL: x is normalised first (RMSNorm over its K columns, times gain).
+enum { F32_STORE = 0, F32_ADD = 1, F32_SWIGLU = 2 };
+int launch_gemm_f32(const float* x, const float* w, int M, int N, int K, float* y, hipStream_t s, int mode = F32_STORE,
+                    const float* gain = nullptr, float eps = 0.f);
 
 // The QKV projection's result as the attention kernel can take it directly (bf16 path): K-range
 // partial sums [n_split][M][ld] with columns q heads | k heads | v heads, the row scale of the

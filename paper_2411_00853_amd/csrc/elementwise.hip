@@ -11,32 +11,15 @@ namespace {
 
 constexpr int TPB = 256;
 
-__device__ __forceinline__ double block_sum(double v, double* sh)
+// Emit 8 consecutive values of a row as the next GEMM's operand: x * gain, as fragments (the fp32 path has none:
+// its GEMM takes the plain rows).
+__device__ __forceinline__ void emit_operand(const XOut& xo, int m, int k8, const float (&v)[8], const float* __restrict__ gain)
 {
+    if (!xo.frags) return;
+    float g[8];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    const double r = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-    __syncthreads();
-    return r;
-}
-
-// Emit 8 consecutive values of a row as the next GEMM's operand: x * gain, as fragments (bf16 path)
-// and/or plain fp32 (fp32 path, where the normalisation is applied separately).
-__device__ __forceinline__ void emit_operand(const XOut& xo, int m, int k8, int d, const float (&v)[8],
-                                             const float* __restrict__ gain)
-{
-    if (xo.frags) {
-        float g[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) g[e] = v[e] * (gain ? gain[k8 * 8 + e] : 1.f);
-        store_x_unit(static_cast<uint4*>(xo.frags), xo.mt, xo.planes, m, k8, g);
-    }
-    if (xo.plain) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) xo.plain[(size_t)m * d + k8 * 8 + e] = v[e];
-    }
+    for (int e = 0; e < 8; ++e) g[e] = v[e] * (gain ? gain[k8 * 8 + e] : 1.f);
+    store_x_unit(static_cast<uint4*>(xo.frags), xo.mt, xo.planes, m, k8, g);
 }
 
 constexpr int UNIT_TPB = SSQ_CHUNK / 8;   // one thread per 8 columns of a chunk
@@ -75,7 +58,7 @@ __global__ void __launch_bounds__(UNIT_TPB) resid_kernel(const T* __restrict__ E
         *reinterpret_cast<float4*>(xp + 4) = make_float4(v[4], v[5], v[6], v[7]);
 #pragma unroll
         for (int i = 0; i < 8; ++i) ss += (double)v[i] * v[i];
-        emit_operand(xo, m, k8, d, v, gain);
+        emit_operand(xo, m, k8, v, gain);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
@@ -84,30 +67,16 @@ __global__ void __launch_bounds__(UNIT_TPB) resid_kernel(const T* __restrict__ E
     if (threadIdx.x == 0) ssq[(size_t)m * gridDim.y + chunk] = (float)(sh[0] + sh[1]);
 }
 
-// h = x / sqrt(mean(x^2) + eps) * gain from the partial sums of squares
-__global__ void __launch_bounds__(TPB) rmsnorm_apply_kernel(const float* __restrict__ x, const float* __restrict__ ssq,
-                                                            int n_ssq, const float* __restrict__ gain, float eps, int d,
-                                                            float* __restrict__ h)
-{
-    const int m = blockIdx.x;
-    float ss = 0.f;
-    for (int i = 0; i < n_ssq; ++i) ss += ssq[(size_t)m * n_ssq + i];
-    const float inv = 1.0f / sqrtf(ss / (float)d + eps);
-    for (int i = threadIdx.x; i < d; i += TPB) h[(size_t)m * d + i] = x[(size_t)m * d + i] * inv * gain[i];
-}
-
 // act[m][f] = silu(gate) * up for 8 consecutive f per thread, gate and up first scaled by the row's
-// 1/rms (the FFN norm's scale, see NormScale).  Interleaved: the GEMM's columns come in 16-wide
-// tiles alternating gate and up (see spec_pack_weight); otherwise gate columns [0,F) then up
-// columns [F,2F).  The result goes out as the down projection's operand.  F is a multiple of 8.
+// 1/rms (the FFN norm's scale, see NormScale).  The GEMM's columns come in 16-wide tiles alternating gate
+// and up (see spec_pack_weight).  The result goes out as the down projection's operand.  F is a multiple of 8.
 __global__ void __launch_bounds__(TPB) silu_mul_kernel(const float* __restrict__ partial, int n_split, size_t split_stride,
-                                                       int ld, int M, int F, int interleaved, NormScale ns, XOut xo)
+                                                       int ld, int M, int F, NormScale ns, XOut xo)
 {
     const int units = F / 8;
     for (int i = blockIdx.x * TPB + threadIdx.x; i < M * units; i += gridDim.x * TPB) {
         const int m = i / units, k8 = i % units, f = k8 * 8;
-        const int cg = interleaved ? ((f >> 4) << 5) + (f & 15) : f;
-        const int cu = interleaved ? cg + 16 : F + f;
+        const int cg = ((f >> 4) << 5) + (f & 15), cu = cg + 16;
         const float r = row_inv_rms(ns.ssq, ns.n_ssq, m, ns.d, ns.eps);
         const float* pg = partial + (size_t)m * ld + cg;
         const float* pu = partial + (size_t)m * ld + cu;
@@ -123,7 +92,7 @@ __global__ void __launch_bounds__(TPB) silu_mul_kernel(const float* __restrict__
             const float ge = g[e] * r;
             v[e] = ge / (1.f + expf(-ge)) * (u[e] * r);
         }
-        emit_operand(xo, m, k8, F, v, nullptr);
+        emit_operand(xo, m, k8, v, nullptr);
     }
 }
 
@@ -384,20 +353,12 @@ int launch_resid(const float* partial, int n_split, size_t split_stride, int ld,
     return SPEC_OK;
 }
 
-int launch_rmsnorm_apply(const float* x, const float* ssq, const float* gain, float eps, int M, int d, float* h,
-                         hipStream_t s)
-{
-    hipLaunchKernelGGL(rmsnorm_apply_kernel, dim3(M), dim3(TPB), 0, s, x, ssq, ssq_chunks(d), gain, eps, d, h);
-    SPECV_LAUNCH_CHECK("rmsnorm_apply_kernel");
-    return SPEC_OK;
-}
-
-int launch_silu_mul(const float* partial, int n_split, size_t split_stride, int ld, int M, int F, bool interleaved,
-                    const NormScale& ns, const XOut& xo, hipStream_t s)
+int launch_silu_mul(const float* partial, int n_split, size_t split_stride, int ld, int M, int F, const NormScale& ns,
+                    const XOut& xo, hipStream_t s)
 {
     if (F % 8 || ld % 4 || split_stride % 4) return fail(SPEC_ERR_SHAPE, "d_ffn must be a multiple of 8");
     hipLaunchKernelGGL(silu_mul_kernel, dim3(blocks_for((size_t)M * F / 8)), dim3(TPB), 0, s, partial, n_split,
-                       split_stride, ld, M, F, interleaved ? 1 : 0, ns, xo);
+                       split_stride, ld, M, F, ns, xo);
     SPECV_LAUNCH_CHECK("silu_mul_kernel");
     return SPEC_OK;
 }

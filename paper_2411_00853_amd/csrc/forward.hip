@@ -47,7 +47,6 @@ int forward_init(spec_handle* h, int max_rows)
         if (rc == SPEC_OK) rc = a.alloc(reinterpret_cast<void**>(p), count * sizeof(float));
     };
     A(&h->x, (size_t)max_rows * z.d);
-    A(&h->hn, (size_t)max_rows * z.d);
     A(&h->ssq, (size_t)max_rows * ssq_chunks(z.d));
     A(&h->q, (size_t)max_rows * z.dq);
     A(&h->att, (size_t)max_rows * z.dq);
@@ -75,8 +74,7 @@ int forward_init(spec_handle* h, int max_rows)
         A(&h->attn_part_ml, po / c.head_dim * 2);
         h->attn_part_cap = po;
     } else {
-        // fp32 path: GEMM results are written whole; one buffer wide enough for any of them
-        part = (size_t)max_rows * (size_t)std::max(std::max(z.nqkv, 2 * z.F), z.d);
+        part = (size_t)max_rows * z.nqkv;   // fp32 path: the QKV result, written whole
     }
     A(&h->partial, part);
     h->partial_cap = part;
@@ -197,8 +195,8 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
 
     // bf16 path: every producer writes the next GEMM's operand as fragments of (value * gain); the
     // GEMM leaves K-range partial sums in h->partial, and its consumer adds them up and applies the
-    // row's 1/rms where the operand was a normalised residual.  fp32 path: plain rows, normalisation
-    // materialised, GEMM results whole.
+    // row's 1/rms where the operand was a normalised residual.  fp32 path (below): plain rows, GEMM
+    // results whole, the norms, the residual additions and SwiGLU inside the GEMMs.
     struct Out {
         int n_split;
         size_t stride;
@@ -207,61 +205,64 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
     const int n_ssq = ssq_chunks(z.d);
     const int mt = bf16 ? gemm_row_tiles(M) : 0;
     const int planes = h->split_act ? 2 : 1;
-    const XOut to_xf{bf16 ? h->xf : nullptr, mt, planes, nullptr};            // operand of QKV / gate-up / LM head
-    const XOut to_att{bf16 ? h->xf : nullptr, mt, planes, bf16 ? nullptr : h->att};
-    const XOut to_act{bf16 ? h->xf : nullptr, mt, planes, bf16 ? nullptr : h->act};
-    const NormScale scaled{bf16 ? h->ssq : nullptr, n_ssq, z.d, c.rms_eps};
-    const NormScale unscaled{nullptr, 0, 0, 0.f};
-    auto gemm = [&](int cls, const float* plain_in, const float* gain, const void* w, int N, int K, Out* o,
-                    const void* in_frags = nullptr) -> int {
-        if (bf16) {
-            const GemmPlan p = plan_gemm(M, N, K, h->cu_count, h->split_act);
-            // the plan follows process-wide tuning knobs; the buffer was sized with those in force at init
-            if (gemm_partial_elems(p, M) > h->partial_cap)
-                return fail(SPEC_ERR_SHAPE, "this step's GEMM plan (%d K ranges) needs %zu partial sums, the handle holds %zu: "
-                            "set the GEMM tuning knobs before spec_verify_init", p.n_split, gemm_partial_elems(p, M),
-                            h->partial_cap);
-            o->n_split = p.n_split;
-            o->ld = p.n_pad;
-            o->stride = (size_t)M * p.n_pad;
-            ProfScope ps_(&h->prof, cls, s);
-            return launch_gemm_bf16(p, in_frags ? in_frags : h->xf, w, M, N, K, h->partial, s);
-        }
-        o->n_split = 1;
-        o->ld = N;
-        o->stride = 0;
-        if (gain) {
-            ProfScope ps_(&h->prof, SPEC_PROF_GLUE, s);
-            int r = launch_rmsnorm_apply(plain_in, h->ssq, gain, c.rms_eps, M, z.d, h->hn, s);
-            if (r) return r;
-            plain_in = h->hn;
-        }
+    const XOut to_xf{bf16 ? h->xf : nullptr, mt, planes, nullptr};            // operand of the next GEMM
+    const NormScale scaled{h->ssq, n_ssq, z.d, c.rms_eps};
+    auto gemm = [&](int cls, const void* w, int N, int K, Out* o, const void* in_frags) -> int {
+        const GemmPlan p = plan_gemm(M, N, K, h->cu_count, h->split_act);
+        // the plan follows process-wide tuning knobs; the buffer was sized with those in force at init
+        if (gemm_partial_elems(p, M) > h->partial_cap)
+            return fail(SPEC_ERR_SHAPE, "this step's GEMM plan (%d K ranges) needs %zu partial sums, the handle holds %zu: "
+                        "set the GEMM tuning knobs before spec_verify_init", p.n_split, gemm_partial_elems(p, M),
+                        h->partial_cap);
+        o->n_split = p.n_split;
+        o->ld = p.n_pad;
+        o->stride = (size_t)M * p.n_pad;
         ProfScope ps_(&h->prof, cls, s);
-        return launch_gemm_f32(plain_in, (const float*)w, M, N, K, h->partial, s);
+        return launch_gemm_bf16(p, in_frags, w, M, N, K, h->partial, s);
     };
 
     RUN(SPEC_PROF_GLUE, launch_embed(c.dtype, h->tok_embed, t.row_tok, M, z.d, h->x, h->ssq, h->layers[0].attn_norm, to_xf, s));
+    if (!bf16) {
+        if (z.F % 8) return fail(SPEC_ERR_SHAPE, "d_ffn must be a multiple of 8");
+        auto mul = [&](int cls, const float* in, const void* w, int N, int K, float* out, int mode, const float* gain) -> int {
+            ProfScope ps_(&h->prof, cls, s);
+            return launch_gemm_f32(in, (const float*)w, M, N, K, out, s, mode, gain, c.rms_eps);
+        };
+        for (int l = 0; l < c.n_layers; ++l) {
+            const spec_layer_weights& w = h->layers[l];
+            if ((rc = mul(SPEC_PROF_GEMM_QKV, h->x, w.w_qkv, z.nqkv, z.d, h->partial, F32_STORE, w.attn_norm))) return rc;
+            RUN(SPEC_PROF_GLUE, launch_rope_append(h->partial, 1, 0, z.nqkv, t, M, h->geom, c.n_q_heads, l, h->cos_sin,
+                                                   NormScale{nullptr, 0, 0, 0.f}, h->kv_cache, h->q, s));
+            rc = launch_attention(c.max_kv_len, h->cu_count, t, ks, B, M, h->geom, c.n_q_heads, l, h->kv_cache, h->q, nullptr,
+                                  nullptr, 0, XOut{nullptr, 0, 0, h->att}, c.max_lookahead + 1, &h->prof, s);
+            if (rc) return rc;
+            if ((rc = mul(SPEC_PROF_GEMM_O, h->att, w.w_o, z.d, z.dq, h->x, F32_ADD, nullptr))) return rc;
+            if ((rc = mul(SPEC_PROF_GEMM_GATE_UP, h->x, w.w_gate_up, z.F, z.d, h->act, F32_SWIGLU, w.ffn_norm))) return rc;
+            if ((rc = mul(SPEC_PROF_GEMM_DOWN, h->act, w.w_down, z.d, z.F, h->x, F32_ADD, nullptr))) return rc;
+        }
+        return mul(SPEC_PROF_GEMM_LM_HEAD, h->x, h->lm_head, z.V, z.d, logits_out, F32_STORE, h->final_norm);
+    }
     Out o;
-    const bool swiglu_in_gemm = bf16 && gemm_swiglu_fits(M, z.F, h->cu_count);
+    const bool swiglu_in_gemm = gemm_swiglu_fits(M, z.F, h->cu_count);
     const bool fuse = h->fuse_rope && attention_takes_qkv(h->geom, c.n_q_heads, ks, B, c.max_kv_len, h->cu_count);
     for (int l = 0; l < c.n_layers; ++l) {
         const spec_layer_weights& w = h->layers[l];
-        rc = gemm(SPEC_PROF_GEMM_QKV, h->x, w.attn_norm, w.w_qkv, z.nqkv, z.d, &o);
+        rc = gemm(SPEC_PROF_GEMM_QKV, w.w_qkv, z.nqkv, z.d, &o, h->xf);
         if (rc) return rc;
         if (fuse) {
             // the attention kernel adds up, scales and rotates q, k, v itself and appends k, v
             const QkvSrc qkv{h->partial, o.n_split, o.stride, o.ld, scaled, h->cos_sin};
             rc = launch_attention(c.max_kv_len, h->cu_count, t, ks, B, M, h->geom, c.n_q_heads, l, h->kv_cache,
-                                  h->q, h->attn_part_o, h->attn_part_ml, h->attn_part_cap, to_att, c.max_lookahead + 1, &h->prof, s, &qkv,
+                                  h->q, h->attn_part_o, h->attn_part_ml, h->attn_part_cap, to_xf, c.max_lookahead + 1, &h->prof, s, &qkv,
                                   h->kv_cache);
         } else {
             RUN(SPEC_PROF_GLUE, launch_rope_append(h->partial, o.n_split, o.stride, o.ld, t, M, h->geom, c.n_q_heads, l,
                                                    h->cos_sin, scaled, h->kv_cache, h->q, s));
             rc = launch_attention(c.max_kv_len, h->cu_count, t, ks, B, M, h->geom, c.n_q_heads, l, h->kv_cache,
-                                  h->q, h->attn_part_o, h->attn_part_ml, h->attn_part_cap, to_att, c.max_lookahead + 1, &h->prof, s);
+                                  h->q, h->attn_part_o, h->attn_part_ml, h->attn_part_cap, to_xf, c.max_lookahead + 1, &h->prof, s);
         }
         if (rc) return rc;
-        rc = gemm(SPEC_PROF_GEMM_O, h->att, nullptr, w.w_o, z.d, z.dq, &o);
+        rc = gemm(SPEC_PROF_GEMM_O, w.w_o, z.d, z.dq, &o, h->xf);
         if (rc) return rc;
         RUN(SPEC_PROF_GLUE, launch_resid(h->partial, o.n_split, o.stride, o.ld, M, z.d, h->x, h->ssq, w.ffn_norm, to_xf, s));
         if (swiglu_in_gemm) {
@@ -269,27 +270,21 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
             // projection's operand (into the second fragment buffer: it is still reading the first)
             RUN(SPEC_PROF_GEMM_GATE_UP, launch_gemm_swiglu(h->xf, planes, w.w_gate_up, M, z.F, z.d, h->ssq, n_ssq, z.d, c.rms_eps,
                                                    h->xf_act, mt, planes, h->cu_count, s));
-            rc = gemm(SPEC_PROF_GEMM_DOWN, h->act, nullptr, w.w_down, z.d, z.F, &o, h->xf_act);
+            rc = gemm(SPEC_PROF_GEMM_DOWN, w.w_down, z.d, z.F, &o, h->xf_act);
         } else {
-            rc = gemm(SPEC_PROF_GEMM_GATE_UP, h->x, w.ffn_norm, w.w_gate_up, 2 * z.F, z.d, &o);
+            rc = gemm(SPEC_PROF_GEMM_GATE_UP, w.w_gate_up, 2 * z.F, z.d, &o, h->xf);
             if (rc) return rc;
-            RUN(SPEC_PROF_GLUE, launch_silu_mul(h->partial, o.n_split, o.stride, o.ld, M, z.F, bf16, scaled, to_act, s));
-            rc = gemm(SPEC_PROF_GEMM_DOWN, h->act, nullptr, w.w_down, z.d, z.F, &o);
+            RUN(SPEC_PROF_GLUE, launch_silu_mul(h->partial, o.n_split, o.stride, o.ld, M, z.F, scaled, to_xf, s));
+            rc = gemm(SPEC_PROF_GEMM_DOWN, w.w_down, z.d, z.F, &o, h->xf);
         }
         if (rc) return rc;
         const float* next_gain = (l + 1 < c.n_layers) ? h->layers[l + 1].attn_norm : h->final_norm;
         RUN(SPEC_PROF_GLUE, launch_resid(h->partial, o.n_split, o.stride, o.ld, M, z.d, h->x, h->ssq, next_gain, to_xf, s));
     }
-    if (bf16) {
-        rc = gemm(SPEC_PROF_GEMM_LM_HEAD, h->x, h->final_norm, h->lm_head, z.V, z.d, &o);
-        if (rc) return rc;
-        RUN(SPEC_PROF_GLUE, launch_reduce_splits(h->partial, o.n_split, o.stride, M, z.V, o.ld, h->ssq, n_ssq, z.d, c.rms_eps,
-                                 logits_out, s));
-    } else {
-        RUN(SPEC_PROF_GLUE, launch_rmsnorm_apply(h->x, h->ssq, h->final_norm, c.rms_eps, M, z.d, h->hn, s));
-        RUN(SPEC_PROF_GEMM_LM_HEAD, launch_gemm_f32(h->hn, (const float*)h->lm_head, M, z.V, z.d, logits_out, s));
-    }
-    (void)unscaled;
+    rc = gemm(SPEC_PROF_GEMM_LM_HEAD, h->lm_head, z.V, z.d, &o, h->xf);
+    if (rc) return rc;
+    RUN(SPEC_PROF_GLUE, launch_reduce_splits(h->partial, o.n_split, o.stride, M, z.V, o.ld, h->ssq, n_ssq, z.d, c.rms_eps,
+                                             logits_out, s));
 #undef RUN
     return SPEC_OK;
 }

@@ -42,7 +42,6 @@ struct spec_handle {
     bool split_act = true;     // feed activations to the matrix cores as bf16 head + remainder
     bool fuse_rope = true;     // bf16: rotary + KV append happen inside the attention kernel
     float* x = nullptr;        // [rows][d_model] residual stream
-    float* hn = nullptr;       // [rows][d_model] normalised activations (fp32 path only)
     void* xf = nullptr;        // operand fragments of the current GEMM's input (bf16 path)
     void* xf_act = nullptr;    // second fragment buffer: the down projection's operand when the gate/up GEMM writes it
     float* ssq = nullptr;      // [rows][ssq chunks] partial sums of squares of x
