@@ -184,8 +184,9 @@ CacheGeom make_cache_geom(const spec_model_cfg& c);
 // Row-wise sums of squares travel as SSQ_CHUNK-column partial sums ([M][n_ssq]).  RMSNorm is split
 // in two: the producer of a GEMM's input multiplies by the gain; the row's 1/rms factors out of the
 // dot product and is applied by the consumer of the GEMM's output (NormScale).
-constexpr int SSQ_CHUNK = 1024;
-inline int ssq_chunks(int d) { return (d + SSQ_CHUNK - 1) / SSQ_CHUNK; }
+// (A row has a multiple of four chunks, the last ones zero where need be: the consumer reads them 16 bytes at a time.)
+constexpr int SSQ_CHUNK = 512;
+inline int ssq_chunks(int d) { return ((d + SSQ_CHUNK - 1) / SSQ_CHUNK + 3) / 4 * 4; }
 struct NormScale {
     const float* ssq;   // NULL: no scaling
     int n_ssq;

@@ -22,20 +22,19 @@ __device__ __forceinline__ void emit_operand(const XOut& xo, int m, int k8, cons
     store_x_unit(static_cast<uint4*>(xo.frags), xo.mt, xo.planes, m, k8, g);
 }
 
-constexpr int UNIT_TPB = SSQ_CHUNK / 8;   // one thread per 8 columns of a chunk
-
-// One workgroup per (row, SSQ_CHUNK columns): x = E[token] (or x += partial sums); ssq[m][chunk] =
-// sum x^2 over the chunk; x * gain goes out as the next GEMM's operand.  d is a multiple of 8.
+// One wavefront per (row, SSQ_CHUNK columns), 8 columns per lane: x = E[token] (or x += partial sums);
+// ssq[m][chunk] = sum x^2 over the chunk; x * gain goes out as the next GEMM's operand.  d is a multiple of 8.
+// Latency up to a hundred rows, then the partial sums and the fragment stores (16 bytes into a line each); single
+// wavefronts spread best over the chip: 352 rows of 4096 with eight ranges 12.1 us as workgroups of two, 10.1
+// as single ones; a wavefront per 16 rows x 32 columns, whose stores are contiguous, 10.9 (and slower at 48 rows).
 template <typename T, bool EMBED>
-__global__ void __launch_bounds__(UNIT_TPB) resid_kernel(const T* __restrict__ E, const int32_t* __restrict__ row_tok,
+__global__ void __launch_bounds__(64) resid_kernel(const T* __restrict__ E, const int32_t* __restrict__ row_tok,
                                                          const float* __restrict__ partial, int n_split,
                                                          size_t split_stride, int ld, int d, float* __restrict__ x,
                                                          float* __restrict__ ssq, const float* __restrict__ gain,
                                                          XOut xo)
 {
-    __shared__ double sh[2];
-    const int m = blockIdx.x, chunk = blockIdx.y;
-    const int k8 = chunk * UNIT_TPB + threadIdx.x;
+    const int m = blockIdx.y, k8 = blockIdx.x * 64 + threadIdx.x;
     double ss = 0.0;
     if (k8 * 8 < d) {
         float v[8];
@@ -49,7 +48,7 @@ __global__ void __launch_bounds__(UNIT_TPB) resid_kernel(const T* __restrict__ E
             const float* pp = partial + (size_t)m * ld + k8 * 8;
             const float* cols[2] = {pp, pp + 4};
             float4 sums[2];
-            sum_splits4_many<2, 8>(cols, n_split, split_stride, sums);   // up to 8 ranges in one round trip
+            sum_ranges(cols, n_split, split_stride, sums);   // up to 8 ranges in one round trip
             const float4 pa = sums[0], pb = sums[1];
             v[0] = a.x + pa.x; v[1] = a.y + pa.y; v[2] = a.z + pa.z; v[3] = a.w + pa.w;
             v[4] = b.x + pb.x; v[5] = b.y + pb.y; v[6] = b.z + pb.z; v[7] = b.w + pb.w;
@@ -62,48 +61,118 @@ __global__ void __launch_bounds__(UNIT_TPB) resid_kernel(const T* __restrict__ E
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = ss;
-    __syncthreads();
-    if (threadIdx.x == 0) ssq[(size_t)m * gridDim.y + chunk] = (float)(sh[0] + sh[1]);
+    if (threadIdx.x == 0) ssq[(size_t)m * gridDim.x + blockIdx.x] = (float)ss;
 }
 
 // act[m][f] = silu(gate) * up for 8 consecutive f per thread, gate and up first scaled by the row's
 // 1/rms (the FFN norm's scale, see NormScale).  The GEMM's columns come in 16-wide tiles alternating gate
 // and up (see spec_pack_weight).  The result goes out as the down projection's operand.  F is a multiple of 8.
+// A wavefront covers 16 rows x 32 columns, lane 16 * g + r the 8 columns from 8 * g on of row r: what it stores is
+// one contiguous 1 KiB of the fragment buffer per plane, while its rows are still read in 128-byte runs.  Along a
+// row every 16-byte store opened a line of its own, and those stores were most of the time (352 x 11008, one
+// range: 18.6 us, 7.5 without them; this way 12.1 in the step, 20.4 before).
 __global__ void __launch_bounds__(TPB) silu_mul_kernel(const float* __restrict__ partial, int n_split, size_t split_stride,
                                                        int ld, int M, int F, NormScale ns, XOut xo)
 {
-    const int units = F / 8;
-    for (int i = blockIdx.x * TPB + threadIdx.x; i < M * units; i += gridDim.x * TPB) {
-        const int m = i / units, k8 = i % units, f = k8 * 8;
-        const int cg = ((f >> 4) << 5) + (f & 15), cu = cg + 16;
-        const float r = row_inv_rms(ns.ssq, ns.n_ssq, m, ns.d, ns.eps);
-        const float* pg = partial + (size_t)m * ld + cg;
-        const float* pu = partial + (size_t)m * ld + cu;
-        const float* cols[4] = {pg, pg + 4, pu, pu + 4};
-        float4 sums[4];
-        sum_splits4_many(cols, n_split, split_stride, sums);   // one memory round trip for all four
-        const float4 g0 = sums[0], g1 = sums[1], u0 = sums[2], u1 = sums[3];
-        const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-        const float u[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
-        float v[8];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int m = blockIdx.y * 16 + (lane & 15);
+    const int k8 = (blockIdx.x * (TPB / 64) + wave) * 4 + (lane >> 4), f = k8 * 8;
+    if (m >= M || f >= F) return;
+    const float* pg = partial + (size_t)m * ld + ((f >> 4) << 5) + (f & 15);
+    const float* cols[4] = {pg, pg + 4, pg + 16, pg + 20};
+    float4 sums[4];
+    const float r = row_inv_rms(ns.ssq, ns.n_ssq, m, ns.d, ns.eps);
+    sum_ranges(cols, n_split, split_stride, sums);   // one memory round trip for all four
+    const float4 g0 = sums[0], g1 = sums[1], u0 = sums[2], u1 = sums[3];
+    const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+    const float u[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float ge = g[e] * r;
+        v[e] = ge / (1.f + expf(-ge)) * (u[e] * r);
+    }
+    emit_operand(xo, m, k8, v, nullptr);
+}
+
+// Sum the partial ranges, rotate q and k heads at the row's absolute position (pairs (i, i+hd/2), angle from the
+// table), write q, and put k and v -- rounded to the cache's storage type -- into the row's slot at that position.
+// bf16 caches: a thread takes eight rotary pairs of a q or k head, or sixteen dims of a v head; a wavefront 16 rows x 4
+// such units, so that neighbouring positions of a window, which are neighbours in the cache's tiles, are stored
+// together (keys 16 bytes each in runs, values 2 bytes each).  A lane per dim along a row took 23 us for 352 rows
+// of 96 128-dim heads, most of it the stores; this way 18.
+__global__ void __launch_bounds__(TPB) rope_append_tiled_kernel(const float* __restrict__ partial, int n_split,
+                                                                size_t split_stride, int ld, StepTables t, CacheGeom g,
+                                                                int n_q_heads, int M, int layer, const float* __restrict__ cos_sin,
+                                                                NormScale ns, uint16_t* cache, float* __restrict__ q_out)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int m = blockIdx.y * 16 + (lane & 15);
+    const int hd = g.head_dim, half = hd >> 1, per = hd >> 4;       // units per head (a power of two)
+    const int unit = (blockIdx.x * (TPB / 64) + wave) * 4 + (lane >> 4);
+    const int head = unit / per, u = unit % per;
+    if (m >= M || head >= n_q_heads + 2 * g.n_kv_heads) return;
+    const int pos = t.row_pos[m];
+    const int rope_pos = t.tree ? t.row_rope[m] : max(pos, 0);
+    const int slot = t.seq_slot[t.row_seq[m]];
+    const bool is_v = head >= n_q_heads + g.n_kv_heads;
+    const float* row = partial + (size_t)m * ld + head * hd;
+    const float* lo = is_v ? row + 16 * u : row + 8 * u;
+    const float* hi = is_v ? lo + 8 : lo + half;
+    const float* cols[4] = {lo, lo + 4, hi, hi + 4};
+    const float rs = row_inv_rms(ns.ssq, ns.n_ssq, m, ns.d, ns.eps);   // the attention norm's row scale
+    float4 sums[4];
+    sum_ranges(cols, n_split, split_stride, sums);
+    const float a[8] = {sums[0].x * rs, sums[0].y * rs, sums[0].z * rs, sums[0].w * rs,
+                        sums[1].x * rs, sums[1].y * rs, sums[1].z * rs, sums[1].w * rs};
+    const float b[8] = {sums[2].x * rs, sums[2].y * rs, sums[2].z * rs, sums[2].w * rs,
+                        sums[3].x * rs, sums[3].y * rs, sums[3].z * rs, sums[3].w * rs};
+    auto bits = [](float v) { return __builtin_bit_cast(uint16_t, static_cast<__bf16>(v)); };
+    if (is_v) {
+        if (pos < 0) return;   // row of a skipped sequence: no cache write
+        uint16_t* c = cache + cache_block_base(g, layer, slot, head - n_q_heads - g.n_kv_heads, pos >> 5);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float ge = g[e] * r;
-            v[e] = ge / (1.f + expf(-ge)) * (u[e] * r);
+            c[tiled_v_within(hd, pos & 31, 16 * u + e)] = bits(a[e]);
+            c[tiled_v_within(hd, pos & 31, 16 * u + 8 + e)] = bits(b[e]);
         }
-        emit_operand(xo, m, k8, v, nullptr);
+        return;
+    }
+    const float* cs = cos_sin + (size_t)rope_pos * hd + 16 * u;   // [half][2]; depth in the window, not the slot
+    float ra[8], rb[8];
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        const float4 c2 = *reinterpret_cast<const float4*>(cs + 2 * e);   // cos, sin of two dims
+        ra[e] = a[e] * c2.x - b[e] * c2.y;
+        rb[e] = a[e] * c2.y + b[e] * c2.x;
+        ra[e + 1] = a[e + 1] * c2.z - b[e + 1] * c2.w;
+        rb[e + 1] = a[e + 1] * c2.w + b[e + 1] * c2.z;
+    }
+    if (head < n_q_heads) {
+        const bool live = pos >= 0;   // row of a skipped sequence: defined output
+        float* q = q_out + (size_t)m * n_q_heads * hd + head * hd + 8 * u;
+#pragma unroll
+        for (int e = 0; e < 8; e += 4) {
+            *reinterpret_cast<float4*>(q + e) = live ? make_float4(ra[e], ra[e + 1], ra[e + 2], ra[e + 3]) : make_float4(0.f, 0.f, 0.f, 0.f);
+            *reinterpret_cast<float4*>(q + half + e) = live ? make_float4(rb[e], rb[e + 1], rb[e + 2], rb[e + 3]) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    } else if (pos >= 0) {
+        uint16_t* c = cache + cache_block_base(g, layer, slot, head - n_q_heads, pos >> 5);
+        Frag ka, kb;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            ka.h[e] = bits(ra[e]);
+            kb.h[e] = bits(rb[e]);
+        }
+        *reinterpret_cast<uint4*>(c + tiled_k_within(hd, pos & 31, 8 * u)) = ka.u;
+        *reinterpret_cast<uint4*>(c + tiled_k_within(hd, pos & 31, 8 * u + half)) = kb.u;
     }
 }
 
-// One 64-lane workgroup per (row, head of the q|k|v projection): sum the partial ranges, rotate
-// q and k heads at the row's absolute position (pairs (i, i+hd/2), angle from the table), write q,
-// and put k and v -- rounded to the cache's storage type -- into the row's slot at that position.
-template <bool BF16>
-__global__ void __launch_bounds__(64) rope_append_kernel(const float* __restrict__ partial, int n_split,
-                                                         size_t split_stride, int ld, StepTables t, CacheGeom g,
+// The same for fp32 caches, any even head size: one 64-lane workgroup per (row, head of the q|k|v projection).
+__global__ void __launch_bounds__(64) rope_append_kernel(const float* __restrict__ partial, int ld, StepTables t, CacheGeom g,
                                                          int n_q_heads, int layer, const float* __restrict__ cos_sin,
-                                                         NormScale ns, void* cache, float* __restrict__ q_out)
+                                                         float* cache, float* __restrict__ q_out)
 {
     const int m = blockIdx.x, head = blockIdx.y;
     const int pos = t.row_pos[m];
@@ -117,53 +186,47 @@ __global__ void __launch_bounds__(64) rope_append_kernel(const float* __restrict
         return;
     }
     const int slot = t.seq_slot[t.row_seq[m]];
-    const float rs = row_inv_rms(ns.ssq, ns.n_ssq, m, ns.d, ns.eps);   // the attention norm's row scale
     if (head < n_q_heads + g.n_kv_heads) {
         const float* cs = cos_sin + (size_t)rope_pos * hd;   // [half][2]; depth in the window, not the slot
         for (int i = threadIdx.x; i < half; i += 64) {
-            const float a = sum_splits(row + i, n_split, split_stride) * rs;
-            const float b = sum_splits(row + i + half, n_split, split_stride) * rs;
+            const float a = row[i], b = row[i + half];
             const float c = cs[2 * i], s = cs[2 * i + 1];
             const float ra = a * c - b * s, rb = a * s + b * c;
             if (head < n_q_heads) {
                 q_out[(size_t)m * dq + head * hd + i] = ra;
                 q_out[(size_t)m * dq + head * hd + i + half] = rb;
             } else {
-                if constexpr (BF16) {
-                    __bf16* c16 = static_cast<__bf16*>(cache);
-                    const size_t blk = cache_block_base(g, layer, slot, head - n_q_heads, pos >> 5);
-                    c16[blk + tiled_k_within(hd, pos & 31, i)] = static_cast<__bf16>(ra);
-                    c16[blk + tiled_k_within(hd, pos & 31, i + half)] = static_cast<__bf16>(rb);
-                } else {
-                    const size_t base = cache_head_base(g, layer, slot, head - n_q_heads);
-                    float* c32 = static_cast<float*>(cache);
-                    c32[base + plain_offset(g, 0, pos, i)] = ra;
-                    c32[base + plain_offset(g, 0, pos, i + half)] = rb;
-                }
+                const size_t base = cache_head_base(g, layer, slot, head - n_q_heads);
+                cache[base + plain_offset(g, 0, pos, i)] = ra;
+                cache[base + plain_offset(g, 0, pos, i + half)] = rb;
             }
         }
     } else {
-        const int hv = head - n_q_heads - g.n_kv_heads;
-        const size_t base = BF16 ? cache_block_base(g, layer, slot, hv, pos >> 5) : cache_head_base(g, layer, slot, hv);
-        for (int i = threadIdx.x; i < hd; i += 64) {
-            const float v = sum_splits(row + i, n_split, split_stride) * rs;
-            if constexpr (BF16)
-                static_cast<__bf16*>(cache)[base + tiled_v_within(hd, pos & 31, i)] = static_cast<__bf16>(v);
-            else
-                static_cast<float*>(cache)[base + plain_offset(g, 1, pos, i)] = v;
-        }
+        const size_t base = cache_head_base(g, layer, slot, head - n_q_heads - g.n_kv_heads);
+        for (int i = threadIdx.x; i < hd; i += 64) cache[base + plain_offset(g, 1, pos, i)] = row[i];
     }
 }
 
+// out[m][n] = sum of the ranges * the row's 1/rms; four columns per thread (rows of out start at any 4-byte address)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 __global__ void __launch_bounds__(TPB) reduce_splits_kernel(const float* __restrict__ partial, int n_split,
-                                                            size_t split_stride, int M, int N, int ld, NormScale ns,
+                                                            size_t split_stride, int N, int ld, NormScale ns,
                                                             float* __restrict__ out)
 {
-    const size_t total = (size_t)M * N;
-    for (size_t i = (size_t)blockIdx.x * TPB + threadIdx.x; i < total; i += (size_t)gridDim.x * TPB) {
-        const int m = (int)(i / N), n = (int)(i % N);
-        out[i] = sum_splits(partial + (size_t)m * ld + n, n_split, split_stride)
-                 * row_inv_rms(ns.ssq, ns.n_ssq, m, ns.d, ns.eps);
+    const int m = blockIdx.y, n = (blockIdx.x * TPB + threadIdx.x) * 4;
+    if (n >= N) return;
+    const float* cols[1] = {partial + (size_t)m * ld + n};   // ld is a multiple of 16: the last columns are there to read
+    const float r = row_inv_rms(ns.ssq, ns.n_ssq, m, ns.d, ns.eps);
+    float4 v[1];
+    sum_ranges(cols, n_split, split_stride, v);
+    float* o = out + (size_t)m * N + n;
+    if (n + 4 <= N) {
+        *reinterpret_cast<f32x4u*>(o) = f32x4u{v[0].x * r, v[0].y * r, v[0].z * r, v[0].w * r};
+    } else {
+        const float t[4] = {v[0].x, v[0].y, v[0].z, v[0].w};
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (n + e < N) o[e] = t[e] * r;
     }
 }
 
@@ -331,12 +394,12 @@ int launch_embed(int dtype, const void* tok_embed, const int32_t* row_tok, int M
                  const float* gain, const XOut& xo, hipStream_t s)
 {
     if (d % 8) return fail(SPEC_ERR_SHAPE, "d_model must be a multiple of 8");
-    const dim3 grid(M, ssq_chunks(d));
+    const dim3 grid(ssq_chunks(d), M);
     if (dtype == SPEC_DTYPE_BF16)
-        hipLaunchKernelGGL((resid_kernel<__bf16, true>), grid, dim3(UNIT_TPB), 0, s, (const __bf16*)tok_embed, row_tok,
+        hipLaunchKernelGGL((resid_kernel<__bf16, true>), grid, dim3(64), 0, s, (const __bf16*)tok_embed, row_tok,
                            nullptr, 0, 0, 0, d, x, ssq, gain, xo);
     else
-        hipLaunchKernelGGL((resid_kernel<float, true>), grid, dim3(UNIT_TPB), 0, s, (const float*)tok_embed, row_tok,
+        hipLaunchKernelGGL((resid_kernel<float, true>), grid, dim3(64), 0, s, (const float*)tok_embed, row_tok,
                            nullptr, 0, 0, 0, d, x, ssq, gain, xo);
     SPECV_LAUNCH_CHECK("resid_kernel<embed>");
     return SPEC_OK;
@@ -346,8 +409,8 @@ int launch_resid(const float* partial, int n_split, size_t split_stride, int ld,
                  const float* gain, const XOut& xo, hipStream_t s)
 {
     if (d % 8 || ld % 4 || split_stride % 4) return fail(SPEC_ERR_SHAPE, "residual rows must be multiples of 8 wide");
-    const dim3 grid(M, ssq_chunks(d));
-    hipLaunchKernelGGL((resid_kernel<float, false>), grid, dim3(UNIT_TPB), 0, s, nullptr, nullptr, partial, n_split,
+    const dim3 grid(ssq_chunks(d), M);
+    hipLaunchKernelGGL((resid_kernel<float, false>), grid, dim3(64), 0, s, nullptr, nullptr, partial, n_split,
                        split_stride, ld, d, x, ssq, gain, xo);
     SPECV_LAUNCH_CHECK("resid_kernel");
     return SPEC_OK;
@@ -357,7 +420,8 @@ int launch_silu_mul(const float* partial, int n_split, size_t split_stride, int 
                     const XOut& xo, hipStream_t s)
 {
     if (F % 8 || ld % 4 || split_stride % 4) return fail(SPEC_ERR_SHAPE, "d_ffn must be a multiple of 8");
-    hipLaunchKernelGGL(silu_mul_kernel, dim3(blocks_for((size_t)M * F / 8)), dim3(TPB), 0, s, partial, n_split,
+    const int cols = 32 * (TPB / 64);   // per workgroup
+    hipLaunchKernelGGL(silu_mul_kernel, dim3((F + cols - 1) / cols, (M + 15) / 16), dim3(TPB), 0, s, partial, n_split,
                        split_stride, ld, M, F, ns, xo);
     SPECV_LAUNCH_CHECK("silu_mul_kernel");
     return SPEC_OK;
@@ -367,13 +431,16 @@ int launch_rope_append(const float* partial, int n_split, size_t split_stride, i
                        const CacheGeom& g, int n_q_heads, int layer, const float* cos_sin, const NormScale& ns,
                        void* cache, float* q_out, hipStream_t s)
 {
-    const dim3 grid(M, n_q_heads + 2 * g.n_kv_heads);
-    if (g.dtype == SPEC_DTYPE_BF16)
-        hipLaunchKernelGGL(rope_append_kernel<true>, grid, dim3(64), 0, s, partial, n_split, split_stride, ld, t, g,
-                           n_q_heads, layer, cos_sin, ns, cache, q_out);
-    else
-        hipLaunchKernelGGL(rope_append_kernel<false>, grid, dim3(64), 0, s, partial, n_split, split_stride, ld, t, g,
-                           n_q_heads, layer, cos_sin, ns, cache, q_out);
+    const int heads = n_q_heads + 2 * g.n_kv_heads;
+    if (g.dtype == SPEC_DTYPE_BF16) {
+        if (ld % 4 || split_stride % 4) return fail(SPEC_ERR_SHAPE, "QKV rows must be multiples of 4 wide");
+        const int per_wg = 4 * (TPB / 64);   // units of 16 values
+        hipLaunchKernelGGL(rope_append_tiled_kernel, dim3((heads * (g.head_dim / 16) + per_wg - 1) / per_wg, (M + 15) / 16), dim3(TPB), 0, s,
+                           partial, n_split, split_stride, ld, t, g, n_q_heads, M, layer, cos_sin, ns, (uint16_t*)cache, q_out);
+    } else {
+        hipLaunchKernelGGL(rope_append_kernel, dim3(M, heads), dim3(64), 0, s, partial, ld, t, g, n_q_heads, layer, cos_sin,
+                           (float*)cache, q_out);
+    }
     SPECV_LAUNCH_CHECK("rope_append_kernel");
     return SPEC_OK;
 }
@@ -382,8 +449,9 @@ int launch_reduce_splits(const float* partial, int n_split, size_t split_stride,
                          const float* ssq, int n_ssq, int d, float eps, float* out, hipStream_t s)
 {
     NormScale ns{ssq, n_ssq, d, eps};
-    hipLaunchKernelGGL(reduce_splits_kernel, dim3(blocks_for((size_t)M * N)), dim3(TPB), 0, s, partial, n_split,
-                       split_stride, M, N, ld, ns, out);
+    if (ld % 4 || split_stride % 4) return fail(SPEC_ERR_SHAPE, "partial sums must come in rows of multiples of 4");
+    hipLaunchKernelGGL(reduce_splits_kernel, dim3((N + 4 * TPB - 1) / (4 * TPB), M), dim3(TPB), 0, s, partial, n_split,
+                       split_stride, N, ld, ns, out);
     SPECV_LAUNCH_CHECK("reduce_splits_kernel");
     return SPEC_OK;
 }

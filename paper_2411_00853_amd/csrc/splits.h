@@ -6,59 +6,10 @@
 
 namespace specv {
 
-// Sum of the K ranges' partial sums at p, ranges in index order.  The loads of a batch of ranges
-// are issued together (indices past the end clamped, values dropped) so the memory latency is paid
-// once per batch; the batch is 2, 4 or 8 wide depending on the (uniform) number of ranges.
-template <int W>
-__device__ __forceinline__ float4 sum_splits4_w(const float* p, int n_split, size_t stride)
-{
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s0 = 0; s0 < n_split; s0 += W) {
-        float4 a[W];
-#pragma unroll
-        for (int i = 0; i < W; ++i) a[i] = *reinterpret_cast<const float4*>(p + (size_t)min(s0 + i, n_split - 1) * stride);
-#pragma unroll
-        for (int i = 0; i < W; ++i) {
-            const bool ok = s0 + i < n_split;
-            v.x += ok ? a[i].x : 0.f; v.y += ok ? a[i].y : 0.f; v.z += ok ? a[i].z : 0.f; v.w += ok ? a[i].w : 0.f;
-        }
-    }
-    return v;
-}
-
-__device__ __forceinline__ float4 sum_splits4(const float* p, int n_split, size_t stride)
-{
-    if (n_split == 1) return *reinterpret_cast<const float4*>(p);
-    if (n_split <= 2) return sum_splits4_w<2>(p, n_split, stride);
-    if (n_split <= 4) return sum_splits4_w<4>(p, n_split, stride);
-    return sum_splits4_w<8>(p, n_split, stride);
-}
-
-template <int W>
-__device__ __forceinline__ float sum_splits_w(const float* p, int n_split, size_t stride)
-{
-    float v = 0.f;
-    for (int s0 = 0; s0 < n_split; s0 += W) {
-        float a[W];
-#pragma unroll
-        for (int i = 0; i < W; ++i) a[i] = p[(size_t)min(s0 + i, n_split - 1) * stride];
-#pragma unroll
-        for (int i = 0; i < W; ++i) v += (s0 + i < n_split) ? a[i] : 0.f;
-    }
-    return v;
-}
-
-__device__ __forceinline__ float sum_splits(const float* p, int n_split, size_t stride)
-{
-    if (n_split == 1) return p[0];
-    if (n_split <= 2) return sum_splits_w<2>(p, n_split, stride);
-    if (n_split <= 4) return sum_splits_w<4>(p, n_split, stride);
-    return sum_splits_w<8>(p, n_split, stride);
-}
-
-// Many sums at once: N float4 columns of one row, all loads of a batch of (up to) W ranges issued
-// before the first addition (calling sum_splits4 N times makes N dependent round trips: the
-// compiler keeps each call's loads next to its additions).  Ranges are added in index order.
+// N float4 columns of one row, all loads of a batch of (up to) W ranges issued before the first addition
+// (indices past the end clamped, values dropped), so that the memory latency is paid once per batch: summing
+// the columns one after the other makes N dependent round trips (the compiler keeps each sum's loads next
+// to its additions).  Ranges are added in index order.
 template <int N, int W = 4>
 __device__ __forceinline__ void sum_splits4_many(const float* const (&p)[N], int n_split, size_t stride, float4 (&out)[N])
 {
@@ -79,6 +30,38 @@ __device__ __forceinline__ void sum_splits4_many(const float* const (&p)[N], int
                 out[x].x += ok ? a[x][i].x : 0.f; out[x].y += ok ? a[x][i].y : 0.f;
                 out[x].z += ok ? a[x][i].z : 0.f; out[x].w += ok ? a[x][i].w : 0.f;
             }
+    }
+}
+
+// The same with as many loads as there are ranges (1, 2, 4 or 8; more come in batches of 8): the clamped
+// loads above cost the kernels that run over many rows more than the bytes they need.
+template <int S, int N>
+__device__ __forceinline__ void sum_exact(const float* const (&p)[N], size_t stride, float4 (&out)[N])
+{
+    float4 a[N][S];
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+#pragma unroll
+        for (int x = 0; x < N; ++x) a[x][i] = *reinterpret_cast<const float4*>(p[x] + i * stride);
+#pragma unroll
+    for (int x = 0; x < N; ++x) {
+        out[x] = a[x][0];
+#pragma unroll
+        for (int i = 1; i < S; ++i) {
+            out[x].x += a[x][i].x; out[x].y += a[x][i].y; out[x].z += a[x][i].z; out[x].w += a[x][i].w;
+        }
+    }
+}
+
+template <int N>
+__device__ __forceinline__ void sum_ranges(const float* const (&p)[N], int n_split, size_t stride, float4 (&out)[N])
+{
+    switch (n_split) {
+    case 1: sum_exact<1>(p, stride, out); break;
+    case 2: sum_exact<2>(p, stride, out); break;
+    case 4: sum_exact<4>(p, stride, out); break;
+    case 8: sum_exact<8>(p, stride, out); break;
+    default: sum_splits4_many<N, 8>(p, n_split, stride, out); break;
     }
 }
 
