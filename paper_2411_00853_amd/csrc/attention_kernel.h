@@ -36,9 +36,13 @@ __device__ __forceinline__ int seq_chunk_keys(int total, int max_chunks)
 // of a prefetch never waits for memory.
 // FUSED: the kernel takes the QKV projection's partial sums instead of finished queries: every
 // wavefront adds up, scales and rotates the queries it needs, and the wavefront whose chunk holds
-// window positions does the same for the window's keys and values of its kv head, stores them in
-// the cache (for later steps) and only then starts to stream -- so no separate rotary/append kernel
-// runs between the projection and the attention.
+// window positions does the same for the window's keys and values of its kv head and stores them in
+// the cache (for later steps) -- so no separate rotary/append kernel runs between the projection and the
+// attention.  It attends to them from a copy in LDS that patches the blocks they belong to, so nothing waits for
+// those stores, and the requests for the queries and for the window go out in one stretch, before the first of either
+// is used.  (Waiting for the stores, fetching the block again and walking the two parts one after the other was
+// slower: 33.8 against 31.7 us per launch for a draft model of 16 kv heads at batch 8, 237.5 against 232.8 with 32
+// ragged sequences on the page pool, 52.4 against 51.4 at the 7B-shape, batch 8.)
 // CW > 0: one workgroup of CW wavefronts per (sequence, kv head), wavefront c taking chunk c; the
 // chunk results meet in LDS and the workgroup itself writes the merged, normalised output as the
 // output projection's operand fragments (same arithmetic and order as attn_merge_kernel): no second
@@ -51,27 +55,28 @@ __device__ __forceinline__ int seq_chunk_keys(int total, int max_chunks)
 // from the memory-side cache, and streaming loads cost the 1B-shape step 5 % of its attention time.
 typedef unsigned int kv_u32x4 __attribute__((ext_vector_type(4)));
 template <bool STREAM>
-__device__ __forceinline__ uint4 kv_load(const uint4* p)
+__device__ __forceinline__ kv_u32x4 kv_load(const kv_u32x4* p)
 {
-    if constexpr (STREAM) {
-        const kv_u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const kv_u32x4*>(p));
-        return make_uint4(v.x, v.y, v.z, v.w);
-    } else {
-        return *p;
-    }
+    if constexpr (STREAM) return __builtin_nontemporal_load(p);
+    else return *p;
 }
 
 template <int HD, int RT, bool PAGED, bool FUSED, int CW, bool STREAM>
 __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
     attn_chunk_kernel(StepTables t, LookaheadPack ks, CacheGeom g, int n_q_heads, int kv_share, int layer,
-                      const uint4* cache, const float* __restrict__ q, int max_chunks, int lag_keys, int r_cap, float scale_log2e,
+                      const kv_u32x4* cache, const float* __restrict__ q, int max_chunks, int lag_keys, int r_cap, float scale_log2e,
                       float* __restrict__ part_o, float* __restrict__ part_ml, QkvSrc src, uint16_t* cache_w, XOut xo)
 {
     constexpr int STEPS = HD / 32;     // 32-dim steps of the score product
     constexpr int DT = HD / 16;        // 16-dim tiles of the output
     const int lane = threadIdx.x & 63, c16 = lane & 15, gq = lane >> 4;
-    const int item = CW > 0 ? blockIdx.x * max_chunks + (threadIdx.x >> 6) : blockIdx.x;   // ((b, hkv), chunk)
-    const int chunk = CW > 0 ? (int)(threadIdx.x >> 6) : item % max_chunks;
+    // The chunk is the same for a whole wavefront, and the compiler has to know: everything that follows from it is
+    // then scalar and the loops over blocks and window positions branch instead of masking lanes.  (Taken as a
+    // vector value, the compiler restored registers parked in the accumulation registers behind a masked loop, where
+    // no lane was active.)
+    const int wave = CW > 0 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+    const int item = CW > 0 ? blockIdx.x * max_chunks + wave : blockIdx.x;   // ((b, hkv), chunk)
+    const int chunk = CW > 0 ? wave : item % max_chunks;
     // kv_share > 1: the query heads of one kv head are dealt to kv_share work items ("hkv" counts those,
     // "group" is the heads of one item), which all stream the keys and values of cache head hkc
     const int n_items_kv = g.n_kv_heads * kv_share;
@@ -81,8 +86,8 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
     const int K = ks.k[b];
     const int group = n_q_heads / n_items_kv;
     const int rows = (K + 1) * group;
-    const int row0 = t.seq_row0[b];
-    if (!t.seq_ok[b]) {
+    const int row0 = t.seq_row0[b], ok = t.seq_ok[b], n = t.seq_n[b], slot = t.seq_slot[b];   // one round trip
+    if (!ok) {
         if constexpr (CW > 0) {   // rows of a skipped sequence: zero operand rows, as the merge kernel writes them
             const float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
             for (int u = threadIdx.x; u < rows * (HD / 8); u += 64 * CW) {
@@ -93,7 +98,6 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
         }
         return;
     }
-    const int n = t.seq_n[b];
     const int total = n + K + 1;
     // Equal chunks, except that the chunks before the last are lag_keys longer when the last one stays
     // long enough: its wavefront first puts the window's keys and values together (FUSED), and with a
@@ -123,27 +127,34 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
     const int key1 = min(key0 + ck, total);
 
     const int blk0 = key0 >> 5, blk1 = (key1 + 31) >> 5;
-    const uint4* head;
+    const kv_u32x4* head;
     int my_page = 0;
     if constexpr (PAGED) {
         head = cache + ((size_t)layer * g.n_kv_heads + hkc) * (64 * HD) / 8;   // offset inside a page
-        const int p = g.table[(size_t)t.seq_slot[b] * g.blocks_per_slot + min(blk0 + lane, blk1 - 1)];
+        const int p = g.table[(size_t)slot * g.blocks_per_slot + min(blk0 + lane, blk1 - 1)];
         my_page = p < 0 ? 0 : p;
     } else {
-        head = cache + cache_head_base(g, layer, t.seq_slot[b], hkc) / 8;
+        head = cache + cache_head_base(g, layer, slot, hkc) / 8;
     }
     const size_t blk_u4 = g.blk_stride / 8;   // from one block of this head to the next (contiguous cache)
 
-    uint4 ka[2][STEPS], va[DT], kb[2][STEPS], vb[DT];
-    // unconditional loads (a block index past the chunk re-reads the chunk's last block): with no
-    // branch around them the compiler counts outstanding loads exactly and the prefetch stays in flight
-    auto load_block = [&](int blk, uint4(&kk)[2][STEPS], uint4(&vv)[DT]) {
-        const int bb = min(blk, blk1 - 1);
-        const uint4* p;
+    // Blocks in registers.  128-dim heads: one processed, the next in flight (16 KiB).  64-dim blocks are half as
+    // large, so of those that come from memory three are kept in flight: with one, 512 wavefronts had 4 MB under way,
+    // which a memory round trip of about 1 us turns into 4.4 TB/s (28.4 -> 26.6 us at 32 sequences of 8 kv heads).
+    // Out of a cache (kv_share > 1) the round trip is short and the fourth buffer only costs registers: a step at
+    // the 1B shape, batch 1, takes 842 us with it and 827 without.
+    constexpr int NBUF = HD == 128 || !STREAM ? 2 : 4;
+    kv_u32x4 kbuf[NBUF][2][STEPS], vbuf[NBUF][DT];
+    // Unconditional loads: with no branch around them the compiler counts outstanding loads exactly and the
+    // prefetch stays in flight.  Past the chunk's end every lane reads the same 16 bytes of its last block,
+    // a few lines instead of a block nobody needs.
+    auto load_block = [&](int blk, kv_u32x4(&kk)[2][STEPS], kv_u32x4(&vv)[DT]) {
+        const int bb = min(blk, blk1 - 1), at = blk < blk1 ? lane : 0;
+        const kv_u32x4* p;
         if constexpr (PAGED)
-            p = head + (size_t)__builtin_amdgcn_readlane(my_page, bb - blk0) * (g.page_stride / 8) + lane;
+            p = head + (size_t)__builtin_amdgcn_readlane(my_page, bb - blk0) * (g.page_stride / 8) + at;
         else
-            p = head + (size_t)bb * blk_u4 + lane;
+            p = head + (size_t)bb * blk_u4 + at;
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
@@ -151,30 +162,85 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
 #pragma unroll
         for (int d = 0; d < DT; ++d) vv[d] = kv_load<STREAM>(p + 4 * HD + d * 64);
     };
-    load_block(blk0, ka, va);   // the stream starts before anything else is fetched
+    load_block(blk0, kbuf[0], vbuf[0]);   // the stream starts before anything else is fetched
 
     // queries, pre-scaled by log2(e)/sqrt(hd), as bf16 head + remainder operand fragments
     Frag qh[RT][STEPS], ql[RT][STEPS];
     int n_vis[RT];           // cached positions below this are visible to the query (0 for padding rows)
     uint32_t wmask[RT];      // window slots (positions n + i) the query attends to
-    // Where this lane's share of a row tile's queries starts in the partial sums: 8 dims of every
-    // 32-dim step, i.e. 2 * STEPS float4 columns.
-    auto q_columns = [&](int rt, const float** cols, float& rs) {
-        const int r = rt * 16 + c16;
-        const bool real = r < rows;
-        const int j = real ? r / group : 0, hl = real ? r % group : 0;
-        const int m = row0 + j;
-        rs = row_inv_rms(src.ns.ssq, src.ns.n_ssq, m, src.ns.d, src.ns.eps);
-        const float* pq = src.partial + (size_t)m * src.ld + (hkv * group + hl) * HD + 8 * gq;
-#pragma unroll
-        for (int s = 0; s < STEPS; ++s) {
-            cols[2 * s] = pq + 32 * s;
-            cols[2 * s + 1] = pq + 32 * s + 4;
-        }
+    // FUSED: a request for a row tile's queries or for eight window positions fetches the first W0 ranges of 16
+    // float4 columns' worth, the row's sums of squares and its rotary factors; the rest of a longer list is
+    // fetched when the request is finished.
+    constexpr int QC = 2 * STEPS, W0 = HD == 128 ? 2 : 4;
+    struct RowScale {
+        float4 a, b;
     };
-    // Scale, rotate and split them: dims d and d + HD/2 (a rotary pair) sit in steps s and
+    auto scale_issue = [&](int m, RowScale& r) {
+        if (!src.ns.ssq) return;
+        const float4* p = reinterpret_cast<const float4*>(src.ns.ssq + (size_t)m * src.ns.n_ssq);
+        r.a = p[0];
+        r.b = p[min(1, (src.ns.n_ssq >> 2) - 1)];
+    };
+    auto scale_finish = [&](int m, const RowScale& r) -> float {   // the arithmetic of row_inv_rms
+        if (!src.ns.ssq) return 1.f;
+        const int n4 = src.ns.n_ssq >> 2;
+        const float4* p = reinterpret_cast<const float4*>(src.ns.ssq + (size_t)m * src.ns.n_ssq);
+        float ss = (r.a.x + r.a.y) + (r.a.z + r.a.w);
+        ss += n4 > 1 ? (r.b.x + r.b.y) + (r.b.z + r.b.w) : 0.f;
+        for (int i = 2; i < n4; ++i) {
+            const float4 v = p[i];
+            ss += (v.x + v.y) + (v.z + v.w);
+        }
+        return 1.0f / sqrtf(ss / (float)src.ns.d + src.ns.eps);
+    };
+    auto range_issue = [&](const float* p, float4(&a)[W0]) {
+#pragma unroll
+        for (int i = 0; i < W0; ++i) a[i] = *reinterpret_cast<const float4*>(p + (size_t)min(i, src.n_split - 1) * src.stride);
+    };
+    auto range_finish = [&](const float4(&a)[W0]) -> float4 {   // ranges in index order
+        float4 v = a[0];
+#pragma unroll
+        for (int i = 1; i < W0; ++i) {
+            const bool on = i < src.n_split;
+            v.x += on ? a[i].x : 0.f; v.y += on ? a[i].y : 0.f; v.z += on ? a[i].z : 0.f; v.w += on ? a[i].w : 0.f;
+        }
+        return v;
+    };
+    struct QRaw {
+        float4 a[QC][W0], cs[STEPS / 2][4];
+        RowScale rs;
+        const float* p;
+        int m;
+    };
+    auto q_issue = [&](int rt, QRaw& r) {
+        const int rr = rt * 16 + c16;
+        const bool real = rr < rows;
+        const int j = real ? rr / group : 0, hl = real ? rr % group : 0;
+        r.m = row0 + j;
+        r.p = src.partial + (size_t)r.m * src.ld + (hkv * group + hl) * HD + 8 * gq;   // 8 dims of every 32-dim step
+        scale_issue(r.m, r.rs);
+#pragma unroll
+        for (int c = 0; c < QC; ++c) range_issue(r.p + 32 * (c >> 1) + 4 * (c & 1), r.a[c]);
+        const int rpos = t.tree ? t.row_rope[r.m] : n + j;
+        const float* cs = src.cos_sin + (size_t)rpos * HD + 2 * (8 * gq);   // [HD/2][2] per position
+#pragma unroll
+        for (int s = 0; s < STEPS / 2; ++s)
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) r.cs[s][e4] = *reinterpret_cast<const float4*>(cs + 2 * (32 * s) + 4 * e4);
+    };
+    // Add up, scale, rotate and split them: dims d and d + HD/2 (a rotary pair) sit in steps s and
     // s + STEPS/2 of the same lane.
-    auto q_finish = [&](int rt, const float4* sums, float rs, int j, float sc) {
+    auto q_finish = [&](int rt, const QRaw& r, float sc) {
+        const float rs = scale_finish(r.m, r.rs);
+        float4 sums[QC];
+#pragma unroll
+        for (int c = 0; c < QC; ++c) sums[c] = range_finish(r.a[c]);
+        if (src.n_split > W0) {
+            const float* cols[QC];
+#pragma unroll
+            for (int c = 0; c < QC; ++c) cols[c] = r.p + 32 * (c >> 1) + 4 * (c & 1) + W0 * src.stride;
+            add_splits4_many<QC, W0>(cols, src.n_split - W0, src.stride, sums);
+        }
         float raw[STEPS][8];
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
@@ -182,14 +248,12 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
             raw[s][0] = a.x * rs; raw[s][1] = a.y * rs; raw[s][2] = a.z * rs; raw[s][3] = a.w * rs;
             raw[s][4] = b.x * rs; raw[s][5] = b.y * rs; raw[s][6] = b.z * rs; raw[s][7] = b.w * rs;
         }
-        const int rpos = t.tree ? t.row_rope[row0 + j] : n + j;
-        const float* cs = src.cos_sin + (size_t)rpos * HD + 2 * (8 * gq);   // [HD/2][2] per position
 #pragma unroll
         for (int s = 0; s < STEPS / 2; ++s) {
             float x0[8], x1[8];
 #pragma unroll
             for (int e4 = 0; e4 < 4; ++e4) {
-                const float4 c2 = *reinterpret_cast<const float4*>(cs + 2 * (32 * s) + 4 * e4);   // cos,sin of 2 dims
+                const float4 c2 = r.cs[s][e4];   // cos,sin of 2 dims
                 const float ca[2] = {c2.x, c2.z}, sa[2] = {c2.y, c2.w};
 #pragma unroll
                 for (int h2 = 0; h2 < 2; ++h2) {
@@ -203,26 +267,6 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
             split_frag(x1, qh[rt][s + STEPS / 2], ql[rt][s + STEPS / 2]);
         }
     };
-    // 64-dim heads: the partial sums of two row tiles are requested together (the same number of
-    // loads in flight as one tile of a 128-dim head)
-    constexpr int RB = (FUSED && HD == 64 && RT >= 2) ? 2 : 1;
-    float4 pre[RB > 1 ? RT + 1 : 1][2 * STEPS];   // sums fetched ahead (batched variant only)
-    float pre_rs[RB > 1 ? RT + 1 : 1];
-    if constexpr (RB > 1) {
-#pragma unroll
-        for (int rt0 = 0; rt0 < RT; rt0 += 2) {
-            const float* cols[2][2 * STEPS];
-            q_columns(rt0, cols[0], pre_rs[rt0]);
-            q_columns(min(rt0 + 1, RT - 1), cols[1], pre_rs[rt0 + 1]);
-            const float* flat[4 * STEPS];
-            float4 fsum[4 * STEPS];
-#pragma unroll
-            for (int x = 0; x < 4 * STEPS; ++x) flat[x] = cols[x / (2 * STEPS)][x % (2 * STEPS)];
-            sum_splits4_many(flat, src.n_split, src.stride, fsum);
-#pragma unroll
-            for (int x = 0; x < 4 * STEPS; ++x) pre[rt0 + x / (2 * STEPS)][x % (2 * STEPS)] = fsum[x];
-        }
-    }
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
         const int r = rt * 16 + c16;
@@ -230,17 +274,8 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
         const int j = real ? r / group : 0, hl = real ? r % group : 0;
         n_vis[rt] = real ? n : 0;
         wmask[rt] = !real ? 0u : (t.tree ? t.row_mask[row0 + j] : (2u << j) - 1u);
-        const float sc = real ? scale_log2e : 0.f;   // rows past the window contribute zeros
-        if constexpr (FUSED && RB > 1) {
-            q_finish(rt, pre[rt], pre_rs[rt], j, sc);
-        } else if constexpr (FUSED) {
-            const float* cols[2 * STEPS];
-            float rs;
-            q_columns(rt, cols, rs);
-            float4 sums[2 * STEPS];
-            sum_splits4_many(cols, src.n_split, src.stride, sums);
-            q_finish(rt, sums, rs, j, sc);
-        } else {
+        if constexpr (!FUSED) {
+            const float sc = real ? scale_log2e : 0.f;   // rows past the window contribute zeros
             const float4* qsrc = reinterpret_cast<const float4*>(q + (size_t)(row0 + j) * dq + (hkv * group + hl) * HD + 8 * gq);
 #pragma unroll
             for (int s = 0; s < STEPS; ++s) {
@@ -250,22 +285,139 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
             }
         }
     }
+    // the window's keys [slot][dim] and values [dim][slot] (bf16), each position put there by the wavefront
+    // whose chunk it falls into and read by that wavefront only
+    constexpr int WK_LD = HD + 8, WV_LD = 18;
+    static_assert(SPEC_MAX_LOOKAHEAD < 16, "a window has at most 16 positions");
+    __shared__ __align__(16) uint16_t s_wk[FUSED ? 16 * WK_LD : 8], s_wv[FUSED ? HD * WV_LD : 8];
+    if constexpr (FUSED) {
+        QRaw q0;
+        q_issue(0, q0);
+        // The window's keys (rotated) and values of this kv head that fall into this chunk.  HD/8
+        // lanes share a position (each 4 rotary pairs of the key and 8 dims of the value), so a
+        // wavefront covers 8 positions per trip in rounds of 64 / (HD/8), all of a trip requested together.
+        const int w0 = max(key0, n), w1 = key1;   // positions [w0, w1) are window slots of this chunk
+        if (w0 < w1) {
+            constexpr int HALF = HD / 2, LP = HD / 8, PPR = 64 / LP, NR = 8 / PPR;
+            const int u = lane / LP, tq = lane % LP;
+            const int kcol = n_q_heads * HD + hkc * HD, vcol = (n_q_heads + g.n_kv_heads) * HD + hkc * HD;
+            for (int p0 = w0; p0 < w1; p0 += 8) {
+                float4 raw[NR][4][W0], cs[NR][2];
+                RowScale rsr[NR];
+                int posr[NR];
+                auto col = [&](int h, int x) {
+                    const float* prow = src.partial + (size_t)(row0 + (posr[h] - n)) * src.ld;
+                    return x == 0 ? prow + kcol + 4 * tq : x == 1 ? prow + kcol + HALF + 4 * tq : prow + vcol + 8 * tq + 4 * (x - 2);
+                };
+#pragma unroll
+                for (int h = 0; h < NR; ++h) {
+                    posr[h] = min(p0 + PPR * h + u, w1 - 1);   // clamped: the loads are unconditional
+                    const int m = row0 + (posr[h] - n);
+                    scale_issue(m, rsr[h]);
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) range_issue(col(h, x), raw[h][x]);
+                    const float* c2 = src.cos_sin + (size_t)(t.tree ? t.row_rope[m] : posr[h]) * HD + 2 * (4 * tq);
+                    cs[h][0] = *reinterpret_cast<const float4*>(c2);
+                    cs[h][1] = *reinterpret_cast<const float4*>(c2 + 4);
+                }
+#pragma unroll
+                for (int h = 0; h < NR; ++h) {
+                    const float rs = scale_finish(row0 + (posr[h] - n), rsr[h]);
+                    float4 kv4[4];
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) kv4[x] = range_finish(raw[h][x]);
+                    if (src.n_split > W0) {
+                        const float* cols[4] = {col(h, 0) + W0 * src.stride, col(h, 1) + W0 * src.stride, col(h, 2) + W0 * src.stride,
+                                                col(h, 3) + W0 * src.stride};
+                        add_splits4_many<4, W0>(cols, src.n_split - W0, src.stride, kv4);
+                    }
+                    const float a[4] = {kv4[0].x * rs, kv4[0].y * rs, kv4[0].z * rs, kv4[0].w * rs};
+                    const float bk[4] = {kv4[1].x * rs, kv4[1].y * rs, kv4[1].z * rs, kv4[1].w * rs};
+                    const float v[8] = {kv4[2].x * rs, kv4[2].y * rs, kv4[2].z * rs, kv4[2].w * rs,
+                                        kv4[3].x * rs, kv4[3].y * rs, kv4[3].z * rs, kv4[3].w * rs};
+                    const float co[4] = {cs[h][0].x, cs[h][0].z, cs[h][1].x, cs[h][1].z};
+                    const float si[4] = {cs[h][0].y, cs[h][0].w, cs[h][1].y, cs[h][1].w};
+                    size_t blk;
+                    if constexpr (PAGED)
+                        blk = (size_t)__shfl(my_page, (posr[h] >> 5) - blk0) * g.page_stride + ((size_t)layer * g.n_kv_heads + hkc) * (64 * HD);
+                    else
+                        blk = cache_block_base(g, layer, slot, hkc, posr[h] >> 5);
+                    if (p0 + PPR * h + u < w1) {
+                        const int t32 = posr[h] & 31, w = posr[h] - n;
+                        union {
+                            ushort4 v;
+                            uint16_t h[4];
+                        } k0, k1;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            k0.h[e] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(a[e] * co[e] - bk[e] * si[e]));
+                            k1.h[e] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(a[e] * si[e] + bk[e] * co[e]));
+                        }
+                        *reinterpret_cast<ushort4*>(s_wk + w * WK_LD + 4 * tq) = k0.v;
+                        *reinterpret_cast<ushort4*>(s_wk + w * WK_LD + 4 * tq + HALF) = k1.v;
+                        *reinterpret_cast<ushort4*>(cache_w + blk + tiled_k_within(HD, t32, 4 * tq)) = k0.v;
+                        *reinterpret_cast<ushort4*>(cache_w + blk + tiled_k_within(HD, t32, 4 * tq + HALF)) = k1.v;
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const uint16_t vb = __builtin_bit_cast(uint16_t, static_cast<__bf16>(v[e]));
+                            s_wv[(8 * tq + e) * WV_LD + w] = vb;
+                            cache_w[blk + tiled_v_within(HD, t32, 8 * tq + e)] = vb;
+                        }
+                    }
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the copy in LDS is read by other lanes
+        }
+        auto q_scale = [&](int rt) { return rt * 16 + c16 < rows ? scale_log2e : 0.f; };   // rows past the window contribute zeros
+        if constexpr (RT == 1) {
+            q_finish(0, q0, q_scale(0));
+        } else {
+            QRaw q1;   // the next row tile's request goes out before a tile is finished
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                QRaw& cur = rt & 1 ? q1 : q0;
+                if (rt + 1 < RT) q_issue(rt + 1, rt & 1 ? q0 : q1);
+                q_finish(rt, cur, q_scale(rt));
+            }
+        }
+    }
 
-    auto process = [&](int blk, const uint4(&kk)[2][STEPS], uint4(&vv)[DT]) {
+    auto process = [&](int blk, kv_u32x4(&kk)[2][STEPS], kv_u32x4(&vv)[DT]) {
         const int kbase = blk * 32;
-        const bool tail = kbase + 32 > n || kbase >= key1;   // reaches the window / the end: mask per element
+        const bool tail = kbase + 32 > n;   // reaches the window / the end: mask per element
         if (tail) {
+            if constexpr (FUSED) {   // the window's own entries from LDS
+#pragma unroll
+                for (int sub = 0; sub < 2; ++sub) {
+                    const int w = kbase + 16 * sub + c16 - n;
+                    const bool in = w >= 0 && w <= K;
+#pragma unroll
+                    for (int s = 0; s < STEPS; ++s) {
+                        const kv_u32x4 l = *reinterpret_cast<const kv_u32x4*>(s_wk + (in ? w : 0) * WK_LD + 8 * (4 * s + gq));
+                        kk[sub][s] = in ? l : kk[sub][s];
+                    }
+                }
+#pragma unroll
+                for (int d = 0; d < DT; ++d) {
+#pragma unroll
+                    for (int e2 = 0; e2 < 4; ++e2) {   // two positions
+                        const int w = kbase + (e2 < 2 ? 4 * gq + 2 * e2 : 12 + 4 * gq + 2 * e2) - n;
+                        const bool i0 = w >= 0 && w <= K, i1 = w + 1 >= 0 && w + 1 <= K;
+                        const uint16_t* l = s_wv + (16 * d + c16) * WV_LD;
+                        const uint32_t own = l[i0 ? w : 0] | (uint32_t)l[i1 ? w + 1 : 0] << 16;
+                        const uint32_t mask = (i0 ? 0xffffu : 0u) | (i1 ? 0xffff0000u : 0u);
+                        vv[d][e2] = (vv[d][e2] & ~mask) | (own & mask);
+                    }
+                }
+            }
             // values of positions that do not exist yet may hold anything: zero them
 #pragma unroll
             for (int d = 0; d < DT; ++d) {
-                Frag f;
-                f.u = vv[d];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int key = kbase + (e < 4 ? 4 * gq + e : 16 + 4 * gq + e - 4);
-                    if (key >= total) f.h[e] = 0;
+                for (int e2 = 0; e2 < 4; ++e2) {
+                    const int key = kbase + (e2 < 2 ? 4 * gq + 2 * e2 : 12 + 4 * gq + 2 * e2);
+                    vv[d][e2] &= (key < total ? 0xffffu : 0u) | (key + 1 < total ? 0xffff0000u : 0u);
                 }
-                vv[d] = f.u;
             }
         }
 #pragma unroll
@@ -276,10 +428,9 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
                 st[sub] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int s = 0; s < STEPS; ++s) {
-                    Frag kf;
-                    kf.u = kk[sub][s];
-                    st[sub] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf.v, qh[rt][s].v, st[sub], 0, 0, 0);
-                    st[sub] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf.v, ql[rt][s].v, st[sub], 0, 0, 0);
+                    const bf16x8 kf = __builtin_bit_cast(bf16x8, kk[sub][s]);
+                    st[sub] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qh[rt][s].v, st[sub], 0, 0, 0);
+                    st[sub] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, ql[rt][s].v, st[sub], 0, 0, 0);
                 }
             }
             float sv[8];
@@ -291,7 +442,7 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
                     const int key = kbase + (e < 4 ? 4 * gq + e : 16 + 4 * gq + e - 4);
                     const int w = key - n;   // window slot, if >= 0
                     const bool vis = key < n_vis[rt] || (w >= 0 && w < 32 && ((wmask[rt] >> w) & 1u));
-                    if (!vis || kbase >= key1) sv[e] = -INFINITY;
+                    if (!vis) sv[e] = -INFINITY;
                 }
             }
             float mx = sv[0];
@@ -329,91 +480,35 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
             split_frag(sv, ph, pl);
 #pragma unroll
             for (int d = 0; d < DT; ++d) {
-                Frag vf;
-                vf.u = vv[d];
+                const bf16x8 vf = __builtin_bit_cast(bf16x8, vv[d]);
                 floatx4 a = acc[rt][d];
-                a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf.v, ph.v, a, 0, 0, 0);
-                a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf.v, pl.v, a, 0, 0, 0);
+                a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, ph.v, a, 0, 0, 0);
+                a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pl.v, a, 0, 0, 0);
                 acc[rt][d] = a;
             }
         }
     };
 
-    // Two blocks per trip, no branch inside: a block index past the chunk holds only positions
-    // >= total, which the tail masking turns into zero weight, so an odd block count just ends with
-    // one idle half trip.
-    if constexpr (FUSED) {
-        // The window's keys (rotated) and values of this kv head that fall into this chunk.  HD/8
-        // lanes share a position (each 4 rotary pairs of the key and 8 dims of the value), so a
-        // wavefront covers 8 positions per trip in rounds of 64 / (HD/8); each round's loads are issued
-        // together.  (Putting both rounds of a 128-dim head in flight at once costs registers the main
-        // loop needs: measured slower.)
-        const int w0 = max(key0, n), w1 = key1;   // positions [w0, w1) are window slots of this chunk
-        if (w0 < w1) {
-            constexpr int HALF = HD / 2, LP = HD / 8, PPR = 64 / LP, NR = 8 / PPR;
-            const int u = lane / LP, tq = lane % LP;
-            const int slot = t.seq_slot[b];
-            const int kcol = n_q_heads * HD + hkc * HD, vcol = (n_q_heads + g.n_kv_heads) * HD + hkc * HD;
-            for (int p0 = w0; p0 < w1; p0 += 8) {
-                float kr[NR][8], vr[NR][8];
-                int posr[NR];
-#pragma unroll
-                for (int h = 0; h < NR; ++h) {
-                    const int pc = min(p0 + PPR * h + u, w1 - 1);   // clamped: the loads are unconditional
-                    posr[h] = pc;
-                    const int m = row0 + (pc - n);
-                    const float rs = row_inv_rms(src.ns.ssq, src.ns.n_ssq, m, src.ns.d, src.ns.eps);
-                    const float* prow = src.partial + (size_t)m * src.ld;
-                    const int rpos = t.tree ? t.row_rope[m] : pc;
-                    const float* cols[4] = {prow + kcol + 4 * tq, prow + kcol + HALF + 4 * tq, prow + vcol + 8 * tq,
-                                            prow + vcol + 8 * tq + 4};
-                    float4 kv4[4];
-                    sum_splits4_many(cols, src.n_split, src.stride, kv4);
-                    const float a[4] = {kv4[0].x, kv4[0].y, kv4[0].z, kv4[0].w};
-                    const float bk[4] = {kv4[1].x, kv4[1].y, kv4[1].z, kv4[1].w};
-                    const float* cs = src.cos_sin + (size_t)rpos * HD + 2 * (4 * tq);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float c = cs[2 * e], sn = cs[2 * e + 1];
-                        const float x = a[e] * rs, y = bk[e] * rs;
-                        kr[h][e] = x * c - y * sn;
-                        kr[h][4 + e] = x * sn + y * c;
-                    }
-                    const float4 A = kv4[2], B = kv4[3];
-                    vr[h][0] = A.x * rs; vr[h][1] = A.y * rs; vr[h][2] = A.z * rs; vr[h][3] = A.w * rs;
-                    vr[h][4] = B.x * rs; vr[h][5] = B.y * rs; vr[h][6] = B.z * rs; vr[h][7] = B.w * rs;
-                }
-#pragma unroll
-                for (int h = 0; h < NR; ++h) {
-                    if (p0 + PPR * h + u < w1) {
-                        const size_t blk = cache_block_base(g, layer, slot, hkc, posr[h] >> 5);
-                        const int t32 = posr[h] & 31;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            cache_w[blk + tiled_k_within(HD, t32, 4 * tq + e)] =
-                                __builtin_bit_cast(uint16_t, static_cast<__bf16>(kr[h][e]));
-                            cache_w[blk + tiled_k_within(HD, t32, 4 * tq + e + HALF)] =
-                                __builtin_bit_cast(uint16_t, static_cast<__bf16>(kr[h][4 + e]));
-                        }
-#pragma unroll
-                        for (int e = 0; e < 8; ++e)
-                            cache_w[blk + tiled_v_within(HD, t32, 8 * tq + e)] =
-                                __builtin_bit_cast(uint16_t, static_cast<__bf16>(vr[h][e]));
-                    }
-                }
-            }
-            // the stores must have landed before this wavefront reads the blocks they belong to; only
-            // the first block was requested before them
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_s_waitcnt(0);
-            if (blk0 >= (w0 >> 5)) load_block(blk0, ka, va);
+    if constexpr (NBUF == 2) {
+        for (int blk = blk0; blk < blk1; blk += 2) {
+            load_block(blk + 1, kbuf[1], vbuf[1]);
+            process(blk, kbuf[0], vbuf[0]);
+            load_block(blk + 2, kbuf[0], vbuf[0]);
+            if (blk + 1 < blk1) process(blk + 1, kbuf[1], vbuf[1]);
         }
-    }
-    for (int blk = blk0; blk < blk1; blk += 2) {
-        load_block(blk + 1, kb, vb);
-        process(blk, ka, va);
-        load_block(blk + 2, ka, va);
-        process(blk + 1, kb, vb);
+    } else {
+        load_block(blk0 + 1, kbuf[1], vbuf[1]);
+        load_block(blk0 + 2, kbuf[2], vbuf[2]);
+        for (int blk = blk0; blk < blk1; blk += 4) {
+            load_block(blk + 3, kbuf[3], vbuf[3]);
+            process(blk, kbuf[0], vbuf[0]);
+            load_block(blk + 4, kbuf[0], vbuf[0]);
+            if (blk + 1 < blk1) process(blk + 1, kbuf[1], vbuf[1]);
+            load_block(blk + 5, kbuf[1], vbuf[1]);
+            if (blk + 2 < blk1) process(blk + 2, kbuf[2], vbuf[2]);
+            load_block(blk + 6, kbuf[2], vbuf[2]);
+            if (blk + 3 < blk1) process(blk + 3, kbuf[3], vbuf[3]);
+        }
     }
     }   // active
 
@@ -504,7 +599,7 @@ static int launch_chunks(int rt, int cw, dim3 grid, dim3 wg_grid, hipStream_t s,
     const int lag_keys = src.partial ? p.lag_keys : 0;   // only the fused prologue delays a wavefront
 #define SPECV_ATTN_CW(RT, PG, FU, CW_)                                                                         \
     hipLaunchKernelGGL((attn_chunk_kernel<HD, RT, PG, FU, CW_, STREAM>), CW_ > 0 ? wg_grid : grid, dim3(CW_ > 0 ? 64 * CW_ : 64), \
-                       0, s, t, ks, g, n_q_heads, kv_share, layer, (const uint4*)cache, q, p.max_chunks, lag_keys, r_cap, sl2, part_o, \
+                       0, s, t, ks, g, n_q_heads, kv_share, layer, (const kv_u32x4*)cache, q, p.max_chunks, lag_keys, r_cap, sl2, part_o, \
                        part_ml, src, (uint16_t*)cache_w, xo)
 #define SPECV_ATTN_GO(RT, PG, FU)                                                                              \
     do {                                                                                                         \

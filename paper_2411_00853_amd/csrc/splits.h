@@ -6,15 +6,13 @@
 
 namespace specv {
 
-// N float4 columns of one row, all loads of a batch of (up to) W ranges issued before the first addition
+// out += N float4 columns of one row, all loads of a batch of (up to) W ranges issued before the first addition
 // (indices past the end clamped, values dropped), so that the memory latency is paid once per batch: summing
 // the columns one after the other makes N dependent round trips (the compiler keeps each sum's loads next
 // to its additions).  Ranges are added in index order.
-template <int N, int W = 4>
-__device__ __forceinline__ void sum_splits4_many(const float* const (&p)[N], int n_split, size_t stride, float4 (&out)[N])
+template <int N, int W>
+__device__ __forceinline__ void add_splits4_many(const float* const (&p)[N], int n_split, size_t stride, float4 (&out)[N])
 {
-#pragma unroll
-    for (int x = 0; x < N; ++x) out[x] = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int s0 = 0; s0 < n_split; s0 += W) {
         float4 a[N][W];
 #pragma unroll
@@ -61,7 +59,11 @@ __device__ __forceinline__ void sum_ranges(const float* const (&p)[N], int n_spl
     case 2: sum_exact<2>(p, stride, out); break;
     case 4: sum_exact<4>(p, stride, out); break;
     case 8: sum_exact<8>(p, stride, out); break;
-    default: sum_splits4_many<N, 8>(p, n_split, stride, out); break;
+    default:
+#pragma unroll
+        for (int x = 0; x < N; ++x) out[x] = make_float4(0.f, 0.f, 0.f, 0.f);
+        add_splits4_many<N, 8>(p, n_split, stride, out);
+        break;
     }
 }
 
