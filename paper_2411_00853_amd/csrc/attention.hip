@@ -438,13 +438,13 @@ int launch_attention(int max_kv_len, int cu_count, const StepTables& t, const Lo
         ProfScope ps(prof, SPEC_PROF_ATTENTION, s);
         // several work items per cache head: its second reader should find it in the caches
         if (share > 1)
-            rc = launch_chunks_reuse(hd, rt, cw, grid, wg_grid, s, t, ks, g, n_q_heads, share, layer, cache, q, p, r_cap, sl2,
+            rc = launch_chunks_reuse(hd, rt, cw, grid, wg_grid, s, t, g, n_q_heads, share, layer, cache, q, p, r_cap, sl2,
                                      part_o, part_ml, src, cache_w, xo);
         else if (hd == 128)
-            rc = launch_chunks<128, true>(rt, cw, grid, wg_grid, s, t, ks, g, n_q_heads, share, layer, cache, q, p, r_cap, sl2,
+            rc = launch_chunks<128, true>(rt, cw, grid, wg_grid, s, t, g, n_q_heads, share, layer, cache, q, p, r_cap, sl2,
                                           part_o, part_ml, src, cache_w, xo);
         else
-            rc = launch_chunks<64, true>(rt, cw, grid, wg_grid, s, t, ks, g, n_q_heads, share, layer, cache, q, p, r_cap, sl2,
+            rc = launch_chunks<64, true>(rt, cw, grid, wg_grid, s, t, g, n_q_heads, share, layer, cache, q, p, r_cap, sl2,
                                          part_o, part_ml, src, cache_w, xo);
     }
     if (rc) return rc;

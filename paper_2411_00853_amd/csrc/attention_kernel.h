@@ -63,7 +63,7 @@ __device__ __forceinline__ kv_u32x4 kv_load(const kv_u32x4* p)
 
 template <int HD, int RT, bool PAGED, bool FUSED, int CW, bool STREAM>
 __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
-    attn_chunk_kernel(StepTables t, LookaheadPack ks, CacheGeom g, int n_q_heads, int kv_share, int layer,
+    attn_chunk_kernel(StepTables t, CacheGeom g, int n_q_heads, int kv_share, int layer,
                       const kv_u32x4* cache, const float* __restrict__ q, int max_chunks, int lag_keys, int r_cap, float scale_log2e,
                       float* __restrict__ part_o, float* __restrict__ part_ml, QkvSrc src, uint16_t* cache_w, XOut xo)
 {
@@ -75,18 +75,19 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
     // vector value, the compiler restored registers parked in the accumulation registers behind a masked loop, where
     // no lane was active.)
     const int wave = CW > 0 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
-    const int item = CW > 0 ? blockIdx.x * max_chunks + wave : blockIdx.x;   // ((b, hkv), chunk)
-    const int chunk = CW > 0 ? wave : item % max_chunks;
+    const int pair = CW > 0 ? blockIdx.x : blockIdx.x / max_chunks;   // (place of the sequence by length, hkv)
+    const int chunk = CW > 0 ? wave : blockIdx.x % max_chunks;
     // kv_share > 1: the query heads of one kv head are dealt to kv_share work items ("hkv" counts those,
     // "group" is the heads of one item), which all stream the keys and values of cache head hkc
     const int n_items_kv = g.n_kv_heads * kv_share;
-    const int hkv = (CW > 0 ? blockIdx.x : item / max_chunks) % n_items_kv;
-    const int b = (CW > 0 ? blockIdx.x : item / max_chunks) / n_items_kv;
-    const int hkc = hkv / kv_share;
-    const int K = ks.k[b];
+    const int hkv = pair % n_items_kv, hkc = hkv / kv_share;
     const int group = n_q_heads / n_items_kv;
+    const int4* desc = reinterpret_cast<const int4*>(t.seq_desc + pair / n_items_kv);   // scalar, like the chunk
+    const int4 d0 = desc[0], d1 = desc[1];
+    const int b = __builtin_amdgcn_readfirstlane(d0.x), row0 = __builtin_amdgcn_readfirstlane(d0.y);
+    const int K = __builtin_amdgcn_readfirstlane(d0.z), n = __builtin_amdgcn_readfirstlane(d0.w);
+    const int slot = __builtin_amdgcn_readfirstlane(d1.x), ok = __builtin_amdgcn_readfirstlane(d1.y);
     const int rows = (K + 1) * group;
-    const int row0 = t.seq_row0[b], ok = t.seq_ok[b], n = t.seq_n[b], slot = t.seq_slot[b];   // one round trip
     if (!ok) {
         if constexpr (CW > 0) {   // rows of a skipped sequence: zero operand rows, as the merge kernel writes them
             const float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -489,25 +490,13 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
         }
     };
 
-    if constexpr (NBUF == 2) {
-        for (int blk = blk0; blk < blk1; blk += 2) {
-            load_block(blk + 1, kbuf[1], vbuf[1]);
-            process(blk, kbuf[0], vbuf[0]);
-            load_block(blk + 2, kbuf[0], vbuf[0]);
-            if (blk + 1 < blk1) process(blk + 1, kbuf[1], vbuf[1]);
-        }
-    } else {
-        load_block(blk0 + 1, kbuf[1], vbuf[1]);
-        load_block(blk0 + 2, kbuf[2], vbuf[2]);
-        for (int blk = blk0; blk < blk1; blk += 4) {
-            load_block(blk + 3, kbuf[3], vbuf[3]);
-            process(blk, kbuf[0], vbuf[0]);
-            load_block(blk + 4, kbuf[0], vbuf[0]);
-            if (blk + 1 < blk1) process(blk + 1, kbuf[1], vbuf[1]);
-            load_block(blk + 5, kbuf[1], vbuf[1]);
-            if (blk + 2 < blk1) process(blk + 2, kbuf[2], vbuf[2]);
-            load_block(blk + 6, kbuf[2], vbuf[2]);
-            if (blk + 3 < blk1) process(blk + 3, kbuf[3], vbuf[3]);
+#pragma unroll
+    for (int u = 1; u < NBUF - 1; ++u) load_block(blk0 + u, kbuf[u], vbuf[u]);
+    for (int blk = blk0; blk < blk1; blk += NBUF) {
+#pragma unroll
+        for (int u = 0; u < NBUF; ++u) {
+            load_block(blk + u + NBUF - 1, kbuf[(u + NBUF - 1) % NBUF], vbuf[(u + NBUF - 1) % NBUF]);
+            if (u == 0 || blk + u < blk1) process(blk + u, kbuf[u], vbuf[u]);
         }
     }
     }   // active
@@ -520,13 +509,14 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
             l += __shfl_xor(l, 32);
             const int r = rt * 16 + c16;
             if (r < rows) {
-                float* o = part_o + ((size_t)item * r_cap + r) * HD + 4 * gq;
+                const size_t item = ((size_t)b * n_items_kv + hkv) * max_chunks + chunk;
+                float* o = part_o + (item * r_cap + r) * HD + 4 * gq;
 #pragma unroll
                 for (int d = 0; d < DT; ++d)
                     *reinterpret_cast<float4*>(o + 16 * d) = make_float4(acc[rt][d][0], acc[rt][d][1], acc[rt][d][2], acc[rt][d][3]);
                 if (gq == 0) {
-                    part_ml[((size_t)item * r_cap + r) * 2 + 0] = m_run[rt];
-                    part_ml[((size_t)item * r_cap + r) * 2 + 1] = l;
+                    part_ml[(item * r_cap + r) * 2 + 0] = m_run[rt];
+                    part_ml[(item * r_cap + r) * 2 + 1] = l;
                 }
             }
         }
@@ -591,7 +581,7 @@ constexpr bool merge_fits(int hd, int rt, int cw)
 }
 
 template <int HD, bool STREAM>
-static int launch_chunks(int rt, int cw, dim3 grid, dim3 wg_grid, hipStream_t s, const StepTables& t, const LookaheadPack& ks,
+static int launch_chunks(int rt, int cw, dim3 grid, dim3 wg_grid, hipStream_t s, const StepTables& t,
                          const CacheGeom& g, int n_q_heads, int kv_share, int layer, const void* cache, const float* q,
                          const AttnPlan& p, int r_cap, float sl2, float* part_o, float* part_ml, const QkvSrc& src,
                          void* cache_w, const XOut& xo)
@@ -599,7 +589,7 @@ static int launch_chunks(int rt, int cw, dim3 grid, dim3 wg_grid, hipStream_t s,
     const int lag_keys = src.partial ? p.lag_keys : 0;   // only the fused prologue delays a wavefront
 #define SPECV_ATTN_CW(RT, PG, FU, CW_)                                                                         \
     hipLaunchKernelGGL((attn_chunk_kernel<HD, RT, PG, FU, CW_, STREAM>), CW_ > 0 ? wg_grid : grid, dim3(CW_ > 0 ? 64 * CW_ : 64), \
-                       0, s, t, ks, g, n_q_heads, kv_share, layer, (const kv_u32x4*)cache, q, p.max_chunks, lag_keys, r_cap, sl2, part_o, \
+                       0, s, t, g, n_q_heads, kv_share, layer, (const kv_u32x4*)cache, q, p.max_chunks, lag_keys, r_cap, sl2, part_o, \
                        part_ml, src, (uint16_t*)cache_w, xo)
 #define SPECV_ATTN_GO(RT, PG, FU)                                                                              \
     do {                                                                                                         \
@@ -639,7 +629,7 @@ static int launch_chunks(int rt, int cw, dim3 grid, dim3 wg_grid, hipStream_t s,
 
 // launch_chunks<HD, false>, compiled in attention_reuse.hip
 int launch_chunks_reuse(int hd, int rt, int cw, dim3 grid, dim3 wg_grid, hipStream_t s, const StepTables& t,
-                        const LookaheadPack& ks, const CacheGeom& g, int n_q_heads, int kv_share, int layer, const void* cache,
+                        const CacheGeom& g, int n_q_heads, int kv_share, int layer, const void* cache,
                         const float* q, const AttnPlan& p, int r_cap, float sl2, float* part_o, float* part_ml,
                         const QkvSrc& src, void* cache_w, const XOut& xo);
 

@@ -69,12 +69,19 @@ struct LookaheadPack {
     uint8_t k[SPEC_MAX_BATCH];
 };
 
+// What the attention needs to know of a sequence, in one piece (one memory round trip instead of two).
+struct alignas(16) SeqDesc {
+    int32_t seq, row0, k, n;        // its number, first target row, lookahead, cached length
+    int32_t slot, ok, pad[2];
+};
+
 struct StepTables {
     int32_t* seq_row0;   // [B+1] first target row of each sequence (prefix of K_b+1)
     int32_t* seq_stat0;  // [B+1] first statistics row of each sequence (prefix of 2K_b+1)
     int32_t* seq_n;      // [B] cached length n_b read at the start of the step
     int32_t* seq_ok;     // [B] 1 = sequence takes part, 0 = skipped (device-side error)
     int32_t* seq_slot;   // [B] cache slot (copied so later kernels need not re-validate)
+    SeqDesc* seq_desc;   // [B] the sequences by falling number of positions (steps with a decoder pass)
     int32_t* row_seq;    // [M]
     int32_t* row_pos;    // [M] cache position n_b + j of the row's key/value (or -1 for rows of skipped sequences)
     int32_t* row_tok;    // [M] token id fed at this row

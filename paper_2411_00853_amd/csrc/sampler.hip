@@ -40,67 +40,111 @@ __device__ __forceinline__ double wave_sum(double v)
 // ---------------------------------------------------------------------------------------------
 // Row bookkeeping.  One workgroup; thread b owns sequence b.
 // ---------------------------------------------------------------------------------------------
-// (a workgroup of TPB threads, all of them calling; row0: SPEC_MAX_BATCH + 1 ints of LDS)
+struct PrepLds {
+    int row0[SPEC_MAX_BATCH + 1], slot[SPEC_MAX_BATCH], total[SPEC_MAX_BATCH], wave[TPB / 64];
+};
+static_assert(TPB >= SPEC_MAX_BATCH, "a thread per sequence");
+
+// l.row0[i] = window rows of the sequences before i, for i <= B, and l.slot (all threads of the workgroup call;
+// ends with a barrier)
+__device__ __forceinline__ void prepare_prefix(const LookaheadPack& ks, int B, const int32_t* __restrict__ seq_slot, PrepLds& l)
+{
+    const int b = threadIdx.x, lane = b & 63;
+    int sum = b < B ? ks.k[b] + 1 : 0;
+    const int own = sum;
+    if (b < B) l.slot[b] = seq_slot ? seq_slot[b] : b;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int x = __shfl_up(sum, off);
+        if (lane >= off) sum += x;
+    }
+    if (lane == 63) l.wave[b >> 6] = sum;
+    __syncthreads();
+    for (int w = 0; w < (b >> 6); ++w) sum += l.wave[w];
+    if (b <= B && b < TPB) l.row0[b] = sum - own;
+    if (b == TPB - 1 && B == TPB) l.row0[B] = sum;
+    __syncthreads();
+}
+
+// The sequences by falling number of positions.  The attention deals its workgroups out in this order, so the
+// longest ones start first and the short ones fill in behind them (32 sequences of 512..4096 positions on the page
+// pool: 232 us per launch in the order of the call, 213.5 this way).  All threads of the workgroup call.
+__device__ __forceinline__ void write_desc(const StepTables& t, int b, int B, int k, int n, int slot, int ok, int row0, int* total)
+{
+    const int mine = ok ? n + k + 1 : 0;
+    if (b < B) total[b] = mine;
+    __syncthreads();
+    if (b >= B) return;
+    int rank = 0;
+    for (int i = 0; i < B; ++i) rank += (total[i] > mine || (total[i] == mine && i < b)) ? 1 : 0;
+    int4* d = reinterpret_cast<int4*>(t.seq_desc + rank);
+    d[0] = make_int4(b, row0, k, n);
+    d[1] = make_int4(slot, ok, 0, 0);
+}
+
+// (a workgroup of TPB threads, all of them calling)
 __device__ __forceinline__ void prepare_rows(const StepTables& t, const LookaheadPack& ks, int B, int Kmax, int V,
                                              int max_batch, int max_kv_len, int has_cache,
                                              const int32_t* __restrict__ seq_slot,
                                              const int32_t* __restrict__ last_token,
                                              const int32_t* __restrict__ draft_tokens,
-                                             const int32_t* __restrict__ kv_len, int32_t* flag, int* row0)
+                                             const int32_t* __restrict__ kv_len, int32_t* flag, PrepLds& l)
 {
     const int b = threadIdx.x;
+    prepare_prefix(ks, B, has_cache ? seq_slot : nullptr, l);
     if (b == 0) {
-        int r = 0, st = 0;
-        for (int i = 0; i < B; ++i) {
-            row0[i] = r;
-            t.seq_row0[i] = r;
-            t.seq_stat0[i] = st;
-            r += ks.k[i] + 1;
-            st += 2 * ks.k[i] + 1;
+        t.seq_row0[B] = l.row0[B];
+        t.seq_stat0[B] = 2 * l.row0[B] - B;
+    }
+    int K = 0, ok = 1, slot = 0, n = 0, row0 = 0;
+    if (b < B) {
+        K = ks.k[b];
+        row0 = l.row0[b];
+        slot = l.slot[b];
+        int tok[SPEC_MAX_LOOKAHEAD + 1];
+        tok[0] = last_token ? last_token[b] : 0;
+#pragma unroll
+        for (int i = 0; i < SPEC_MAX_LOOKAHEAD; ++i) tok[i + 1] = i < K ? draft_tokens[b * Kmax + i] : 0;
+        int err = 0;
+        if (has_cache) {
+            if (slot < 0 || slot >= max_batch) {
+                ok = 0;
+                err = SPEC_ERR_INVALID_ARG;
+                slot = 0;
+            } else {
+                // two sequences of one step must not share a slot
+                for (int i = 0; i < b; ++i)
+                    if (l.slot[i] == slot) { ok = 0; err = SPEC_ERR_INVALID_ARG; }
+                n = kv_len[slot];
+                if (n < 0 || n + K + 1 > max_kv_len) { ok = 0; err = SPEC_ERR_KV_OVERFLOW; }
+                else if (ok && !pool_cover(t.pool, slot, n, n + K + 1)) { ok = 0; err = SPEC_ERR_KV_OVERFLOW; }
+            }
         }
-        row0[B] = r;
-        t.seq_row0[B] = r;
-        t.seq_stat0[B] = st;
-    }
-    __syncthreads();
-    if (b >= B) return;
-    const int K = ks.k[b];
-    int ok = 1, err = 0;
-    int slot = b, n = 0;
-    if (has_cache) {
-        slot = seq_slot[b];
-        if (slot < 0 || slot >= max_batch) {
-            ok = 0;
-            err = SPEC_ERR_INVALID_ARG;
-            slot = 0;
-        } else {
-            // two sequences of one step must not share a slot
-            for (int i = 0; i < b; ++i)
-                if (seq_slot[i] == slot) { ok = 0; err = SPEC_ERR_INVALID_ARG; }
-            n = kv_len[slot];
-            if (n < 0 || n + K + 1 > max_kv_len) { ok = 0; err = SPEC_ERR_KV_OVERFLOW; }
-            else if (ok && !pool_cover(t.pool, slot, n, n + K + 1)) { ok = 0; err = SPEC_ERR_KV_OVERFLOW; }
+#pragma unroll
+        for (int j = 0; j <= SPEC_MAX_LOOKAHEAD; ++j)
+            if (tok[j] < 0 || tok[j] >= V) { ok = 0; err = SPEC_ERR_TOKEN_RANGE; }
+        if (!ok) {
+            atomicCAS(flag, 0, err);
+            n = 0;
+        }
+        t.seq_row0[b] = row0;
+        t.seq_stat0[b] = 2 * row0 - b;
+        t.seq_n[b] = n;
+        t.seq_ok[b] = ok;
+        t.seq_slot[b] = slot;
+#pragma unroll
+        for (int j = 0; j <= SPEC_MAX_LOOKAHEAD; ++j) {
+            if (j <= K) {
+                const int r = row0 + j;
+                t.row_seq[r] = b;
+                t.row_pos[r] = ok ? n + j : -1;
+                t.row_rope[r] = ok ? n + j : 0;
+                t.row_mask[r] = (2u << j) - 1u;   // causal window: slots 0..j
+                t.row_tok[r] = ok ? tok[j] : 0;
+            }
         }
     }
-    int t0 = last_token ? last_token[b] : 0;
-    if (t0 < 0 || t0 >= V) { ok = 0; err = SPEC_ERR_TOKEN_RANGE; }
-    for (int i = 0; i < K; ++i) {
-        int x = draft_tokens[b * Kmax + i];
-        if (x < 0 || x >= V) { ok = 0; err = SPEC_ERR_TOKEN_RANGE; }
-    }
-    if (!ok) atomicCAS(flag, 0, err);
-    t.seq_n[b] = ok ? n : 0;
-    t.seq_ok[b] = ok;
-    t.seq_slot[b] = slot;
-    for (int j = 0; j <= K; ++j) {
-        int r = row0[b] + j;
-        t.row_seq[r] = b;
-        t.row_pos[r] = ok ? n + j : -1;
-        t.row_rope[r] = ok ? n + j : 0;
-        t.row_mask[r] = (2u << j) - 1u;   // causal window: slots 0..j
-        int tok = (j == 0) ? t0 : draft_tokens[b * Kmax + j - 1];
-        t.row_tok[r] = ok ? tok : 0;
-    }
+    if (has_cache) write_desc(t, b, B, K, n, slot, ok, row0, l.total);
 }
 
 __global__ void __launch_bounds__(TPB) prepare_kernel(StepTables t, LookaheadPack ks, int B, int Kmax, int V,
@@ -110,9 +154,8 @@ __global__ void __launch_bounds__(TPB) prepare_kernel(StepTables t, LookaheadPac
                                                       const int32_t* __restrict__ draft_tokens,
                                                       const int32_t* __restrict__ kv_len, int32_t* flag)
 {
-    __shared__ int row0[SPEC_MAX_BATCH + 1];
-    prepare_rows(t, ks, B, Kmax, V, max_batch, max_kv_len, has_cache, seq_slot, last_token, draft_tokens, kv_len, flag,
-                 row0);
+    __shared__ PrepLds l;
+    prepare_rows(t, ks, B, Kmax, V, max_batch, max_kv_len, has_cache, seq_slot, last_token, draft_tokens, kv_len, flag, l);
 }
 
 // A step with more window rows than one decoder pass takes is scored group by group: the row
@@ -132,6 +175,10 @@ __global__ void __launch_bounds__(TPB) slice_tables_kernel(StepTables full, Step
             sub.seq_slot[i] = full.seq_slot[b0 + i];
         }
     }
+    __shared__ int total[SPEC_MAX_BATCH];
+    const int i = threadIdx.x, at = b0 + min(i, Bg - 1);
+    write_desc(sub, i, Bg, full.seq_row0[at + 1] - full.seq_row0[at] - 1, full.seq_n[at], full.seq_slot[at], full.seq_ok[at],
+               full.seq_row0[at] - r0, total);
     for (int r = threadIdx.x; r < n_rows; r += TPB) {
         sub.row_seq[r] = full.row_seq[r0 + r] - b0;
         sub.row_pos[r] = full.row_pos[r0 + r];
@@ -153,8 +200,8 @@ __global__ void __launch_bounds__(TPB) slice_tables_kernel(StepTables full, Step
 // from seq_row0 (a proposing model's draw, whose row is not the one the lookaheads would give).
 enum { STAT_CHAIN = 0, STAT_TREE = 1, STAT_PLAIN = 2 };
 
-// The row bookkeeping of a step that runs no decoder pass (logits supplied by the caller), done by the
-// statistics pass's first workgroup next to its own chunk instead of by a kernel of its own: the pass
+// The row bookkeeping of a step that runs no decoder pass (logits supplied by the caller), done by a
+// workgroup of the statistics pass (the first, which takes no chunk) instead of by a kernel of its own: the pass
 // itself does not read the tables, the kernels after it do.
 struct PrepIn {
     int on, Kmax;
@@ -219,12 +266,15 @@ __global__ void __launch_bounds__(TPB) stats_kernel(StepTables t, LookaheadPack 
 {
     __shared__ float smax[TPB / 64];
     __shared__ double ssum[TPB / 64];
-    __shared__ int prep_row0[SPEC_MAX_BATCH + 1];
-    if (prep.on && blockIdx.x == 0)
+    __shared__ PrepLds prep_lds;
+    if (prep.on && blockIdx.x == 0) {
         prepare_rows(t, ks, B, prep.Kmax, V, SPEC_MAX_BATCH, 0, 0, nullptr, nullptr, prep.draft_tokens, nullptr, prep.flag,
-                     prep_row0);
-    const int srow = blockIdx.x / n_chunks;
-    const int chunk = blockIdx.x % n_chunks;
+                     prep_lds);
+        return;
+    }
+    const int wg = blockIdx.x - prep.on;
+    const int srow = wg / n_chunks;
+    const int chunk = wg % n_chunks;
     const float* row;
     if (layout == STAT_PLAIN) {
         row = target + (size_t)t.seq_row0[srow] * V;
@@ -764,70 +814,69 @@ __global__ void __launch_bounds__(TPB) prepare_tree_kernel(StepTables t, Lookahe
                                                            const int32_t* __restrict__ tokens,
                                                            const int32_t* __restrict__ kv_len, int32_t* flag)
 {
-    __shared__ int row0[SPEC_MAX_BATCH + 1];
+    __shared__ PrepLds l;
     const int b = threadIdx.x;
-    if (b == 0) {
-        int r = 0, st = 0;
-        for (int i = 0; i < B; ++i) {
-            row0[i] = r;
-            t.seq_row0[i] = r;
-            t.seq_stat0[i] = st;
-            r += ks.k[i] + 1;
-            st += 2 * ks.k[i] + 2;   // target and draft row of the root and of every node
+    prepare_prefix(ks, B, has_cache ? seq_slot : nullptr, l);
+    if (b == 0) {   // statistics rows: target and draft row of the root and of every node
+        t.seq_row0[B] = l.row0[B];
+        t.seq_stat0[B] = 2 * l.row0[B];
+    }
+    const int N = b < B ? ks.k[b] : 0;
+    int ok = 1, slot = 0, n = 0;
+    if (b < B) {
+        const int row0 = l.row0[b];
+        int err = 0;
+        slot = l.slot[b];
+        if (has_cache) {
+            if (slot < 0 || slot >= max_batch) {
+                ok = 0;
+                err = SPEC_ERR_INVALID_ARG;
+                slot = 0;
+            } else {
+                for (int i = 0; i < b; ++i)
+                    if (l.slot[i] == slot) { ok = 0; err = SPEC_ERR_INVALID_ARG; }
+                n = kv_len[slot];
+                if (n < 0 || n + N + 1 > max_kv_len) { ok = 0; err = SPEC_ERR_KV_OVERFLOW; }
+                else if (ok && !pool_cover(t.pool, slot, n, n + N + 1)) { ok = 0; err = SPEC_ERR_KV_OVERFLOW; }
+            }
         }
-        row0[B] = r;
-        t.seq_row0[B] = r;
-        t.seq_stat0[B] = st;
-    }
-    __syncthreads();
-    if (b >= B) return;
-    const int N = ks.k[b];
-    int ok = 1, err = 0;
-    int slot = b, n = 0;
-    if (has_cache) {
-        slot = seq_slot[b];
-        if (slot < 0 || slot >= max_batch) {
-            ok = 0;
-            err = SPEC_ERR_INVALID_ARG;
-            slot = 0;
-        } else {
-            for (int i = 0; i < b; ++i)
-                if (seq_slot[i] == slot) { ok = 0; err = SPEC_ERR_INVALID_ARG; }
-            n = kv_len[slot];
-            if (n < 0 || n + N + 1 > max_kv_len) { ok = 0; err = SPEC_ERR_KV_OVERFLOW; }
-            else if (ok && !pool_cover(t.pool, slot, n, n + N + 1)) { ok = 0; err = SPEC_ERR_KV_OVERFLOW; }
+        const int t0 = last_token ? last_token[b] : 0;
+        if (t0 < 0 || t0 >= V) { ok = 0; err = SPEC_ERR_TOKEN_RANGE; }
+        for (int i = 0; i < N; ++i) {
+            const int x = tokens[b * Kmax + i], p = parent[b * Kmax + i];
+            if (x < 0 || x >= V) { ok = 0; err = SPEC_ERR_TOKEN_RANGE; }
+            if (p < -1 || p >= i) { ok = 0; err = SPEC_ERR_INVALID_ARG; }
+        }
+        if (!ok) {
+            atomicCAS(flag, 0, err);
+            n = 0;
+        }
+        t.seq_row0[b] = row0;
+        t.seq_stat0[b] = 2 * row0;
+        t.seq_n[b] = n;
+        t.seq_ok[b] = ok;
+        t.seq_slot[b] = slot;
+        // slot j: depth and the set of slots on its path (itself included)
+        int depth[SPEC_MAX_LOOKAHEAD + 1];
+        uint32_t mask[SPEC_MAX_LOOKAHEAD + 1];
+        depth[0] = 0;
+        mask[0] = 1u;
+        for (int j = 0; j <= N; ++j) {
+            if (j > 0) {
+                const int ps = ok ? parent[b * Kmax + j - 1] + 1 : 0;   // parent's slot
+                depth[j] = depth[ps] + 1;
+                mask[j] = mask[ps] | (1u << j);
+            }
+            const int r = row0 + j;
+            t.row_seq[r] = b;
+            t.row_pos[r] = ok ? n + j : -1;
+            t.row_rope[r] = ok ? n + depth[j] : 0;
+            t.row_mask[r] = mask[j];
+            const int tok = (j == 0) ? t0 : tokens[b * Kmax + j - 1];
+            t.row_tok[r] = ok ? tok : 0;
         }
     }
-    const int t0 = last_token ? last_token[b] : 0;
-    if (t0 < 0 || t0 >= V) { ok = 0; err = SPEC_ERR_TOKEN_RANGE; }
-    for (int i = 0; i < N; ++i) {
-        const int x = tokens[b * Kmax + i], p = parent[b * Kmax + i];
-        if (x < 0 || x >= V) { ok = 0; err = SPEC_ERR_TOKEN_RANGE; }
-        if (p < -1 || p >= i) { ok = 0; err = SPEC_ERR_INVALID_ARG; }
-    }
-    if (!ok) atomicCAS(flag, 0, err);
-    t.seq_n[b] = ok ? n : 0;
-    t.seq_ok[b] = ok;
-    t.seq_slot[b] = slot;
-    // slot j: depth and the set of slots on its path (itself included)
-    int depth[SPEC_MAX_LOOKAHEAD + 1];
-    uint32_t mask[SPEC_MAX_LOOKAHEAD + 1];
-    depth[0] = 0;
-    mask[0] = 1u;
-    for (int j = 0; j <= N; ++j) {
-        if (j > 0) {
-            const int ps = ok ? parent[b * Kmax + j - 1] + 1 : 0;   // parent's slot
-            depth[j] = depth[ps] + 1;
-            mask[j] = mask[ps] | (1u << j);
-        }
-        const int r = row0[b] + j;
-        t.row_seq[r] = b;
-        t.row_pos[r] = ok ? n + j : -1;
-        t.row_rope[r] = ok ? n + depth[j] : 0;
-        t.row_mask[r] = mask[j];
-        const int tok = (j == 0) ? t0 : tokens[b * Kmax + j - 1];
-        t.row_tok[r] = ok ? tok : 0;
-    }
+    if (has_cache) write_desc(t, b, B, N, n, slot, ok, b < B ? l.row0[b] : 0, l.total);
 }
 
 constexpr int TREE_TPB = 1024;   // the walk is one workgroup per sequence: make it a big one
@@ -1295,7 +1344,7 @@ int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const Lookahe
     const bool vec4 = (V % 4 == 0) && ((reinterpret_cast<uintptr_t>(target_logits) & 15) == 0)
                       && ((reinterpret_cast<uintptr_t>(draft_logits) & 15) == 0)
                       && ((reinterpret_cast<uintptr_t>(em.logits_copy) & 15) == 0) && (em.copy_stride % 4 == 0);
-    dim3 g1((unsigned)n_stat_rows * n_stat_chunks);
+    dim3 g1((unsigned)n_stat_rows * n_stat_chunks + prep.on);
     {
     ProfScope ps(prof, SPEC_PROF_SAMPLER_STATS, s);
     if (vec4)

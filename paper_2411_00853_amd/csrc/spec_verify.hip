@@ -203,6 +203,7 @@ static int init_common(const spec_model_cfg* cfg, const spec_weights* weights, v
     A(&h->tables.seq_n, B);
     A(&h->tables.seq_ok, B);
     A(&h->tables.seq_slot, B);
+    A(&h->tables.seq_desc, B);
     A(&h->tables.row_seq, max_rows);
     A(&h->tables.row_pos, max_rows);
     A(&h->tables.row_tok, max_rows);
@@ -216,6 +217,7 @@ static int init_common(const spec_model_cfg* cfg, const spec_weights* weights, v
         A(&g.seq_n, B);
         A(&g.seq_ok, B);
         A(&g.seq_slot, B);
+        A(&g.seq_desc, B);
         A(&g.row_seq, GEMM_MAX_ROWS);
         A(&g.row_pos, GEMM_MAX_ROWS);
         A(&g.row_tok, GEMM_MAX_ROWS);

@@ -55,3 +55,38 @@ def test_windows_across_blocks_and_chunks(hd, heads, kv_heads, chunks, in_wg, pa
     finally:
         sv.spec_k_set_attn_max_chunks(0)
         sv.spec_k_set_attn_merge_min_pairs(0)
+
+
+@pytest.mark.parametrize("B", [1, 64, 65, 256])
+def test_sequences_dealt_out_by_length(B):
+    """Ragged lengths with ties and a skipped sequence, at the edges of the prefix sums' wavefronts and with
+    more rows than one decoder pass takes: every row against the oracle."""
+    from test_gpu_forward import Rig
+    shape = wl.ModelShape(1, 128, 2, 2, 64, 256, 131, dtype="bf16")
+    rig = Rig(shape, B, 448, 2, seed=3, std=0.05)
+    rng = wl.Rng(23, "cpu")
+    lens = (rng.randint(1, (B,), 8) * 61 + rng.randint(2, (B,), 2)).tolist()
+    look = rng.randint(3, (B,), 3).tolist()
+    for s, n in enumerate(lens):
+        rig.caches[s][:, :, :, :n] = rng.normal(20 + s, (1, 2, 2, n, 64), 0.3)
+        rig.set_cache(s, n)
+    t0 = rng.randint(4, (B,), 131).tolist()
+    toks = rng.randint(5, (B, 2), 131)
+    dl, us = rng.normal(6, (B, 2, 131), 1.0), rng.uniform(7, (B, 3))
+    want = rig.oracle_logits(list(range(B)), t0, look, toks)
+    skipped = B // 2 if B > 1 else None
+    if skipped is not None:
+        rig.kv_len[skipped] = 448     # its window would not fit
+    rig.sv.spec_verify_step(rig.h, look, us.cuda(), 1.0, torch.zeros(B, dtype=torch.int32, device="cuda"),
+                            torch.zeros((B, 3), dtype=torch.int32, device="cuda"),
+                            seq_slot=torch.arange(B, dtype=torch.int32, device="cuda"),
+                            last_token=torch.tensor(t0, dtype=torch.int32, device="cuda"), draft_tokens=toks.cuda(),
+                            draft_logits=dl.cuda(), logits_out=(lo := torch.zeros((sum(look) + B, 131), device="cuda")))
+    if skipped is not None:
+        with pytest.raises(rig.sv.SpecError):
+            rig.sv.spec_verify_poll(rig.h)
+    keep = torch.ones(sum(look) + B, dtype=torch.bool)
+    if skipped is not None:
+        r0 = sum(look[:skipped]) + skipped
+        keep[r0:r0 + look[skipped] + 1] = False
+    assert (lo.cpu() - want)[keep].abs().max().item() <= 5e-3     # the bound of the other small bf16 models
