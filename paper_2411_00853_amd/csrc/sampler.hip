@@ -225,6 +225,7 @@ __device__ __forceinline__ void find_stat_row(const LookaheadPack& ks, int B, in
     int base_st = 0, base_r = 0, b = 0, st = 0, r0 = 0, K = 0;
 #pragma unroll
     for (int g = 0; g < ROUNDS; ++g) {
+        if (g * 64 >= B) break;
         const int i = g * 64 + lane;
         const int k = kk[g];
         const int n = i < B ? 2 * k + 1 + (tree ? 1 : 0) : 0, r = i < B ? k + 1 : 0;
@@ -346,40 +347,80 @@ __global__ void __launch_bounds__(TPB) stats_kernel(StepTables t, LookaheadPack 
     }
 }
 
-// Combine the chunk statistics of one row: max of maxima, sums rescaled to it.
-__device__ __forceinline__ void combine_row(const float* pm, const double* ps, int n_chunks, double inv_T, float* m_out,
-                                            double* z_out)
+// Combine the chunk statistics of n_rows rows from row0 on: max of maxima, sums rescaled to it.  Every thread takes
+// its share of the (row, chunk) pairs -- one exp() each instead of one thread's row of them in turn, which was the
+// longest stretch of the kernels that begin with this -- and one thread per row adds them up in chunk order.
+// All THREADS threads of the workgroup call; row_m and row_z are in LDS and valid after the barrier it ends with.
+struct CombineLds {
+    static constexpr int PAIRS = 512;
+    float m[PAIRS];
+    double sum[PAIRS], e[PAIRS];
+};
+template <int THREADS>
+__device__ __forceinline__ void combine_rows(const float* part_max, const double* part_sum, int row0, int n_rows, int n_chunks,
+                                             double inv_T, float* row_m, double* row_z, CombineLds& l)
 {
-    // chunks eight at a time, the loads of a batch issued together (indices past the end clamped,
-    // their terms dropped): a plain loop over a run-time count waits for every load in turn
-    float m = -INFINITY;
-    for (int c0 = 0; c0 < n_chunks; c0 += 8) {
-        float v[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = pm[min(c0 + i, n_chunks - 1)];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) m = fmaxf(m, v[i]);   // a repeated value does not change the maximum
-    }
-    double z = 0.0;
-    for (int c0 = 0; c0 < n_chunks; c0 += 8) {
-        float v[8];
-        double sv[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            v[i] = pm[min(c0 + i, n_chunks - 1)];
-            sv[i] = ps[min(c0 + i, n_chunks - 1)];
+    constexpr int PER = (CombineLds::PAIRS + THREADS - 1) / THREADS;
+    const int tid = threadIdx.x;
+    if (n_chunks > CombineLds::PAIRS) {   // (vocabularies of millions: a thread per row walks its chunks)
+        if (tid < n_rows) {
+            const float* pm = part_max + (size_t)(row0 + tid) * n_chunks;
+            const double* ps = part_sum + (size_t)(row0 + tid) * n_chunks;
+            float m = -INFINITY;
+            for (int c = 0; c < n_chunks; ++c) m = fmaxf(m, pm[c]);
+            double z = 0.0;
+            for (int c = 0; c < n_chunks; ++c) z += ps[c] * exp((double)(pm[c] - m) * inv_T);
+            row_m[tid] = m;
+            row_z[tid] = z;
         }
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (c0 + i < n_chunks) z += sv[i] * exp((double)(v[i] - m) * inv_T);
+        __syncthreads();
+        return;
     }
-    *m_out = m;
-    *z_out = z;
+    // as many rows at a time as there is room for (their pairs lie one after the other in memory)
+    const int step = min(n_rows, CombineLds::PAIRS / n_chunks);
+    for (int r0 = 0; r0 < n_rows; r0 += step) {
+        const int rows = min(step, n_rows - r0), pairs = rows * n_chunks;
+        const float* pm = part_max + (size_t)(row0 + r0) * n_chunks;
+        const double* ps = part_sum + (size_t)(row0 + r0) * n_chunks;
+        float mv[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int p = tid + k * THREADS;
+            mv[k] = 0.f;
+            if (p < pairs) {
+                mv[k] = pm[p];
+                l.m[p] = mv[k];
+                l.sum[p] = ps[p];
+            }
+        }
+        __syncthreads();
+        if (tid < rows) {
+            float m = -INFINITY;
+            for (int c = 0; c < n_chunks; ++c) m = fmaxf(m, l.m[tid * n_chunks + c]);
+            row_m[r0 + tid] = m;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int p = tid + k * THREADS;
+            if (p < pairs) l.e[p] = exp((double)(mv[k] - row_m[r0 + p / n_chunks]) * inv_T);
+        }
+        __syncthreads();
+        if (tid < rows) {
+            double z = 0.0;
+            for (int c = 0; c < n_chunks; ++c) z += l.sum[tid * n_chunks + c] * l.e[tid * n_chunks + c];
+            row_z[r0 + tid] = z;
+        }
+        __syncthreads();
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
 // Pass 2: accept scan (every workgroup of a sequence repeats it: a handful of scalars) and the
 // mass of the final-draw distribution inside this workgroup's chunk of the vocabulary.
+// Two rows of logits stream through it, but what it waits for is the chain in front of them: statistics, test, and
+// only then the address of the rows (64 sequences x 32 chunks of a 128256 vocabulary: 18.5 us of which 10 are the
+// bytes; 20.5 with one thread per row combining the statistics and the proposals' logits requested after that).
 // ---------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(TPB) accept_mass_kernel(StepTables t, LookaheadPack ks, int Kmax, int V,
                                                           int n_stat_chunks, int n_res_chunks,
@@ -399,27 +440,29 @@ __global__ void __launch_bounds__(TPB) accept_mass_kernel(StepTables t, Lookahea
     const int K = ks.k[b];
     const double inv_T = (double)inv_T_f;
     const int st0 = t.seq_stat0[b];
-    if ((int)threadIdx.x < 2 * K + 1)
-        combine_row(part_max + (size_t)(st0 + threadIdx.x) * n_stat_chunks,
-                    part_sum + (size_t)(st0 + threadIdx.x) * n_stat_chunks, n_stat_chunks, inv_T,
-                    &row_m[threadIdx.x], &row_z[threadIdx.x]);
-    __syncthreads();
     const float* trow0 = target + (size_t)t.seq_row0[b] * V;
     const float* drow0 = draft + (size_t)b * Kmax * V;
+    // lane i tests proposal i (all positions at once: the tests are independent, only the first
+    // failure matters); padding lanes repeat the last proposal and are masked out.  Its logits are requested
+    // before the statistics are put together: that is one chain of memory round trips less in a row.
+    const int i = min((int)threadIdx.x, max(K - 1, 0));
+    float lp_x = 0.f, lq_x = 0.f;
+    double u = 0.0;
+    if (threadIdx.x < 64 && K > 0) {
+        const int x = draft_tokens[b * Kmax + i];
+        const bool xin = x >= 0 && x < V;   // out-of-range ids were flagged by prepare; stay in bounds
+        u = (double)uniforms[b * u_stride + i];
+        lp_x = xin ? trow0[(size_t)i * V + x] : 0.f;
+        lq_x = xin ? drow0[(size_t)i * V + x] : 0.f;
+    }
+    __shared__ CombineLds comb;
+    combine_rows<TPB>(part_max, part_sum, st0, 2 * K + 1, n_stat_chunks, inv_T, row_m, row_z, comb);
     if (threadIdx.x < 64) {
-        // lane i tests proposal i (all positions at once: the tests are independent, only the first
-        // failure matters); padding lanes repeat the last proposal and are masked out
-        const int i = min((int)threadIdx.x, max(K - 1, 0));
         bool keep = true;
         if (K > 0) {
-            const int x = draft_tokens[b * Kmax + i];
-            const bool xin = x >= 0 && x < V;   // out-of-range ids were flagged by prepare; stay in bounds
-            const float lp = xin ? trow0[(size_t)i * V + x] : 0.f;
-            const float lq = xin ? drow0[(size_t)i * V + x] : 0.f;
-            const double ep = exp((double)(lp - row_m[i]) * inv_T);
-            const double eq = exp((double)(lq - row_m[K + 1 + i]) * inv_T);
+            const double ep = exp((double)(lp_x - row_m[i]) * inv_T);
+            const double eq = exp((double)(lq_x - row_m[K + 1 + i]) * inv_T);
             // keep iff u * q(x) < p(x)  <=>  u * eq * Zp < ep * Zq
-            const double u = (double)uniforms[b * u_stride + i];
             keep = u * eq * row_z[i] < ep * row_z[K + 1 + i];
         }
         const unsigned long long failed = __ballot(!keep && (int)threadIdx.x < K);
@@ -474,6 +517,8 @@ __global__ void __launch_bounds__(TPB) accept_mass_kernel(StepTables t, Lookahea
 
 // ---------------------------------------------------------------------------------------------
 // Pass 3: locate u*S among the chunk masses, scan that chunk in ascending token id, emit.
+// Latency only, one workgroup per sequence (11 -> 9.3 us at 64 sequences: the masses walked eight at a time, padding
+// between the lanes' ids in LDS, where 128 bytes from lane to lane put all of them on one bank).
 // ---------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(TPB) final_draw_kernel(StepTables t, LookaheadPack ks, int Kmax, int V,
                                                          int n_res_chunks, const float* __restrict__ target,
@@ -484,7 +529,7 @@ __global__ void __launch_bounds__(TPB) final_draw_kernel(StepTables t, Lookahead
                                                          int32_t* kv_len, int32_t* __restrict__ n_accepted,
                                                          int32_t* __restrict__ out_tokens, DrawEmit emit)
 {
-    __shared__ double r[RES_CHUNK];
+    __shared__ double r[RES_CHUNK + RES_CHUNK / 16];   // 16 consecutive ids per lane, a word of padding between lanes
     __shared__ double wave_tot[TPB / 64];
     __shared__ int s_chunk, s_tok;
     __shared__ double s_before, s_target;
@@ -502,32 +547,58 @@ __global__ void __launch_bounds__(TPB) final_draw_kernel(StepTables t, Lookahead
         for (int i = threadIdx.x; i <= Kmax; i += TPB) out_tokens[b * (Kmax + 1) + i] = -1;
         return;
     }
+    // everything that does not depend on the chunk is requested at once, the chunk masses by as many lanes
     const int a = w.accepted[b];
+    const int row0 = t.seq_row0[b];
+    const float mp = w.row_max[2 * b], mq = w.row_max[2 * b + 1];
+    const double izp = w.row_inv_z[2 * b], izq = w.row_inv_z[2 * b + 1];
+    const double u = (double)uniforms[b * u_stride + K];
     bool residual = a < K;
-    // the chunk masses, fetched by as many lanes at once and then walked by one from LDS
     __shared__ double s_mass[TPB];
     const double* mass = w.chunk_mass + (size_t)b * n_res_chunks;
-    if (n_res_chunks <= TPB) {
-        if ((int)threadIdx.x < n_res_chunks) s_mass[threadIdx.x] = mass[threadIdx.x];
-        __syncthreads();
-        mass = s_mass;
-    }
+    const bool in_lds = n_res_chunks <= TPB;
+    if (in_lds) s_mass[threadIdx.x] = (int)threadIdx.x < n_res_chunks ? mass[threadIdx.x] : 0.0;
+    __syncthreads();
     if (threadIdx.x == 0) {
+        // one lane walks the masses in chunk order, eight at a time (past the end: zeros, which change nothing)
+        auto eight = [&](int c, double(&v)[8]) {
+            if (in_lds) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = s_mass[min(c + k, TPB - 1)];
+            } else {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = mass[min(c + k, n_res_chunks - 1)];
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = c + k < n_res_chunks ? v[k] : 0.0;
+        };
         double S = 0.0;
-        for (int c = 0; c < n_res_chunks; ++c) S += mass[c];
+        for (int c = 0; c < n_res_chunks; c += 8) {
+            double v[8];
+            eight(c, v);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) S += v[k];
+        }
         // S > 0 always holds for the extra-token row; for a residual it holds in exact arithmetic
         // (a rejection means p(x) < q(x), so p exceeds q elsewhere).  S <= 0 falls back to p_a below.
         s_before = S;
         s_chunk = -1;
         if (S > 0.0) {
-            const double target_mass = (double)uniforms[b * u_stride + K] * S;
+            const double target_mass = u * S;
             double c0 = 0.0;
             int pick = -1, last_pos = -1;
             double last_before = 0.0;
-            for (int c = 0; c < n_res_chunks; ++c) {
-                if (mass[c] > 0.0) { last_pos = c; last_before = c0; }
-                if (c0 + mass[c] > target_mass) { pick = c; break; }
-                c0 += mass[c];
+            for (int c = 0; c < n_res_chunks && pick < 0; c += 8) {
+                double v[8];
+                eight(c, v);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    if (pick < 0) {
+                        if (v[k] > 0.0) { last_pos = c + k; last_before = c0; }
+                        if (c0 + v[k] > target_mass) pick = c + k;
+                        else c0 += v[k];
+                    }
+                }
             }
             if (pick < 0) { pick = last_pos; c0 = last_before; }
             s_chunk = pick;
@@ -536,10 +607,8 @@ __global__ void __launch_bounds__(TPB) final_draw_kernel(StepTables t, Lookahead
         }
     }
     __syncthreads();
-    const float* prow = target + (size_t)(t.seq_row0[b] + a) * V;
+    const float* prow = target + (size_t)(row0 + a) * V;
     const float* qrow = draft + ((size_t)b * Kmax + (residual ? a : 0)) * V;
-    const float mp = w.row_max[2 * b], mq = w.row_max[2 * b + 1];
-    const double izp = w.row_inv_z[2 * b], izq = w.row_inv_z[2 * b + 1];
     int c_lo = s_chunk, c_hi = s_chunk + 1;
     double before = s_before, target_mass = s_target;
     if (s_chunk < 0) {   // degenerate residual: draw from p_a over the whole vocabulary, chunk by chunk
@@ -547,7 +616,7 @@ __global__ void __launch_bounds__(TPB) final_draw_kernel(StepTables t, Lookahead
         c_lo = 0;
         c_hi = n_res_chunks;
         before = 0.0;
-        target_mass = (double)uniforms[b * u_stride + K];   // p_a sums to 1
+        target_mass = u;   // p_a sums to 1
     }
     if (threadIdx.x == 0) s_tok = -1;
     int last_positive = -1;
@@ -573,7 +642,7 @@ __global__ void __launch_bounds__(TPB) final_draw_kernel(StepTables t, Lookahead
                     double qv = (double)__expf((lq[k] - mq) * inv_T_f) * izq;
                     pv = pv > qv ? pv - qv : 0.0;
                 }
-                r[i] = i < lim ? pv : 0.0;
+                r[i + i / PER] = i < lim ? pv : 0.0;
             }
         }
         __syncthreads();
@@ -582,7 +651,7 @@ __global__ void __launch_bounds__(TPB) final_draw_kernel(StepTables t, Lookahead
         int my_last = -1;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            double x = r[threadIdx.x * PER + i];
+            double x = r[threadIdx.x * (PER + 1) + i];
             loc += x;
             if (x > 0.0) my_last = base + threadIdx.x * PER + i;
         }
@@ -604,7 +673,7 @@ __global__ void __launch_bounds__(TPB) final_draw_kernel(StepTables t, Lookahead
             int tok = -1;
 #pragma unroll
             for (int i = 0; i < PER; ++i) {
-                cdf += r[threadIdx.x * PER + i];
+                cdf += r[threadIdx.x * (PER + 1) + i];
                 if (tok < 0 && cdf > target_mass) tok = base + threadIdx.x * PER + i;
             }
             if (tok < 0) tok = my_last;   // rounding between the lane sum and the running sum
@@ -814,6 +883,7 @@ __global__ void __launch_bounds__(TPB) prepare_tree_kernel(StepTables t, Lookahe
                                                            const int32_t* __restrict__ tokens,
                                                            const int32_t* __restrict__ kv_len, int32_t* flag)
 {
+    __shared__ uint16_t s_mask[SPEC_MAX_LOOKAHEAD + 1][TPB];
     __shared__ PrepLds l;
     const int b = threadIdx.x;
     prepare_prefix(ks, B, has_cache ? seq_slot : nullptr, l);
@@ -825,6 +895,14 @@ __global__ void __launch_bounds__(TPB) prepare_tree_kernel(StepTables t, Lookahe
     int ok = 1, slot = 0, n = 0;
     if (b < B) {
         const int row0 = l.row0[b];
+        // all of a sequence's nodes requested together
+        int tok[SPEC_MAX_LOOKAHEAD + 1], par[SPEC_MAX_LOOKAHEAD];
+        tok[0] = last_token ? last_token[b] : 0;
+#pragma unroll
+        for (int i = 0; i < SPEC_MAX_LOOKAHEAD; ++i) {
+            tok[i + 1] = i < N ? tokens[b * Kmax + i] : 0;
+            par[i] = i < N ? parent[b * Kmax + i] : -1;
+        }
         int err = 0;
         slot = l.slot[b];
         if (has_cache) {
@@ -840,12 +918,11 @@ __global__ void __launch_bounds__(TPB) prepare_tree_kernel(StepTables t, Lookahe
                 else if (ok && !pool_cover(t.pool, slot, n, n + N + 1)) { ok = 0; err = SPEC_ERR_KV_OVERFLOW; }
             }
         }
-        const int t0 = last_token ? last_token[b] : 0;
-        if (t0 < 0 || t0 >= V) { ok = 0; err = SPEC_ERR_TOKEN_RANGE; }
-        for (int i = 0; i < N; ++i) {
-            const int x = tokens[b * Kmax + i], p = parent[b * Kmax + i];
-            if (x < 0 || x >= V) { ok = 0; err = SPEC_ERR_TOKEN_RANGE; }
-            if (p < -1 || p >= i) { ok = 0; err = SPEC_ERR_INVALID_ARG; }
+        if (tok[0] < 0 || tok[0] >= V) { ok = 0; err = SPEC_ERR_TOKEN_RANGE; }
+#pragma unroll
+        for (int i = 0; i < SPEC_MAX_LOOKAHEAD; ++i) {
+            if (tok[i + 1] < 0 || tok[i + 1] >= V) { ok = 0; err = SPEC_ERR_TOKEN_RANGE; }
+            if (par[i] < -1 || par[i] >= i) { ok = 0; err = SPEC_ERR_INVALID_ARG; }
         }
         if (!ok) {
             atomicCAS(flag, 0, err);
@@ -856,30 +933,27 @@ __global__ void __launch_bounds__(TPB) prepare_tree_kernel(StepTables t, Lookahe
         t.seq_n[b] = n;
         t.seq_ok[b] = ok;
         t.seq_slot[b] = slot;
-        // slot j: depth and the set of slots on its path (itself included)
-        int depth[SPEC_MAX_LOOKAHEAD + 1];
-        uint32_t mask[SPEC_MAX_LOOKAHEAD + 1];
-        depth[0] = 0;
-        mask[0] = 1u;
-        for (int j = 0; j <= N; ++j) {
-            if (j > 0) {
-                const int ps = ok ? parent[b * Kmax + j - 1] + 1 : 0;   // parent's slot
-                depth[j] = depth[ps] + 1;
-                mask[j] = mask[ps] | (1u << j);
+        // slot j's set of slots on its path (itself included); its depth is their number
+#pragma unroll
+        for (int j = 0; j <= SPEC_MAX_LOOKAHEAD; ++j) {
+            if (j <= N) {
+                uint32_t mask = 1u;
+                if (j > 0) mask = s_mask[ok ? par[j - 1] + 1 : 0][b] | (1u << j);   // its parent's slot
+                s_mask[j][b] = (uint16_t)mask;
+                const int r = row0 + j;
+                t.row_seq[r] = b;
+                t.row_pos[r] = ok ? n + j : -1;
+                t.row_rope[r] = ok ? n + __popc(mask) - 1 : 0;
+                t.row_mask[r] = mask;
+                t.row_tok[r] = ok ? tok[j] : 0;
             }
-            const int r = row0 + j;
-            t.row_seq[r] = b;
-            t.row_pos[r] = ok ? n + j : -1;
-            t.row_rope[r] = ok ? n + depth[j] : 0;
-            t.row_mask[r] = mask[j];
-            const int tok = (j == 0) ? t0 : tokens[b * Kmax + j - 1];
-            t.row_tok[r] = ok ? tok : 0;
         }
     }
     if (has_cache) write_desc(t, b, B, N, n, slot, ok, b < B ? l.row0[b] : 0, l.total);
 }
 
 constexpr int TREE_TPB = 1024;   // the walk is one workgroup per sequence: make it a big one
+constexpr int TREE_CHUNKS = 64;  // its final draw keeps the masses of as many chunks of RES_CHUNK ids
 
 struct TreeOut {
     int32_t* n_accepted;   // [B]
@@ -891,6 +965,9 @@ struct TreeOut {
 // distribution p; a child with token x is kept iff u * q(x) < r(x); every rejection replaces r by
 // max(0, r - q) renormalised.  r is never materialised: r_k(v) is recomputed from p(v), q(v) and the
 // masses S_1..S_k of the earlier levels, so a rejection costs one pass over the two logits rows.
+// One compute unit does a sequence: the passes are bound by its fp64 rate (divisions by the masses most of all) and by
+// memory round trips.  8 sequences, 10 nodes, vocabulary 32000: 77 us with full divisions, 8 elements in flight and a
+// barrier per chunk of the final draw; 59 as it is.
 __global__ void __launch_bounds__(TREE_TPB) tree_walk_kernel(StepTables t, LookaheadPack ks, int Kmax, int V,
                                                         int n_stat_chunks, const float* __restrict__ target,
                                                         const float* __restrict__ draft,
@@ -905,8 +982,9 @@ __global__ void __launch_bounds__(TREE_TPB) tree_walk_kernel(StepTables t, Looka
     __shared__ float row_m[2 * MAXN + 2];
     __shared__ double row_z[2 * MAXN + 2];
     __shared__ double level_S[MAXN + 1];     // level_S[k]: mass of the unnormalised r_k, k >= 1
+    __shared__ double level_I[MAXN + 1];     // 1 / level_S[k]
     __shared__ double wsum[TREE_TPB / 64];
-    __shared__ double r[RES_CHUNK];
+    __shared__ double r[RES_CHUNK + TREE_TPB];   // 4 consecutive ids per lane, a word of padding between lanes
     __shared__ int s_tok, s_chunk;
     __shared__ double s_val, s_before, s_target;
     const int b = blockIdx.x;
@@ -919,11 +997,8 @@ __global__ void __launch_bounds__(TREE_TPB) tree_walk_kernel(StepTables t, Looka
     }
     const double inv_T = (double)inv_T_f;
     const int st0 = t.seq_stat0[b];
-    if ((int)threadIdx.x < 2 * N + 2)
-        combine_row(part_max + (size_t)(st0 + threadIdx.x) * n_stat_chunks,
-                    part_sum + (size_t)(st0 + threadIdx.x) * n_stat_chunks, n_stat_chunks, inv_T,
-                    &row_m[threadIdx.x], &row_z[threadIdx.x]);
-    __syncthreads();
+    __shared__ CombineLds comb;
+    combine_rows<TREE_TPB>(part_max, part_sum, st0, 2 * N + 2, n_stat_chunks, inv_T, row_m, row_z, comb);
     const float* trow0 = target + (size_t)t.seq_row0[b] * V;
     const float* drow0 = draft + (size_t)b * (Kmax + 1) * V;
     const int32_t* par = parent + b * Kmax;
@@ -934,6 +1009,13 @@ __global__ void __launch_bounds__(TREE_TPB) tree_walk_kernel(StepTables t, Looka
     const float* qrow = drow0;
     float mp = row_m[0], mq = row_m[N + 1];
     double izp = 1.0 / row_z[0], izq = 1.0 / row_z[N + 1];
+    // x / level_S[k], rounded as a division is: y is the rounded reciprocal, the remainder of the rounded product is
+    // exact, and one step with it gives the rounded quotient (Markstein 1990; masses and values stay far from the ends
+    // of the exponent range).  3 fp64 instructions instead of 11, for each element and level.
+    auto div_S = [&](double x, int k) -> double {
+        const double y = level_I[k], q = x * y;
+        return fma(fma(-q, level_S[k], x), y, q);
+    };
     // r_level(v) from the two rows (level and the masses are uniform over the workgroup)
     auto resid = [&](float lp, float lq, int lev) -> double {
         double pv = (double)__expf((lp - mp) * inv_T_f) * izp;
@@ -941,7 +1023,7 @@ __global__ void __launch_bounds__(TREE_TPB) tree_walk_kernel(StepTables t, Looka
             const double qv = (double)__expf((lq - mq) * inv_T_f) * izq;
             pv = pv > qv ? pv - qv : 0.0;
             for (int k = 1; k < lev; ++k) {
-                pv = pv / level_S[k];
+                pv = div_S(pv, k);
                 pv = pv > qv ? pv - qv : 0.0;
             }
         }
@@ -1011,64 +1093,71 @@ __global__ void __launch_bounds__(TREE_TPB) tree_walk_kernel(StepTables t, Looka
         }
         // rejected: mass of max(0, r/S - q)
         double acc = 0.0;
-        const double div = level > 0 ? level_S[level] : 1.0;
-        for (int v0 = threadIdx.x; v0 < V; v0 += 8 * TREE_TPB) {
-            // eight elements per trip, loads first (indices past the end clamped, their terms dropped)
-            float lpv[8], lqv[8];
+        constexpr int UN = 16;
+        for (int v0 = threadIdx.x; v0 < V; v0 += UN * TREE_TPB) {
+            // sixteen elements per trip, loads first (indices past the end clamped, their terms dropped)
+            float lpv[UN], lqv[UN];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
+            for (int k = 0; k < UN; ++k) {
                 const int v = min(v0 + k * TREE_TPB, V - 1);
                 lpv[k] = prow[v];
                 lqv[k] = qrow[v];
             }
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
+            for (int k = 0; k < UN; ++k) {
                 double pv = resid(lpv[k], lqv[k], level);
-                if (level > 0) pv = pv / div;
+                if (level > 0) pv = div_S(pv, level);
                 const double qv = (double)__expf((lqv[k] - mq) * inv_T_f) * izq;
                 if (v0 + k * TREE_TPB < V) acc += pv > qv ? pv - qv : 0.0;
             }
         }
         const double S_new = block_sum(acc);
         if (S_new > 0.0) {   // <= 0 cannot happen in exact arithmetic; then r stays as it is
-            if (threadIdx.x == 0) level_S[level + 1] = S_new;
+            if (threadIdx.x == 0) {
+                level_S[level + 1] = S_new;
+                level_I[level + 1] = 1.0 / S_new;
+            }
             ++level;
         }
         __syncthreads();
     }
 
-    // final draw from r_level of the current node: chunk masses, then a scan inside one chunk
-    const int n_res_chunks = (V + RES_CHUNK - 1) / RES_CHUNK;
-    constexpr int PER = RES_CHUNK / TREE_TPB;
-    double total = 0.0;   // meaningful in thread 0
-    __shared__ double mass[64];
-    for (int c0 = 0; c0 < n_res_chunks; c0 += 64) {
-        for (int cc = c0; cc < min(c0 + 64, n_res_chunks); ++cc) {
-            const int base = cc * RES_CHUNK;
-            const int lim = min(RES_CHUNK, V - base);
-            double acc = 0.0;
-            {
-                float lpv[PER], lqv[PER];
+    // final draw from r_level of the current node: chunk masses, then a scan inside one chunk.  The loads of four
+    // chunks are in flight at a time, and the chunks' sums over the wavefronts meet behind one barrier.
+    const int n_res_chunks = (V + RES_CHUNK - 1) / RES_CHUNK;   // at most TREE_CHUNKS: the launch wrapper sees to it
+    constexpr int PER = RES_CHUNK / TREE_TPB, GR = 4, WAVES = TREE_TPB / 64;
+    __shared__ double mass[TREE_CHUNKS], mass_w[TREE_CHUNKS * WAVES];
+    for (int c0 = 0; c0 < n_res_chunks; c0 += GR) {
+        float lpv[GR][PER], lqv[GR][PER];
 #pragma unroll
-                for (int k = 0; k < PER; ++k) {
-                    const int i = min((int)threadIdx.x + k * TREE_TPB, lim - 1);
-                    lpv[k] = prow[base + i];
-                    lqv[k] = qrow[base + i];
-                }
+        for (int g = 0; g < GR; ++g)
 #pragma unroll
-                for (int k = 0; k < PER; ++k)
-                    if ((int)threadIdx.x + k * TREE_TPB < lim) acc += resid(lpv[k], lqv[k], level);
+            for (int k = 0; k < PER; ++k) {
+                const int v = min((c0 + g) * RES_CHUNK + (int)threadIdx.x + k * TREE_TPB, V - 1);
+                lpv[g][k] = prow[v];
+                lqv[g][k] = qrow[v];
             }
-            const double m = block_sum(acc);
-            if (threadIdx.x == 0) mass[cc - c0] = m;
+#pragma unroll
+        for (int g = 0; g < GR; ++g) {
+            double acc = 0.0;
+#pragma unroll
+            for (int k = 0; k < PER; ++k)
+                if ((c0 + g) * RES_CHUNK + (int)threadIdx.x + k * TREE_TPB < V) acc += resid(lpv[g][k], lqv[g][k], level);
+            acc = wave_sum(acc);
+            if ((threadIdx.x & 63) == 0 && c0 + g < n_res_chunks) mass_w[(c0 + g) * WAVES + (threadIdx.x >> 6)] = acc;
         }
-        __syncthreads();
-        if (threadIdx.x == 0)
-            for (int cc = c0; cc < min(c0 + 64, n_res_chunks); ++cc) total += mass[cc - c0];
-        if (n_res_chunks > 64) __syncthreads();
     }
-    // (vocabularies beyond 64 chunks of 4096 would need the masses kept in global memory; the
-    // launch wrapper rejects them)
+    __syncthreads();
+    if ((int)threadIdx.x < n_res_chunks) {
+        double m = 0.0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) m += mass_w[threadIdx.x * WAVES + w];   // fixed order
+        mass[threadIdx.x] = m;
+    }
+    __syncthreads();
+    double total = 0.0;   // meaningful in thread 0
+    if (threadIdx.x == 0)
+        for (int cc = 0; cc < n_res_chunks; ++cc) total += mass[cc];
     if (threadIdx.x == 0) {
         const double target_mass = (double)uniforms[b * (Kmax + 1) + N] * total;
         double c0 = 0.0, last_before = 0.0;
@@ -1101,7 +1190,7 @@ __global__ void __launch_bounds__(TREE_TPB) tree_walk_kernel(StepTables t, Looka
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
                 const int i = threadIdx.x + k * TREE_TPB;
-                r[i] = i < lim ? resid(lpv[k], lqv[k], level) : 0.0;
+                r[i + i / PER] = i < lim ? resid(lpv[k], lqv[k], level) : 0.0;
             }
         }
         __syncthreads();
@@ -1109,7 +1198,7 @@ __global__ void __launch_bounds__(TREE_TPB) tree_walk_kernel(StepTables t, Looka
         int my_last = -1;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const double x = r[threadIdx.x * PER + i];
+            const double x = r[threadIdx.x * (PER + 1) + i];
             loc += x;
             if (x > 0.0) my_last = base + threadIdx.x * PER + i;
         }
@@ -1130,7 +1219,7 @@ __global__ void __launch_bounds__(TREE_TPB) tree_walk_kernel(StepTables t, Looka
             int y = -1;
 #pragma unroll
             for (int i = 0; i < PER; ++i) {
-                cdf += r[threadIdx.x * PER + i];
+                cdf += r[threadIdx.x * (PER + 1) + i];
                 if (y < 0 && cdf > target_mass) y = base + threadIdx.x * PER + i;
             }
             if (y < 0) y = my_last;
@@ -1262,8 +1351,8 @@ int launch_tree_sampler(const StepTables& t, const SamplerWorkspace& w, const Lo
                         int32_t* path, Profiler* prof, hipStream_t s)
 {
     const int n_stat_chunks = (V + STAT_CHUNK - 1) / STAT_CHUNK;
-    if ((V + RES_CHUNK - 1) / RES_CHUNK > 64)
-        return fail(SPEC_ERR_SHAPE, "tree verification supports vocabularies up to %d", 64 * RES_CHUNK);
+    if ((V + RES_CHUNK - 1) / RES_CHUNK > TREE_CHUNKS)
+        return fail(SPEC_ERR_SHAPE, "tree verification supports vocabularies up to %d", TREE_CHUNKS * RES_CHUNK);
     const float inv_T = 1.0f / temperature;
     const bool vec4 = (V % 4 == 0) && ((reinterpret_cast<uintptr_t>(target_logits) & 15) == 0)
                       && ((reinterpret_cast<uintptr_t>(draft_logits) & 15) == 0);
@@ -1427,11 +1516,6 @@ int scratch_of_current_device(NoAllocScratch** out)
     return SPEC_OK;
 }
 
-__global__ void fill_i32_kernel(int32_t* __restrict__ p, int n, int32_t v)
-{
-    if ((int)threadIdx.x < n) p[threadIdx.x] = v;
-}
-
 }  // namespace
 }  // namespace specv
 
@@ -1471,10 +1555,8 @@ extern "C" int spec_sample_step_noalloc(int32_t vocab, int32_t max_lookahead, co
     int rc = scratch_of_current_device(&w);
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
-    // the array keeps the last call's contents: the flag must start at zero (a fill kernel, so that
-    // the call can be captured); every other entry that is read was written earlier in this call
-    hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, s, w->flag, 4, 0);
-    SPECV_LAUNCH_CHECK("fill_i32_kernel");
+    // the array keeps the last call's contents: every entry that is read was written earlier in this call (the flag is
+    // where the row bookkeeping reports; a call without a handle has no poll that would read it)
     StepTables t{};
     t.seq_row0 = w->seq_row0;
     t.seq_stat0 = w->seq_stat0;
