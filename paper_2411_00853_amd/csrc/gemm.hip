@@ -682,6 +682,14 @@ GemmPlan plan_gemm(int M, int N, int K, int cu_count, bool split_x)
         const int n2 = ranges_for((n_tiles + 2 * p.nt - 1) / (2 * p.nt));
         if ((kb_total + n2 - 1) / n2 * 32 <= 2048) p.cg = 2;
     }
+    // The same for wider matrices from 8 row tiles on, where the partial sums, written and read back (8 bytes per column
+    // for each range and row), move at least as much as the weights (2 K bytes).  Measured in steps of four layers with
+    // two tiles per wavefront against four: K = 2048 (1 to 3 times the weights), 120-189 rows -2.0..-3.0 %;
+    // K = 4096 (0.5 to 0.75 times: the 7B-shape QKV), 120-189 rows +0.3..+1.0 %.
+    if (p.mt >= 8 && p.nt == 4) {
+        const int s4 = ranges_for((n_tiles + 15) / 16);
+        if (8 * s4 * 16 * p.mt >= 2 * K && ranges_for((n_tiles + 7) / 8) < s4) p.nt = 2;
+    }
     const int wg_x = (n_tiles + p.cg * p.nt - 1) / (p.cg * p.nt);
     const int s = ranges_for(wg_x);
     p.n_split = s;
@@ -710,6 +718,13 @@ GemmPlan plan_gemm(int M, int N, int K, int cu_count, bool split_x)
             else p.cg = 3;
         }
     }
+    // Five and six row tiles: the same, as four column groups of three tiles (7B-shape, 88 rows: QKV 192 -> 256
+    // workgroups, gate/up 172 -> 230; a step of three layers 72 rows -3.0 %, 88 rows -1.4 %, a draft-sized model's
+    // -3.1 and -2.1 %).
+    if (p.mt >= 5 && p.mt <= 6 && p.nt == 4) {
+        const int wg3 = (n_tiles + 4 * 3 - 1) / (4 * 3) * s;
+        if (wg_x * s * 5 < cu_count * 4 && wg3 <= cu_count) p.nt = 3;
+    }
     // ranges start on a K group of the packed order so that every chunk is one contiguous run
     p.kb_per_split = ((kb_total + s - 1) / s + WPACK_KG - 1) / WPACK_KG * WPACK_KG;
     return p;
@@ -736,6 +751,8 @@ int launch_gemm_bf16(const GemmPlan& p, const void* x_frags, const void* w_packe
     SPECV_GEMM(4, 2, 2);
     SPECV_GEMM(5, 2, 2);
     SPECV_GEMM(6, 2, 2);
+    SPECV_GEMM(5, 3, 2);
+    SPECV_GEMM(6, 3, 2);
     SPECV_GEMM(5, 4, 2);
     SPECV_GEMM(6, 4, 2);
     SPECV_GEMM(8, 2, 1, 2);
