@@ -353,7 +353,8 @@ static AttnLaunchPlan plan_launch(const CacheGeom& g, bool paged, int n_q_heads,
     }
     // Two blocks: measured over 0..128 positions, 7B-shape paged step 5.04 -> 4.95 ms, decoding round 6.69 -> 6.62 ms,
     // contiguous 7B-shape, tree and long-context steps 0.2-0.7 % shorter, nothing longer (32 and 96 positions were
-    // slower than none: the main loop takes two blocks per trip).
+    // slower than none: the main loop takes two blocks per trip).  With the window attended to from LDS: a draft model's
+    // decode at batch 8 339.0 us with none, 337.9 with 32, 331.6 with 64; the other steps within 0.5 %.
     lp.p.lag_keys = 64;
     return lp;
 }
