@@ -173,24 +173,21 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
     // float4 columns' worth, the row's sums of squares and its rotary factors; the rest of a longer list is
     // fetched when the request is finished.
     constexpr int QC = 2 * STEPS, W0 = HD == 128 ? 2 : 4;
-    struct RowScale {
-        float4 a, b;
-    };
-    auto scale_issue = [&](int m, RowScale& r) {
-        if (!src.ns.ssq) return;
-        const float4* p = reinterpret_cast<const float4*>(src.ns.ssq + (size_t)m * src.ns.n_ssq);
-        r.a = p[0];
-        r.b = p[min(1, (src.ns.n_ssq >> 2) - 1)];
-    };
-    auto scale_finish = [&](int m, const RowScale& r) -> float {   // the arithmetic of row_inv_rms
-        if (!src.ns.ssq) return 1.f;
-        const int n4 = src.ns.n_ssq >> 2;
-        const float4* p = reinterpret_cast<const float4*>(src.ns.ssq + (size_t)m * src.ns.n_ssq);
-        float ss = (r.a.x + r.a.y) + (r.a.z + r.a.w);
-        ss += n4 > 1 ? (r.b.x + r.b.y) + (r.b.z + r.b.w) : 0.f;
-        for (int i = 2; i < n4; ++i) {
-            const float4 v = p[i];
-            ss += (v.x + v.y) + (v.z + v.w);
+    // Several lanes share a row: each fetches one pair of its sums of squares and they pass them around, so that
+    // a row of up to four pairs (4096 columns) costs a lane one 16-byte load and four registers.
+    auto scale_issue = [&](int m, int sub, double2& r) { r = src.ns.ssq[(size_t)m * src.ns.n_ssq + min(sub, src.ns.n_ssq - 1)]; };
+    // (lane0 + i * stride: the lane that fetched pair i; the arithmetic of row_inv_rms)
+    auto scale_finish = [&](int m, const double2& r, int lane0, int stride) -> float {
+        const float own = (float)(r.x + r.y);
+        float ss = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float v = __shfl(own, lane0 + i * stride);
+            ss += i < src.ns.n_ssq ? v : 0.f;
+        }
+        for (int i = 4; i < src.ns.n_ssq; ++i) {
+            const double2 v = src.ns.ssq[(size_t)m * src.ns.n_ssq + i];
+            ss += (float)(v.x + v.y);
         }
         return 1.0f / sqrtf(ss / (float)src.ns.d + src.ns.eps);
     };
@@ -209,7 +206,7 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
     };
     struct QRaw {
         float4 a[QC][W0], cs[STEPS / 2][4];
-        RowScale rs;
+        double2 ss;
         const float* p;
         int m;
     };
@@ -219,7 +216,7 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
         const int j = real ? rr / group : 0, hl = real ? rr % group : 0;
         r.m = row0 + j;
         r.p = src.partial + (size_t)r.m * src.ld + (hkv * group + hl) * HD + 8 * gq;   // 8 dims of every 32-dim step
-        scale_issue(r.m, r.rs);
+        scale_issue(r.m, gq, r.ss);
 #pragma unroll
         for (int c = 0; c < QC; ++c) range_issue(r.p + 32 * (c >> 1) + 4 * (c & 1), r.a[c]);
         const int rpos = t.tree ? t.row_rope[r.m] : n + j;
@@ -232,7 +229,7 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
     // Add up, scale, rotate and split them: dims d and d + HD/2 (a rotary pair) sit in steps s and
     // s + STEPS/2 of the same lane.
     auto q_finish = [&](int rt, const QRaw& r, float sc) {
-        const float rs = scale_finish(r.m, r.rs);
+        const float rs = scale_finish(r.m, r.ss, c16, 16);
         float4 sums[QC];
 #pragma unroll
         for (int c = 0; c < QC; ++c) sums[c] = range_finish(r.a[c]);
@@ -259,9 +256,9 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
 #pragma unroll
                 for (int h2 = 0; h2 < 2; ++h2) {
                     const int e = 2 * e4 + h2;
-                    const float a = raw[s][e], bq = raw[s + STEPS / 2][e];
-                    x0[e] = (a * ca[h2] - bq * sa[h2]) * sc;
-                    x1[e] = (a * sa[h2] + bq * ca[h2]) * sc;
+                    rotate_pair(raw[s][e], raw[s + STEPS / 2][e], ca[h2], sa[h2], x0[e], x1[e]);
+                    x0[e] *= sc;
+                    x1[e] *= sc;
                 }
             }
             split_frag(x0, qh[rt][s], ql[rt][s]);
@@ -304,7 +301,7 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
             const int kcol = n_q_heads * HD + hkc * HD, vcol = (n_q_heads + g.n_kv_heads) * HD + hkc * HD;
             for (int p0 = w0; p0 < w1; p0 += 8) {
                 float4 raw[NR][4][W0], cs[NR][2];
-                RowScale rsr[NR];
+                double2 ssr[NR];
                 int posr[NR];
                 auto col = [&](int h, int x) {
                     const float* prow = src.partial + (size_t)(row0 + (posr[h] - n)) * src.ld;
@@ -314,7 +311,7 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
                 for (int h = 0; h < NR; ++h) {
                     posr[h] = min(p0 + PPR * h + u, w1 - 1);   // clamped: the loads are unconditional
                     const int m = row0 + (posr[h] - n);
-                    scale_issue(m, rsr[h]);
+                    scale_issue(m, tq, ssr[h]);
 #pragma unroll
                     for (int x = 0; x < 4; ++x) range_issue(col(h, x), raw[h][x]);
                     const float* c2 = src.cos_sin + (size_t)(t.tree ? t.row_rope[m] : posr[h]) * HD + 2 * (4 * tq);
@@ -323,7 +320,7 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
                 }
 #pragma unroll
                 for (int h = 0; h < NR; ++h) {
-                    const float rs = scale_finish(row0 + (posr[h] - n), rsr[h]);
+                    const float rs = scale_finish(row0 + (posr[h] - n), ssr[h], u * LP, 1);
                     float4 kv4[4];
 #pragma unroll
                     for (int x = 0; x < 4; ++x) kv4[x] = range_finish(raw[h][x]);
@@ -351,8 +348,10 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
                         } k0, k1;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            k0.h[e] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(a[e] * co[e] - bk[e] * si[e]));
-                            k1.h[e] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(a[e] * si[e] + bk[e] * co[e]));
+                            float ra, rb;
+                            rotate_pair(a[e], bk[e], co[e], si[e], ra, rb);
+                            k0.h[e] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(ra));
+                            k1.h[e] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(rb));
                         }
                         *reinterpret_cast<ushort4*>(s_wk + w * WK_LD + 4 * tq) = k0.v;
                         *reinterpret_cast<ushort4*>(s_wk + w * WK_LD + 4 * tq + HALF) = k1.v;

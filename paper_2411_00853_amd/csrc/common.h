@@ -188,14 +188,16 @@ struct CacheGeom {
 
 CacheGeom make_cache_geom(const spec_model_cfg& c);
 
-// Row-wise sums of squares travel as SSQ_CHUNK-column partial sums ([M][n_ssq]).  RMSNorm is split
-// in two: the producer of a GEMM's input multiplies by the gain; the row's 1/rms factors out of the
-// dot product and is applied by the consumer of the GEMM's output (NormScale).
-// (A row has a multiple of four chunks, the last ones zero where need be: the consumer reads them 16 bytes at a time.)
+// Row-wise sums of squares travel as SSQ_CHUNK-column partial sums in fp64, two to a double2 ([M][n_ssq], n_ssq =
+// ssq_pairs(d), the last half zero where need be).  RMSNorm is split in two: the producer of a GEMM's input multiplies
+// by the gain; the row's 1/rms factors out of the dot product and is applied by the consumer of the GEMM's output
+// (NormScale).  A pair is rounded to fp32 once its halves have met, and the pairs are added in index order
+// (row_inv_rms): how many wavefronts share a row shows in no bit of the result.  (Chunks rounded one by one
+// move the logits by 1e-5, and a draw whose uniform lies that close to a step of the distribution with them.)
 constexpr int SSQ_CHUNK = 512;
-inline int ssq_chunks(int d) { return ((d + SSQ_CHUNK - 1) / SSQ_CHUNK + 3) / 4 * 4; }
+inline int ssq_pairs(int d) { return (d + 2 * SSQ_CHUNK - 1) / (2 * SSQ_CHUNK); }
 struct NormScale {
-    const float* ssq;   // NULL: no scaling
+    const double2* ssq;   // NULL: no scaling
     int n_ssq;
     int d;              // row length the mean is taken over
     float eps;
@@ -206,11 +208,11 @@ struct XOut {
     int mt, planes;
     float* plain;       // NULL on the bf16 path
 };
-int launch_embed(int dtype, const void* tok_embed, const int32_t* row_tok, int M, int d, float* x, float* ssq,
+int launch_embed(int dtype, const void* tok_embed, const int32_t* row_tok, int M, int d, float* x, double2* ssq,
                  const float* gain, const XOut& xo, hipStream_t s);
 // x[m] += sum of the n_split partial ranges ([n_split][M][ld], added in index order); ssq updated;
 // x * gain written as the next GEMM's operand
-int launch_resid(const float* partial, int n_split, size_t split_stride, int ld, int M, int d, float* x, float* ssq,
+int launch_resid(const float* partial, int n_split, size_t split_stride, int ld, int M, int d, float* x, double2* ssq,
                  const float* gain, const XOut& xo, hipStream_t s);
 int launch_silu_mul(const float* partial, int n_split, size_t split_stride, int ld, int M, int F, const NormScale& ns,
                     const XOut& xo, hipStream_t s);
@@ -218,7 +220,7 @@ int launch_rope_append(const float* partial, int n_split, size_t split_stride, i
                        const CacheGeom& g, int n_q_heads, int layer, const float* cos_sin, const NormScale& ns,
                        void* cache, float* q_out, hipStream_t s);
 int launch_reduce_splits(const float* partial, int n_split, size_t split_stride, int M, int N, int ld,
-                         const float* ssq, int n_ssq, int d, float eps, float* out, hipStream_t s);
+                         const double2* ssq, int n_ssq, int d, float eps, float* out, hipStream_t s);
 int launch_kv_copy(const CacheGeom& g, void* cache, int slot, int pos0, int n_pos, void* plain, bool to_cache,
                    hipStream_t s);
 int launch_tree_greedy(const StepTables& t, const SamplerWorkspace& w, const LookaheadPack& ks, int B, int Kmax, int V,
@@ -256,7 +258,7 @@ void set_gemm_wg_target(int workgroups);
 bool gemm_swiglu_fits(int M, int F, int cu_count);
 void set_swiglu_min_wgs(int workgroups);
 void set_swiglu_column_groups(int groups);
-int launch_gemm_swiglu(const void* x_frags, int planes, const void* w_gate_up, int M, int F, int K, const float* ssq,
+int launch_gemm_swiglu(const void* x_frags, int planes, const void* w_gate_up, int M, int F, int K, const double2* ssq,
                        int n_ssq, int d, float eps, void* act_frags, int act_mt, int act_planes, int cu_count, hipStream_t s);
 // fp32: y = x * W^T (F32_STORE), y += x * W^T (F32_ADD), or y[m][n] = silu(gate) * up with W = N gate rows then N up
 // rows (F32_SWIGLU).  gain != NULL: x is normalised first (RMSNorm over its K columns, times gain).

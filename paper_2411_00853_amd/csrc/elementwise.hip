@@ -31,7 +31,7 @@ template <typename T, bool EMBED>
 __global__ void __launch_bounds__(64) resid_kernel(const T* __restrict__ E, const int32_t* __restrict__ row_tok,
                                                          const float* __restrict__ partial, int n_split,
                                                          size_t split_stride, int ld, int d, float* __restrict__ x,
-                                                         float* __restrict__ ssq, const float* __restrict__ gain,
+                                                         double2* __restrict__ ssq, const float* __restrict__ gain,
                                                          XOut xo)
 {
     const int m = blockIdx.y, k8 = blockIdx.x * 64 + threadIdx.x;
@@ -61,7 +61,7 @@ __global__ void __launch_bounds__(64) resid_kernel(const T* __restrict__ E, cons
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-    if (threadIdx.x == 0) ssq[(size_t)m * gridDim.x + blockIdx.x] = (float)ss;
+    if (threadIdx.x == 0) reinterpret_cast<double*>(ssq)[(size_t)m * gridDim.x + blockIdx.x] = ss;
 }
 
 // act[m][f] = silu(gate) * up for 8 consecutive f per thread, gate and up first scaled by the row's
@@ -143,10 +143,8 @@ __global__ void __launch_bounds__(TPB) rope_append_tiled_kernel(const float* __r
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
         const float4 c2 = *reinterpret_cast<const float4*>(cs + 2 * e);   // cos, sin of two dims
-        ra[e] = a[e] * c2.x - b[e] * c2.y;
-        rb[e] = a[e] * c2.y + b[e] * c2.x;
-        ra[e + 1] = a[e + 1] * c2.z - b[e + 1] * c2.w;
-        rb[e + 1] = a[e + 1] * c2.w + b[e + 1] * c2.z;
+        rotate_pair(a[e], b[e], c2.x, c2.y, ra[e], rb[e]);
+        rotate_pair(a[e + 1], b[e + 1], c2.z, c2.w, ra[e + 1], rb[e + 1]);
     }
     if (head < n_q_heads) {
         const bool live = pos >= 0;   // row of a skipped sequence: defined output
@@ -190,8 +188,8 @@ __global__ void __launch_bounds__(64) rope_append_kernel(const float* __restrict
         const float* cs = cos_sin + (size_t)rope_pos * hd;   // [half][2]; depth in the window, not the slot
         for (int i = threadIdx.x; i < half; i += 64) {
             const float a = row[i], b = row[i + half];
-            const float c = cs[2 * i], s = cs[2 * i + 1];
-            const float ra = a * c - b * s, rb = a * s + b * c;
+            float ra, rb;
+            rotate_pair(a, b, cs[2 * i], cs[2 * i + 1], ra, rb);
             if (head < n_q_heads) {
                 q_out[(size_t)m * dq + head * hd + i] = ra;
                 q_out[(size_t)m * dq + head * hd + i + half] = rb;
@@ -390,11 +388,11 @@ CacheGeom make_cache_geom(const spec_model_cfg& c)
     return g;
 }
 
-int launch_embed(int dtype, const void* tok_embed, const int32_t* row_tok, int M, int d, float* x, float* ssq,
+int launch_embed(int dtype, const void* tok_embed, const int32_t* row_tok, int M, int d, float* x, double2* ssq,
                  const float* gain, const XOut& xo, hipStream_t s)
 {
     if (d % 8) return fail(SPEC_ERR_SHAPE, "d_model must be a multiple of 8");
-    const dim3 grid(ssq_chunks(d), M);
+    const dim3 grid(2 * ssq_pairs(d), M);
     if (dtype == SPEC_DTYPE_BF16)
         hipLaunchKernelGGL((resid_kernel<__bf16, true>), grid, dim3(64), 0, s, (const __bf16*)tok_embed, row_tok,
                            nullptr, 0, 0, 0, d, x, ssq, gain, xo);
@@ -405,11 +403,11 @@ int launch_embed(int dtype, const void* tok_embed, const int32_t* row_tok, int M
     return SPEC_OK;
 }
 
-int launch_resid(const float* partial, int n_split, size_t split_stride, int ld, int M, int d, float* x, float* ssq,
+int launch_resid(const float* partial, int n_split, size_t split_stride, int ld, int M, int d, float* x, double2* ssq,
                  const float* gain, const XOut& xo, hipStream_t s)
 {
     if (d % 8 || ld % 4 || split_stride % 4) return fail(SPEC_ERR_SHAPE, "residual rows must be multiples of 8 wide");
-    const dim3 grid(ssq_chunks(d), M);
+    const dim3 grid(2 * ssq_pairs(d), M);
     hipLaunchKernelGGL((resid_kernel<float, false>), grid, dim3(64), 0, s, nullptr, nullptr, partial, n_split,
                        split_stride, ld, d, x, ssq, gain, xo);
     SPECV_LAUNCH_CHECK("resid_kernel");
@@ -446,7 +444,7 @@ int launch_rope_append(const float* partial, int n_split, size_t split_stride, i
 }
 
 int launch_reduce_splits(const float* partial, int n_split, size_t split_stride, int M, int N, int ld,
-                         const float* ssq, int n_ssq, int d, float eps, float* out, hipStream_t s)
+                         const double2* ssq, int n_ssq, int d, float eps, float* out, hipStream_t s)
 {
     NormScale ns{ssq, n_ssq, d, eps};
     if (ld % 4 || split_stride % 4) return fail(SPEC_ERR_SHAPE, "partial sums must come in rows of multiples of 4");

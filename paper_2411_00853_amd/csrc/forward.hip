@@ -47,7 +47,7 @@ int forward_init(spec_handle* h, int max_rows)
         if (rc == SPEC_OK) rc = a.alloc(reinterpret_cast<void**>(p), count * sizeof(float));
     };
     A(&h->x, (size_t)max_rows * z.d);
-    A(&h->ssq, (size_t)max_rows * ssq_chunks(z.d));
+    A(reinterpret_cast<float**>(&h->ssq), (size_t)max_rows * ssq_pairs(z.d) * (sizeof(double2) / sizeof(float)));
     A(&h->q, (size_t)max_rows * z.dq);
     A(&h->att, (size_t)max_rows * z.dq);
     A(&h->act, (size_t)max_rows * z.F);
@@ -202,7 +202,7 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
         size_t stride;
         int ld;
     };
-    const int n_ssq = ssq_chunks(z.d);
+    const int n_ssq = ssq_pairs(z.d);
     const int mt = bf16 ? gemm_row_tiles(M) : 0;
     const int planes = h->split_act ? 2 : 1;
     const XOut to_xf{bf16 ? h->xf : nullptr, mt, planes, nullptr};            // operand of the next GEMM

@@ -56,20 +56,30 @@ __host__ __device__ inline size_t xfrag_uint4s(int mt_count, int planes, int K)
     return (size_t)(K / 32 + XFRAG_PAD_KB) * planes * mt_count * 64;
 }
 
+// A rotary pair (a, b) turned by the angle with cosine c and sine s.  Which product of each sum is rounded first is
+// written out: left to itself the compiler fuses one or the other from kernel to kernel and build to build, and
+// queries and keys come out an ulp apart.
+__device__ __forceinline__ void rotate_pair(float a, float b, float c, float s, float& ra, float& rb)
+{
+    ra = fmaf(a, c, -(b * s));
+    rb = fmaf(b, c, a * s);
+}
+
 // 1 / rms of a row from its partial sums of squares (eps inside the root); ssq == NULL -> 1
-// The partial sums (a multiple of four per row) are fetched eight at a time with clamped indices (surplus values
-// dropped), so that all loads of a batch are in flight together: a plain loop over a run-time count waits for
-// every load in turn, and this sits on the critical path of kernels that are nothing but latency.
-__device__ __forceinline__ float row_inv_rms(const float* ssq, int n_ssq, int m, int d, float eps)
+// The pairs are fetched four at a time with clamped indices (surplus values dropped), so that all loads of a
+// batch are in flight together: a plain loop over a run-time count waits for every load in turn, and this
+// sits on the critical path of kernels that are nothing but latency.
+__device__ __forceinline__ float row_inv_rms(const double2* ssq, int n_ssq, int m, int d, float eps)
 {
     if (!ssq) return 1.f;
     float ss = 0.f;
-    const float4* p = reinterpret_cast<const float4*>(ssq + (size_t)m * n_ssq);
-    const int n4 = n_ssq >> 2;
-    for (int i = 0; i < n4; i += 2) {
-        const float4 a = p[i], b = p[min(i + 1, n4 - 1)];
-        ss += (a.x + a.y) + (a.z + a.w);
-        ss += i + 1 < n4 ? (b.x + b.y) + (b.z + b.w) : 0.f;
+    const double2* p = ssq + (size_t)m * n_ssq;
+    for (int i0 = 0; i0 < n_ssq; i0 += 4) {
+        double2 v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = p[min(i0 + i, n_ssq - 1)];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ss += i0 + i < n_ssq ? (float)(v[i].x + v[i].y) : 0.f;
     }
     return 1.0f / sqrtf(ss / (float)d + eps);
 }

@@ -63,7 +63,7 @@ constexpr int WPACK_KG = 4;   // K blocks per group of the packed weight order
 // any X traffic both take 30 us): what a compute unit can pull from L2 per unit of time, X included,
 // is the limit there, not HBM.
 struct SwigluOut {
-    const float* ssq;   // NormScale of the rows (sums of squares in n_ssq chunks)
+    const double2* ssq; // NormScale of the rows (sums of squares in n_ssq pairs of chunks)
     int n_ssq, d;
     float eps;
     uint4* frags;       // fragment buffer of the down projection's operand
@@ -829,7 +829,7 @@ static int launch_swiglu_variant(int planes, const void* xf, const void* w, int 
     }
 }
 
-int launch_gemm_swiglu(const void* x_frags, int planes, const void* w_gate_up, int M, int F, int K, const float* ssq,
+int launch_gemm_swiglu(const void* x_frags, int planes, const void* w_gate_up, int M, int F, int K, const double2* ssq,
                        int n_ssq, int d, float eps, void* act_frags, int act_mt, int act_planes, int cu_count, hipStream_t s)
 {
     if (K % 32 || F % 16) return fail(SPEC_ERR_SHAPE, "SwiGLU GEMM needs K %% 32 == 0 and F %% 16 == 0");
