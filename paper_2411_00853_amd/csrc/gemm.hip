@@ -319,6 +319,12 @@ __global__ void __launch_bounds__(64 * CG * RS) gemm_skinny_kernel(const u32x4* 
         static_assert(EPI == 0 || (NT == 2 && RS == 1), "the SwiGLU epilogue pairs the two column tiles of a wavefront");
         static_assert(EPI == 0 || sizeof(xs) >= CG * MT * 256 * sizeof(float), "tile staging fits the X chunk buffers");
         __shared__ float rsv[MT * 16];
+        // The accumulators are read next, by vector instructions, which have to wait seven states for the last products.
+        // The compiler's own wait is lost where the branches above meet (one row tile: two states; the last
+        // product's remainder was missing from rows 0, 4, 8 and 12, 1.6e-4 of their values), so it is written out here,
+        // and the accumulators pass through it.
+#pragma unroll
+        for (int a = 0; a < MT; ++a) asm volatile("s_nop 15" : "+a"(acc[a][0]), "+a"(acc[a][1]));
         __syncthreads();                                      // everyone is done with the X chunk buffers
         float* tw = reinterpret_cast<float*>(&xs[0][0]) + wave * (MT * 256);   // [MT*16 rows][16 units]
         for (int m = threadIdx.x; m < MT * 16; m += TPBK)
