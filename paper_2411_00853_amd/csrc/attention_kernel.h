@@ -144,7 +144,12 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
     // which a memory round trip of about 1 us turns into 4.4 TB/s (28.4 -> 26.6 us at 32 sequences of 8 kv heads).
     // Out of a cache (kv_share > 1) the round trip is short and the fourth buffer only costs registers: a step at
     // the 1B shape, batch 1, takes 842 us with it and 827 without.
-    constexpr int NBUF = HD == 128 || !STREAM ? 2 : 4;
+    // Four buffers and four ranges at a time (W0 below) take 258-268 registers at one and two row tiles: one wavefront
+    // on a SIMD.  Three and two take 196-231: two.  Steps of four layers, three and two against four and four: 512 wavefronts
+    // -0.3..-0.6 %, 1024 +1.0..+1.6, 2048 -0.8..-3.3, 4096 -1.4..-1.6; 1B shape, batch 32 +0.6, batch 1 +0.5, batch 8 -1.4.  The
+    // variants of eight wavefronts have to fit two on a SIMD, spilled with four (36 bytes a lane), and take three:
+    // 16 sequences of 15900 positions, 256 pairs, 422.6 -> 417.2 us per step.
+    constexpr int NBUF = HD == 128 || !STREAM ? 2 : CW == 8 ? 3 : 4;
     kv_u32x4 kbuf[NBUF][2][STEPS], vbuf[NBUF][DT];
     // Unconditional loads: with no branch around them the compiler counts outstanding loads exactly and the
     // prefetch stays in flight.  Past the chunk's end every lane reads the same 16 bytes of its last block,
@@ -171,8 +176,8 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
     uint32_t wmask[RT];      // window slots (positions n + i) the query attends to
     // FUSED: a request for a row tile's queries or for eight window positions fetches the first W0 ranges of 16
     // float4 columns' worth, the row's sums of squares and its rotary factors; the rest of a longer list is
-    // fetched when the request is finished.
-    constexpr int QC = 2 * STEPS, W0 = HD == 128 ? 2 : 4;
+    // fetched when the request is finished.  (Two ranges where four do not fit: 128-dim heads, and eight wavefronts per workgroup.)
+    constexpr int QC = 2 * STEPS, W0 = HD == 128 || CW == 8 ? 2 : 4;
     // Several lanes share a row: each fetches one pair of its sums of squares and they pass them around, so that
     // a row of up to four pairs (4096 columns) costs a lane one 16-byte load and four registers.
     auto scale_issue = [&](int m, int sub, double2& r) { r = src.ns.ssq[(size_t)m * src.ns.n_ssq + min(sub, src.ns.n_ssq - 1)]; };

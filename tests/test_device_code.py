@@ -1,4 +1,4 @@
-"""What the compiler made of the kernels, read from the built library's disassembly (no GPU).  Two things that no
+"""What the compiler made of the kernels, read from the built library's disassembly (no GPU).  Three things that no
 source line shows and that have gone wrong:
 
 * The result of a matrix instruction may be read by a vector instruction only some wait states later, and the hardware
@@ -6,7 +6,9 @@ source line shows and that have gone wrong:
   SwiGLU products of one row tile read an accumulator two instructions after its last product and lost what that
   product had added.
 * A register parked in the accumulation registers must not be fetched back where no lane is active: behind the exit of
-  a loop that masks lanes off, before the mask is restored, the copy does nothing."""
+  a loop that masks lanes off, before the mask is restored, the copy does nothing.
+* A kernel whose vector registers do not fit keeps some of them in memory.  The attention variants of eight wavefronts per
+  workgroup, two of which have to fit a SIMD, did when a request fetched more ahead than was left for it."""
 import os
 import re
 import shutil
@@ -46,7 +48,7 @@ def _functions(text):
             yield Code(m.group(1), part.split("\n")[1:])
 
 
-def _library(tmp_path_factory):
+def _objects(tmp_path_factory):
     from paper_2411_00853_amd import build
     lib = build.build_library()
     data, out, at = open(lib, "rb").read(), [], 0
@@ -62,14 +64,23 @@ def _library(tmp_path_factory):
     for i, elf in enumerate(out):
         path = folder / ("%d.elf" % i)
         path.write_bytes(elf)
-        yield from _functions(subprocess.run([OBJDUMP, "-d", str(path)], capture_output=True, text=True, check=True).stdout)
+        yield str(path)
+
+
+def _tool(name, *args):
+    return subprocess.run([os.path.join(os.path.dirname(OBJDUMP), name), *args], capture_output=True, text=True, check=True).stdout
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
+def objects(tmp_path_factory):
     if OBJDUMP is None:
         pytest.skip("no llvm-objdump")
-    return [k for k in _library(tmp_path_factory) if k.ins]
+    return list(_objects(tmp_path_factory))
+
+
+@pytest.fixture(scope="module")
+def kernels(objects):
+    return [k for o in objects for k in _functions(_tool("llvm-objdump", "-d", o)) if k.ins]
 
 
 def _regs(operand):
@@ -150,6 +161,13 @@ def test_matrix_results_are_waited_for(kernels):
 
 def test_no_register_is_fetched_back_without_lanes(kernels):
     assert [(k.name, c) for k in kernels if (c := copies_without_lanes(k))] == []
+
+
+def test_no_kernel_keeps_vector_registers_in_memory(objects):
+    found = [m for o in objects for m in re.findall(r"\.name:\s+(_Z\S+).*?\.vgpr_spill_count:\s+(\d+)",
+                                                    _tool("llvm-readelf", "--notes", o), re.S)]
+    assert len(found) > 300
+    assert [(n, count) for n, count in found if count != "0"] == []
 
 
 def _listing(lines):
