@@ -41,42 +41,50 @@ __device__ __forceinline__ double wave_sum(double v)
 // Row bookkeeping.  One workgroup; thread b owns sequence b.
 // ---------------------------------------------------------------------------------------------
 struct PrepLds {
-    int row0[SPEC_MAX_BATCH + 1], slot[SPEC_MAX_BATCH], total[SPEC_MAX_BATCH], wave[TPB / 64];
+    int2 seq[SPEC_MAX_BATCH];   // window rows, slot
+    int total[SPEC_MAX_BATCH];
 };
 static_assert(TPB >= SPEC_MAX_BATCH, "a thread per sequence");
 
-// l.row0[i] = window rows of the sequences before i, for i <= B, and l.slot (all threads of the workgroup call;
-// ends with a barrier)
-__device__ __forceinline__ void prepare_prefix(const LookaheadPack& ks, int B, const int32_t* __restrict__ seq_slot, PrepLds& l)
+// What a sequence has to know of the others: the window rows before it, all of them, and whether one before it names
+// its slot.  All threads of the workgroup call.  One walk over LDS, eight entries in flight.  (With prefix sums by
+// wavefront scans, a second walk for the slots and the loads behind both, the kernel took 4.8 us in a decoding round of 8
+// sequences, 7.5 for trees and 9.4 for 32 ragged sequences on the page pool; this way 3.9, 7.1 and 8.9.)
+struct Others {
+    int row0, rows;
+    bool same_slot;
+};
+__device__ __forceinline__ Others look_at_others(int K, int slot, int B, PrepLds& l)
 {
-    const int b = threadIdx.x, lane = b & 63;
-    int sum = b < B ? ks.k[b] + 1 : 0;
-    const int own = sum;
-    if (b < B) l.slot[b] = seq_slot ? seq_slot[b] : b;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int x = __shfl_up(sum, off);
-        if (lane >= off) sum += x;
+    const int b = threadIdx.x;
+    if (b < B) l.seq[b] = make_int2(K + 1, slot);
+    __syncthreads();
+    Others r{0, 0, false};
+#pragma unroll 8
+    for (int i = 0; i < B; ++i) {
+        const int2 o = l.seq[i];
+        r.rows += o.x;
+        r.row0 += i < b ? o.x : 0;
+        r.same_slot |= i < b && o.y == slot;
     }
-    if (lane == 63) l.wave[b >> 6] = sum;
-    __syncthreads();
-    for (int w = 0; w < (b >> 6); ++w) sum += l.wave[w];
-    if (b <= B && b < TPB) l.row0[b] = sum - own;
-    if (b == TPB - 1 && B == TPB) l.row0[B] = sum;
-    __syncthreads();
+    return r;
 }
 
 // The sequences by falling number of positions.  The attention deals its workgroups out in this order, so the
 // longest ones start first and the short ones fill in behind them (32 sequences of 512..4096 positions on the page
-// pool: 232 us per launch in the order of the call, 213.5 this way).  All threads of the workgroup call.
-__device__ __forceinline__ void write_desc(const StepTables& t, int b, int B, int k, int n, int slot, int ok, int row0, int* total)
+// pool: 232 us per launch in the order of the call, 213.5..220.5 this way).  All threads of the workgroup call desc_rank.
+__device__ __forceinline__ int desc_rank(int b, int B, int positions, int* total)
 {
-    const int mine = ok ? n + k + 1 : 0;
-    if (b < B) total[b] = mine;
+    if (b < B) total[b] = positions;
     __syncthreads();
-    if (b >= B) return;
     int rank = 0;
-    for (int i = 0; i < B; ++i) rank += (total[i] > mine || (total[i] == mine && i < b)) ? 1 : 0;
+#pragma unroll 8
+    for (int i = 0; i < B; ++i) rank += (total[i] > positions || (total[i] == positions && i < b)) ? 1 : 0;
+    return rank;
+}
+
+__device__ __forceinline__ void write_desc(const StepTables& t, int rank, int b, int k, int n, int slot, int ok, int row0)
+{
     int4* d = reinterpret_cast<int4*>(t.seq_desc + rank);
     d[0] = make_int4(b, row0, k, n);
     d[1] = make_int4(slot, ok, 0, 0);
@@ -91,20 +99,23 @@ __device__ __forceinline__ void prepare_rows(const StepTables& t, const Lookahea
                                              const int32_t* __restrict__ kv_len, int32_t* flag, PrepLds& l)
 {
     const int b = threadIdx.x;
-    prepare_prefix(ks, B, has_cache ? seq_slot : nullptr, l);
-    if (b == 0) {
-        t.seq_row0[B] = l.row0[B];
-        t.seq_stat0[B] = 2 * l.row0[B] - B;
-    }
-    int K = 0, ok = 1, slot = 0, n = 0, row0 = 0;
+    // Two memory round trips, both under way before the first barrier: lookahead, slot and last token, then what they
+    // lead to.  (Asked for behind the prefix sums, one more.)
+    int K = 0, ok = 1, slot = 0, n = 0;
+    int tok[SPEC_MAX_LOOKAHEAD + 1];
     if (b < B) {
         K = ks.k[b];
-        row0 = l.row0[b];
-        slot = l.slot[b];
-        int tok[SPEC_MAX_LOOKAHEAD + 1];
+        slot = has_cache ? seq_slot[b] : b;
         tok[0] = last_token ? last_token[b] : 0;
 #pragma unroll
-        for (int i = 0; i < SPEC_MAX_LOOKAHEAD; ++i) tok[i + 1] = i < K ? draft_tokens[b * Kmax + i] : 0;
+        for (int i = 0; i < SPEC_MAX_LOOKAHEAD; ++i) {
+            if (i >= Kmax) break;   // (the whole workgroup skips what is left of the unrolled code)
+            tok[i + 1] = i < K ? draft_tokens[b * Kmax + i] : 0;
+        }
+        if (has_cache) n = kv_len[slot >= 0 && slot < max_batch ? slot : 0];
+    }
+    const Others o = look_at_others(K, slot, B, l);
+    if (b < B) {
         int err = 0;
         if (has_cache) {
             if (slot < 0 || slot >= max_batch) {
@@ -113,20 +124,29 @@ __device__ __forceinline__ void prepare_rows(const StepTables& t, const Lookahea
                 slot = 0;
             } else {
                 // two sequences of one step must not share a slot
-                for (int i = 0; i < b; ++i)
-                    if (l.slot[i] == slot) { ok = 0; err = SPEC_ERR_INVALID_ARG; }
-                n = kv_len[slot];
+                if (o.same_slot) { ok = 0; err = SPEC_ERR_INVALID_ARG; }
                 if (n < 0 || n + K + 1 > max_kv_len) { ok = 0; err = SPEC_ERR_KV_OVERFLOW; }
                 else if (ok && !pool_cover(t.pool, slot, n, n + K + 1)) { ok = 0; err = SPEC_ERR_KV_OVERFLOW; }
             }
         }
 #pragma unroll
-        for (int j = 0; j <= SPEC_MAX_LOOKAHEAD; ++j)
+        for (int j = 0; j <= SPEC_MAX_LOOKAHEAD; ++j) {
+            if (j > Kmax) break;
             if (tok[j] < 0 || tok[j] >= V) { ok = 0; err = SPEC_ERR_TOKEN_RANGE; }
+        }
         if (!ok) {
             atomicCAS(flag, 0, err);
             n = 0;
         }
+    }
+    const int rank = has_cache ? desc_rank(b, B, ok ? n + K + 1 : 0, l.total) : 0;
+    if (b == 0) {
+        t.seq_row0[B] = o.rows;
+        t.seq_stat0[B] = 2 * o.rows - B;
+    }
+    if (b < B) {
+        const int row0 = o.row0;
+        if (has_cache) write_desc(t, rank, b, K, n, slot, ok, row0);
         t.seq_row0[b] = row0;
         t.seq_stat0[b] = 2 * row0 - b;
         t.seq_n[b] = n;
@@ -134,6 +154,7 @@ __device__ __forceinline__ void prepare_rows(const StepTables& t, const Lookahea
         t.seq_slot[b] = slot;
 #pragma unroll
         for (int j = 0; j <= SPEC_MAX_LOOKAHEAD; ++j) {
+            if (j > Kmax) break;
             if (j <= K) {
                 const int r = row0 + j;
                 t.row_seq[r] = b;
@@ -144,7 +165,6 @@ __device__ __forceinline__ void prepare_rows(const StepTables& t, const Lookahea
             }
         }
     }
-    if (has_cache) write_desc(t, b, B, K, n, slot, ok, row0, l.total);
 }
 
 __global__ void __launch_bounds__(TPB) prepare_kernel(StepTables t, LookaheadPack ks, int B, int Kmax, int V,
@@ -166,6 +186,11 @@ __global__ void __launch_bounds__(TPB) slice_tables_kernel(StepTables full, Step
 {
     const int r0 = full.seq_row0[b0], st0 = full.seq_stat0[b0];
     const int n_rows = full.seq_row0[b0 + Bg] - r0;
+    __shared__ int total[SPEC_MAX_BATCH];
+    const int b = threadIdx.x, at = b0 + min(b, Bg - 1);
+    const int row0 = full.seq_row0[at], k = full.seq_row0[at + 1] - row0 - 1, n = full.seq_n[at], ok = full.seq_ok[at];
+    const int rank = desc_rank(b, Bg, ok ? n + k + 1 : 0, total);
+    if (b < Bg) write_desc(sub, rank, b, k, n, full.seq_slot[at], ok, row0 - r0);
     for (int i = threadIdx.x; i <= Bg; i += TPB) {
         sub.seq_row0[i] = full.seq_row0[b0 + i] - r0;
         sub.seq_stat0[i] = full.seq_stat0[b0 + i] - st0;
@@ -175,10 +200,6 @@ __global__ void __launch_bounds__(TPB) slice_tables_kernel(StepTables full, Step
             sub.seq_slot[i] = full.seq_slot[b0 + i];
         }
     }
-    __shared__ int total[SPEC_MAX_BATCH];
-    const int i = threadIdx.x, at = b0 + min(i, Bg - 1);
-    write_desc(sub, i, Bg, full.seq_row0[at + 1] - full.seq_row0[at] - 1, full.seq_n[at], full.seq_slot[at], full.seq_ok[at],
-               full.seq_row0[at] - r0, total);
     for (int r = threadIdx.x; r < n_rows; r += TPB) {
         sub.row_seq[r] = full.row_seq[r0 + r] - b0;
         sub.row_pos[r] = full.row_pos[r0 + r];
@@ -886,34 +907,30 @@ __global__ void __launch_bounds__(TPB) prepare_tree_kernel(StepTables t, Lookahe
     __shared__ uint16_t s_mask[SPEC_MAX_LOOKAHEAD + 1][TPB];
     __shared__ PrepLds l;
     const int b = threadIdx.x;
-    prepare_prefix(ks, B, has_cache ? seq_slot : nullptr, l);
-    if (b == 0) {   // statistics rows: target and draft row of the root and of every node
-        t.seq_row0[B] = l.row0[B];
-        t.seq_stat0[B] = 2 * l.row0[B];
-    }
     const int N = b < B ? ks.k[b] : 0;
     int ok = 1, slot = 0, n = 0;
+    int tok[SPEC_MAX_LOOKAHEAD + 1], par[SPEC_MAX_LOOKAHEAD];
     if (b < B) {
-        const int row0 = l.row0[b];
         // all of a sequence's nodes requested together
-        int tok[SPEC_MAX_LOOKAHEAD + 1], par[SPEC_MAX_LOOKAHEAD];
         tok[0] = last_token ? last_token[b] : 0;
 #pragma unroll
         for (int i = 0; i < SPEC_MAX_LOOKAHEAD; ++i) {
             tok[i + 1] = i < N ? tokens[b * Kmax + i] : 0;
             par[i] = i < N ? parent[b * Kmax + i] : -1;
         }
+        slot = has_cache ? seq_slot[b] : b;
+        if (has_cache) n = kv_len[slot >= 0 && slot < max_batch ? slot : 0];
+    }
+    const Others o = look_at_others(N, slot, B, l);   // (the loads above are under way meanwhile)
+    if (b < B) {
         int err = 0;
-        slot = l.slot[b];
         if (has_cache) {
             if (slot < 0 || slot >= max_batch) {
                 ok = 0;
                 err = SPEC_ERR_INVALID_ARG;
                 slot = 0;
             } else {
-                for (int i = 0; i < b; ++i)
-                    if (l.slot[i] == slot) { ok = 0; err = SPEC_ERR_INVALID_ARG; }
-                n = kv_len[slot];
+                if (o.same_slot) { ok = 0; err = SPEC_ERR_INVALID_ARG; }
                 if (n < 0 || n + N + 1 > max_kv_len) { ok = 0; err = SPEC_ERR_KV_OVERFLOW; }
                 else if (ok && !pool_cover(t.pool, slot, n, n + N + 1)) { ok = 0; err = SPEC_ERR_KV_OVERFLOW; }
             }
@@ -928,6 +945,15 @@ __global__ void __launch_bounds__(TPB) prepare_tree_kernel(StepTables t, Lookahe
             atomicCAS(flag, 0, err);
             n = 0;
         }
+    }
+    const int rank = has_cache ? desc_rank(b, B, ok ? n + N + 1 : 0, l.total) : 0;
+    if (b == 0) {   // statistics rows: target and draft row of the root and of every node
+        t.seq_row0[B] = o.rows;
+        t.seq_stat0[B] = 2 * o.rows;
+    }
+    if (b < B) {
+        const int row0 = o.row0;
+        if (has_cache) write_desc(t, rank, b, N, n, slot, ok, row0);
         t.seq_row0[b] = row0;
         t.seq_stat0[b] = 2 * row0;
         t.seq_n[b] = n;
@@ -949,7 +975,6 @@ __global__ void __launch_bounds__(TPB) prepare_tree_kernel(StepTables t, Lookahe
             }
         }
     }
-    if (has_cache) write_desc(t, b, B, N, n, slot, ok, b < B ? l.row0[b] : 0, l.total);
 }
 
 constexpr int TREE_TPB = 1024;   // the walk is one workgroup per sequence: make it a big one
