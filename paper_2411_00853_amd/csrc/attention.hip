@@ -104,18 +104,20 @@ __global__ void __launch_bounds__(64) attn_merge_kernel(StepTables t, LookaheadP
 }
 
 // Plain fp32 attention for fp32 caches: one workgroup per (row, query head).  LP lanes share a position (four
-// dims each), so keys and values are read in contiguous runs, four positions per group in flight; at a
-// hundred or a thousand positions the launch is a few memory round trips.  (A thread per key, and one per dim walking
-// all values, took 9.8 us at 133 positions of 64 dims.)
+// dims each), so keys and values are read in contiguous runs, four positions per group in flight, whose sums over
+// the lanes go step by step side by side.  Latency: round trips to memory and across lanes.  Per launch of 20 (row,
+// head) pairs of 64 dims, at 133 and 1029 positions: 7.2 and 29.6 us; a thread per key, and one per dim walking all values,
+// 9.4 and 80; the number of lanes a run-time value, each sum over the lanes a rolled loop of its own, 10.8 and 41.
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-__global__ void __launch_bounds__(256) attn_f32_kernel(StepTables t, CacheGeom g, int n_q_heads, int layer, int lp,
+template <int LP>
+__global__ void __launch_bounds__(256) attn_f32_kernel(StepTables t, CacheGeom g, int n_q_heads, int layer,
                                                        const float* __restrict__ cache, const float* __restrict__ q,
                                                        float scale, float* __restrict__ out)
 {
     extern __shared__ float4 dyn[];
     __shared__ float red[4];
-    float* osum = reinterpret_cast<float*>(dyn);   // [4][4 * lp] outputs of the wavefronts
-    float* sc = osum + 16 * lp;                    // [n_keys] scores
+    float* osum = reinterpret_cast<float*>(dyn);   // [4][4 * LP] outputs of the wavefronts
+    float* sc = osum + 16 * LP;                    // [n_keys] scores
     const int m = blockIdx.x, hq = blockIdx.y;
     const int hd = g.head_dim;
     const int pos = t.row_pos[m];
@@ -131,7 +133,9 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(StepTables t, CacheGeom g
     const int hkv = hq / (n_q_heads / g.n_kv_heads);
     const float* kbase = cache + cache_head_base(g, layer, slot, hkv) + plain_offset(g, 0, 0, 0);
     const float* vbase = cache + cache_head_base(g, layer, slot, hkv) + plain_offset(g, 1, 0, 0);
-    const int sub = threadIdx.x & (lp - 1), grp = threadIdx.x / lp, n_grp = 256 / lp;   // lp: power of two, 4 * lp >= hd
+    static_assert((LP & (LP - 1)) == 0 && LP <= 64, "a group of lanes lies within a wavefront");   // 4 * LP >= hd
+    constexpr int n_grp = 256 / LP;
+    const int sub = threadIdx.x & (LP - 1), grp = threadIdx.x / LP;
     const int d0 = 4 * sub;
     // four dims of a row from d0 on; a head's last lanes may have fewer
     auto load4 = [&](const float* row) -> float4 {
@@ -148,16 +152,21 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(StepTables t, CacheGeom g
         float4 kv[U];
 #pragma unroll
         for (int i = 0; i < U; ++i) kv[i] = load4(kbase + (size_t)min(k0 + i * n_grp, n_keys - 1) * hd);
+        float a[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) a[i] = fmaf(qv.x, kv[i].x, fmaf(qv.y, kv[i].y, fmaf(qv.z, kv[i].z, qv.w * kv[i].w)));
+#pragma unroll
+        for (int o = LP >> 1; o > 0; o >>= 1)   // the positions' sums step by step, side by side
+#pragma unroll
+            for (int i = 0; i < U; ++i) a[i] += __shfl_xor(a[i], o);
 #pragma unroll
         for (int i = 0; i < U; ++i) {
-            float a = fmaf(qv.x, kv[i].x, fmaf(qv.y, kv[i].y, fmaf(qv.z, kv[i].z, qv.w * kv[i].w)));
-            for (int o = lp >> 1; o > 0; o >>= 1) a += __shfl_xor(a, o);
             const int k = k0 + i * n_grp;
             if (k < n_keys) {
-                a *= scale;
-                if (k >= n_cached && !((wmask >> (k - n_cached)) & 1u)) a = -INFINITY;   // window slot not on this row's path
-                if (sub == 0) sc[k] = a;
-                mx = fmaxf(mx, a);
+                a[i] *= scale;
+                if (k >= n_cached && !((wmask >> (k - n_cached)) & 1u)) a[i] = -INFINITY;   // window slot not on this row's path
+                if (sub == 0) sc[k] = a[i];
+                mx = fmaxf(mx, a[i]);
             }
         }
     }
@@ -198,17 +207,18 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(StepTables t, CacheGeom g
             o4.w = on ? fmaf(p[i], vv[i].w, o4.w) : o4.w;
         }
     }
-    for (int o = lp; o < 64; o <<= 1) {
+#pragma unroll
+    for (int o = LP; o < 64; o <<= 1) {
         o4.x += __shfl_xor(o4.x, o);
         o4.y += __shfl_xor(o4.y, o);
         o4.z += __shfl_xor(o4.z, o);
         o4.w += __shfl_xor(o4.w, o);
     }
-    if ((threadIdx.x & 63) < lp) *reinterpret_cast<float4*>(osum + (threadIdx.x >> 6) * 4 * lp + d0) = o4;
+    if ((threadIdx.x & 63) < LP) *reinterpret_cast<float4*>(osum + (threadIdx.x >> 6) * 4 * LP + d0) = o4;
     __syncthreads();
     if ((int)threadIdx.x < hd) {
         const int e = threadIdx.x;
-        dst[e] = ((osum[e] + osum[4 * lp + e]) + (osum[8 * lp + e] + osum[12 * lp + e])) / z;
+        dst[e] = ((osum[e] + osum[4 * LP + e]) + (osum[8 * LP + e] + osum[12 * LP + e])) / z;
     }
 }
 
@@ -406,11 +416,17 @@ int launch_attention(int max_kv_len, int cu_count, const StepTables& t, const Lo
         // scores for one row live in LDS: positions * 4 bytes
         if ((size_t)(hd + g.t_pad) * sizeof(float) > 60 * 1024) return fail(SPEC_ERR_SHAPE, "fp32 attention supports max_kv_len up to ~15000");
         ProfScope ps(prof, SPEC_PROF_ATTENTION, s);
-        int lp = 1;   // lanes per position, four dims each
-        while (4 * lp < hd) lp *= 2;
-        const size_t lds = (size_t)(16 * lp + g.t_pad) * sizeof(float);
-        hipLaunchKernelGGL(attn_f32_kernel, dim3(M, n_q_heads), dim3(256), lds, s, t, g, n_q_heads, layer, lp,
-                           (const float*)cache, q, scale, xo.plain);
+#define SPECV_ATTN_F32(LP)                                                                                         \
+    hipLaunchKernelGGL(attn_f32_kernel<LP>, dim3(M, n_q_heads), dim3(256), (size_t)(16 * LP + g.t_pad) * sizeof(float), s, t, g, \
+                       n_q_heads, layer, (const float*)cache, q, scale, xo.plain)
+        if (hd <= 4) SPECV_ATTN_F32(1);
+        else if (hd <= 8) SPECV_ATTN_F32(2);
+        else if (hd <= 16) SPECV_ATTN_F32(4);
+        else if (hd <= 32) SPECV_ATTN_F32(8);
+        else if (hd <= 64) SPECV_ATTN_F32(16);
+        else if (hd <= 128) SPECV_ATTN_F32(32);
+        else SPECV_ATTN_F32(64);   // head_dim <= 256: spec_verify_init sees to it
+#undef SPECV_ATTN_F32
         SPECV_LAUNCH_CHECK("attn_f32_kernel");
         return SPEC_OK;
     }
