@@ -34,6 +34,7 @@ __global__ void __launch_bounds__(64) resid_kernel(const T* __restrict__ E, cons
                                                          double2* __restrict__ ssq, const float* __restrict__ gain,
                                                          XOut xo)
 {
+    // (ssq == NULL, the fp32 path's embedding: its GEMM sums the squares itself)
     const int m = blockIdx.y, k8 = blockIdx.x * 64 + threadIdx.x;
     double ss = 0.0;
     if (k8 * 8 < d) {
@@ -59,6 +60,7 @@ __global__ void __launch_bounds__(64) resid_kernel(const T* __restrict__ E, cons
         for (int i = 0; i < 8; ++i) ss += (double)v[i] * v[i];
         emit_operand(xo, m, k8, v, gain);
     }
+    if (!ssq) return;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
     if (threadIdx.x == 0) reinterpret_cast<double*>(ssq)[(size_t)m * gridDim.x + blockIdx.x] = ss;
@@ -436,6 +438,7 @@ int launch_rope_append(const float* partial, int n_split, size_t split_stride, i
         hipLaunchKernelGGL(rope_append_tiled_kernel, dim3((heads * (g.head_dim / 16) + per_wg - 1) / per_wg, (M + 15) / 16), dim3(TPB), 0, s,
                            partial, n_split, split_stride, ld, t, g, n_q_heads, M, layer, cos_sin, ns, (uint16_t*)cache, q_out);
     } else {
+        if (n_split != 1 || ns.ssq) return fail(SPEC_ERR_SHAPE, "fp32 rotation takes whole, normalised projections");
         hipLaunchKernelGGL(rope_append_kernel, dim3(M, heads), dim3(64), 0, s, partial, ld, t, g, n_q_heads, layer, cos_sin,
                            (float*)cache, q_out);
     }

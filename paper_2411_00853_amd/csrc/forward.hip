@@ -47,14 +47,12 @@ int forward_init(spec_handle* h, int max_rows)
         if (rc == SPEC_OK) rc = a.alloc(reinterpret_cast<void**>(p), count * sizeof(float));
     };
     A(&h->x, (size_t)max_rows * z.d);
-    A(reinterpret_cast<float**>(&h->ssq), (size_t)max_rows * ssq_pairs(z.d) * (sizeof(double2) / sizeof(float)));
     A(&h->q, (size_t)max_rows * z.dq);
-    A(&h->att, (size_t)max_rows * z.dq);
-    A(&h->act, (size_t)max_rows * z.F);
     A(&h->logits, (size_t)all_rows * z.V);
     A(&h->cos_sin, (size_t)c.max_kv_len * c.head_dim);
     size_t part = 0;
     if (c.dtype == SPEC_DTYPE_BF16) {
+        A(reinterpret_cast<float**>(&h->ssq), (size_t)max_rows * ssq_pairs(z.d) * (sizeof(double2) / sizeof(float)));
         // operand fragments: the widest GEMM input (d_model, q width or d_ffn), both planes, at the
         // row-tile count of the largest step; zeroed once so that padding blocks stay zero
         const int kmax = std::max(std::max(z.d, z.dq), z.F);
@@ -74,6 +72,8 @@ int forward_init(spec_handle* h, int max_rows)
         A(&h->attn_part_ml, po / c.head_dim * 2);
         h->attn_part_cap = po;
     } else {
+        A(&h->att, (size_t)max_rows * z.dq);
+        A(&h->act, (size_t)max_rows * z.F);
         part = (size_t)max_rows * z.nqkv;   // fp32 path: the QKV result, written whole
     }
     A(&h->partial, part);
@@ -221,7 +221,8 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
         return launch_gemm_bf16(p, in_frags, w, M, N, K, h->partial, s);
     };
 
-    RUN(SPEC_PROF_GLUE, launch_embed(c.dtype, h->tok_embed, t.row_tok, M, z.d, h->x, h->ssq, h->layers[0].attn_norm, to_xf, s));
+    RUN(SPEC_PROF_GLUE, launch_embed(c.dtype, h->tok_embed, t.row_tok, M, z.d, h->x, h->ssq, bf16 ? h->layers[0].attn_norm : nullptr,
+                                     to_xf, s));
     if (!bf16) {
         if (z.F % 8) return fail(SPEC_ERR_SHAPE, "d_ffn must be a multiple of 8");
         auto mul = [&](int cls, const float* in, const void* w, int N, int K, float* out, int mode, const float* gain) -> int {

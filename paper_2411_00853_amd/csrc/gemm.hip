@@ -866,21 +866,18 @@ int launch_gemm_f32(const float* x, const float* w, int M, int N, int K, float* 
     // row tiles per workgroup: up to four share a workgroup's reads of W
     const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
     const dim3 grid((N + 15) / 16, (M + 16 * mt - 1) / (16 * mt));
-#define SPECV_F32(MT, NT)                                                                                                       \
-    do {                                                                                                                        \
-        if (gain)                                                                                                               \
-            hipLaunchKernelGGL((gemm_f32_kernel<MT, NT, true>), grid, dim3(64 * F32_WAVES), 0, s, x, w, gain, eps, mode, y, M, N, K); \
-        else                                                                                                                    \
-            hipLaunchKernelGGL((gemm_f32_kernel<MT, NT, false>), grid, dim3(64 * F32_WAVES), 0, s, x, w, gain, eps, mode, y, M, N, K); \
+#define SPECV_F32(NT, NORM)                                                                                             \
+    do {                                                                                                                \
+        auto* k = mt == 1 ? gemm_f32_kernel<1, NT, NORM> : mt == 2 ? gemm_f32_kernel<2, NT, NORM> : gemm_f32_kernel<4, NT, NORM>; \
+        hipLaunchKernelGGL(k, grid, dim3(64 * F32_WAVES), 0, s, x, w, gain, eps, mode, y, M, N, K);                     \
     } while (0)
     if (mode == F32_SWIGLU) {
-        if (mt == 1) SPECV_F32(1, 2);
-        else if (mt == 2) SPECV_F32(2, 2);
-        else SPECV_F32(4, 2);
+        if (!gain) return fail(SPEC_ERR_SHAPE, "the fp32 SwiGLU product normalises its input");
+        SPECV_F32(2, true);
+    } else if (gain) {
+        SPECV_F32(1, true);
     } else {
-        if (mt == 1) SPECV_F32(1, 1);
-        else if (mt == 2) SPECV_F32(2, 1);
-        else SPECV_F32(4, 1);
+        SPECV_F32(1, false);
     }
 #undef SPECV_F32
     SPECV_LAUNCH_CHECK("gemm_f32_kernel");

@@ -44,10 +44,10 @@ struct spec_handle {
     float* x = nullptr;        // [rows][d_model] residual stream
     void* xf = nullptr;        // operand fragments of the current GEMM's input (bf16 path)
     void* xf_act = nullptr;    // second fragment buffer: the down projection's operand when the gate/up GEMM writes it
-    double2* ssq = nullptr;    // [rows][ssq_pairs] partial sums of squares of x
+    double2* ssq = nullptr;    // [rows][ssq_pairs] partial sums of squares of x (bf16 path)
     float* q = nullptr;        // [rows][n_q_heads*head_dim] rotated queries
-    float* att = nullptr;      // [rows][n_q_heads*head_dim] attention output
-    float* act = nullptr;      // [rows][d_ffn]
+    float* att = nullptr;      // [rows][n_q_heads*head_dim] attention output (fp32 path)
+    float* act = nullptr;      // [rows][d_ffn] (fp32 path)
     float* partial = nullptr;  // K-range partial sums of the current GEMM
     size_t partial_cap = 0;    // its capacity in floats (sized at init from the plans of every row count)
     float* logits = nullptr;   // [rows][vocab] when the caller gives no logits_out

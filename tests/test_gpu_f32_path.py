@@ -28,6 +28,10 @@ def test_products_at_the_edges_of_the_tiles(M, N, K):
     (2, 2, 50, 72, 130, [33], [2]),                 # head_dim not a multiple of 4
     (1, 1, 136, 24, 50, [257, 7], [5, 5]),          # more than 32 lanes per position
     (4, 2, 8, 16, 33, [20] * 9, [7] * 9),           # 72 rows: several row tiles
+    (2, 2, 4, 16, 33, [70], [3]),                   # one lane per position; then four, thirty-two, and all of a wavefront
+    (2, 1, 16, 16, 33, [5, 300], [3, 1]),
+    (2, 2, 128, 16, 33, [33, 140], [0, 4]),
+    (1, 1, 256, 16, 33, [70], [2]),
 ])
 def test_fp32_steps_match_the_oracle(heads, kv_heads, head_dim, d_ffn, vocab, lens, look):
     from paper_2411_00853_amd import binding as sv
