@@ -7,8 +7,8 @@
 //
 //  * The cache is stored in operand order (cache_layout.h): every 16-byte lane load of a key or
 //    value operand is part of a contiguous 1 KiB wavefront read, and a 32-position block (keys then
-//    values) is one contiguous 64*hd*2-byte run.  The next block is in flight while the current
-//    one is processed (two register buffers per wavefront).
+//    values) is one contiguous 64*hd*2-byte run.  While one block is processed
+//    the next is in flight (of 64-dim blocks that come from memory the next three, or two: see NBUF).
 //  * Scores are computed transposed (S^T = K * Q^T) so that the exponentiated scores leave the
 //    matrix instruction in exactly the register order the second product (O^T = V^T * P^T) wants:
 //    no LDS round trip, no cross-lane movement except the 2-step maximum over a query's 4 lanes.
@@ -241,8 +241,8 @@ void set_attn_small_positions(int n) { g_small_positions = n >= 0 ? n : 2816; }
 AttnPlan plan_attention(int max_kv_len, int batch, int n_kv_heads, int cu_count, bool paged)
 {
     // One wavefront per (sequence, kv head, position chunk).  Measured on MI355X: a few long
-    // streams beat many short ones (each wavefront keeps 32 KiB in flight and HBM likes long
-    // sequential runs), so aim for two wavefronts per compute unit when every sequence is at full
+    // streams beat many short ones (each wavefront keeps 16 to 24 KiB in flight and HBM likes
+    // long sequential runs), so aim for two wavefronts per compute unit when every sequence is at full
     // length.  Chunks are whole 32-position cache blocks.
     AttnPlan p{};
     const long want_items = (long)(g_items_per_cu > 0 ? g_items_per_cu : 2) * cu_count;
@@ -362,8 +362,8 @@ static AttnLaunchPlan plan_launch(const CacheGeom& g, bool paged, int n_q_heads,
         lp.p.max_chunks = (max_kv_len + lp.p.chunk_keys - 1) / lp.p.chunk_keys;
     }
     // Two blocks: measured over 0..128 positions, 7B-shape paged step 5.04 -> 4.95 ms, decoding round 6.69 -> 6.62 ms,
-    // contiguous 7B-shape, tree and long-context steps 0.2-0.7 % shorter, nothing longer (32 and 96 positions were
-    // slower than none: the main loop takes two blocks per trip).  With the window attended to from LDS: a draft model's
+    // contiguous 7B-shape, tree and long-context steps 0.2-0.7 % shorter, nothing longer (32 and 96 positions, an
+    // odd number of blocks with two buffers, were slower than none).  With the window attended to from LDS: a draft model's
     // decode at batch 8 339.0 us with none, 337.9 with 32, 331.6 with 64; the other steps within 0.5 %.
     lp.p.lag_keys = 64;
     return lp;

@@ -689,9 +689,10 @@ GemmPlan plan_gemm(int M, int N, int K, int cu_count, bool split_x)
         if ((kb_total + n2 - 1) / n2 * 32 <= 2048) p.cg = 2;
     }
     // The same for wider matrices from 8 row tiles on, where the partial sums, written and read back (8 bytes per column
-    // for each range and row), move at least as much as the weights (2 K bytes).  Measured in steps of four layers with
-    // two tiles per wavefront against four: K = 2048 (1 to 3 times the weights), 120-189 rows -2.0..-3.0 %;
-    // K = 4096 (0.5 to 0.75 times: the 7B-shape QKV), 120-189 rows +0.3..+1.0 %.
+    // for each range and row), move at least as much as the weights (2 K bytes).  Measured in steps of three layers with
+    // two tiles per wavefront against four, 113, 128, 176 and 192 rows: models 1024 wide -0.4..-5.9 %, 1536 -1.4..-3.1,
+    // 2048 (FFN 5504 and 8192) -2.6..-7.6, 2560 -3.4..-6.4, 3072 -1.8..-4.5.  At K = 4096 (0.5 to 0.75 times the weights: the
+    // 7B-shape QKV) it costs 0.3 to 1.0 % and is not made.
     if (p.mt >= 8 && p.nt == 4) {
         const int s4 = ranges_for((n_tiles + 15) / 16);
         if (8 * s4 * 16 * p.mt >= 2 * K && ranges_for((n_tiles + 7) / 8) < s4) p.nt = 2;
@@ -725,8 +726,9 @@ GemmPlan plan_gemm(int M, int N, int K, int cu_count, bool split_x)
         }
     }
     // Five and six row tiles: the same, as four column groups of three tiles (7B-shape, 88 rows: QKV 192 -> 256
-    // workgroups, gate/up 172 -> 230; a step of three layers 72 rows -3.0 %, 88 rows -1.4 %, a draft-sized model's
-    // -3.1 and -2.1 %).
+    // workgroups, gate/up 172 -> 230).  Steps of three layers with and without, 72, 88 and 96 rows: 7B shape -1.2..-1.4 %,
+    // 2048 wide with an FFN of 5504 -1.7..-2.4, 1536 wide -1.9..-2.6; 1024, 2560 and 3072 wide and an FFN of 8192, where it is
+    // not made or changes little, within 0.5 %.
     if (p.mt >= 5 && p.mt <= 6 && p.nt == 4) {
         const int wg3 = (n_tiles + 4 * 3 - 1) / (4 * 3) * s;
         if (wg_x * s * 5 < cu_count * 4 && wg3 <= cu_count) p.nt = 3;
