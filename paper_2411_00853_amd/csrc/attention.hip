@@ -346,6 +346,8 @@ static AttnLaunchPlan plan_launch(const CacheGeom& g, bool paged, int n_q_heads,
     // fits them, one chunk, all wavefronts resident at once, is faster (7B-shape, 2048 positions,
     // attention per layer: batch 20 161 -> 140 us, batch 24 176 -> 163, batch 28 and 32 -2 %; 32 sequences
     // of 512..4096 positions 8.74 -> 8.55 ms per step; from batch 40 on, where neither fits, two chunks win).
+    // The 64-dim variants of one and two row tiles have one wavefront per SIMD as well, by a few registers; the rule was
+    // measured with 128-dim heads and holds for those only.
     {
         const long pairs = (long)B * g.n_kv_heads * lp.share, slots = 4L * cu_count;
         const int rt1 = ((kmax + 1) * (group / lp.share) + 15) / 16;
