@@ -11,8 +11,11 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspecverify.so")
 SOURCES = ["attention.hip", "attention_reuse.hip", "spec_verify.hip", "forward.hip", "sampler.hip", "gemm.hip",
            "elementwise.hip", "probe.hip", "decode.hip", "lookahead.hip"]
-# packed-fp32 instructions are disabled for all device code
-FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
+# packed-fp32 instructions are disabled for all device code.  The first kernel arguments (up to 14 dwords, whole structs
+# excepted) come in scalar registers with the wavefront instead of by a load that every wavefront waits for before its
+# first address: a step is a chain of small launches (1B shape, batch 1, 120 of them: 812 -> 787 us).  Kernels list
+# what their first loads need in front.
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 # Per-source additions.  The attention kernels: matrix instructions take their accumulators in ordinary vector
 # registers; left to its default the compiler parks them in the accumulation registers and copies all

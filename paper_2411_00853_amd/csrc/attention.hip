@@ -448,7 +448,7 @@ int launch_attention(int max_kv_len, int cu_count, const StepTables& t, const Lo
                     "chunk results, the handle holds %zu: set the attention tuning knobs before spec_verify_init",
                     p.max_chunks, part_need, part_cap);
     const int rt = ((kmax + 1) * group + 15) / 16;
-    const dim3 grid((unsigned)B * n_items_kv * p.max_chunks), wg_grid((unsigned)B * n_items_kv);
+    const dim3 grid(p.max_chunks, n_items_kv, B), wg_grid(n_items_kv, B);
     const float sl2 = scale * 1.4426950408889634f;
     if (hd != 64 && hd != 128) return fail(SPEC_ERR_SHAPE, "bf16 attention needs head_dim 64 or 128");
     const int cw = rt >= 1 && rt <= 4 ? merge_width(hd, rt, p.max_chunks, B * n_items_kv, cu_count, lp.small) : 0;

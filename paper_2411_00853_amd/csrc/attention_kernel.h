@@ -63,8 +63,8 @@ __device__ __forceinline__ kv_u32x4 kv_load(const kv_u32x4* p)
 
 template <int HD, int RT, bool PAGED, bool FUSED, int CW, bool STREAM>
 __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
-    attn_chunk_kernel(StepTables t, CacheGeom g, int n_q_heads, int kv_share, int layer,
-                      const kv_u32x4* cache, const float* __restrict__ q, int max_chunks, int lag_keys, int r_cap, float scale_log2e,
+    attn_chunk_kernel(const SeqDesc* seq_desc, const kv_u32x4* cache, int max_chunks, int lag_keys, int n_q_heads, int kv_share,
+                      int layer, int r_cap, float scale_log2e, const float* __restrict__ q, StepTables t, CacheGeom g,
                       float* __restrict__ part_o, float* __restrict__ part_ml, QkvSrc src, uint16_t* cache_w, XOut xo)
 {
     constexpr int STEPS = HD / 32;     // 32-dim steps of the score product
@@ -75,14 +75,14 @@ __global__ void __launch_bounds__(CW > 0 ? 64 * CW : 64)
     // vector value, the compiler restored registers parked in the accumulation registers behind a masked loop, where
     // no lane was active.)
     const int wave = CW > 0 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
-    const int pair = CW > 0 ? blockIdx.x : blockIdx.x / max_chunks;   // (place of the sequence by length, hkv)
-    const int chunk = CW > 0 ? wave : blockIdx.x % max_chunks;
+    // grid: (head items, sequences by falling length), in front of them the chunks where a workgroup takes one
+    const int chunk = CW > 0 ? wave : (int)blockIdx.x;
     // kv_share > 1: the query heads of one kv head are dealt to kv_share work items ("hkv" counts those,
     // "group" is the heads of one item), which all stream the keys and values of cache head hkc
     const int n_items_kv = g.n_kv_heads * kv_share;
-    const int hkv = pair % n_items_kv, hkc = hkv / kv_share;
+    const int hkv = CW > 0 ? blockIdx.x : blockIdx.y, hkc = hkv / kv_share;
     const int group = n_q_heads / n_items_kv;
-    const int4* desc = reinterpret_cast<const int4*>(t.seq_desc + pair / n_items_kv);   // scalar, like the chunk
+    const int4* desc = reinterpret_cast<const int4*>(seq_desc + (CW > 0 ? blockIdx.y : blockIdx.z));   // scalar, like the chunk
     const int4 d0 = desc[0], d1 = desc[1];
     const int b = __builtin_amdgcn_readfirstlane(d0.x), row0 = __builtin_amdgcn_readfirstlane(d0.y);
     const int K = __builtin_amdgcn_readfirstlane(d0.z), n = __builtin_amdgcn_readfirstlane(d0.w);
@@ -593,8 +593,8 @@ static int launch_chunks(int rt, int cw, dim3 grid, dim3 wg_grid, hipStream_t s,
     const int lag_keys = src.partial ? p.lag_keys : 0;   // only the fused prologue delays a wavefront
 #define SPECV_ATTN_CW(RT, PG, FU, CW_)                                                                         \
     hipLaunchKernelGGL((attn_chunk_kernel<HD, RT, PG, FU, CW_, STREAM>), CW_ > 0 ? wg_grid : grid, dim3(CW_ > 0 ? 64 * CW_ : 64), \
-                       0, s, t, g, n_q_heads, kv_share, layer, (const kv_u32x4*)cache, q, p.max_chunks, lag_keys, r_cap, sl2, part_o, \
-                       part_ml, src, (uint16_t*)cache_w, xo)
+                       0, s, t.seq_desc, (const kv_u32x4*)cache, p.max_chunks, lag_keys, n_q_heads, kv_share, layer, r_cap, sl2, q, t, g, \
+                       part_o, part_ml, src, (uint16_t*)cache_w, xo)
 #define SPECV_ATTN_GO(RT, PG, FU)                                                                              \
     do {                                                                                                         \
         if (cw == 1) SPECV_ATTN_CW(RT, PG, FU, 1);                                                               \

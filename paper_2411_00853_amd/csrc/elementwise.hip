@@ -28,11 +28,10 @@ __device__ __forceinline__ void emit_operand(const XOut& xo, int m, int k8, cons
 // wavefronts spread best over the chip: 352 rows of 4096 with eight ranges 12.1 us as workgroups of two, 10.1
 // as single ones; a wavefront per 16 rows x 32 columns, whose stores are contiguous, 10.9 (and slower at 48 rows).
 template <typename T, bool EMBED>
-__global__ void __launch_bounds__(64) resid_kernel(const T* __restrict__ E, const int32_t* __restrict__ row_tok,
-                                                         const float* __restrict__ partial, int n_split,
-                                                         size_t split_stride, int ld, int d, float* __restrict__ x,
-                                                         double2* __restrict__ ssq, const float* __restrict__ gain,
-                                                         XOut xo)
+__global__ void __launch_bounds__(64) resid_kernel(const float* __restrict__ partial, float* __restrict__ x, size_t split_stride,
+                                                   int n_split, int ld, int d, int xmt, void* frags, const float* __restrict__ gain,
+                                                   double2* __restrict__ ssq, int planes, const T* __restrict__ E,
+                                                   const int32_t* __restrict__ row_tok)
 {
     // (ssq == NULL, the fp32 path's embedding: its GEMM sums the squares itself)
     const int m = blockIdx.y, k8 = blockIdx.x * 64 + threadIdx.x;
@@ -58,7 +57,7 @@ __global__ void __launch_bounds__(64) resid_kernel(const T* __restrict__ E, cons
         *reinterpret_cast<float4*>(xp + 4) = make_float4(v[4], v[5], v[6], v[7]);
 #pragma unroll
         for (int i = 0; i < 8; ++i) ss += (double)v[i] * v[i];
-        emit_operand(xo, m, k8, v, gain);
+        emit_operand(XOut{frags, xmt, planes, nullptr}, m, k8, v, gain);
     }
     if (!ssq) return;
 #pragma unroll
@@ -396,11 +395,11 @@ int launch_embed(int dtype, const void* tok_embed, const int32_t* row_tok, int M
     if (d % 8) return fail(SPEC_ERR_SHAPE, "d_model must be a multiple of 8");
     const dim3 grid(2 * ssq_pairs(d), M);
     if (dtype == SPEC_DTYPE_BF16)
-        hipLaunchKernelGGL((resid_kernel<__bf16, true>), grid, dim3(64), 0, s, (const __bf16*)tok_embed, row_tok,
-                           nullptr, 0, 0, 0, d, x, ssq, gain, xo);
+        hipLaunchKernelGGL((resid_kernel<__bf16, true>), grid, dim3(64), 0, s, nullptr, x, 0, 0, 0, d, xo.mt, xo.frags, gain, ssq,
+                           xo.planes, (const __bf16*)tok_embed, row_tok);
     else
-        hipLaunchKernelGGL((resid_kernel<float, true>), grid, dim3(64), 0, s, (const float*)tok_embed, row_tok,
-                           nullptr, 0, 0, 0, d, x, ssq, gain, xo);
+        hipLaunchKernelGGL((resid_kernel<float, true>), grid, dim3(64), 0, s, nullptr, x, 0, 0, 0, d, xo.mt, xo.frags, gain, ssq,
+                           xo.planes, (const float*)tok_embed, row_tok);
     SPECV_LAUNCH_CHECK("resid_kernel<embed>");
     return SPEC_OK;
 }
@@ -410,8 +409,8 @@ int launch_resid(const float* partial, int n_split, size_t split_stride, int ld,
 {
     if (d % 8 || ld % 4 || split_stride % 4) return fail(SPEC_ERR_SHAPE, "residual rows must be multiples of 8 wide");
     const dim3 grid(2 * ssq_pairs(d), M);
-    hipLaunchKernelGGL((resid_kernel<float, false>), grid, dim3(64), 0, s, nullptr, nullptr, partial, n_split,
-                       split_stride, ld, d, x, ssq, gain, xo);
+    hipLaunchKernelGGL((resid_kernel<float, false>), grid, dim3(64), 0, s, partial, x, split_stride, n_split, ld, d, xo.mt, xo.frags,
+                       gain, ssq, xo.planes, nullptr, nullptr);
     SPECV_LAUNCH_CHECK("resid_kernel");
     return SPEC_OK;
 }

@@ -225,7 +225,7 @@ enum { STAT_CHAIN = 0, STAT_TREE = 1, STAT_PLAIN = 2 };
 // workgroup of the statistics pass (the first, which takes no chunk) instead of by a kernel of its own: the pass
 // itself does not read the tables, the kernels after it do.
 struct PrepIn {
-    int on, Kmax;
+    int Kmax;
     const int32_t* draft_tokens;
     int32_t* flag;
 };
@@ -279,22 +279,22 @@ __device__ __forceinline__ void find_stat_row(const LookaheadPack& ks, int B, in
 }
 
 template <bool VEC4>
-__global__ void __launch_bounds__(TPB) stats_kernel(StepTables t, LookaheadPack ks, int B, int draft_rows, int V,
-                                                    int n_chunks, const float* __restrict__ target,
-                                                    const float* __restrict__ draft, float inv_T,
-                                                    float* __restrict__ part_max, double* __restrict__ part_sum,
-                                                    float* __restrict__ copy_out, size_t copy_stride, int layout,
-                                                    PrepIn prep)
+__global__ void __launch_bounds__(TPB) stats_kernel(int prep_on, int layout, int B, int draft_rows, int V, int n_chunks,
+                                                    const float* __restrict__ target,
+                                                    const float* __restrict__ draft, float* __restrict__ copy_out,
+                                                    float inv_T, float* __restrict__ part_max,
+                                                    double* __restrict__ part_sum, size_t copy_stride,
+                                                    StepTables t, LookaheadPack ks, PrepIn prep)
 {
     __shared__ float smax[TPB / 64];
     __shared__ double ssum[TPB / 64];
     __shared__ PrepLds prep_lds;
-    if (prep.on && blockIdx.x == 0) {
+    if (prep_on && blockIdx.x == 0) {
         prepare_rows(t, ks, B, prep.Kmax, V, SPEC_MAX_BATCH, 0, 0, nullptr, nullptr, prep.draft_tokens, nullptr, prep.flag,
                      prep_lds);
         return;
     }
-    const int wg = blockIdx.x - prep.on;
+    const int wg = blockIdx.x - prep_on;
     const int srow = wg / n_chunks;
     const int chunk = wg % n_chunks;
     const float* row;
@@ -443,14 +443,15 @@ __device__ __forceinline__ void combine_rows(const float* part_max, const double
 // only then the address of the rows (64 sequences x 32 chunks of a 128256 vocabulary: 18.5 us of which 10 are the
 // bytes; 20.5 with one thread per row combining the statistics and the proposals' logits requested after that).
 // ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(TPB) accept_mass_kernel(StepTables t, LookaheadPack ks, int Kmax, int V,
-                                                          int n_stat_chunks, int n_res_chunks,
-                                                          const float* __restrict__ target,
-                                                          const float* __restrict__ draft,
+__global__ void __launch_bounds__(TPB) accept_mass_kernel(const int32_t* seq_stat0, const int32_t* seq_row0,
                                                           const int32_t* __restrict__ draft_tokens,
-                                                          const float* __restrict__ uniforms, int u_stride,
-                                                          float inv_T_f, const float* __restrict__ part_max,
-                                                          const double* __restrict__ part_sum, SamplerWorkspace w)
+                                                          const float* __restrict__ part_max,
+                                                          const double* __restrict__ part_sum, int Kmax, int V,
+                                                          int n_stat_chunks, int u_stride,
+                                                          const float* __restrict__ uniforms,
+                                                          const float* __restrict__ target,
+                                                          const float* __restrict__ draft, int n_res_chunks, float inv_T_f,
+                                                          LookaheadPack ks, SamplerWorkspace w)
 {
     __shared__ float row_m[2 * SPEC_MAX_LOOKAHEAD + 2];
     __shared__ double row_z[2 * SPEC_MAX_LOOKAHEAD + 2];
@@ -460,8 +461,8 @@ __global__ void __launch_bounds__(TPB) accept_mass_kernel(StepTables t, Lookahea
     const int chunk = blockIdx.x;
     const int K = ks.k[b];
     const double inv_T = (double)inv_T_f;
-    const int st0 = t.seq_stat0[b];
-    const float* trow0 = target + (size_t)t.seq_row0[b] * V;
+    const int st0 = seq_stat0[b];
+    const float* trow0 = target + (size_t)seq_row0[b] * V;
     const float* drow0 = draft + (size_t)b * Kmax * V;
     // lane i tests proposal i (all positions at once: the tests are independent, only the first
     // failure matters); padding lanes repeat the last proposal and are masked out.  Its logits are requested
@@ -541,14 +542,15 @@ __global__ void __launch_bounds__(TPB) accept_mass_kernel(StepTables t, Lookahea
 // Latency only, one workgroup per sequence (11 -> 9.3 us at 64 sequences: the masses walked eight at a time, padding
 // between the lanes' ids in LDS, where 128 bytes from lane to lane put all of them on one bank).
 // ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(TPB) final_draw_kernel(StepTables t, LookaheadPack ks, int Kmax, int V,
-                                                         int n_res_chunks, const float* __restrict__ target,
+__global__ void __launch_bounds__(TPB) final_draw_kernel(const int32_t* accepted, const double* chunk_mass, const int32_t* seq_row0,
+                                                         const float* __restrict__ uniforms, int u_stride, int n_res_chunks,
+                                                         int Kmax, int V, const float* row_max, float inv_T_f,
+                                                         const double* row_inv_z, const float* __restrict__ target,
                                                          const float* __restrict__ draft,
-                                                         const int32_t* __restrict__ draft_tokens,
-                                                         const float* __restrict__ uniforms, int u_stride,
-                                                         float inv_T_f, SamplerWorkspace w, int auto_rollback,
+                                                         const int32_t* __restrict__ draft_tokens, int auto_rollback,
                                                          int32_t* kv_len, int32_t* __restrict__ n_accepted,
-                                                         int32_t* __restrict__ out_tokens, DrawEmit emit)
+                                                         int32_t* __restrict__ out_tokens, StepTables t, LookaheadPack ks,
+                                                         DrawEmit emit)
 {
     __shared__ double r[RES_CHUNK + RES_CHUNK / 16];   // 16 consecutive ids per lane, a word of padding between lanes
     __shared__ double wave_tot[TPB / 64];
@@ -569,14 +571,14 @@ __global__ void __launch_bounds__(TPB) final_draw_kernel(StepTables t, Lookahead
         return;
     }
     // everything that does not depend on the chunk is requested at once, the chunk masses by as many lanes
-    const int a = w.accepted[b];
-    const int row0 = t.seq_row0[b];
-    const float mp = w.row_max[2 * b], mq = w.row_max[2 * b + 1];
-    const double izp = w.row_inv_z[2 * b], izq = w.row_inv_z[2 * b + 1];
+    const int a = accepted[b];
+    const int row0 = seq_row0[b];
+    const float mp = row_max[2 * b], mq = row_max[2 * b + 1];
+    const double izp = row_inv_z[2 * b], izq = row_inv_z[2 * b + 1];
     const double u = (double)uniforms[b * u_stride + K];
     bool residual = a < K;
     __shared__ double s_mass[TPB];
-    const double* mass = w.chunk_mass + (size_t)b * n_res_chunks;
+    const double* mass = chunk_mass + (size_t)b * n_res_chunks;
     const bool in_lds = n_res_chunks <= TPB;
     if (in_lds) s_mass[threadIdx.x] = (int)threadIdx.x < n_res_chunks ? mass[threadIdx.x] : 0.0;
     __syncthreads();
@@ -1385,13 +1387,13 @@ int launch_tree_sampler(const StepTables& t, const SamplerWorkspace& w, const Lo
     {
         ProfScope ps(prof, SPEC_PROF_SAMPLER_STATS, s);
         if (vec4)
-            hipLaunchKernelGGL(stats_kernel<true>, g1, dim3(TPB), 0, s, t, ks, B, Kmax + 1, V, n_stat_chunks,
-                               target_logits, draft_logits, inv_T, w.part_max, w.part_sum, (float*)nullptr, (size_t)0,
-                               (int)STAT_TREE, PrepIn{});
+            hipLaunchKernelGGL(stats_kernel<true>, g1, dim3(TPB), 0, s, 0, (int)STAT_TREE, B, Kmax + 1, V, n_stat_chunks,
+                               target_logits, draft_logits, (float*)nullptr, inv_T, w.part_max, w.part_sum, (size_t)0, t, ks,
+                               PrepIn{});
         else
-            hipLaunchKernelGGL(stats_kernel<false>, g1, dim3(TPB), 0, s, t, ks, B, Kmax + 1, V, n_stat_chunks,
-                               target_logits, draft_logits, inv_T, w.part_max, w.part_sum, (float*)nullptr, (size_t)0,
-                               (int)STAT_TREE, PrepIn{});
+            hipLaunchKernelGGL(stats_kernel<false>, g1, dim3(TPB), 0, s, 0, (int)STAT_TREE, B, Kmax + 1, V, n_stat_chunks,
+                               target_logits, draft_logits, (float*)nullptr, inv_T, w.part_max, w.part_sum, (size_t)0, t, ks,
+                               PrepIn{});
         SPECV_LAUNCH_CHECK("stats_kernel");
     }
     ProfScope ps(prof, SPEC_PROF_SAMPLER_DRAW, s);
@@ -1443,8 +1445,8 @@ int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const Lookahe
     const int n_res_chunks = (V + RES_CHUNK - 1) / RES_CHUNK;
     const float inv_T = 1.0f / temperature;
     PrepIn prep{};
+    const int prep_on = prepare_flag ? 1 : 0;
     if (prepare_flag) {   // no decoder pass ran: the statistics pass fills the row tables itself
-        prep.on = 1;
         prep.Kmax = Kmax;
         prep.draft_tokens = draft_tokens;
         prep.flag = prepare_flag;
@@ -1458,27 +1460,27 @@ int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const Lookahe
     const bool vec4 = (V % 4 == 0) && ((reinterpret_cast<uintptr_t>(target_logits) & 15) == 0)
                       && ((reinterpret_cast<uintptr_t>(draft_logits) & 15) == 0)
                       && ((reinterpret_cast<uintptr_t>(em.logits_copy) & 15) == 0) && (em.copy_stride % 4 == 0);
-    dim3 g1((unsigned)n_stat_rows * n_stat_chunks + prep.on);
+    dim3 g1((unsigned)n_stat_rows * n_stat_chunks + prep_on);
     {
     ProfScope ps(prof, SPEC_PROF_SAMPLER_STATS, s);
     if (vec4)
-        hipLaunchKernelGGL(stats_kernel<true>, g1, dim3(TPB), 0, s, t, ks, B, Kmax, V, n_stat_chunks,
-                           target_logits, draft_logits, inv_T, w.part_max, w.part_sum, em.logits_copy, em.copy_stride,
-                           layout, prep);
+        hipLaunchKernelGGL(stats_kernel<true>, g1, dim3(TPB), 0, s, prep_on, layout, B, Kmax, V, n_stat_chunks,
+                           target_logits, draft_logits, em.logits_copy, inv_T, w.part_max, w.part_sum, em.copy_stride, t, ks,
+                           prep);
     else
-        hipLaunchKernelGGL(stats_kernel<false>, g1, dim3(TPB), 0, s, t, ks, B, Kmax, V, n_stat_chunks,
-                           target_logits, draft_logits, inv_T, w.part_max, w.part_sum, em.logits_copy, em.copy_stride,
-                           layout, prep);
+        hipLaunchKernelGGL(stats_kernel<false>, g1, dim3(TPB), 0, s, prep_on, layout, B, Kmax, V, n_stat_chunks,
+                           target_logits, draft_logits, em.logits_copy, inv_T, w.part_max, w.part_sum, em.copy_stride, t, ks,
+                           prep);
     SPECV_LAUNCH_CHECK("stats_kernel");
     }
     ProfScope ps(prof, SPEC_PROF_SAMPLER_DRAW, s);
-    hipLaunchKernelGGL(accept_mass_kernel, dim3(n_res_chunks, B), dim3(TPB), 0, s, t, ks, Kmax, V, n_stat_chunks,
-                       n_res_chunks, target_logits, draft_logits, draft_tokens, uniforms, u_stride, inv_T, w.part_max,
-                       w.part_sum, w);
+    hipLaunchKernelGGL(accept_mass_kernel, dim3(n_res_chunks, B), dim3(TPB), 0, s, t.seq_stat0, t.seq_row0, draft_tokens, w.part_max,
+                       w.part_sum, Kmax, V, n_stat_chunks, u_stride, uniforms, target_logits, draft_logits, n_res_chunks, inv_T,
+                       ks, w);
     SPECV_LAUNCH_CHECK("accept_mass_kernel");
-    hipLaunchKernelGGL(final_draw_kernel, dim3(B), dim3(TPB), 0, s, t, ks, Kmax, V, n_res_chunks, target_logits,
-                       draft_logits, draft_tokens, uniforms, u_stride, inv_T, w, auto_rollback, kv_len, n_accepted,
-                       out_tokens, em);
+    hipLaunchKernelGGL(final_draw_kernel, dim3(B), dim3(TPB), 0, s, w.accepted, w.chunk_mass, t.seq_row0, uniforms, u_stride,
+                       n_res_chunks, Kmax, V, w.row_max, inv_T, w.row_inv_z, target_logits, draft_logits, draft_tokens,
+                       auto_rollback, kv_len, n_accepted, out_tokens, t, ks, em);
     SPECV_LAUNCH_CHECK("final_draw_kernel");
     return SPEC_OK;
 }
