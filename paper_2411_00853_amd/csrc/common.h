@@ -92,6 +92,31 @@ struct StepTables {
                          // 0..j, so the kernels need not load them), 1 = token trees
 };
 
+// Row-wise sums of squares travel as SSQ_CHUNK-column partial sums in fp64, two to a double2 ([M][n_ssq], n_ssq =
+// ssq_pairs(d), the last half zero where need be).  RMSNorm is split in two: the producer of a GEMM's input multiplies
+// by the gain; the row's 1/rms factors out of the dot product and is applied by the consumer of the GEMM's output
+// (NormScale).  A pair is rounded to fp32 once its halves have met, and the pairs are added in index order
+// (row_inv_rms): how many wavefronts share a row shows in no bit of the result.  (Chunks rounded one by one
+// move the logits by 1e-5, and a draw whose uniform lies that close to a step of the distribution with them.)
+constexpr int SSQ_CHUNK = 512;
+inline int ssq_pairs(int d) { return (d + 2 * SSQ_CHUNK - 1) / (2 * SSQ_CHUNK); }
+struct NormScale {
+    const double2* ssq;   // NULL: no scaling
+    int n_ssq;
+    int d;              // row length the mean is taken over
+    float eps;
+};
+// The logits of a decoder pass as its last product leaves them: K-range partial sums [n_split][rows][ld], the row scale
+// of the final norm, and where the finished rows go ([rows][vocab]).  The sampler's first kernel adds them up on
+// the way.  partial == NULL: the logits are whole.
+struct LogitsSrc {
+    const float* partial;
+    size_t stride;
+    int n_split, ld;
+    NormScale ns;
+    float* out;
+};
+
 // ---- sampler (sampler.hip) ---------------------------------------------------------------------
 constexpr int STAT_CHUNK = 16384;   // logits per workgroup in the statistics pass
 constexpr int RES_CHUNK = 4096;    // logits per workgroup in the residual pass / final scan
@@ -130,6 +155,8 @@ struct DrawEmit {
     size_t copy_stride;
 };
 
+// src != NULL and src->partial != NULL: target_logits (= src->out) is still to be written, from the partial sums; a
+// plain draw (emit) writes the rows it draws from only
 // uniforms: sequence b reads uniforms[b * u_stride + i] (i < K_b: proposal i; i = K_b: the final draw)
 // prepare_flag != NULL: no launch_prepare ran for this step (no decoder pass, no cache); the statistics pass
 // fills t itself, reporting bad tokens through that flag
@@ -137,7 +164,8 @@ int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const Lookahe
                    int V, int n_stat_rows, const float* target_logits, const float* draft_logits,
                    const int32_t* draft_tokens, const float* uniforms, int u_stride, float temperature,
                    int auto_rollback, int32_t* kv_len, int32_t* n_accepted, int32_t* out_tokens,
-                   const DrawEmit* emit, Profiler* prof, hipStream_t s, int32_t* prepare_flag = nullptr);
+                   const DrawEmit* emit, Profiler* prof, hipStream_t s, int32_t* prepare_flag = nullptr,
+                   const LogitsSrc* src = nullptr);
 
 // Token-tree variants: parent/tokens [B][Kmax], draft logits [B][Kmax+1][V] (row 0: the root)
 int launch_prepare_tree(const StepTables& t, const LookaheadPack& ks, int B, int Kmax, int V, int max_batch,
@@ -148,7 +176,7 @@ int launch_tree_sampler(const StepTables& t, const SamplerWorkspace& w, const Lo
                         int V, int n_stat_rows, const float* target_logits, const float* draft_logits,
                         const int32_t* parent, const int32_t* tokens, const float* uniforms, float temperature,
                         int auto_rollback, int32_t* kv_len, int32_t* n_accepted, int32_t* out_tokens,
-                        int32_t* path, Profiler* prof, hipStream_t s);
+                        int32_t* path, Profiler* prof, hipStream_t s, const LogitsSrc* src = nullptr);
 
 struct RollbackPack {
     int32_t slot[SPEC_MAX_BATCH];
@@ -188,20 +216,6 @@ struct CacheGeom {
 
 CacheGeom make_cache_geom(const spec_model_cfg& c);
 
-// Row-wise sums of squares travel as SSQ_CHUNK-column partial sums in fp64, two to a double2 ([M][n_ssq], n_ssq =
-// ssq_pairs(d), the last half zero where need be).  RMSNorm is split in two: the producer of a GEMM's input multiplies
-// by the gain; the row's 1/rms factors out of the dot product and is applied by the consumer of the GEMM's output
-// (NormScale).  A pair is rounded to fp32 once its halves have met, and the pairs are added in index order
-// (row_inv_rms): how many wavefronts share a row shows in no bit of the result.  (Chunks rounded one by one
-// move the logits by 1e-5, and a draw whose uniform lies that close to a step of the distribution with them.)
-constexpr int SSQ_CHUNK = 512;
-inline int ssq_pairs(int d) { return (d + 2 * SSQ_CHUNK - 1) / (2 * SSQ_CHUNK); }
-struct NormScale {
-    const double2* ssq;   // NULL: no scaling
-    int n_ssq;
-    int d;              // row length the mean is taken over
-    float eps;
-};
 // Where a producer puts a GEMM operand: fragment buffer (bf16 path) and/or plain fp32 rows.
 struct XOut {
     void* frags;        // NULL on the fp32 path

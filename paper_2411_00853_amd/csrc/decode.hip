@@ -293,7 +293,8 @@ extern "C" int spec_decode_round(spec_decoder* d, const spec_round_args* args, v
             rc = launch_prepare(dr->tables, ks, B, d->Kd, V, dr->cfg.max_batch, dr->cfg.max_kv_len, true, d->seq_slot,
                                 i == 0 ? d->prev_tok : d->cur_tok, d->win, dr->kv_len, dr->flag, s);
             if (rc) return rc;
-            rc = forward_run_grouped(dr, ks, B, rows, dr->logits, s);
+            LogitsSrc src{};
+            rc = forward_run_grouped(dr, ks, B, rows, dr->logits, s, greedy ? nullptr : &src);
             if (rc) return rc;
             DrawEmit em{};
             em.tokens = d->draft_tokens;
@@ -310,7 +311,7 @@ extern "C" int spec_decode_round(spec_decoder* d, const spec_round_args* args, v
             else
                 rc = launch_sampler(i == 0 ? d->draw_first : d->draw_next, dr->sampler, zero, B, 0, V, B, dr->logits,
                                     nullptr, nullptr, args->draft_uniforms + i, Kt, args->temperature, 0, nullptr,
-                                    nullptr, nullptr, &em, &dr->prof, s);
+                                    nullptr, nullptr, &em, &dr->prof, s, nullptr, &src);
             if (rc) return rc;
         }
     }
@@ -326,7 +327,8 @@ extern "C" int spec_decode_round(spec_decoder* d, const spec_round_args* args, v
     rc = launch_prepare(tg->tables, ks, B, Kt, V, tg->cfg.max_batch, tg->cfg.max_kv_len, true, d->seq_slot, d->last_tok,
                         d->draft_tokens, tg->kv_len, tg->flag, s);
     if (rc) return rc;
-    rc = forward_run_grouped(tg, ks, B, M, tg->logits, s);
+    LogitsSrc src{};
+    rc = forward_run_grouped(tg, ks, B, M, tg->logits, s, greedy ? nullptr : &src);
     if (rc) return rc;
     if (greedy)
         rc = launch_greedy(tg->tables, tg->sampler, ks, B, Kt, V, M, tg->logits, d->draft_tokens, 1, tg->kv_len,
@@ -334,7 +336,7 @@ extern "C" int spec_decode_round(spec_decoder* d, const spec_round_args* args, v
     else
         rc = launch_sampler(tg->tables, tg->sampler, ks, B, Kt, V, n_stat, tg->logits, d->draft_logits,
                             d->draft_tokens, args->verify_uniforms, Kt + 1, args->temperature, 1, tg->kv_len,
-                            d->n_accepted, d->round_out, nullptr, &tg->prof, s);
+                            d->n_accepted, d->round_out, nullptr, &tg->prof, s, nullptr, &src);
     if (rc) return rc;
     d->last_rows = M;
     hipLaunchKernelGGL(advance_kernel, dim3(1), dim3(TPB), 0, s, B, Kt, d->Kd, d->cap, d->n_accepted, d->round_out,

@@ -152,9 +152,10 @@ int plan_passes(const LookaheadPack& ks, int B, int M, int cap, int* pass_seqs, 
     return fill(limit, true);
 }
 
-int forward_run_grouped(spec_handle* h, const LookaheadPack& ks, int B, int M, float* logits_out, hipStream_t s)
+int forward_run_grouped(spec_handle* h, const LookaheadPack& ks, int B, int M, float* logits_out, hipStream_t s, LogitsSrc* last)
 {
-    if (M <= h->row_cap) return forward_run(h, h->tables, ks, B, M, logits_out, s);
+    if (last) *last = LogitsSrc{};
+    if (M <= h->row_cap) return forward_run(h, h->tables, ks, B, M, logits_out, s, last);
     if (!h->group_tables.seq_row0) return fail(SPEC_ERR_SHAPE, "%d window rows exceed the %d the handle takes", M, h->row_cap);
     int pass_seqs[SPEC_PLAN_MAX_PASSES], pass_rows[SPEC_PLAN_MAX_PASSES];
     const int n_passes = plan_passes(ks, B, M, h->row_cap, pass_seqs, pass_rows, SPEC_PLAN_MAX_PASSES);
@@ -177,7 +178,8 @@ int forward_run_grouped(spec_handle* h, const LookaheadPack& ks, int B, int M, f
     return SPEC_OK;
 }
 
-int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, int B, int M, float* logits_out, hipStream_t s)
+int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, int B, int M, float* logits_out, hipStream_t s,
+                LogitsSrc* last)
 {
     const spec_model_cfg& c = h->cfg;
     const Dims z = dims_of(c);
@@ -284,6 +286,10 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
     }
     rc = gemm(SPEC_PROF_GEMM_LM_HEAD, h->lm_head, z.V, z.d, &o, h->xf);
     if (rc) return rc;
+    if (last) {
+        *last = LogitsSrc{h->partial, o.stride, o.n_split, o.ld, scaled, logits_out};
+        return SPEC_OK;
+    }
     RUN(SPEC_PROF_GLUE, launch_reduce_splits(h->partial, o.n_split, o.stride, M, z.V, o.ld, h->ssq, n_ssq, z.d, c.rms_eps,
                                              logits_out, s));
 #undef RUN

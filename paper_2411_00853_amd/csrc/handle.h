@@ -62,9 +62,13 @@ struct spec_handle {
 namespace specv {
 int forward_init(spec_handle* h, int max_rows);
 // one decoder pass over the B sequences (M <= row_cap window rows) that t describes
-int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, int B, int M, float* logits_out, hipStream_t s);
+// last != NULL (bf16): the logits stay partial sums, *last says where; else they are written to logits_out
+int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, int B, int M, float* logits_out, hipStream_t s,
+                LogitsSrc* last = nullptr);
 // the same for any M: sequences are taken in groups of at most row_cap rows, one pass each (t = h->tables)
-int forward_run_grouped(spec_handle* h, const LookaheadPack& ks, int B, int M, float* logits_out, hipStream_t s);
+// (last->partial == NULL where the logits are written after all: fp32 models, several passes)
+int forward_run_grouped(spec_handle* h, const LookaheadPack& ks, int B, int M, float* logits_out, hipStream_t s,
+                        LogitsSrc* last = nullptr);
 // host logic behind the two (no device work): see forward.hip
 size_t gemm_partial_capacity(const spec_model_cfg& c, int max_rows, int cu_count);
 void projection_shapes(const spec_model_cfg& c, int* n_out, int* n_in);   // [SPEC_PLAN_PROJECTIONS]

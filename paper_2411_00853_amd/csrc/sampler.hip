@@ -13,7 +13,9 @@
 // fixed order (no floating-point atomics), so results are reproducible bit for bit.
 #include "cache_layout.h"
 #include "common.h"
+#include "frag.h"
 
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 
@@ -23,17 +25,68 @@ namespace {
 
 constexpr int TPB = 256;
 
-__device__ __forceinline__ float wave_max(float v)
+// Exchanges inside a wavefront by DPP (a few cycles a step where a shuffle through LDS takes a hundred, and every kernel
+// here is a chain of such steps).  Lanes without a source keep `old`.
+enum { DPP_XOR1 = 0xb1, DPP_XOR2 = 0x4e, DPP_SHR1 = 0x111, DPP_SHR2 = 0x112, DPP_SHR4 = 0x114, DPP_SHR8 = 0x118, DPP_MIRROR = 0x140,
+       DPP_HALF_MIRROR = 0x141, DPP_BCAST15 = 0x142, DPP_BCAST31 = 0x143 };
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp(int old, int v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
+    return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double v)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)dpp<CTRL, ROWS>(0, (int)(uint32_t)u), hi = (uint32_t)dpp<CTRL, ROWS>(0, (int)(uint32_t)(u >> 32));
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double read_lane(double v, int lane)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
-__device__ __forceinline__ double wave_sum(double v)
+__device__ __forceinline__ float wave_max(float v)   // (the same for all lanes)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    auto step = [&](int o) { v = fmaxf(v, __builtin_bit_cast(float, o)); };
+    auto bits = [&] { return __builtin_bit_cast(int, v); };
+    step(dpp<DPP_XOR1, 0xf>(bits(), bits()));
+    step(dpp<DPP_XOR2, 0xf>(bits(), bits()));
+    step(dpp<DPP_HALF_MIRROR, 0xf>(bits(), bits()));
+    step(dpp<DPP_MIRROR, 0xf>(bits(), bits()));
+    step(dpp<DPP_BCAST15, 0xa>(bits(), bits()));
+    step(dpp<DPP_BCAST31, 0xc>(bits(), bits()));
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(bits(), 63));
+}
+
+__device__ __forceinline__ double wave_sum(double v)   // (the same for all lanes; a fixed order)
+{
+    v += dpp_or_zero<DPP_XOR1, 0xf>(v);
+    v += dpp_or_zero<DPP_XOR2, 0xf>(v);
+    v += dpp_or_zero<DPP_HALF_MIRROR, 0xf>(v);
+    v += dpp_or_zero<DPP_MIRROR, 0xf>(v);
+    v += dpp_or_zero<DPP_BCAST15, 0xa>(v);
+    v += dpp_or_zero<DPP_BCAST31, 0xc>(v);
+    return read_lane(v, 63);
+}
+
+// inclusive running sums over the lanes (of the first 16 lanes: the first four steps)
+__device__ __forceinline__ double row_scan(double v)
+{
+    v += dpp_or_zero<DPP_SHR1, 0xf>(v);
+    v += dpp_or_zero<DPP_SHR2, 0xf>(v);
+    v += dpp_or_zero<DPP_SHR4, 0xf>(v);
+    v += dpp_or_zero<DPP_SHR8, 0xf>(v);
+    return v;
+}
+__device__ __forceinline__ double wave_scan(double v)
+{
+    v = row_scan(v);
+    v += dpp_or_zero<DPP_BCAST15, 0xa>(v);
+    v += dpp_or_zero<DPP_BCAST31, 0xc>(v);
     return v;
 }
 
@@ -278,13 +331,46 @@ __device__ __forceinline__ void find_stat_row(const LookaheadPack& ks, int B, in
     *K_out = K;
 }
 
-template <bool VEC4>
+// (sum of the ranges, in index order) * row scale of N float4 columns AT apart, as many loads in flight as make 32 of them
+template <int S, int N>
+__device__ __forceinline__ void logits_from(const float* p, size_t stride, int at, int lim, int first, float r, floatx4 (&v)[N])
+{
+    constexpr int W = S <= 2 ? N : N * 2 / S > 0 ? N * 2 / S : 1;   // columns at a time
+#pragma unroll
+    for (int i0 = 0; i0 < N; i0 += W) {
+        floatx4 a[W][S];
+#pragma unroll
+        for (int i = 0; i < W; ++i)
+#pragma unroll
+            for (int q = 0; q < S; ++q)   // (columns past the end: the last ones again)
+                a[i][q] = *reinterpret_cast<const floatx4*>(p + q * stride + min(first + (i0 + i) * at, lim - 4));
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            floatx4 t = a[i][0];
+#pragma unroll
+            for (int q = 1; q < S; ++q) t += a[i][q];
+            v[i0 + i] = t * r;
+        }
+    }
+}
+
+// any number of ranges, for column c of the row
+__device__ __forceinline__ float logit_from(const LogitsSrc& src, const float* p, int c, float r)
+{
+    float t = p[c];
+    for (int q = 1; q < src.n_split; ++q) t += p[q * src.stride + c];
+    return t * r;
+}
+
+// SRC: target rows come as the LM head's partial sums; the workgroup adds up its chunk, writes it to src.out and goes on
+// from registers (as a kernel of its own in front of this one the sum took 4.5-5.4 us a step, 9.4-15.8 at 128-352 rows).
+template <bool VEC4, bool SRC>
 __global__ void __launch_bounds__(TPB) stats_kernel(int prep_on, int layout, int B, int draft_rows, int V, int n_chunks,
                                                     const float* __restrict__ target,
                                                     const float* __restrict__ draft, float* __restrict__ copy_out,
                                                     float inv_T, float* __restrict__ part_max,
                                                     double* __restrict__ part_sum, size_t copy_stride,
-                                                    StepTables t, LookaheadPack ks, PrepIn prep)
+                                                    StepTables t, LookaheadPack ks, PrepIn prep, LogitsSrc src)
 {
     __shared__ float smax[TPB / 64];
     __shared__ double ssum[TPB / 64];
@@ -298,12 +384,15 @@ __global__ void __launch_bounds__(TPB) stats_kernel(int prep_on, int layout, int
     const int srow = wg / n_chunks;
     const int chunk = wg % n_chunks;
     const float* row;
+    int m = -1;   // target row, -1: a draft row
     if (layout == STAT_PLAIN) {
-        row = target + (size_t)t.seq_row0[srow] * V;
+        m = t.seq_row0[srow];
+        row = target + (size_t)m * V;
     } else {
         int b, local, r0, K;
         find_stat_row(ks, B, srow, layout == STAT_TREE, &b, &local, &r0, &K);
-        row = local <= K ? target + (size_t)(r0 + local) * V : draft + ((size_t)b * draft_rows + (local - K - 1)) * V;
+        if (local <= K) m = r0 + local;
+        row = local <= K ? target + (size_t)m * V : draft + ((size_t)b * draft_rows + (local - K - 1)) * V;
     }
     const int base = chunk * STAT_CHUNK;
     const int lim = min(STAT_CHUNK, V - base);
@@ -311,7 +400,40 @@ __global__ void __launch_bounds__(TPB) stats_kernel(int prep_on, int layout, int
     constexpr int PER = STAT_CHUNK / TPB;   // 64 values per lane
     float v[PER];
     // copy_out: plain-draw mode (one statistics row per sequence): keep the row for the verifier
-    if constexpr (VEC4) {
+    if (SRC && m >= 0) {
+        const float rs = row_inv_rms(src.ns.ssq, src.ns.n_ssq, m, src.ns.d, src.ns.eps);
+        const float* p = src.partial + (size_t)m * src.ld + base;
+        float* o = src.out + (size_t)m * V + base;
+        if constexpr (VEC4) {
+            floatx4 x[PER / 4];
+            const int first = 4 * threadIdx.x;
+            switch (src.n_split) {
+            case 1: logits_from<1>(p, src.stride, 4 * TPB, lim, first, rs, x); break;
+            case 2: logits_from<2>(p, src.stride, 4 * TPB, lim, first, rs, x); break;
+            case 4: logits_from<4>(p, src.stride, 4 * TPB, lim, first, rs, x); break;
+            case 8: logits_from<8>(p, src.stride, 4 * TPB, lim, first, rs, x); break;
+            default: logits_from<16>(p, src.stride, 4 * TPB, lim, first, rs, x); break;
+            }
+#pragma unroll
+            for (int i = 0; i < PER / 4; ++i) {
+                const int idx = first + i * 4 * TPB;
+                const bool in = idx < lim;
+                if (in) *reinterpret_cast<floatx4*>(o + idx) = x[i];
+                v[4 * i + 0] = in ? x[i].x : -INFINITY; v[4 * i + 1] = in ? x[i].y : -INFINITY;
+                v[4 * i + 2] = in ? x[i].z : -INFINITY; v[4 * i + 3] = in ? x[i].w : -INFINITY;
+            }
+        } else {
+#pragma unroll 8
+            for (int i = 0; i < PER; ++i) {
+                const int idx = i * TPB + threadIdx.x;
+                v[i] = -INFINITY;
+                if (idx < lim) {
+                    v[i] = logit_from(src, p, idx, rs);
+                    o[idx] = v[i];
+                }
+            }
+        }
+    } else if constexpr (VEC4) {
         const float4* p4 = reinterpret_cast<const float4*>(row + base);
 #pragma unroll
         for (int i = 0; i < PER / 4; ++i) {
@@ -324,19 +446,19 @@ __global__ void __launch_bounds__(TPB) stats_kernel(int prep_on, int layout, int
             }
             v[4 * i + 0] = x.x; v[4 * i + 1] = x.y; v[4 * i + 2] = x.z; v[4 * i + 3] = x.w;
         }
-        if (copy_out) {   // whole 16-byte stores (the launcher checked the alignment of the copy as well)
-            float4* d4 = reinterpret_cast<float4*>(copy_out + (size_t)srow * copy_stride + base);
-#pragma unroll
-            for (int i = 0; i < PER / 4; ++i) {
-                const int idx = i * TPB + threadIdx.x;
-                if (idx * 4 < lim) d4[idx] = make_float4(v[4 * i + 0], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
-            }
-        }
     } else {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             int idx = i * TPB + threadIdx.x;
             v[i] = idx < lim ? row[base + idx] : -INFINITY;
+        }
+    }
+    if (VEC4 && copy_out) {   // whole 16-byte stores (the launcher checked the alignment of the copy as well)
+        float4* d4 = reinterpret_cast<float4*>(copy_out + (size_t)srow * copy_stride + base);
+#pragma unroll
+        for (int i = 0; i < PER / 4; ++i) {
+            const int idx = i * TPB + threadIdx.x;
+            if (idx * 4 < lim) d4[idx] = make_float4(v[4 * i + 0], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
         }
     }
     if (!VEC4 && copy_out) {
@@ -347,14 +469,14 @@ __global__ void __launch_bounds__(TPB) stats_kernel(int prep_on, int layout, int
             if (idx < lim) dst[idx] = v[i];
         }
     }
-    float m = -INFINITY;
+    float mx = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) m = fmaxf(m, v[i]);
-    m = wave_max(m);
-    if ((threadIdx.x & 63) == 0) smax[threadIdx.x >> 6] = m;
+    for (int i = 0; i < PER; ++i) mx = fmaxf(mx, v[i]);
+    mx = wave_max(mx);
+    if ((threadIdx.x & 63) == 0) smax[threadIdx.x >> 6] = mx;
     __syncthreads();
-    m = fmaxf(fmaxf(smax[0], smax[1]), fmaxf(smax[2], smax[3]));
-    const float mm = (m == -INFINITY) ? 0.f : m;   // a chunk of -inf logits contributes nothing
+    mx = fmaxf(fmaxf(smax[0], smax[1]), fmaxf(smax[2], smax[3]));
+    const float mm = (mx == -INFINITY) ? 0.f : mx;   // a chunk of -inf logits contributes nothing
 
     double acc = 0.0;
 #pragma unroll
@@ -363,7 +485,7 @@ __global__ void __launch_bounds__(TPB) stats_kernel(int prep_on, int layout, int
     if ((threadIdx.x & 63) == 0) ssum[threadIdx.x >> 6] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
-        part_max[(size_t)srow * n_chunks + chunk] = m;
+        part_max[(size_t)srow * n_chunks + chunk] = mx;
         part_sum[(size_t)srow * n_chunks + chunk] = (ssum[0] + ssum[1]) + (ssum[2] + ssum[3]);
     }
 }
@@ -678,12 +800,7 @@ __global__ void __launch_bounds__(TPB) final_draw_kernel(const int32_t* accepted
             loc += x;
             if (x > 0.0) my_last = base + threadIdx.x * PER + i;
         }
-        double inc = loc;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            double up = __shfl_up(inc, o);
-            if ((int)(threadIdx.x & 63) >= o) inc += up;
-        }
+        double inc = wave_scan(loc);
         if ((threadIdx.x & 63) == 63) wave_tot[threadIdx.x >> 6] = inc;
         __syncthreads();
         double off = before;
@@ -736,6 +853,365 @@ __global__ void __launch_bounds__(TPB) final_draw_kernel(const int32_t* accepted
             pool_trim(t.pool, t.seq_slot[b], t.seq_n[b] + (auto_rollback ? a : K) + 1);
         }
     }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Vocabularies of up to DRAW_MAX: one workgroup per sequence keeps the row (or the two rows) of the draw in registers, so
+// what the two passes above do -- and for a plain draw the statistics in front of them -- is one launch, without a second
+// read of the rows.  RUNS runs of 256 ids per wavefront: wavefront w holds ids [256 RUNS w, 256 RUNS (w + 1)), lane l of it
+// the ids 4 l .. 4 l + 3 of every run.
+// ---------------------------------------------------------------------------------------------
+constexpr int DRAW_TPB = 1024, DRAW_WAVES = DRAW_TPB / 64, DRAW_MAX_RUNS = 8;
+constexpr int DRAW_MAX = DRAW_WAVES * 256 * DRAW_MAX_RUNS;   // 32768
+static_assert(STAT_CHUNK % (256 * DRAW_MAX_RUNS) == 0, "a wavefront's ids lie in one statistics chunk");
+static_assert(DRAW_WAVES == 16, "the wavefronts' sums are scanned by 16 lanes");
+constexpr int STATS_MAX = 2048;                              // a row in a wavefront's registers
+inline int draw_runs(int V) { return V <= 4096 ? 1 : V <= 8192 ? 2 : V <= 16384 ? 4 : 8; }
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // global memory takes 16-byte accesses at any 4-byte address
+
+// four ids from id0 on of each of N runs of a row of V logits; past the end -inf
+template <int N>
+__device__ __forceinline__ void draw_load(const float* row, int V, int id0, floatx4 (&v)[N])
+{
+    if (V >= 4) {   // every lane loads four ids that exist, the row's last ones shifted into place
+        f32x4u x[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) x[j] = *reinterpret_cast<const f32x4u*>(row + min(id0 + 256 * j, V - 4));
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const int id = id0 + 256 * j, sh = id - min(id, V - 4);
+            v[j].x = sh == 0 ? x[j].x : sh == 1 ? x[j].y : sh == 2 ? x[j].z : sh == 3 ? x[j].w : -INFINITY;
+            v[j].y = sh == 0 ? x[j].y : sh == 1 ? x[j].z : sh == 2 ? x[j].w : -INFINITY;
+            v[j].z = sh == 0 ? x[j].z : sh == 1 ? x[j].w : -INFINITY;
+            v[j].w = sh == 0 ? x[j].w : -INFINITY;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const int id = id0 + 256 * j;
+            v[j] = floatx4{id < V ? row[id] : -INFINITY, id + 1 < V ? row[id + 1] : -INFINITY, id + 2 < V ? row[id + 2] : -INFINITY, -INFINITY};
+        }
+    }
+}
+template <int RUNS>
+__device__ __forceinline__ int draw_id0() { return (threadIdx.x >> 6) * (256 * RUNS) + 4 * (threadIdx.x & 63); }
+
+template <int N>
+__device__ __forceinline__ void draw_store(float* row, int V, int id0, const floatx4 (&v)[N])
+{
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const int id = id0 + 256 * j;
+        if (id + 4 <= V) {
+            *reinterpret_cast<f32x4u*>(row + id) = f32x4u{v[j].x, v[j].y, v[j].z, v[j].w};
+        } else {
+            if (id < V) row[id] = v[j].x;
+            if (id + 1 < V) row[id + 1] = v[j].y;
+            if (id + 2 < V) row[id + 2] = v[j].z;
+        }
+    }
+}
+
+struct DrawLds {
+    double tot[DRAW_WAVES];
+    int last[DRAW_WAVES];
+    int tok;
+};
+
+// The id at which the running sum of the masses (never negative) first exceeds u times the whole (absolute: u itself), ids
+// ascending; if rounding leaves no crossing, the last id with mass of the stretch looked at.  run: this thread's sums of
+// its four ids of every run; four(j, x): those ids' masses again.  Returns false if there is no mass (nothing drawn).  All
+// threads call; the result is in l.tok for all of them.
+template <int RUNS, typename F>
+__device__ __forceinline__ bool draw_locate(double (&run)[RUNS], F four, double u, bool absolute, DrawLds& l)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    double t = 0.0;
+#pragma unroll
+    for (int j = 0; j < RUNS; ++j) t += run[j];
+    t = wave_sum(t);
+    if (lane == 0) l.tot[wave] = t;
+    __syncthreads();
+    // lane w takes wavefront w's sum: the first of them whose running sum passes the target
+    const double tw = lane < DRAW_WAVES ? l.tot[lane] : 0.0;
+    const double upto = row_scan(tw), S = read_lane(upto, DRAW_WAVES - 1);
+    if (!absolute && !(S > 0.0)) return false;
+    const double target = absolute ? u : u * S;
+    const unsigned long long over = __ballot(lane < DRAW_WAVES && upto > target), some = __ballot(tw > 0.0);
+    const int pick = over ? __ffsll((long long)over) - 1 : some ? 63 - __clzll((long long)some) : 0;
+    const double before = pick > 0 ? read_lane(upto, pick - 1) : 0.0;
+    if (wave == pick) {   // the only wavefront that looks closer: which run, which lane, which id
+        int at = -1, last_run = 0;
+        double c0 = before, at_before = before, last_before = before;
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j) {
+            const double r = wave_sum(run[j]);
+            if (r > 0.0) { last_run = j; last_before = c0; }
+            if (at < 0 && c0 + r > target) { at = j; at_before = c0; }
+            c0 += r;
+        }
+        if (at < 0) { at = last_run; at_before = last_before; }
+        double x[4];
+        four(at, x);
+        const double loc = (x[0] + x[1]) + (x[2] + x[3]);
+        const double inc = wave_scan(loc) + at_before;
+        // the first lane whose running sum passes the target; its ids one by one
+        const int id0 = wave * (256 * RUNS) + 256 * at + 4 * lane;
+        double cdf = inc - loc;
+        int mine = -1, mine_last = -1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            cdf += x[e];
+            if (mine < 0 && cdf > target) mine = id0 + e;
+            if (x[e] > 0.0) mine_last = id0 + e;
+        }
+        if (mine < 0) mine = mine_last;   // rounding between the lane's sum and the running one
+        const unsigned long long hit = __ballot(inc > target && mine >= 0), any = __ballot(mine_last >= 0);
+        const int from = hit ? __ffsll((long long)hit) - 1 : any ? 63 - __clzll((long long)any) : 0;
+        const int tok = __shfl(hit ? mine : mine_last, from);
+        if (lane == 0) l.tok = max(tok, 0);
+    }
+    __syncthreads();
+    return true;
+}
+
+// what a draw leaves behind, as final_draw_kernel does it; the first wavefront calls.  x: lane i holds proposal i.
+__device__ __forceinline__ void draw_emit(const StepTables& t, const DrawEmit& emit, int b, int slot, int n, int K, int Kmax, int a,
+                                          int y, int x, int auto_rollback, int32_t* kv_len, int32_t* n_accepted, int32_t* out_tokens)
+{
+    const int i = threadIdx.x;
+    if (emit.tokens) {
+        if (i == 0) {
+            emit.tokens[b * emit.stride + emit.offset] = y;
+            emit.next_token[b] = y;
+            if (emit.kv_len) emit.kv_len[slot] = n + emit.kv_add;
+        }
+        return;
+    }
+    if (i <= Kmax) out_tokens[b * (Kmax + 1) + i] = i < a ? x : i == a ? y : -1;
+    if (i == 0) {
+        n_accepted[b] = a;
+        if (kv_len) {
+            const int len = n + (auto_rollback ? a : K) + 1;
+            kv_len[slot] = len;
+            pool_trim(t.pool, slot, len);
+        }
+    }
+}
+
+// a sequence that the row bookkeeping skipped; all threads call
+__device__ __forceinline__ void draw_skip(const DrawEmit& emit, int b, int Kmax, int32_t* n_accepted, int32_t* out_tokens)
+{
+    const int i = threadIdx.x;
+    if (emit.tokens) {   // an invalid id makes whoever consumes it skip the sequence too
+        if (i == 0) {
+            emit.tokens[b * emit.stride + emit.offset] = -1;
+            emit.next_token[b] = -1;
+        }
+        return;
+    }
+    if (i == 0) n_accepted[b] = -1;
+    if (i <= Kmax) out_tokens[b * (Kmax + 1) + i] = -1;
+}
+
+// After the statistics: accept scan, mass of the final draw's distribution, the draw, the results.
+// (accept_mass_kernel and final_draw_kernel in one.)  STATS: the statistics as well, a wavefront per row -- at most 31 rows of
+// STATS_MAX logits, which one compute unit reads in the time that a launch takes (fp32 model of vocabulary 1024, one sequence of
+// five rows: 4.3 + 5.9 us as two launches, 7.8 as one).
+template <int RUNS, bool STATS>
+__global__ void __launch_bounds__(DRAW_TPB) accept_draw_kernel(const int32_t* seq_stat0, const int32_t* seq_row0,
+                                                               const int32_t* __restrict__ draft_tokens,
+                                                               const float* __restrict__ part_max,
+                                                               const double* __restrict__ part_sum, int Kmax, int V,
+                                                               int n_stat_chunks, int u_stride,
+                                                               const float* __restrict__ uniforms,
+                                                               const float* __restrict__ target,
+                                                               const float* __restrict__ draft, float inv_T_f, int auto_rollback,
+                                                               int32_t* kv_len, int32_t* __restrict__ n_accepted,
+                                                               int32_t* __restrict__ out_tokens, StepTables t, LookaheadPack ks)
+{
+    __shared__ float row_m[2 * SPEC_MAX_LOOKAHEAD + 2];
+    __shared__ double row_z[2 * SPEC_MAX_LOOKAHEAD + 2];
+    __shared__ int s_a;
+    __shared__ double s_iz[2];
+    __shared__ DrawLds l;
+    const int b = blockIdx.x;
+    const int st0 = seq_stat0[b], row0 = seq_row0[b], ok = t.seq_ok[b], slot = t.seq_slot[b], n = t.seq_n[b];
+    const int K = ks.k[b];
+    const double inv_T = (double)inv_T_f;
+    const float* trow0 = target + (size_t)row0 * V;
+    const float* drow0 = draft + (size_t)b * Kmax * V;
+    const int i = min((int)threadIdx.x, max(K - 1, 0));   // lane i tests proposal i, see accept_mass_kernel
+    float lp_x = 0.f, lq_x = 0.f;
+    double u = 0.0;
+    int x = 0;
+    if (threadIdx.x < 64 && K > 0) {
+        x = draft_tokens[b * Kmax + i];
+        const bool xin = x >= 0 && x < V;   // out-of-range ids were flagged by prepare; stay in bounds
+        u = (double)uniforms[b * u_stride + i];
+        lp_x = xin ? trow0[(size_t)i * V + x] : 0.f;
+        lq_x = xin ? drow0[(size_t)i * V + x] : 0.f;
+    }
+    const double u_draw = (double)uniforms[b * u_stride + K];
+    if (!ok) {
+        draw_skip(DrawEmit{}, b, Kmax, n_accepted, out_tokens);
+        return;
+    }
+    if constexpr (STATS) {
+        for (int r = threadIdx.x >> 6; r < 2 * K + 1; r += DRAW_WAVES) {
+            const float* row = r <= K ? trow0 + (size_t)r * V : drow0 + (size_t)(r - K - 1) * V;
+            constexpr int N = STATS_MAX / 256;
+            floatx4 v[N];
+            draw_load(row, V, 4 * (threadIdx.x & 63), v);
+            float mx = -INFINITY;
+#pragma unroll
+            for (int j = 0; j < N; ++j) mx = fmaxf(fmaxf(mx, fmaxf(v[j].x, v[j].y)), fmaxf(v[j].z, v[j].w));
+            mx = wave_max(mx);
+            const float mm = mx == -INFINITY ? 0.f : mx;
+            double z = 0.0;
+#pragma unroll
+            for (int j = 0; j < N; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) z += (double)__expf((v[j][e] - mm) * inv_T_f);
+            z = wave_sum(z);
+            if ((threadIdx.x & 63) == 0) {
+                row_m[r] = mx;
+                row_z[r] = z;
+            }
+        }
+        __syncthreads();
+    } else {
+        __shared__ CombineLds comb;
+        combine_rows<DRAW_TPB>(part_max, part_sum, st0, 2 * K + 1, n_stat_chunks, inv_T, row_m, row_z, comb);
+    }
+    if (threadIdx.x < 64) {
+        bool keep = true;
+        if (K > 0) {
+            const double ep = exp((double)(lp_x - row_m[i]) * inv_T);
+            const double eq = exp((double)(lq_x - row_m[K + 1 + i]) * inv_T);
+            keep = u * eq * row_z[i] < ep * row_z[K + 1 + i];   // u * q(x) < p(x)
+        }
+        const unsigned long long failed = __ballot(!keep && (int)threadIdx.x < K);
+        const int first = failed ? __builtin_ctzll(failed) : K;
+        if (threadIdx.x < 2) s_iz[threadIdx.x] = 1.0 / row_z[threadIdx.x == 0 ? first : first < K ? K + 1 + first : 0];
+        if (threadIdx.x == 0) s_a = first;
+    }
+    __syncthreads();
+    const int a = s_a;
+    const bool residual = a < K;
+    const float mp = row_m[a], mq = residual ? row_m[K + 1 + a] : 0.f;
+    const double izp = s_iz[0], izq = s_iz[1];
+    const float* prow = trow0 + (size_t)a * V;            // a == K: the extra-token row
+    const float* qrow = drow0 + (size_t)(residual ? a : 0) * V;
+    auto mass = [&](float lp, float lq) {
+        const double pv = (double)__expf((lp - mp) * inv_T_f) * izp, qv = residual ? (double)__expf((lq - mq) * inv_T_f) * izq : 0.0;
+        return pv > qv ? pv - qv : 0.0;
+    };
+    double run[RUNS];
+    {
+        floatx4 p[RUNS], q[RUNS];
+        draw_load(prow, V, draw_id0<RUNS>(), p);
+        if (residual) draw_load(qrow, V, draw_id0<RUNS>(), q);
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j)
+            run[j] = (mass(p[j].x, q[j].x) + mass(p[j].y, q[j].y)) + (mass(p[j].z, q[j].z) + mass(p[j].w, q[j].w));
+    }
+    auto four = [&](int j, double (&x)[4]) {   // (read again rather than kept: both rows are 64 registers)
+        floatx4 p[1], q[1];
+        draw_load(prow, V, draw_id0<RUNS>() + 256 * j, p);
+        if (residual) draw_load(qrow, V, draw_id0<RUNS>() + 256 * j, q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = mass(p[0][e], q[0][e]);
+    };
+    if (!draw_locate(run, four, u_draw, false, l)) {   // no mass left (impossible in exact arithmetic): draw from p_a, which sums to 1
+        __syncthreads();
+        auto plain = [&](float lp) { return (double)__expf((lp - mp) * inv_T_f) * izp; };
+        floatx4 p[RUNS];
+        draw_load(prow, V, draw_id0<RUNS>(), p);
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j) run[j] = (plain(p[j].x) + plain(p[j].y)) + (plain(p[j].z) + plain(p[j].w));
+        draw_locate(run, [&](int j, double (&x)[4]) {
+            floatx4 p1[1];
+            draw_load(prow, V, draw_id0<RUNS>() + 256 * j, p1);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = plain(p1[0][e]);
+        }, u_draw, true, l);
+    }
+    if (threadIdx.x < 64) draw_emit(t, DrawEmit{}, b, slot, n, K, Kmax, a, l.tok, x, auto_rollback, kv_len, n_accepted, out_tokens);
+}
+
+// A plain draw (no proposals): maximum, weights and draw of one row per sequence, which comes whole or as the LM head's
+// partial sums (SRC; written to src.out on the way).  The draft model's draw was four launches (row sum, statistics, mass, draw).
+template <bool SRC, int RUNS>
+__global__ void __launch_bounds__(DRAW_TPB) plain_draw_kernel(const int32_t* seq_row0, const float* __restrict__ target,
+                                                              const float* __restrict__ uniforms, int u_stride, int V, int Kmax,
+                                                              float inv_T_f, int auto_rollback, int32_t* kv_len,
+                                                              int32_t* __restrict__ n_accepted, int32_t* __restrict__ out_tokens,
+                                                              StepTables t, DrawEmit emit, LogitsSrc src)
+{
+    __shared__ float s_max[DRAW_WAVES];
+    __shared__ DrawLds l;
+    const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int m = seq_row0[b], ok = t.seq_ok[b], slot = t.seq_slot[b], n = t.seq_n[b];
+    const double u = (double)uniforms[b * u_stride];
+    const int first = draw_id0<RUNS>();
+    floatx4 v[RUNS];
+    if constexpr (SRC) {
+        const float rs = row_inv_rms(src.ns.ssq, src.ns.n_ssq, m, src.ns.d, src.ns.eps);
+        const float* p = src.partial + (size_t)m * src.ld;   // (a row has ld >= V columns, a multiple of 16, to read)
+        switch (src.n_split) {
+        case 1: logits_from<1>(p, src.stride, 256, src.ld, first, rs, v); break;
+        case 2: logits_from<2>(p, src.stride, 256, src.ld, first, rs, v); break;
+        case 4: logits_from<4>(p, src.stride, 256, src.ld, first, rs, v); break;
+        case 8: logits_from<8>(p, src.stride, 256, src.ld, first, rs, v); break;
+        default: logits_from<16>(p, src.stride, 256, src.ld, first, rs, v); break;
+        }
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j) {
+            const int id = first + 256 * j;
+            if (id >= V) v[j].x = -INFINITY;
+            if (id + 1 >= V) v[j].y = -INFINITY;
+            if (id + 2 >= V) v[j].z = -INFINITY;
+            if (id + 3 >= V) v[j].w = -INFINITY;
+        }
+        draw_store(src.out + (size_t)m * V, V, first, v);
+    } else {
+        draw_load(target + (size_t)m * V, V, draw_id0<RUNS>(), v);
+    }
+    if (emit.logits_copy) draw_store(emit.logits_copy + (size_t)b * emit.copy_stride, V, first, v);
+    if (!ok) {
+        draw_skip(emit, b, Kmax, n_accepted, out_tokens);
+        return;
+    }
+    // the weights relative to the row's maximum are all a draw needs: their sum takes the place of the normaliser
+    float mw = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < RUNS; ++j) mw = fmaxf(fmaxf(mw, fmaxf(v[j].x, v[j].y)), fmaxf(v[j].z, v[j].w));
+    mw = wave_max(mw);
+    if (lane == 0) s_max[wave] = mw;
+    __syncthreads();
+    const float mp = wave_max(s_max[lane % DRAW_WAVES]);
+    double run[RUNS];
+#pragma unroll
+    for (int j = 0; j < RUNS; ++j) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[j][e] = __expf((v[j][e] - mp) * inv_T_f);
+        run[j] = ((double)v[j].x + (double)v[j].y) + ((double)v[j].z + (double)v[j].w);
+    }
+    // (no mass at all takes a row without a finite logit; the draw is then what rounding makes of it)
+    if (!draw_locate(run, [&](int j, double (&x)[4]) {
+            floatx4 e4 = v[0];
+#pragma unroll
+            for (int i = 1; i < RUNS; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) e4[e] = j == i ? v[i][e] : e4[e];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = (double)e4[e];
+        }, u, false, l)) {
+        if (threadIdx.x == 0) l.tok = 0;
+        __syncthreads();
+    }
+    if (threadIdx.x < 64) draw_emit(t, emit, b, slot, n, 0, Kmax, 0, l.tok, 0, auto_rollback, kv_len, n_accepted, out_tokens);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1229,12 +1705,7 @@ __global__ void __launch_bounds__(TREE_TPB) tree_walk_kernel(StepTables t, Looka
             loc += x;
             if (x > 0.0) my_last = base + threadIdx.x * PER + i;
         }
-        double inc = loc;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const double up = __shfl_up(inc, o);
-            if ((int)(threadIdx.x & 63) >= o) inc += up;
-        }
+        double inc = wave_scan(loc);
         if ((threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = inc;
         __syncthreads();
         double off = before;
@@ -1375,7 +1846,7 @@ int launch_tree_sampler(const StepTables& t, const SamplerWorkspace& w, const Lo
                         int V, int n_stat_rows, const float* target_logits, const float* draft_logits,
                         const int32_t* parent, const int32_t* tokens, const float* uniforms, float temperature,
                         int auto_rollback, int32_t* kv_len, int32_t* n_accepted, int32_t* out_tokens,
-                        int32_t* path, Profiler* prof, hipStream_t s)
+                        int32_t* path, Profiler* prof, hipStream_t s, const LogitsSrc* src)
 {
     const int n_stat_chunks = (V + STAT_CHUNK - 1) / STAT_CHUNK;
     if ((V + RES_CHUNK - 1) / RES_CHUNK > TREE_CHUNKS)
@@ -1386,14 +1857,11 @@ int launch_tree_sampler(const StepTables& t, const SamplerWorkspace& w, const Lo
     dim3 g1((unsigned)n_stat_rows * n_stat_chunks);
     {
         ProfScope ps(prof, SPEC_PROF_SAMPLER_STATS, s);
-        if (vec4)
-            hipLaunchKernelGGL(stats_kernel<true>, g1, dim3(TPB), 0, s, 0, (int)STAT_TREE, B, Kmax + 1, V, n_stat_chunks,
-                               target_logits, draft_logits, (float*)nullptr, inv_T, w.part_max, w.part_sum, (size_t)0, t, ks,
-                               PrepIn{});
-        else
-            hipLaunchKernelGGL(stats_kernel<false>, g1, dim3(TPB), 0, s, 0, (int)STAT_TREE, B, Kmax + 1, V, n_stat_chunks,
-                               target_logits, draft_logits, (float*)nullptr, inv_T, w.part_max, w.part_sum, (size_t)0, t, ks,
-                               PrepIn{});
+        const LogitsSrc from = src ? *src : LogitsSrc{};
+        auto* k = from.partial ? (vec4 ? stats_kernel<true, true> : stats_kernel<false, true>)
+                               : (vec4 ? stats_kernel<true, false> : stats_kernel<false, false>);
+        hipLaunchKernelGGL(k, g1, dim3(TPB), 0, s, 0, (int)STAT_TREE, B, Kmax + 1, V, n_stat_chunks, target_logits, draft_logits,
+                           (float*)nullptr, inv_T, w.part_max, w.part_sum, (size_t)0, t, ks, PrepIn{}, from);
         SPECV_LAUNCH_CHECK("stats_kernel");
     }
     ProfScope ps(prof, SPEC_PROF_SAMPLER_DRAW, s);
@@ -1439,7 +1907,7 @@ int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const Lookahe
                    int V, int n_stat_rows, const float* target_logits, const float* draft_logits,
                    const int32_t* draft_tokens, const float* uniforms, int u_stride, float temperature,
                    int auto_rollback, int32_t* kv_len, int32_t* n_accepted, int32_t* out_tokens,
-                   const DrawEmit* emit, Profiler* prof, hipStream_t s, int32_t* prepare_flag)
+                   const DrawEmit* emit, Profiler* prof, hipStream_t s, int32_t* prepare_flag, const LogitsSrc* src)
 {
     const int n_stat_chunks = (V + STAT_CHUNK - 1) / STAT_CHUNK;
     const int n_res_chunks = (V + RES_CHUNK - 1) / RES_CHUNK;
@@ -1460,20 +1928,40 @@ int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const Lookahe
     const bool vec4 = (V % 4 == 0) && ((reinterpret_cast<uintptr_t>(target_logits) & 15) == 0)
                       && ((reinterpret_cast<uintptr_t>(draft_logits) & 15) == 0)
                       && ((reinterpret_cast<uintptr_t>(em.logits_copy) & 15) == 0) && (em.copy_stride % 4 == 0);
+    const LogitsSrc from = src ? *src : LogitsSrc{};
+    if (n_stat_rows == B && V <= DRAW_MAX && !prepare_flag) {   // nothing to test: one launch
+        ProfScope ps(prof, SPEC_PROF_SAMPLER_DRAW, s);
+        const int runs = draw_runs(V);
+        auto* k = from.partial ? (runs == 1 ? plain_draw_kernel<true, 1> : runs == 2 ? plain_draw_kernel<true, 2> :
+                                  runs == 4 ? plain_draw_kernel<true, 4> : plain_draw_kernel<true, 8>)
+                               : (runs == 1 ? plain_draw_kernel<false, 1> : runs == 2 ? plain_draw_kernel<false, 2> :
+                                  runs == 4 ? plain_draw_kernel<false, 4> : plain_draw_kernel<false, 8>);
+        hipLaunchKernelGGL(k, dim3(B), dim3(DRAW_TPB), 0, s, t.seq_row0, target_logits, uniforms, u_stride, V, Kmax, inv_T,
+                           auto_rollback, kv_len, n_accepted, out_tokens, t, em, from);
+        SPECV_LAUNCH_CHECK("plain_draw_kernel");
+        return SPEC_OK;
+    }
+    const bool stats_inside = V <= STATS_MAX && !emit && !prepare_flag && !from.partial;
     dim3 g1((unsigned)n_stat_rows * n_stat_chunks + prep_on);
-    {
+    if (!stats_inside) {
     ProfScope ps(prof, SPEC_PROF_SAMPLER_STATS, s);
-    if (vec4)
-        hipLaunchKernelGGL(stats_kernel<true>, g1, dim3(TPB), 0, s, prep_on, layout, B, Kmax, V, n_stat_chunks,
-                           target_logits, draft_logits, em.logits_copy, inv_T, w.part_max, w.part_sum, em.copy_stride, t, ks,
-                           prep);
-    else
-        hipLaunchKernelGGL(stats_kernel<false>, g1, dim3(TPB), 0, s, prep_on, layout, B, Kmax, V, n_stat_chunks,
-                           target_logits, draft_logits, em.logits_copy, inv_T, w.part_max, w.part_sum, em.copy_stride, t, ks,
-                           prep);
+    auto* k = from.partial ? (vec4 ? stats_kernel<true, true> : stats_kernel<false, true>)
+                           : (vec4 ? stats_kernel<true, false> : stats_kernel<false, false>);
+    hipLaunchKernelGGL(k, g1, dim3(TPB), 0, s, prep_on, layout, B, Kmax, V, n_stat_chunks, target_logits, draft_logits,
+                       em.logits_copy, inv_T, w.part_max, w.part_sum, em.copy_stride, t, ks, prep, from);
     SPECV_LAUNCH_CHECK("stats_kernel");
     }
     ProfScope ps(prof, SPEC_PROF_SAMPLER_DRAW, s);
+    if (V <= DRAW_MAX && !emit) {
+        const int runs = draw_runs(V);
+        auto* k = stats_inside ? accept_draw_kernel<1, true> : runs == 1 ? accept_draw_kernel<1, false> : runs == 2 ? accept_draw_kernel<2, false>
+                  : runs == 4 ? accept_draw_kernel<4, false> : accept_draw_kernel<8, false>;
+        hipLaunchKernelGGL(k, dim3(B), dim3(DRAW_TPB), 0, s, t.seq_stat0, t.seq_row0, draft_tokens, w.part_max,
+                           w.part_sum, Kmax, V, n_stat_chunks, u_stride, uniforms, target_logits, draft_logits, inv_T, auto_rollback,
+                           kv_len, n_accepted, out_tokens, t, ks);
+        SPECV_LAUNCH_CHECK("accept_draw_kernel");
+        return SPEC_OK;
+    }
     hipLaunchKernelGGL(accept_mass_kernel, dim3(n_res_chunks, B), dim3(TPB), 0, s, t.seq_stat0, t.seq_row0, draft_tokens, w.part_max,
                        w.part_sum, Kmax, V, n_stat_chunks, u_stride, uniforms, target_logits, draft_logits, n_res_chunks, inv_T,
                        ks, w);

@@ -384,9 +384,10 @@ extern "C" int spec_verify_step(spec_handle* h, const spec_step_args* args, cons
         if (rc) return rc;
     }
     const float* logits = args->target_logits_in;
+    LogitsSrc src{};
     if (run_model) {
         float* dst = out->logits_out ? out->logits_out : h->logits;
-        rc = forward_run_grouped(h, ks, B, M, dst, s);
+        rc = forward_run_grouped(h, ks, B, M, dst, s, greedy ? nullptr : &src);
         if (rc) return rc;
         logits = dst;
     } else if (out->logits_out) {
@@ -400,7 +401,7 @@ extern "C" int spec_verify_step(spec_handle* h, const spec_step_args* args, cons
     return launch_sampler(h->tables, h->sampler, ks, B, Kmax, c.vocab, n_stat, logits, args->draft_logits,
                           args->draft_tokens, args->uniforms, Kmax + 1, args->temperature, args->auto_rollback,
                           run_model ? h->kv_len : nullptr, out->n_accepted, out->out_tokens, nullptr, &h->prof, s,
-                          prepare_in_sampler ? h->flag : nullptr);
+                          prepare_in_sampler ? h->flag : nullptr, &src);
 }
 
 extern "C" int spec_verify_tree_step(spec_handle* h, const spec_tree_args* args, const spec_tree_out* out, void* stream)
@@ -444,9 +445,10 @@ extern "C" int spec_verify_tree_step(spec_handle* h, const spec_tree_args* args,
     }
     if (rc) return rc;
     const float* logits = args->target_logits_in;
+    LogitsSrc src{};
     if (run_model) {
         float* dst = out->logits_out ? out->logits_out : h->logits;
-        rc = forward_run_grouped(h, ks, B, M, dst, s);
+        rc = forward_run_grouped(h, ks, B, M, dst, s, greedy ? nullptr : &src);
         if (rc) return rc;
         logits = dst;
     } else if (out->logits_out) {
@@ -461,7 +463,7 @@ extern "C" int spec_verify_tree_step(spec_handle* h, const spec_tree_args* args,
         rc = launch_tree_sampler(h->tables, h->sampler, ks, B, Kmax, c.vocab, 2 * M, logits, args->draft_logits,
                                  args->parent, args->draft_tokens, args->uniforms, args->temperature,
                                  args->auto_rollback, run_model ? h->kv_len : nullptr, out->n_accepted,
-                                 out->out_tokens, out->path, &h->prof, s);
+                                 out->out_tokens, out->path, &h->prof, s, &src);
     if (rc) return rc;
     if (run_model && args->auto_rollback) {
         ProfScope ps(&h->prof, SPEC_PROF_GLUE, s);
