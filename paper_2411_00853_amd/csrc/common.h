@@ -256,6 +256,7 @@ struct GemmPlan {
     int kb_per_split; // 32-wide K blocks per range
     int rs;           // row parts per workgroup: 1 (every wavefront takes all row tiles), 2 or 4
     int cg;           // column groups (of nt tiles) per workgroup: 4, or 3 for many-row launches that then fill more compute units
+    int ring;         // 0, or gemm_ring_kernel with this many row tiles per workgroup (one or two row blocks)
 };
 constexpr int GEMM_MAX_ROWS = SPEC_MAX_STEP_ROWS;   // rows the largest variant of the bf16 GEMM takes
 GemmPlan plan_gemm(int M, int N, int K, int cu_count, bool split_x);

@@ -18,6 +18,8 @@
 //  * K is cut into ranges across workgroups so that the grid fills all 256 compute units even when
 //    N is small; range sums are left in a partial buffer in a fixed order and added up by the
 //    consumer kernel (no floating-point atomics: bit-reproducible).
+#include <type_traits>
+
 #include "common.h"
 #include "frag.h"
 
@@ -371,6 +373,190 @@ __global__ void __launch_bounds__(64 * CG * RS) gemm_skinny_kernel(const u32x4* 
         }
 }
 
+// ---- many rows ---------------------------------------------------------------------------------------------
+// The product for more than 192 rows (and the widest matrices at 113..128): a tile of 128..192 rows x 128..256 columns per
+// workgroup, both operands fetched straight into LDS (global_load_lds: no registers on the way, so the accumulators of
+// that many tiles fit eight wavefronts, two on every SIMD) through a ring of stages of one K block.
+//
+// What bounds it is the matrix instruction's rate together with the LDS reads that feed it: an X fragment read feeds NT
+// products, and the two overlap only as far as the other wavefront of the SIMD has something to do.  The kernel above
+// takes all rows in one workgroup, which leaves registers for two column tiles per wavefront (one LDS read per two
+// products, and X, the larger operand by far, fetched anew for every 96 or 128 columns); two row blocks of half the rows
+// take three or four, with W fetched twice.  7B shape, us per launch (QKV, gate/up, output, down, LM head), before and now:
+//   256 rows  59.9 109.5 23.1 46.9 122.6    50.3  90.7 22.4 43.6 109.4
+//   320       73.5 136.3 27.9 57.3 151.2    60.6 109.1 27.9 55.4 142.2
+//   352       84.8 157.6 31.2 65.8 173.7    67.9 121.9 30.0 58.6 151.9   (0.95 PFLOP/s of issued products at QKV)
+// Tried: four wavefronts with 32x32x16 products (one per SIMD: fetching, LDS reads and products add up instead of overlapping,
+// 85 and 158 us at 352 rows); fetching on two wavefronts of their own; from 65 to 192 rows, where W from memory is half of the
+// time, this kernel and the one above are within 5 % of each other either way, except for the LM head at eight row tiles
+// (71.6 -> 63.3).
+//
+// A stage: 2 MT X tiles of 1 KiB (head plane, remainder plane) and 4 NT W tiles, requested by all wavefronts alike, S - 1 stages
+// ahead.  Stage i's products run while its last fragments and then stage i + 1's first ones are read: the barrier stands L tiles
+// before a stage's end, where all of stage i is in registers (its slot is free) and stage i + 1 has landed.  The
+// requests are not known to the compiler, which sees no load at all in this kernel; every wait is written here.
+template <bool STREAM>
+__device__ __forceinline__ void fetch_to_lds(const char* base, uint32_t offset, uint32_t lds)   // 16 bytes per lane, to lds + 16 * lane
+{
+    if constexpr (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(offset), "s"(base) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_fetches()   // at most N requests of this wavefront still under way
+{
+    static_assert(N < 64, "the counter has six bits");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void workgroup_barrier()
+{
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+constexpr int RING_GROUPS = 4;   // column groups of a workgroup; times two row halves: eight wavefronts
+constexpr int ring_stages(int mt, int nt, int planes) { return 160 / (planes * mt + RING_GROUPS * nt) < 6 ? 160 / (planes * mt + RING_GROUPS * nt) : 6; }
+
+// STREAM: W by streaming loads (one row block: read once)
+template <int MT, int NT, int PLANES, bool STREAM>
+__global__ void __launch_bounds__(512, 1) gemm_ring_kernel(const char* __restrict__ Xf, const char* __restrict__ Wp, float* __restrict__ partial,
+                                                           int M, int mt, int n_tiles, int kb_total, int kb_per_split, int n_split,
+                                                           int row_blocks, int n_blocks)
+{
+    constexpr int XT = PLANES * MT, ST = XT + RING_GROUPS * NT, U = (ST + 7) / 8;   // KiB tiles per stage; requests per wavefront
+    constexpr int S = ring_stages(MT, NT, PLANES), G = MT / 2, L = 2;                // row tiles of a wavefront; read ahead
+    static_assert(MT % 2 == 0 && G > L && S >= 3, "tile shape");
+    __shared__ u32x4 lds[S * ST * 64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int a0 = (wave & 1) * G, group = wave >> 1;
+    // row blocks of the same columns follow each other on one XCD (map_block's order otherwise): the second reads W from its L2
+    const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
+    int split, nblk;
+    map_block(x + 8 * (j / row_blocks), n_split, &split, &nblk);
+    if (nblk >= n_blocks) return;
+    const int t0 = (j % row_blocks) * MT, c0 = nblk * RING_GROUPS * NT;   // first row and column tile
+    const int kb0 = split * kb_per_split, n = min(kb_per_split, kb_total - kb0);   // stages (none or less: an empty range)
+
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds + wave * 1024;
+    const char* xbase = Xf + (size_t)kb0 * PLANES * mt * 1024;
+    const char* wbase = Wp + (size_t)(kb0 / WPACK_KG) * n_tiles * (WPACK_KG * 1024) + (kb0 % WPACK_KG) * 1024;
+    // tile 8 u + wave of a stage, rows and columns past the end the last ones again (never stored)
+    uint32_t offset[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int tile = min(u * 8 + wave, ST - 1);
+        offset[u] = (tile < XT ? (uint32_t)((tile / MT) * mt + min(t0 + tile % MT, mt - 1)) * 1024u
+                               : (uint32_t)min(c0 + tile - XT, n_tiles - 1) * (WPACK_KG * 1024u)) + lane * 16;
+    }
+    int requested = 0, slot_to = 0;
+    auto request = [&](int u) {
+        const uint32_t to = lds0 + (uint32_t)(slot_to * ST + u * 8) * 1024u;
+        const int tile = u * 8 + wave;
+        if (u * 8 + 8 <= XT || (u * 8 < XT && tile < XT)) fetch_to_lds<false>(xbase, offset[u], to);
+        else if (u * 8 + 8 <= ST || tile < ST) fetch_to_lds<STREAM>(wbase, offset[u], to);
+        else fetch_to_lds<false>(xbase, offset[0], to - u * 8192u);   // (its first tile again: every wavefront counts U a stage)
+    };
+    auto advance = [&]() {
+        xbase += (size_t)PLANES * mt * 1024;
+        wbase += (kb0 + requested) % WPACK_KG == WPACK_KG - 1 ? (size_t)n_tiles * (WPACK_KG * 1024) - (WPACK_KG - 1) * 1024 : (size_t)1024;
+        slot_to = slot_to + 1 == S ? 0 : slot_to + 1;
+        ++requested;
+    };
+    auto landed = [&](int stage) {   // the stages up to this one
+        if (requested - 1 - stage >= S - 2) wait_fetches<(S - 2) * U>();
+        else wait_fetches<0>();
+    };
+    floatx4 acc[G][NT];
+#pragma unroll
+    for (int a = 0; a < G; ++a)
+#pragma unroll
+        for (int i = 0; i < NT; ++i) acc[a][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    const u32x4* xl = lds + a0 * 64 + lane;
+    const u32x4* wl = lds + (XT + group * NT) * 64 + lane;
+    constexpr int R = 4;   // ring of X fragments in registers: tile g of a stage at g % R
+    bf16x8 xh[R], xr[R], wf[2][NT];
+    auto read_x = [&](int slot, int g, int at) {
+        xh[at] = __builtin_bit_cast(bf16x8, xl[(slot * ST + g) * 64]);
+        if constexpr (PLANES == 2) xr[at] = __builtin_bit_cast(bf16x8, xl[(slot * ST + MT + g) * 64]);
+    };
+    auto read_w = [&](int slot, int i) { return __builtin_bit_cast(bf16x8, wl[(slot * ST + i) * 64]); };
+    if (n > 0) {
+        for (int i = min(n, S - 1); i > 0; --i) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) request(u);
+            advance();
+        }
+        landed(0);
+        workgroup_barrier();
+        int stage = 0, slot = 0;
+#pragma unroll
+        for (int i = 0; i < NT; ++i) wf[0][i] = wf[1][i] = read_w(0, i);
+#pragma unroll
+        for (int g = 0; g < L; ++g) read_x(0, g, g);
+        auto step = [&](auto set) {   // which of the two sets of W fragments the stage is in
+            constexpr int cur = decltype(set)::value;
+            const bool more = requested < n;
+            const int next = slot + 1 == S ? 0 : slot + 1;
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                if (g == G - L) {
+                    if (more) advance();
+                    wait_lds_reads();
+                    landed(min(stage + 1, n - 1));
+                    workgroup_barrier();
+#pragma unroll
+                    for (int i = 0; i < NT; ++i) wf[cur ^ 1][i] = read_w(next, i);   // (after the last stage: never used)
+                }
+                if (g + L < G) read_x(slot, g + L, (g + L) % R);
+                else read_x(next, g + L - G, (g + L) % R);
+                if (g < G - L && more) {
+#pragma unroll
+                    for (int u = g; u < U; u += G - L) request(u);
+                }
+#pragma unroll
+                for (int i = 0; i < NT; ++i) acc[g][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh[g % R], wf[cur][i], acc[g][i], 0, 0, 0);
+                if constexpr (PLANES == 2) {
+#pragma unroll
+                    for (int i = 0; i < NT; ++i) acc[g][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xr[g % R], wf[cur][i], acc[g][i], 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (G % R != 0) {   // the next stage's first fragments to where it looks for them
+                bf16x8 h[L], r[L];
+#pragma unroll
+                for (int g = 0; g < L; ++g) { h[g] = xh[(G + g) % R]; r[g] = xr[(G + g) % R]; }
+#pragma unroll
+                for (int g = 0; g < L; ++g) { xh[g] = h[g]; xr[g] = r[g]; }
+            }
+            slot = next;
+            ++stage;
+        };
+        if (n & 1) step(std::integral_constant<int, 1>{});   // (both sets hold stage 0)
+        while (stage < n) {
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+        }
+        wait_lds_reads();
+        wait_fetches<0>();
+    }
+    const int n_pad = n_tiles * 16, g4 = lane >> 4, c16 = lane & 15;
+    float* out = partial + (size_t)split * M * n_pad;
+#pragma unroll
+    for (int a = 0; a < G; ++a)
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const int tile = c0 + group * NT + i;
+            if (tile < n_tiles) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int m = (t0 + a0 + a) * 16 + 4 * g4 + r;
+                    if (m < M) out[(size_t)m * n_pad + tile * 16 + c16] = acc[a][i][r];
+                }
+            }
+        }
+}
+
 // zero a fragment buffer (a kernel rather than a memset node, so that the call can be captured in a graph)
 __global__ void __launch_bounds__(256) zero_kernel(uint4* __restrict__ p, size_t n)
 {
@@ -587,6 +773,19 @@ int launch_variant(const GemmPlan& p, const void* xf, const void* w, int M, int 
     return launch_groups<MT, NT, KC, RS, 4>(p, xf, w, M, K, n_tiles, partial, s);
 }
 
+template <int MT, int NT, bool STREAM>
+int launch_ring(const GemmPlan& p, const void* xf, const void* w, int M, int K, int n_tiles, float* partial, hipStream_t s)
+{
+    const int row_blocks = (p.mt + MT - 1) / MT, n_blocks = (n_tiles + RING_GROUPS * NT - 1) / (RING_GROUPS * NT);
+    int grid = n_blocks * p.n_split;
+    if (p.n_split < 8) grid = (n_blocks + (8 / p.n_split) - 1) / (8 / p.n_split) * 8;   // (a multiple of eight either way)
+    auto* k = p.planes == 2 ? gemm_ring_kernel<MT, NT, 2, STREAM> : gemm_ring_kernel<MT, NT, 1, STREAM>;
+    hipLaunchKernelGGL(k, dim3(grid * row_blocks), dim3(512), 0, s, (const char*)xf, (const char*)w, partial, M, p.mt, n_tiles, K / 32,
+                       p.kb_per_split, p.n_split, row_blocks, n_blocks);
+    SPECV_LAUNCH_CHECK("gemm_ring_kernel");
+    return SPEC_OK;
+}
+
 struct Variant {
     int mt, nt, kc;   // row tiles, column tiles per wave, K blocks per LDS chunk
 };
@@ -600,9 +799,10 @@ struct Variant {
 // rows), faster from 8 on (120 rows -6 %, 160 -7 %, 250 and 320 -20 %).  Those variants come in
 // even row-tile counts only: the two row halves of a workgroup take ceil(mt/2) tiles each, so an
 // odd count costs what the next even one does.
+// (14 row tiles and more: gemm_ring_kernel, see plan_ring; even counts here too, for its two row blocks.)
 constexpr Variant kVariants[] = {{1, 2, 4}, {2, 2, 4}, {3, 2, 4}, {4, 2, 2}, {5, 4, 2}, {6, 4, 2},
-                                 {8, 4, 1}, {10, 4, 1}, {12, 4, 1}, {14, 2, 1}, {16, 2, 1}, {18, 2, 1},
-                                 {20, 2, 1}, {22, 2, 1}};
+                                 {8, 4, 1}, {10, 4, 1}, {12, 4, 1}, {14, 3, 1}, {16, 3, 1}, {18, 3, 1},
+                                 {20, 3, 1}, {22, 3, 1}};
 constexpr int kWideMaxMt = 4;
 // column tiles from which the wide variant is taken (up to 4 row tiles) and below which 5-12 row tiles
 // take two tiles per wavefront.  The wide variant fills the chip from 340 tiles on, but between that
@@ -633,6 +833,42 @@ int gemm_row_tiles(int M)
     return v ? v->mt : 0;
 }
 
+// K ranges are whole K groups of the packed order, so cutting a short K too finely leaves ranges with nothing in them --
+// workgroups that only write zeros for the consumer to add; no cut that leaves more than one range in eight empty.
+static int blocks_per_range(int kb_total, int n) { return ((kb_total + n - 1) / n + WPACK_KG - 1) / WPACK_KG * WPACK_KG; }
+static bool ranges_have_work(int kb_total, int n)
+{
+    const int per = blocks_per_range(kb_total, n);
+    return (kb_total + per - 1) / per * 8 >= n * 7;
+}
+
+// Launch shape of gemm_ring_kernel: two row blocks of 8, 10 or 12 row tiles; column tiles per wavefront and K ranges by the
+// cheapest of what fits, counted in cycles: rounds of workgroups over the chip x stages x a stage's time -- its matrix
+// instructions (32 cycles per pair of tiles and SIMD) plus 0.6 of its LDS reads -- plus, per range, writing the partial sums and
+// reading them back.  (By row tiles, not rows: the space for the partial sums is reserved by row tiles.)  Calibrated on the 7B, 1B and 2048-wide shapes at 256, 320 and 352 rows, where it picks the best of
+// the shapes measured or one within 3 % of it: QKV of the 7B shape three tiles and two ranges (256 workgroups), gate/up three
+// and one (230), output two and four, down (K = 11008) four and eight, LM head four and one (250).
+static void plan_ring(GemmPlan& p, int n_tiles, int kb_total, int cu_count)
+{
+    p.ring = p.mt <= 16 ? 8 : p.mt <= 20 ? 10 : 12;
+    p.cg = RING_GROUPS;
+    double best = 0.0;
+    for (int nt = 2; nt <= 4; ++nt)
+        for (int s = 1; s <= 16; s *= 2) {
+            if (s > 1 && (blocks_per_range(kb_total, s) < 2 * WPACK_KG || !ranges_have_work(kb_total, s))) break;
+            const int wgs = (n_tiles + RING_GROUPS * nt - 1) / (RING_GROUPS * nt) * 2 * s;
+            const int rounds = (wgs + cu_count - 1) / cu_count;
+            const double stage = 32.0 * p.ring * nt + 0.6 * 64.0 * (p.ring + nt);
+            const double cost = rounds * blocks_per_range(kb_total, s) * stage + 0.0025 * s * p.mt * 16 * p.n_pad;
+            if (best == 0.0 || cost < best) {
+                best = cost;
+                p.nt = nt;
+                p.n_split = s;
+            }
+        }
+    p.kb_per_split = blocks_per_range(kb_total, p.n_split);
+}
+
 GemmPlan plan_gemm(int M, int N, int K, int cu_count, bool split_x)
 {
     GemmPlan p{};
@@ -656,23 +892,20 @@ GemmPlan plan_gemm(int M, int N, int K, int cu_count, bool split_x)
     p.cg = 4;
     p.rs = p.mt >= 8 ? 2 : 1;
     const int kb_total = K / 32;
+    if (p.mt >= 14) {
+        plan_ring(p, n_tiles, kb_total, cu_count);
+        return p;
+    }
     // K ranges: a power of two, just enough of them that the launch has about `target` workgroups.
     // Measured on MI355X: every launch pays a few microseconds of ramp-up and tail whatever its
     // size, and long-lived workgroups stream best, so fewer, longer ranges win as long as roughly
     // two thirds of the compute units have a workgroup; more ranges only add partial-sum traffic
     // (M*N*4 bytes each way per range).  At most 16 ranges, each at least two LDS chunks long.
     const int target = g_wg_target > 0 ? g_wg_target : (2 * cu_count) / 3;
-    // Ranges are whole K groups of the packed order (below), so cutting a short K too finely leaves
-    // ranges with nothing in them -- workgroups that only write zeros for the consumer to add; no
-    // doubling that would leave more than one range in eight empty.
-    auto ranges_with_work = [&](int n) {
-        const int per = ((kb_total + n - 1) / n + WPACK_KG - 1) / WPACK_KG * WPACK_KG;
-        return (kb_total + per - 1) / per;
-    };
     auto ranges_for = [&](int blocks_x) {
         int n = 1;
         while (n < 16 && blocks_x * n < target && (kb_total + 2 * n - 1) / (2 * n) >= 2 * kc
-               && ranges_with_work(2 * n) * 8 >= 2 * n * 7)
+               && ranges_have_work(kb_total, 2 * n))
             n *= 2;
         return n;
     };
@@ -734,7 +967,10 @@ GemmPlan plan_gemm(int M, int N, int K, int cu_count, bool split_x)
         if (wg_x * s * 5 < cu_count * 4 && wg3 <= cu_count) p.nt = 3;
     }
     // ranges start on a K group of the packed order so that every chunk is one contiguous run
-    p.kb_per_split = ((kb_total + s - 1) / s + WPACK_KG - 1) / WPACK_KG * WPACK_KG;
+    p.kb_per_split = blocks_per_range(kb_total, s);
+    // eight row tiles with four column tiles per wavefront (the LM head): one row block of the ring (32000 x 4096 at 128 rows
+    // 71.6 -> 63.3 us, 112 rows 72.5 -> 62.4; with three tiles per wavefront or ten and twelve row tiles no difference)
+    if (p.mt == 8 && p.nt == 4 && p.cg == 4) p.ring = 8;
     return p;
 }
 
@@ -746,6 +982,21 @@ int launch_gemm_bf16(const GemmPlan& p, const void* x_frags, const void* w_packe
     if (M < 1 || M > GEMM_MAX_ROWS) return fail(SPEC_ERR_SHAPE, "GEMM supports 1..%d rows, got %d", GEMM_MAX_ROWS, M);
     if (K % 32) return fail(SPEC_ERR_SHAPE, "GEMM needs K %% 32 == 0, got %d", K);
     const int n_tiles = (N + 15) / 16;
+    if (p.ring) {
+#define SPECV_RING(MT_, NT_, STREAM_)                                                                              \
+    if (p.ring == MT_ && p.nt == NT_ && (p.mt <= MT_) == STREAM_) return launch_ring<MT_, NT_, STREAM_>(p, x_frags, w_packed, M, K, n_tiles, partial, s)
+        SPECV_RING(8, 4, true);
+        SPECV_RING(8, 2, false);
+        SPECV_RING(8, 3, false);
+        SPECV_RING(8, 4, false);
+        SPECV_RING(10, 2, false);
+        SPECV_RING(10, 3, false);
+        SPECV_RING(10, 4, false);
+        SPECV_RING(12, 2, false);
+        SPECV_RING(12, 3, false);
+        SPECV_RING(12, 4, false);
+#undef SPECV_RING
+    }
 #define SPECV_GEMM(MT_, NT_, KC_, ...)                                                                  \
     if (p.mt == MT_ && p.nt == NT_ && p.rs == (1, ##__VA_ARGS__))                                         \
         return launch_variant<MT_, NT_, KC_, ##__VA_ARGS__>(p, x_frags, w_packed, M, K, n_tiles, partial, s)
@@ -772,11 +1023,6 @@ int launch_gemm_bf16(const GemmPlan& p, const void* x_frags, const void* w_packe
     SPECV_GEMM(8, 4, 1, 2);
     SPECV_GEMM(10, 4, 1, 2);
     SPECV_GEMM(12, 4, 1, 2);
-    SPECV_GEMM(14, 2, 1, 2);
-    SPECV_GEMM(16, 2, 1, 2);
-    SPECV_GEMM(18, 2, 1, 2);
-    SPECV_GEMM(20, 2, 1, 2);
-    SPECV_GEMM(22, 2, 1, 2);
 #undef SPECV_GEMM
     return fail(SPEC_ERR_SHAPE, "no GEMM variant for %d rows (%d row tiles, %d column tiles per wave)", M, p.mt, p.nt);
 }
