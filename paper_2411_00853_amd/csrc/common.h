@@ -106,6 +106,15 @@ struct NormScale {
     int d;              // row length the mean is taken over
     float eps;
 };
+// The sums of squares of up to 16 rows as the product that wrote them leaves them (launch_gemm_add): one fp64 sum per row and
+// ADD_COLS columns, [M][n_parts].  The next product adds them up: for itself, or into ssq_out for its consumer.  (16 columns:
+// with 8 the SwiGLU product of 8 rows, each of whose workgroups adds all of them up, took 14.1 us instead of 11.9.)
+constexpr int ADD_COLS = 16;
+struct SsqTiles {
+    const double* parts;   // NULL: none
+    double2* ssq_out;
+    int n_parts;
+};
 // The logits of a decoder pass as its last product leaves them: K-range partial sums [n_split][rows][ld], the row scale
 // of the final norm, and where the finished rows go ([rows][vocab]).  The sampler's first kernel adds them up on
 // the way.  partial == NULL: the logits are whole.
@@ -263,8 +272,14 @@ GemmPlan plan_gemm(int M, int N, int K, int cu_count, bool split_x);
 int gemm_row_tiles(int M);   // row tiles (mt) of the variant that serves M rows; 0 if none
 size_t gemm_partial_elems(const GemmPlan& p, int M);
 // x_frags: X as operand fragments (frag.h) with p.mt row tiles and p.planes planes
+// job != NULL (one row tile): the launch also adds up job's sums of squares into job->ssq_out ([M][n_ssq])
 int launch_gemm_bf16(const GemmPlan& p, const void* x_frags, const void* w_packed, int M, int N, int K,
-                     float* partial, hipStream_t s);
+                     float* partial, hipStream_t s, const SsqTiles* job = nullptr, int n_ssq = 0);
+// Up to 16 rows and K 6144: x += X * W^T, the new x times gain as fragments (one row tile), its sums of squares by ADD_COLS columns into
+// parts [M][d / ADD_COLS].  out_frags is not the buffer of x_frags.
+bool gemm_add_fits(const GemmPlan& p, int K);
+int launch_gemm_add(const GemmPlan& p, const void* x_frags, const void* w_packed, int M, int d, int K, float* x, const float* gain,
+                    void* out_frags, double* parts, hipStream_t s);
 int launch_pack_x(const float* x, const float* gain, int M, int K, int mt_count, int planes, void* x_frags,
                   hipStream_t s);
 void set_gemm_wg_target(int workgroups);
@@ -274,7 +289,8 @@ bool gemm_swiglu_fits(int M, int F, int cu_count);
 void set_swiglu_min_wgs(int workgroups);
 void set_swiglu_column_groups(int groups);
 int launch_gemm_swiglu(const void* x_frags, int planes, const void* w_gate_up, int M, int F, int K, const double2* ssq,
-                       int n_ssq, int d, float eps, void* act_frags, int act_mt, int act_planes, int cu_count, hipStream_t s);
+                       int n_ssq, int d, float eps, void* act_frags, int act_mt, int act_planes, int cu_count, hipStream_t s,
+                       const SsqTiles* tiles = nullptr);
 // fp32: y = x * W^T (F32_STORE), y += x * W^T (F32_ADD), or y[m][n] = silu(gate) * up with W = N gate rows then N up
 // rows (F32_SWIGLU).  gain != NULL: x is normalised first (RMSNorm over its K columns, times gain).
 enum { F32_STORE = 0, F32_ADD = 1, F32_SWIGLU = 2 };

@@ -61,9 +61,10 @@ int forward_init(spec_handle* h, int max_rows)
         if (rc == SPEC_OK && hipMemset(h->xf, 0, xf_bytes) != hipSuccess) rc = fail(SPEC_ERR_DEVICE, "hipMemset failed");
         // the gate/up GEMM reads h->xf while its early workgroups already write the down projection's
         // operand, which therefore has a buffer of its own (rows up to the 4 row tiles that path serves)
-        const size_t xa_bytes = xfrag_uint4s(gemm_row_tiles(std::min(max_rows, 64)), 2, z.F) * sizeof(uint4);
+        const size_t xa_bytes = xfrag_uint4s(gemm_row_tiles(std::min(max_rows, 64)), 2, std::max(z.d, z.F)) * sizeof(uint4);
         if (rc == SPEC_OK) rc = a.alloc(&h->xf_act, xa_bytes);
         if (rc == SPEC_OK && hipMemset(h->xf_act, 0, xa_bytes) != hipSuccess) rc = fail(SPEC_ERR_DEVICE, "hipMemset failed");
+        A(reinterpret_cast<float**>(&h->ssq_parts), (size_t)std::min(max_rows, 16) * (z.d / ADD_COLS) * 2);
         part = gemm_partial_capacity(c, max_rows, h->cu_count);
         const int group = c.n_q_heads / c.n_kv_heads;
         const size_t po = attn_partial_floats(c.max_kv_len, c.max_batch, c.n_kv_heads, group, c.max_lookahead + 1,
@@ -209,7 +210,17 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
     const int planes = h->split_act ? 2 : 1;
     const XOut to_xf{bf16 ? h->xf : nullptr, mt, planes, nullptr};            // operand of the next GEMM
     const NormScale scaled{h->ssq, n_ssq, z.d, c.rms_eps};
-    auto gemm = [&](int cls, const void* w, int N, int K, Out* o, const void* in_frags) -> int {
+    // Up to 16 rows the output and down projections finish the residual stream themselves (launch_gemm_add): the normalised
+    // residual stays in the second fragment buffer, the attention's and SwiGLU's results in the first, and the sums of
+    // squares of x come by column tile.
+    const GemmPlan plan_o = plan_gemm(M, z.d, z.dq, h->cu_count, h->split_act), plan_down = plan_gemm(M, z.d, z.F, h->cu_count, h->split_act);
+    const bool few = bf16 && mt == 1;
+    const bool add_o = few && gemm_add_fits(plan_o, z.dq), add_down = few && gemm_add_fits(plan_down, z.F);
+    void* const xn = few ? h->xf_act : h->xf;
+    const XOut to_xn{bf16 ? xn : nullptr, mt, planes, nullptr};
+    const SsqTiles tiles{h->ssq_parts, h->ssq, z.d / ADD_COLS};
+    const SsqTiles* by_tile = nullptr;   // where the last x was written that way
+    auto gemm = [&](int cls, const void* w, int N, int K, Out* o, const void* in_frags, const SsqTiles* sums) -> int {
         const GemmPlan p = plan_gemm(M, N, K, h->cu_count, h->split_act);
         // the plan follows process-wide tuning knobs; the buffer was sized with those in force at init
         if (gemm_partial_elems(p, M) > h->partial_cap)
@@ -220,11 +231,24 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
         o->ld = p.n_pad;
         o->stride = (size_t)M * p.n_pad;
         ProfScope ps_(&h->prof, cls, s);
-        return launch_gemm_bf16(p, in_frags, w, M, N, K, h->partial, s);
+        return launch_gemm_bf16(p, in_frags, w, M, N, K, h->partial, s, sums, n_ssq);
+    };
+    // x += in * w^T, the next product's operand and the sums of squares, in one launch or two
+    auto gemm_resid = [&](int cls, const GemmPlan& p, bool add, const void* w, int K, const void* in_frags, const float* gain) -> int {
+        by_tile = add ? &tiles : nullptr;
+        if (add) {
+            ProfScope ps_(&h->prof, cls, s);
+            return launch_gemm_add(p, in_frags, w, M, z.d, K, h->x, gain, xn, h->ssq_parts, s);
+        }
+        Out r;
+        int e = gemm(cls, w, z.d, K, &r, in_frags, nullptr);
+        if (e) return e;
+        ProfScope ps_(&h->prof, SPEC_PROF_GLUE, s);
+        return launch_resid(h->partial, r.n_split, r.stride, r.ld, M, z.d, h->x, h->ssq, gain, to_xn, s);
     };
 
     RUN(SPEC_PROF_GLUE, launch_embed(c.dtype, h->tok_embed, t.row_tok, M, z.d, h->x, h->ssq, bf16 ? h->layers[0].attn_norm : nullptr,
-                                     to_xf, s));
+                                     to_xn, s));
     if (!bf16) {
         if (z.F % 8) return fail(SPEC_ERR_SHAPE, "d_ffn must be a multiple of 8");
         auto mul = [&](int cls, const float* in, const void* w, int N, int K, float* out, int mode, const float* gain) -> int {
@@ -250,7 +274,7 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
     const bool fuse = h->fuse_rope && attention_takes_qkv(h->geom, c.n_q_heads, ks, B, c.max_kv_len, h->cu_count);
     for (int l = 0; l < c.n_layers; ++l) {
         const spec_layer_weights& w = h->layers[l];
-        rc = gemm(SPEC_PROF_GEMM_QKV, w.w_qkv, z.nqkv, z.d, &o, h->xf);
+        rc = gemm(SPEC_PROF_GEMM_QKV, w.w_qkv, z.nqkv, z.d, &o, xn, by_tile);
         if (rc) return rc;
         if (fuse) {
             // the attention kernel adds up, scales and rotates q, k, v itself and appends k, v
@@ -265,26 +289,24 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
                                   h->q, h->attn_part_o, h->attn_part_ml, h->attn_part_cap, to_xf, c.max_lookahead + 1, &h->prof, s);
         }
         if (rc) return rc;
-        rc = gemm(SPEC_PROF_GEMM_O, w.w_o, z.d, z.dq, &o, h->xf);
+        rc = gemm_resid(SPEC_PROF_GEMM_O, plan_o, add_o, w.w_o, z.dq, h->xf, w.ffn_norm);
         if (rc) return rc;
-        RUN(SPEC_PROF_GLUE, launch_resid(h->partial, o.n_split, o.stride, o.ld, M, z.d, h->x, h->ssq, w.ffn_norm, to_xf, s));
+        void* const act = swiglu_in_gemm && !few ? h->xf_act : h->xf;
         if (swiglu_in_gemm) {
             // the gate/up GEMM applies the norm's row scale and SwiGLU itself and writes the down
-            // projection's operand (into the second fragment buffer: it is still reading the first)
-            RUN(SPEC_PROF_GEMM_GATE_UP, launch_gemm_swiglu(h->xf, planes, w.w_gate_up, M, z.F, z.d, h->ssq, n_ssq, z.d, c.rms_eps,
-                                                   h->xf_act, mt, planes, h->cu_count, s));
-            rc = gemm(SPEC_PROF_GEMM_DOWN, w.w_down, z.d, z.F, &o, h->xf_act);
+            // projection's operand (into the fragment buffer that it is not reading)
+            RUN(SPEC_PROF_GEMM_GATE_UP, launch_gemm_swiglu(xn, planes, w.w_gate_up, M, z.F, z.d, h->ssq, n_ssq, z.d, c.rms_eps,
+                                                   act, mt, planes, h->cu_count, s, by_tile));
         } else {
-            rc = gemm(SPEC_PROF_GEMM_GATE_UP, w.w_gate_up, 2 * z.F, z.d, &o, h->xf);
+            rc = gemm(SPEC_PROF_GEMM_GATE_UP, w.w_gate_up, 2 * z.F, z.d, &o, xn, by_tile);
             if (rc) return rc;
             RUN(SPEC_PROF_GLUE, launch_silu_mul(h->partial, o.n_split, o.stride, o.ld, M, z.F, scaled, to_xf, s));
-            rc = gemm(SPEC_PROF_GEMM_DOWN, w.w_down, z.d, z.F, &o, h->xf);
         }
-        if (rc) return rc;
         const float* next_gain = (l + 1 < c.n_layers) ? h->layers[l + 1].attn_norm : h->final_norm;
-        RUN(SPEC_PROF_GLUE, launch_resid(h->partial, o.n_split, o.stride, o.ld, M, z.d, h->x, h->ssq, next_gain, to_xf, s));
+        rc = gemm_resid(SPEC_PROF_GEMM_DOWN, plan_down, add_down, w.w_down, z.F, act, next_gain);
+        if (rc) return rc;
     }
-    rc = gemm(SPEC_PROF_GEMM_LM_HEAD, h->lm_head, z.V, z.d, &o, h->xf);
+    rc = gemm(SPEC_PROF_GEMM_LM_HEAD, h->lm_head, z.V, z.d, &o, xn, by_tile);
     if (rc) return rc;
     if (last) {
         *last = LogitsSrc{h->partial, o.stride, o.n_split, o.ld, scaled, logits_out};

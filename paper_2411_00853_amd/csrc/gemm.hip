@@ -70,7 +70,31 @@ struct SwigluOut {
     float eps;
     uint4* frags;       // fragment buffer of the down projection's operand
     int mt, planes;
+    SsqTiles tiles;     // one row tile: the sums of squares as gemm_add_kernel leaves them (tiles.parts == NULL: ssq)
 };
+
+// The sums of squares of N groups of 1024 columns of a row, from group q on, from the sums over ADD_COLS columns each, by
+// eight neighbouring lanes (sub 0..7; every lane gets the sums; 0 past the end): one memory round trip.  d is a multiple
+// of 32, so the sums come in pairs.
+template <int N>
+__device__ __forceinline__ void ssq_group_sums(const double* row, int n_parts, int q, int sub, double (&sums)[N])
+{
+    constexpr int PER = 2 * SSQ_CHUNK / ADD_COLS / 8;   // sums per lane
+    const int i0 = q * 8 * PER + sub * PER;
+    double2 v[N][PER / 2];
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+#pragma unroll
+        for (int i = 0; i < PER / 2; ++i) v[j][i] = *reinterpret_cast<const double2*>(row + min(i0 + j * 8 * PER + 2 * i, n_parts - 2));
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        sums[j] = 0.0;
+#pragma unroll
+        for (int i = 0; i < PER / 2; ++i) sums[j] += i0 + j * 8 * PER + 2 * i < n_parts ? v[j][i].x + v[j][i].y : 0.0;
+#pragma unroll
+        for (int o = 1; o < 8; o *= 2) sums[j] += __shfl_xor(sums[j], o);
+    }
+}
 
 template <int MT, int NT, int KC, int PLANES, int RS = 1, int EPI = 0, int CG = 4>
 __global__ void __launch_bounds__(64 * CG * RS) gemm_skinny_kernel(const u32x4* __restrict__ Xf, const u32x4* __restrict__ Wp,
@@ -78,10 +102,28 @@ __global__ void __launch_bounds__(64 * CG * RS) gemm_skinny_kernel(const u32x4* 
                                                           int kb_total, int kb_per_split, int n_split, int n_blocks,
                                                           SwigluOut so)
 {
+    if constexpr (MT == 1 && EPI == 0) {
+        // Eight more workgroups where gemm_add_kernel wrote the operand (the XCDs' turns stay as they are): the first
+        // makes the row sums that the consumer of this product scales with, beside the product.
+        if (so.tiles.parts && blockIdx.x + 8 >= gridDim.x) {
+            if (blockIdx.x + 8 > gridDim.x || threadIdx.x >= 128) return;
+            const int m = min((int)threadIdx.x >> 3, M - 1);
+            for (int q = 0; q < so.n_ssq; q += 2) {
+                double ss[2];
+                ssq_group_sums(so.tiles.parts + (size_t)m * so.tiles.n_parts, so.tiles.n_parts, q, threadIdx.x & 7, ss);
+                if ((threadIdx.x & 7) == 0 && (int)threadIdx.x >> 3 == m) {
+                    so.tiles.ssq_out[(size_t)m * so.n_ssq + q] = make_double2(ss[0], 0.0);
+                    if (q + 1 < so.n_ssq) so.tiles.ssq_out[(size_t)m * so.n_ssq + q + 1] = make_double2(ss[1], 0.0);
+                }
+            }
+            return;
+        }
+    }
     constexpr int CHUNK_U4 = KC * PLANES * MT * 64;     // 16-byte units per X chunk (contiguous in Xf)
     constexpr int TPBK = 64 * CG * RS;                    // threads per workgroup: CG column groups x RS row halves
     constexpr int UPT = (CHUNK_U4 + TPBK - 1) / TPBK;     // per thread
     __shared__ u32x4 xs[2][CHUNK_U4];                   // two chunk buffers
+    __shared__ float rsv[EPI == 1 ? MT * 16 : 1];       // SwiGLU: row scales
 
     int split, nblk;
     map_block(blockIdx.x, n_split, &split, &nblk);
@@ -269,6 +311,21 @@ __global__ void __launch_bounds__(64 * CG * RS) gemm_skinny_kernel(const u32x4* 
     store_x(0);
     load_x(kb0 + KC);
     load_w(kb0 + KC, wb);
+    if constexpr (MT == 1 && EPI == 1) {
+        if (so.tiles.parts) {   // here, where the stream's first round trips cover it (eight lanes a row)
+            if (threadIdx.x < 128) {
+                const int m = min((int)threadIdx.x >> 3, M - 1);
+                float ss = 0.f;
+                for (int q = 0; q < so.n_ssq; q += 2) {   // (past the end a group is 0)
+                    double two[2];
+                    ssq_group_sums(so.tiles.parts + (size_t)m * so.tiles.n_parts, so.tiles.n_parts, q, threadIdx.x & 7, two);
+                    ss += (float)two[0];
+                    ss += (float)two[1];
+                }
+                if ((threadIdx.x & 7) == 0) rsv[threadIdx.x >> 3] = 1.0f / sqrtf(ss / (float)so.d + so.eps);
+            }
+        }
+    }
     __syncthreads();
     // Chunk j is multiplied from LDS buffer j%2 while chunk j+1's X (already in registers) is copied
     // into the other buffer and the loads of chunk j+2 are issued.  The main loop runs while both of
@@ -320,7 +377,6 @@ __global__ void __launch_bounds__(64 * CG * RS) gemm_skinny_kernel(const u32x4* 
     if constexpr (EPI == 1) {
         static_assert(EPI == 0 || (NT == 2 && RS == 1), "the SwiGLU epilogue pairs the two column tiles of a wavefront");
         static_assert(EPI == 0 || sizeof(xs) >= CG * MT * 256 * sizeof(float), "tile staging fits the X chunk buffers");
-        __shared__ float rsv[MT * 16];
         // The accumulators are read next, by vector instructions, which have to wait seven states for the last products.
         // The compiler's own wait is lost where the branches above meet (one row tile: two states; the last
         // product's remainder was missing from rows 0, 4, 8 and 12, 1.6e-4 of their values), so it is written out here,
@@ -329,7 +385,7 @@ __global__ void __launch_bounds__(64 * CG * RS) gemm_skinny_kernel(const u32x4* 
         for (int a = 0; a < MT; ++a) asm volatile("s_nop 15" : "+a"(acc[a][0]), "+a"(acc[a][1]));
         __syncthreads();                                      // everyone is done with the X chunk buffers
         float* tw = reinterpret_cast<float*>(&xs[0][0]) + wave * (MT * 256);   // [MT*16 rows][16 units]
-        for (int m = threadIdx.x; m < MT * 16; m += TPBK)
+        for (int m = threadIdx.x; m < MT * 16 && !(MT == 1 && so.tiles.parts); m += TPBK)
             rsv[m] = m < M ? row_inv_rms(so.ssq, so.n_ssq, m, so.d, so.eps) : 0.f;
         __syncthreads();
 #pragma unroll
@@ -371,6 +427,136 @@ __global__ void __launch_bounds__(64 * CG * RS) gemm_skinny_kernel(const u32x4* 
                 }
             }
         }
+}
+
+// ---- few rows, the projections that end in the residual stream ---------------------------------------------
+// x += X * W^T for up to 16 rows, with what follows it in the chain: the new x times the next norm's gain as operand
+// fragments and the sums of squares of the new x.  A step of a few rows is a chain of launches that are mostly latency, and
+// cut into K ranges across workgroups these two projections needed a launch of their own to add the ranges up.  Here a
+// workgroup takes ADD_COLS columns and wavefront r the r-th K range, with the sums of the ranges met in LDS: the
+// products and additions are those of the cut across workgroups, in the same order (bit for bit the same x).  Nothing
+// else is shared, so both operands go straight into registers, DEPTH groups of four K blocks ahead.
+// Each workgroup reads all of X: the loads of X are two thirds of all, which is what limits this to one row tile and to K up
+// to 6144.  2048 columns, us by trace, product and residual kernel before, this now (128 workgroups): K = 2048 4.3 + 3.1 -> 4.2,
+// K = 5504 6.6 + 3.8 -> 8.6, K = 8192 7.5 + 3.1 -> 11.4 (eight columns per workgroup, twice the workgroups: no faster).
+// 1B shape, batch 1, 787 -> 773 us a step (790 with its down projection, K = 8192, this way), draft decode of 8 rows
+// 302 -> 291, decoding round 2217 -> 2184.
+// The row's whole sum of squares spans all workgroups: it leaves as one fp64 sum per row and workgroup, and the next
+// product adds those up (ssq_group_sums).
+template <int RANGES, int PLANES>
+__global__ void __launch_bounds__(64 * RANGES) gemm_add_kernel(const u32x4* __restrict__ Xf, const u32x4* __restrict__ Wp, float* __restrict__ x,
+                                                               const float* __restrict__ gain, int M, int n_tiles, int kb_total,
+                                                               int kb_per_range, uint16_t* __restrict__ frags, double* __restrict__ parts)
+{
+    constexpr int DEPTH = RANGES > 8 ? 1 : 3;   // register buffers (128 registers a wavefront with sixteen of them, 256 with eight)
+    static_assert(RANGES >= 4, "a thread for every element");
+    __shared__ float red[RANGES][16 * ADD_COLS];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), g = lane >> 4, c = lane & 15;
+    const int n0 = blockIdx.x * ADD_COLS;
+    const int group0 = wave * (kb_per_range / WPACK_KG);
+    const int n = (min(kb_per_range, kb_total - wave * kb_per_range) + WPACK_KG - 1) / WPACK_KG;   // groups (none or less: an empty range)
+    // lanes past the last row ask past the end of the buffer: they get zeros and fetch nothing
+    const __amdgpu_buffer_rsrc_t xb = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4*>(Xf), 0, kb_total * PLANES * 1024, 0x00027000);
+    const uint32_t x_lane = c < M ? lane * 16u : 0x40000000u;
+    const u32x4* wp = Wp + (size_t)blockIdx.x * (WPACK_KG * 64);
+    const size_t group_stride = (size_t)n_tiles * (WPACK_KG * 64);
+    struct Group {
+        u32x4 w[WPACK_KG], x[WPACK_KG][PLANES];
+    };
+    Group buf[DEPTH];
+    auto load = [&](int i, Group& d) {
+        const int group = group0 + i;
+#pragma unroll
+        for (int j = 0; j < WPACK_KG; ++j) d.w[j] = __builtin_nontemporal_load(wp + group * group_stride + j * 64 + (uint32_t)lane);
+#pragma unroll
+        for (int j = 0; j < WPACK_KG; ++j) {   // (past the last block the packed weights are zeros)
+            const int kb = min(group * WPACK_KG + j, kb_total - 1);
+#pragma unroll
+            for (int p = 0; p < PLANES; ++p) d.x[j][p] = __builtin_amdgcn_raw_buffer_load_b128(xb, x_lane, (kb * PLANES + p) * 1024, 0);
+        }
+    };
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](const Group& d) {
+#pragma unroll
+        for (int j = 0; j < WPACK_KG; ++j)
+#pragma unroll
+            for (int p = 0; p < PLANES; ++p)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, d.x[j][p]), __builtin_bit_cast(bf16x8, d.w[j]), acc, 0, 0, 0);
+    };
+    // the last groups, with no branch between a load and its use (the compiler then knows which loads a wait is for):
+    // HAVE of them in flight, MORE to come (fewer than DEPTH, in the buffers of the first ones)
+    auto finish = [&](int i, auto have, auto more) {
+#pragma unroll
+        for (int j = 0; j < decltype(more)::value; ++j) {
+            multiply(buf[j]);
+            load(i + decltype(have)::value + j, buf[j]);
+        }
+#pragma unroll
+        for (int j = decltype(more)::value; j < decltype(have)::value; ++j) multiply(buf[j]);
+#pragma unroll
+        for (int j = 0; j < decltype(more)::value; ++j) multiply(buf[j]);
+    };
+    auto start = [&](auto have) {
+#pragma unroll
+        for (int j = 0; j < decltype(have)::value; ++j) load(j, buf[j]);
+    };
+    float x_old = 0.f, gn = 0.f;   // (requested with the first operands)
+    if ((int)threadIdx.x < M * ADD_COLS) {
+        x_old = x[(size_t)(threadIdx.x / ADD_COLS) * (n_tiles * 16) + n0 + threadIdx.x % ADD_COLS];
+        gn = gain[n0 + threadIdx.x % ADD_COLS];
+    }
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I3 = std::integral_constant<int, 3>;
+    using ID = std::integral_constant<int, DEPTH>;
+    if (n >= DEPTH) {
+        start(ID{});
+        int i = 0;
+        for (; i + 2 * DEPTH <= n; i += DEPTH)
+#pragma unroll
+            for (int j = 0; j < DEPTH; ++j) {
+                multiply(buf[j]);
+                load(i + DEPTH + j, buf[j]);
+            }
+        switch (n - i - DEPTH) {
+        case 0: finish(i, ID{}, I0{}); break;
+        case 1: finish(i, ID{}, I1{}); break;
+        case 2: if constexpr (DEPTH > 2) finish(i, ID{}, I2{}); break;
+        default: if constexpr (DEPTH > 3) finish(i, ID{}, I3{}); break;
+        }
+    } else if (n == 1) {
+        start(I1{});
+        finish(0, I1{}, I0{});
+    } else if (DEPTH > 2 && n == 2) {
+        start(I2{});
+        finish(0, I2{}, I0{});
+    } else if (DEPTH > 3 && n == 3) {
+        start(I3{});
+        finish(0, I3{}, I0{});
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[wave][(4 * g + r) * ADD_COLS + c] = acc[r];
+    __syncthreads();
+    const int row = threadIdx.x / ADD_COLS, col = n0 + threadIdx.x % ADD_COLS;
+    if (row >= M) return;   // (all lanes of a row alike)
+    float sum = red[0][threadIdx.x];
+#pragma unroll
+    for (int w = 1; w < RANGES; ++w) sum += red[w][threadIdx.x];
+    const float v = x_old + sum;
+    x[(size_t)row * (n_tiles * 16) + col] = v;
+    uint16_t* f = frags + ((size_t)(col >> 5) * PLANES * 64 + ((col >> 3) & 3) * 16 + row) * 8 + (col & 7);
+    {
+#pragma clang fp contract(off)   // the product is rounded before it is split, as by resid_kernel
+        const float o = v * gn;
+        const __bf16 head = static_cast<__bf16>(o);
+        *f = __builtin_bit_cast(uint16_t, head);
+        if constexpr (PLANES == 2) f[64 * 8] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(o - static_cast<float>(head)));
+    }
+    double ss = (double)v * v;
+#pragma unroll
+    for (int s = 1; s < ADD_COLS; s *= 2) ss += __shfl_xor(ss, s);
+    if (col == n0) parts[(size_t)row * n_tiles + blockIdx.x] = ss;
 }
 
 // ---- many rows ---------------------------------------------------------------------------------------------
@@ -745,32 +931,38 @@ __global__ void __launch_bounds__(256) pack_weight_kernel(const uint16_t* __rest
 
 template <int MT, int NT, int KC, int RS, int CG>
 int launch_groups(const GemmPlan& p, const void* xf, const void* w, int M, int K, int n_tiles, float* partial,
-                  hipStream_t s)
+                  hipStream_t s, const SsqTiles* job, int n_ssq)
 {
     const int n_blocks = (n_tiles + CG * NT - 1) / (CG * NT);
     int grid = n_blocks * p.n_split;
     if (p.n_split < 8) grid = (n_blocks + (8 / p.n_split) - 1) / (8 / p.n_split) * 8;
+    SwigluOut so{};
+    if (job) {   // (one row tile)
+        so.tiles = *job;
+        so.n_ssq = n_ssq;
+        grid += 8;
+    }
     if (p.planes == 2)
         hipLaunchKernelGGL((gemm_skinny_kernel<MT, NT, KC, 2, RS, 0, CG>), dim3(grid), dim3(64 * CG * RS), 0, s, (const u32x4*)xf,
-                           (const u32x4*)w, partial, M, n_tiles, K / 32, p.kb_per_split, p.n_split, n_blocks, SwigluOut{});
+                           (const u32x4*)w, partial, M, n_tiles, K / 32, p.kb_per_split, p.n_split, n_blocks, so);
     else
         hipLaunchKernelGGL((gemm_skinny_kernel<MT, NT, KC, 1, RS, 0, CG>), dim3(grid), dim3(64 * CG * RS), 0, s, (const u32x4*)xf,
-                           (const u32x4*)w, partial, M, n_tiles, K / 32, p.kb_per_split, p.n_split, n_blocks, SwigluOut{});
+                           (const u32x4*)w, partial, M, n_tiles, K / 32, p.kb_per_split, p.n_split, n_blocks, so);
     SPECV_LAUNCH_CHECK("gemm_skinny_kernel");
     return SPEC_OK;
 }
 
 template <int MT, int NT, int KC, int RS = 1>
 int launch_variant(const GemmPlan& p, const void* xf, const void* w, int M, int K, int n_tiles, float* partial,
-                   hipStream_t s)
+                   hipStream_t s, const SsqTiles* job, int n_ssq)
 {
     if constexpr (RS == 2 || (MT <= 4 && NT == 2)) {
-        if (p.cg == 3) return launch_groups<MT, NT, KC, RS, 3>(p, xf, w, M, K, n_tiles, partial, s);
+        if (p.cg == 3) return launch_groups<MT, NT, KC, RS, 3>(p, xf, w, M, K, n_tiles, partial, s, job, n_ssq);
     }
     if constexpr (MT <= 4 && NT == 2) {
-        if (p.cg == 2) return launch_groups<MT, NT, KC, RS, 2>(p, xf, w, M, K, n_tiles, partial, s);
+        if (p.cg == 2) return launch_groups<MT, NT, KC, RS, 2>(p, xf, w, M, K, n_tiles, partial, s, job, n_ssq);
     }
-    return launch_groups<MT, NT, KC, RS, 4>(p, xf, w, M, K, n_tiles, partial, s);
+    return launch_groups<MT, NT, KC, RS, 4>(p, xf, w, M, K, n_tiles, partial, s, job, n_ssq);
 }
 
 template <int MT, int NT, bool STREAM>
@@ -977,8 +1169,9 @@ GemmPlan plan_gemm(int M, int N, int K, int cu_count, bool split_x)
 size_t gemm_partial_elems(const GemmPlan& p, int M) { return (size_t)p.n_split * M * p.n_pad; }
 
 int launch_gemm_bf16(const GemmPlan& p, const void* x_frags, const void* w_packed, int M, int N, int K, float* partial,
-                     hipStream_t s)
+                     hipStream_t s, const SsqTiles* job, int n_ssq)
 {
+    if (job && p.mt != 1) return fail(SPEC_ERR_SHAPE, "row sums by column tiles are for one row tile, got %d", p.mt);
     if (M < 1 || M > GEMM_MAX_ROWS) return fail(SPEC_ERR_SHAPE, "GEMM supports 1..%d rows, got %d", GEMM_MAX_ROWS, M);
     if (K % 32) return fail(SPEC_ERR_SHAPE, "GEMM needs K %% 32 == 0, got %d", K);
     const int n_tiles = (N + 15) / 16;
@@ -999,7 +1192,7 @@ int launch_gemm_bf16(const GemmPlan& p, const void* x_frags, const void* w_packe
     }
 #define SPECV_GEMM(MT_, NT_, KC_, ...)                                                                  \
     if (p.mt == MT_ && p.nt == NT_ && p.rs == (1, ##__VA_ARGS__))                                         \
-        return launch_variant<MT_, NT_, KC_, ##__VA_ARGS__>(p, x_frags, w_packed, M, K, n_tiles, partial, s)
+        return launch_variant<MT_, NT_, KC_, ##__VA_ARGS__>(p, x_frags, w_packed, M, K, n_tiles, partial, s, job, n_ssq)
     SPECV_GEMM(1, 4, 2);
     SPECV_GEMM(2, 4, 2);
     SPECV_GEMM(3, 4, 2);
@@ -1025,6 +1218,31 @@ int launch_gemm_bf16(const GemmPlan& p, const void* x_frags, const void* w_packe
     SPECV_GEMM(12, 4, 1, 2);
 #undef SPECV_GEMM
     return fail(SPEC_ERR_SHAPE, "no GEMM variant for %d rows (%d row tiles, %d column tiles per wave)", M, p.mt, p.nt);
+}
+
+// (K: see the kernel; widths of 512 to 4096 measured, none slower)
+bool gemm_add_fits(const GemmPlan& p, int K)
+{
+    return K <= 6144 && p.mt == 1 && p.n_pad % 32 == 0 && (p.n_split == 4 || p.n_split == 8 || p.n_split == 16);
+}
+
+int launch_gemm_add(const GemmPlan& p, const void* x_frags, const void* w_packed, int M, int d, int K, float* x, const float* gain,
+                    void* out_frags, double* parts, hipStream_t s)
+{
+    if (!gemm_add_fits(p, K) || M < 1 || M > 16 || d != p.n_pad || K % 32 || K < 32)
+        return fail(SPEC_ERR_SHAPE, "no residual GEMM for %d rows of %d x %d", M, d, K);
+#define SPECV_ADD(R_)                                                                                                          \
+    if (p.n_split == R_) {                                                                                                     \
+        auto* k = p.planes == 2 ? gemm_add_kernel<R_, 2> : gemm_add_kernel<R_, 1>;                                             \
+        hipLaunchKernelGGL(k, dim3(d / ADD_COLS), dim3(64 * R_), 0, s, (const u32x4*)x_frags, (const u32x4*)w_packed, x, gain, M, \
+                           d / 16, K / 32, p.kb_per_split, (uint16_t*)out_frags, parts);                                       \
+    }
+    SPECV_ADD(4)
+    SPECV_ADD(8)
+    SPECV_ADD(16)
+#undef SPECV_ADD
+    SPECV_LAUNCH_CHECK("gemm_add_kernel");
+    return SPEC_OK;
 }
 
 namespace {
@@ -1084,10 +1302,12 @@ static int launch_swiglu_variant(int planes, const void* xf, const void* w, int 
 }
 
 int launch_gemm_swiglu(const void* x_frags, int planes, const void* w_gate_up, int M, int F, int K, const double2* ssq,
-                       int n_ssq, int d, float eps, void* act_frags, int act_mt, int act_planes, int cu_count, hipStream_t s)
+                       int n_ssq, int d, float eps, void* act_frags, int act_mt, int act_planes, int cu_count, hipStream_t s,
+                       const SsqTiles* tiles)
 {
+    if (tiles && gemm_row_tiles(M) != 1) return fail(SPEC_ERR_SHAPE, "row sums by column tiles are for one row tile, got %d rows", M);
     if (K % 32 || F % 16) return fail(SPEC_ERR_SHAPE, "SwiGLU GEMM needs K %% 32 == 0 and F %% 16 == 0");
-    const SwigluOut so{ssq, n_ssq, d, eps, static_cast<uint4*>(act_frags), act_mt, act_planes};
+    const SwigluOut so{ssq, n_ssq, d, eps, static_cast<uint4*>(act_frags), act_mt, act_planes, tiles ? *tiles : SsqTiles{}};
     const int n_tiles = 2 * F / 16;
     switch (gemm_row_tiles(M)) {
     case 1: return launch_swiglu_variant<1, 4>(planes, x_frags, w_gate_up, M, K, n_tiles, so, cu_count, s);

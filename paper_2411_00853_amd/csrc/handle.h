@@ -43,7 +43,9 @@ struct spec_handle {
     bool fuse_rope = true;     // bf16: rotary + KV append happen inside the attention kernel
     float* x = nullptr;        // [rows][d_model] residual stream
     void* xf = nullptr;        // operand fragments of the current GEMM's input (bf16 path)
-    void* xf_act = nullptr;    // second fragment buffer: the down projection's operand when the gate/up GEMM writes it
+    void* xf_act = nullptr;    // second fragment buffer: the down projection's operand when the gate/up GEMM writes it;
+                               // up to 16 rows the normalised residual
+    double* ssq_parts = nullptr;   // [16 rows][d_model / ADD_COLS] sums of squares of x by column tile (up to 16 rows)
     double2* ssq = nullptr;    // [rows][ssq_pairs] partial sums of squares of x (bf16 path)
     float* q = nullptr;        // [rows][n_q_heads*head_dim] rotated queries
     float* att = nullptr;      // [rows][n_q_heads*head_dim] attention output (fp32 path)

@@ -1,0 +1,28 @@
+"""Steps of up to 16 rows, whose output and down projections finish the residual stream themselves: 4, 8 and 16 K ranges, ranges
+that are short or empty, K that is no multiple of the packed order's 128 columns, widths that are no multiple of 1024 (the
+row's sum of squares is added up by groups of that many columns) and, at 17 rows, the chain of launches beyond."""
+import pytest
+import torch
+
+from paper_2411_00853_amd import workload as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("look", [[0], [5, 0], [7, 7], [7, 8]])      # 1, 7, 16 and 17 rows
+@pytest.mark.parametrize("d,heads,hd,F", [(4096, 16, 128, 2048), (2080, 32, 64, 2144), (2048, 17, 128, 6144), (1056, 8, 64, 4128),
+                                          (512, 4, 64, 5664), (160, 2, 64, 96)])
+def test_steps_of_few_rows(d, heads, hd, F, look):
+    from test_gpu_forward import Rig
+    V, B = 131, len(look)
+    shape = wl.ModelShape(2, d, heads, heads, hd, F, V, dtype="bf16")
+    rig = Rig(shape, B, 64, 8, seed=d + F, std=0.5 / d ** 0.5)
+    rng = wl.Rng(F, "cpu")
+    t0, toks = rng.randint(1, (B,), V).tolist(), rng.randint(2, (B, 8), V)
+    for s in range(B):
+        n = 20 + 11 * s
+        rig.caches[s][:, :, :, :n] = rng.normal(20 + s, (2, 2, heads, n, hd), 0.5)
+        rig.set_cache(s, n)
+    got, _, _ = rig.step(list(range(B)), t0, look, toks, rng.normal(3, (B, 8, V), 1.0), rng.uniform(4, (B, 9)), 1.0)
+    want = rig.oracle_logits(list(range(B)), t0, look, toks)
+    assert (got - want).abs().max().item() <= 5e-3     # the bound of the other small bf16 models (test_gpu_row_scale)
