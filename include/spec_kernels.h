@@ -132,7 +132,7 @@ typedef struct {
     int32_t gemm_workgroups[SPEC_PLAN_PROJECTIONS];
     uint64_t gemm_partial_floats[SPEC_PLAN_PROJECTIONS];
     uint64_t gemm_partial_capacity;   /* what spec_verify_init would allocate for them */
-    int32_t gate_up_swiglu_inside;    /* 1: the gate/up projection finishes SwiGLU itself (one K range) */
+    int32_t gate_up_swiglu_inside;    /* 1: up to 4 row tiles, the gate/up projection finishes SwiGLU itself (one K range); from 14 on it does wherever it runs as one K range */
     int32_t reserved0;
     /* operand-fragment buffers, in 16-byte units: what the first pass writes and what init allocates;
      * the second pair is the down projection's operand when SwiGLU is finished inside the GEMM */

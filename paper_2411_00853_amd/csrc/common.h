@@ -285,7 +285,8 @@ int launch_pack_x(const float* x, const float* gain, int M, int K, int mt_count,
 void set_gemm_wg_target(int workgroups);
 // Gate/up projection that finishes SwiGLU itself and writes the down projection's operand fragments
 // (see gemm.hip); `fits` says whether the shape allows it.
-bool gemm_swiglu_fits(int M, int F, int cu_count);
+bool gemm_swiglu_fits(int M, int F, int cu_count);   // up to 4 row tiles
+bool gemm_ring_swiglu_fits(const GemmPlan& p);       // from 14 row tiles on
 void set_swiglu_min_wgs(int workgroups);
 void set_swiglu_column_groups(int groups);
 int launch_gemm_swiglu(const void* x_frags, int planes, const void* w_gate_up, int M, int F, int K, const double2* ssq,

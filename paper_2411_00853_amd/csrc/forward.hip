@@ -60,8 +60,8 @@ int forward_init(spec_handle* h, int max_rows)
         if (rc == SPEC_OK) rc = a.alloc(&h->xf, xf_bytes);
         if (rc == SPEC_OK && hipMemset(h->xf, 0, xf_bytes) != hipSuccess) rc = fail(SPEC_ERR_DEVICE, "hipMemset failed");
         // the gate/up GEMM reads h->xf while its early workgroups already write the down projection's
-        // operand, which therefore has a buffer of its own (rows up to the 4 row tiles that path serves)
-        const size_t xa_bytes = xfrag_uint4s(gemm_row_tiles(std::min(max_rows, 64)), 2, std::max(z.d, z.F)) * sizeof(uint4);
+        // operand, which therefore has a buffer of its own
+        const size_t xa_bytes = xfrag_uint4s(gemm_row_tiles(max_rows), 2, std::max(z.d, z.F)) * sizeof(uint4);
         if (rc == SPEC_OK) rc = a.alloc(&h->xf_act, xa_bytes);
         if (rc == SPEC_OK && hipMemset(h->xf_act, 0, xa_bytes) != hipSuccess) rc = fail(SPEC_ERR_DEVICE, "hipMemset failed");
         A(reinterpret_cast<float**>(&h->ssq_parts), (size_t)std::min(max_rows, 16) * (z.d / ADD_COLS) * 2);
@@ -270,7 +270,8 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
         return mul(SPEC_PROF_GEMM_LM_HEAD, h->x, h->lm_head, z.V, z.d, logits_out, F32_STORE, h->final_norm);
     }
     Out o;
-    const bool swiglu_in_gemm = gemm_swiglu_fits(M, z.F, h->cu_count);
+    const bool swiglu_in_gemm = gemm_swiglu_fits(M, z.F, h->cu_count) ||
+                                gemm_ring_swiglu_fits(plan_gemm(M, 2 * z.F, z.d, h->cu_count, h->split_act));
     const bool fuse = h->fuse_rope && attention_takes_qkv(h->geom, c.n_q_heads, ks, B, c.max_kv_len, h->cu_count);
     for (int l = 0; l < c.n_layers; ++l) {
         const spec_layer_weights& w = h->layers[l];

@@ -596,7 +596,7 @@ extern "C" int spec_k_plan_step(const spec_model_cfg* cfg, int32_t batch, const 
     out->xfrag_units = xfrag_uint4s(gemm_row_tiles(rows[0]), 2, widest);
     out->xfrag_capacity = xfrag_uint4s(gemm_row_tiles(max_rows), 2, widest);
     out->xfrag_act_units = out->gate_up_swiglu_inside ? xfrag_uint4s(gemm_row_tiles(rows[0]), 2, cfg->d_ffn) : 0;
-    out->xfrag_act_capacity = xfrag_uint4s(gemm_row_tiles(std::min(max_rows, 64)), 2, cfg->d_ffn);
+    out->xfrag_act_capacity = xfrag_uint4s(gemm_row_tiles(max_rows), 2, std::max(cfg->d_model, cfg->d_ffn));
     int kmax = 0;
     for (int b = 0; b < seqs[0]; ++b) kmax = ks.k[b] > kmax ? ks.k[b] : kmax;
     const CacheGeom g = make_cache_geom(*cfg);
