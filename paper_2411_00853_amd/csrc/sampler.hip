@@ -958,7 +958,9 @@ __device__ __forceinline__ bool draw_locate(double (&run)[RUNS], F four, double 
     const double upto = row_scan(tw), S = read_lane(upto, DRAW_WAVES - 1);
     if (!absolute && !(S > 0.0)) return false;
     const double target = absolute ? u : u * S;
-    const unsigned long long over = __ballot(lane < DRAW_WAVES && upto > target), some = __ballot(tw > 0.0);
+    // Only what has mass is picked, at each of the three levels below: lanes add the running sums up in different orders, so behind
+    // the last mass before the target one may stand above it by its last bit (two halves alike and u = 0.5: an excluded id in 8 % of the draws).
+    const unsigned long long over = __ballot(tw > 0.0 && upto > target), some = __ballot(tw > 0.0);   // (lanes past the wavefronts: 0)
     const int pick = over ? __ffsll((long long)over) - 1 : some ? 63 - __clzll((long long)some) : 0;
     const double before = pick > 0 ? read_lane(upto, pick - 1) : 0.0;
     if (wave == pick) {   // the only wavefront that looks closer: which run, which lane, which id
@@ -968,7 +970,7 @@ __device__ __forceinline__ bool draw_locate(double (&run)[RUNS], F four, double 
         for (int j = 0; j < RUNS; ++j) {
             const double r = wave_sum(run[j]);
             if (r > 0.0) { last_run = j; last_before = c0; }
-            if (at < 0 && c0 + r > target) { at = j; at_before = c0; }
+            if (at < 0 && r > 0.0 && c0 + r > target) { at = j; at_before = c0; }
             c0 += r;
         }
         if (at < 0) { at = last_run; at_before = last_before; }
@@ -983,7 +985,7 @@ __device__ __forceinline__ bool draw_locate(double (&run)[RUNS], F four, double 
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             cdf += x[e];
-            if (mine < 0 && cdf > target) mine = id0 + e;
+            if (mine < 0 && x[e] > 0.0 && cdf > target) mine = id0 + e;
             if (x[e] > 0.0) mine_last = id0 + e;
         }
         if (mine < 0) mine = mine_last;   // rounding between the lane's sum and the running one
