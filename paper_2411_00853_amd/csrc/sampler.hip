@@ -680,6 +680,26 @@ __global__ void __launch_bounds__(TPB) accept_mass_kernel(const int32_t* seq_sta
     }
 }
 
+// Of the lanes of a wavefront whose running sum inc (own share loc, of PER ids with the masses x) passes the target, the first one
+// that has mass: which of its ids the target falls on, the first whose running sum passes it (rounding between that sum and inc: the
+// last id with mass).  -1 for the other lanes.  The lanes add up in different orders, so neighbours' ranges [inc - loc, inc) may
+// leave a gap or overlap by rounding: a lane is not asked whether the target lies in its range.
+template <int PER>
+__device__ __forceinline__ int lowest_crossing(const double* x, double loc, double inc, double target)
+{
+    const unsigned long long over = __ballot(loc > 0.0 && inc > target);
+    if (!over || (int)(threadIdx.x & 63) != __ffsll((long long)over) - 1) return -1;
+    double cdf = inc - loc;
+    int first = -1, last = -1;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        cdf += x[i];
+        if (first < 0 && x[i] > 0.0 && cdf > target) first = i;
+        if (x[i] > 0.0) last = i;
+    }
+    return first >= 0 ? first : last;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Pass 3: locate u*S among the chunk masses, scan that chunk in ascending token id, emit.
 // Latency only, one workgroup per sequence (11 -> 9.3 us at 64 sequences: the masses walked eight at a time, padding
@@ -784,7 +804,7 @@ __global__ void __launch_bounds__(TPB) final_draw_kernel(const int32_t* accepted
         before = 0.0;
         target_mass = u;   // p_a sums to 1
     }
-    if (threadIdx.x == 0) s_tok = -1;
+    if (threadIdx.x == 0) s_tok = V;   // none yet
     int last_positive = -1;
     constexpr int PER = RES_CHUNK / TPB;   // 16 consecutive ids per lane
     for (int c = c_lo; c < c_hi; ++c) {
@@ -827,26 +847,16 @@ __global__ void __launch_bounds__(TPB) final_draw_kernel(const int32_t* accepted
         double off = before;
         for (int wv = 0; wv < (int)(threadIdx.x >> 6); ++wv) off += wave_tot[wv];
         inc += off;
-        const double exc = inc - loc;
-        // the lane whose range [exc, inc) the target mass falls in walks its ids
-        if (inc > target_mass && !(exc > target_mass)) {
-            double cdf = exc;
-            int tok = -1;
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                cdf += r[threadIdx.x * (PER + 1) + i];
-                if (tok < 0 && cdf > target_mass) tok = base + threadIdx.x * PER + i;
-            }
-            if (tok < 0) tok = my_last;   // rounding between the lane sum and the running sum
-            if (tok >= 0) atomicMax(&s_tok, tok);
-        }
+        // the first lane with mass whose running sum passes the target walks its ids (see lowest_crossing)
+        const int tok = lowest_crossing<PER>(r + threadIdx.x * (PER + 1), loc, inc, target_mass);
+        if (tok >= 0) atomicMin(&s_tok, base + threadIdx.x * PER + tok);
         // remember the last id with positive mass in case rounding leaves no crossing at all
         int wl = my_last;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) wl = max(wl, __shfl_xor(wl, o));
         last_positive = max(last_positive, wl);
         __syncthreads();
-        if (s_tok >= 0) break;
+        if (s_tok < V) break;
         before += (wave_tot[0] + wave_tot[1]) + (wave_tot[2] + wave_tot[3]);
     }
     __syncthreads();
@@ -856,7 +866,7 @@ __global__ void __launch_bounds__(TPB) final_draw_kernel(const int32_t* accepted
     __syncthreads();
     if (threadIdx.x == 0) {
         int y = s_tok;
-        if (y < 0) y = max(max(scratch[0], scratch[1]), max(scratch[2], scratch[3]));
+        if (y >= V) y = max(max(scratch[0], scratch[1]), max(scratch[2], scratch[3]));
         if (y < 0) y = 0;
         if (emit.tokens) {
             emit.tokens[b * emit.stride + emit.offset] = y;
@@ -1698,7 +1708,7 @@ __global__ void __launch_bounds__(TREE_TPB) tree_walk_kernel(StepTables t, Looka
         s_chunk = pick;
         s_before = c0;
         s_target = target_mass;
-        s_tok = -1;
+        s_tok = V;   // none yet
     }
     __syncthreads();
     {
@@ -1734,18 +1744,8 @@ __global__ void __launch_bounds__(TREE_TPB) tree_walk_kernel(StepTables t, Looka
         double off = before;
         for (int wv = 0; wv < (int)(threadIdx.x >> 6); ++wv) off += wsum[wv];
         inc += off;
-        const double exc = inc - loc;
-        if (inc > target_mass && !(exc > target_mass)) {
-            double cdf = exc;
-            int y = -1;
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                cdf += r[threadIdx.x * (PER + 1) + i];
-                if (y < 0 && cdf > target_mass) y = base + threadIdx.x * PER + i;
-            }
-            if (y < 0) y = my_last;
-            if (y >= 0) atomicMax(&s_tok, y);
-        }
+        const int at = lowest_crossing<PER>(r + threadIdx.x * (PER + 1), loc, inc, target_mass);
+        if (at >= 0) atomicMin(&s_tok, base + threadIdx.x * PER + at);
         int wl = my_last;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) wl = max(wl, __shfl_xor(wl, o));
@@ -1755,8 +1755,10 @@ __global__ void __launch_bounds__(TREE_TPB) tree_walk_kernel(StepTables t, Looka
         __syncthreads();
         if (threadIdx.x == 0) {
             int y = s_tok;
-            if (y < 0)
+            if (y >= V) {
+                y = -1;
                 for (int w = 0; w < TREE_TPB / 64; ++w) y = max(y, scratch[w]);
+            }
             if (y < 0) y = 0;
             out.n_accepted[b] = a;
             int32_t* o = out.out_tokens + b * (Kmax + 1);

@@ -1,5 +1,5 @@
 """Draws whose target falls between two halves of a row that weigh the same, with excluded ids (-inf) between them: rounding may
-put the target on either side, and an id without mass is never drawn."""
+put the target on either side, and neither an id without mass nor one further away is ever drawn."""
 import pytest
 import torch
 
@@ -24,7 +24,7 @@ def _rows(B, V, gap):
 
 
 @pytest.mark.parametrize("tree", [False, True])
-@pytest.mark.parametrize("V,gap", [(64, 8), (256, 40), (2048, 300), (4096, 1), (8192, 700), (32768, 5000)])
+@pytest.mark.parametrize("V,gap", [(64, 8), (256, 40), (2048, 300), (4096, 1), (8192, 700), (32768, 5000), (32770, 5000), (50257, 3), (151936, 9000)])
 def test_excluded_ids_between_two_halves(V, gap, tree):
     from helpers import run_sampler_gpu
     from test_gpu_tree import run_tree_sampler
