@@ -124,18 +124,21 @@ typedef struct {
     int32_t rows;                 /* sum of K_b + 1 */
     int32_t n_passes;             /* decoder passes (1 unless rows > SPEC_MAX_STEP_ROWS) */
     int32_t pass_seqs[SPEC_PLAN_MAX_PASSES], pass_rows[SPEC_PLAN_MAX_PASSES];
-    /* the projections of the first pass: variant and launch shape (gate/up: the plan used when SwiGLU is
-     * not finished inside the GEMM) */
+    /* the projections of the first pass: variant and launch shape (gate/up up to 4 row tiles: the plan used when
+     * SwiGLU is not finished inside the GEMM) */
     int32_t gemm_row_tiles[SPEC_PLAN_PROJECTIONS], gemm_col_tiles[SPEC_PLAN_PROJECTIONS];
     int32_t gemm_k_ranges[SPEC_PLAN_PROJECTIONS], gemm_k_blocks_per_range[SPEC_PLAN_PROJECTIONS];
     int32_t gemm_row_parts[SPEC_PLAN_PROJECTIONS], gemm_col_groups[SPEC_PLAN_PROJECTIONS];
     int32_t gemm_workgroups[SPEC_PLAN_PROJECTIONS];
     uint64_t gemm_partial_floats[SPEC_PLAN_PROJECTIONS];
     uint64_t gemm_partial_capacity;   /* what spec_verify_init would allocate for them */
-    int32_t gate_up_swiglu_inside;    /* 1: up to 4 row tiles, the gate/up projection finishes SwiGLU itself (one K range); from 14 on it does wherever it runs as one K range */
-    int32_t reserved0;
+    int32_t gate_up_swiglu_inside;    /* 1: the gate/up projection finishes SwiGLU itself (one K range) */
+    /* bit i: projection i fetches both operands straight into LDS, eight wavefronts as four column groups by two row
+     * halves; from 14 row tiles on as two row blocks per column block, which gemm_workgroups counts */
+    int32_t gemm_ring;
     /* operand-fragment buffers, in 16-byte units: what the first pass writes and what init allocates;
-     * the second pair is the down projection's operand when SwiGLU is finished inside the GEMM */
+     * the second pair holds the normalised residual up to 16 rows, beyond that the down projection's operand when
+     * SwiGLU is finished inside the GEMM */
     uint64_t xfrag_units, xfrag_capacity, xfrag_act_units, xfrag_act_capacity;
     /* the attention launch of the first pass */
     int32_t attn_kv_share;        /* work items per kv head */

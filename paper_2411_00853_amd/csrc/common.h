@@ -271,6 +271,7 @@ constexpr int GEMM_MAX_ROWS = SPEC_MAX_STEP_ROWS;   // rows the largest variant 
 GemmPlan plan_gemm(int M, int N, int K, int cu_count, bool split_x);
 int gemm_row_tiles(int M);   // row tiles (mt) of the variant that serves M rows; 0 if none
 size_t gemm_partial_elems(const GemmPlan& p, int M);
+inline int gemm_row_blocks(const GemmPlan& p) { return p.ring ? (p.mt + p.ring - 1) / p.ring : 1; }   // workgroups per column block and K range
 // x_frags: X as operand fragments (frag.h) with p.mt row tiles and p.planes planes
 // job != NULL (one row tile): the launch also adds up job's sums of squares into job->ssq_out ([M][n_ssq])
 int launch_gemm_bf16(const GemmPlan& p, const void* x_frags, const void* w_packed, int M, int N, int K,

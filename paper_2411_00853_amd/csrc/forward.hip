@@ -61,7 +61,7 @@ int forward_init(spec_handle* h, int max_rows)
         if (rc == SPEC_OK && hipMemset(h->xf, 0, xf_bytes) != hipSuccess) rc = fail(SPEC_ERR_DEVICE, "hipMemset failed");
         // the gate/up GEMM reads h->xf while its early workgroups already write the down projection's
         // operand, which therefore has a buffer of its own
-        const size_t xa_bytes = xfrag_uint4s(gemm_row_tiles(max_rows), 2, std::max(z.d, z.F)) * sizeof(uint4);
+        const size_t xa_bytes = act_frag_capacity(c, max_rows) * sizeof(uint4);
         if (rc == SPEC_OK) rc = a.alloc(&h->xf_act, xa_bytes);
         if (rc == SPEC_OK && hipMemset(h->xf_act, 0, xa_bytes) != hipSuccess) rc = fail(SPEC_ERR_DEVICE, "hipMemset failed");
         A(reinterpret_cast<float**>(&h->ssq_parts), (size_t)std::min(max_rows, 16) * (z.d / ADD_COLS) * 2);
@@ -108,6 +108,24 @@ size_t gemm_partial_capacity(const spec_model_cfg& c, int max_rows, int cu_count
             if (e > part) part = e;
         }
     return part;
+}
+
+// whether the gate/up projection of a pass of M rows finishes SwiGLU itself
+bool swiglu_inside(const spec_model_cfg& c, int M, int cu_count)
+{
+    return gemm_swiglu_fits(M, c.d_ffn, cu_count) || gemm_ring_swiglu_fits(plan_gemm(M, 2 * c.d_ffn, c.d_model, cu_count, true));
+}
+
+size_t act_frag_units(const spec_model_cfg& c, int M, int cu_count)
+{
+    const int mt = gemm_row_tiles(M);
+    if (mt == 1) return xfrag_uint4s(mt, 2, c.d_model);
+    return swiglu_inside(c, M, cu_count) ? xfrag_uint4s(mt, 2, c.d_ffn) : 0;
+}
+
+size_t act_frag_capacity(const spec_model_cfg& c, int max_rows)
+{
+    return xfrag_uint4s(gemm_row_tiles(max_rows), 2, std::max(c.d_model, c.d_ffn));
 }
 
 void projection_shapes(const spec_model_cfg& c, int* n_out, int* n_in)
@@ -270,8 +288,7 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
         return mul(SPEC_PROF_GEMM_LM_HEAD, h->x, h->lm_head, z.V, z.d, logits_out, F32_STORE, h->final_norm);
     }
     Out o;
-    const bool swiglu_in_gemm = gemm_swiglu_fits(M, z.F, h->cu_count) ||
-                                gemm_ring_swiglu_fits(plan_gemm(M, 2 * z.F, z.d, h->cu_count, h->split_act));
+    const bool swiglu_in_gemm = swiglu_inside(c, M, h->cu_count);
     const bool fuse = h->fuse_rope && attention_takes_qkv(h->geom, c.n_q_heads, ks, B, c.max_kv_len, h->cu_count);
     for (int l = 0; l < c.n_layers; ++l) {
         const spec_layer_weights& w = h->layers[l];

@@ -1029,7 +1029,7 @@ int launch_variant(const GemmPlan& p, const void* xf, const void* w, int M, int 
 template <int MT, int NT, bool STREAM>
 int launch_ring(const GemmPlan& p, const void* xf, const void* w, int M, int K, int n_tiles, float* partial, hipStream_t s, const SwigluOut* swiglu)
 {
-    const int row_blocks = (p.mt + MT - 1) / MT, n_blocks = (n_tiles + RING_GROUPS * NT - 1) / (RING_GROUPS * NT);
+    const int row_blocks = gemm_row_blocks(p), n_blocks = (n_tiles + RING_GROUPS * NT - 1) / (RING_GROUPS * NT);
     int grid = n_blocks * p.n_split;
     if (p.n_split < 8) grid = (n_blocks + (8 / p.n_split) - 1) / (8 / p.n_split) * 8;   // (a multiple of eight either way)
     auto* k = swiglu ? p.planes == 2 ? gemm_ring_kernel<MT, NT, 2, false, true> : gemm_ring_kernel<MT, NT, 1, false, true>

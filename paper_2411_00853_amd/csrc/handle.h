@@ -73,6 +73,9 @@ int forward_run_grouped(spec_handle* h, const LookaheadPack& ks, int B, int M, f
                         LogitsSrc* last = nullptr);
 // host logic behind the two (no device work): see forward.hip
 size_t gemm_partial_capacity(const spec_model_cfg& c, int max_rows, int cu_count);
+bool swiglu_inside(const spec_model_cfg& c, int M, int cu_count);
+size_t act_frag_units(const spec_model_cfg& c, int M, int cu_count);   // 16-byte units of xf_act that a pass of M rows writes
+size_t act_frag_capacity(const spec_model_cfg& c, int max_rows);       // at most, over all passes of up to max_rows rows
 void projection_shapes(const spec_model_cfg& c, int* n_out, int* n_in);   // [SPEC_PLAN_PROJECTIONS]
 int plan_passes(const LookaheadPack& ks, int B, int M, int cap, int* pass_seqs, int* pass_rows, int max_passes);
 }  // namespace specv

@@ -587,16 +587,17 @@ extern "C" int spec_k_plan_step(const spec_model_cfg* cfg, int32_t batch, const 
         out->gemm_row_parts[i] = p.rs;
         out->gemm_col_groups[i] = p.cg;
         const int n_tiles = p.n_pad / 16;
-        out->gemm_workgroups[i] = (n_tiles + p.cg * p.nt - 1) / (p.cg * p.nt) * p.n_split;
+        out->gemm_workgroups[i] = (n_tiles + p.cg * p.nt - 1) / (p.cg * p.nt) * gemm_row_blocks(p) * p.n_split;
+        if (p.ring) out->gemm_ring |= 1 << i;
         out->gemm_partial_floats[i] = gemm_partial_elems(p, rows[0]);
     }
     out->gemm_partial_capacity = gemm_partial_capacity(*cfg, max_rows, cu_count);
     const int widest = std::max(std::max(cfg->d_model, cfg->n_q_heads * cfg->head_dim), cfg->d_ffn);
-    out->gate_up_swiglu_inside = gemm_swiglu_fits(rows[0], cfg->d_ffn, cu_count) ? 1 : 0;
+    out->gate_up_swiglu_inside = swiglu_inside(*cfg, rows[0], cu_count) ? 1 : 0;
     out->xfrag_units = xfrag_uint4s(gemm_row_tiles(rows[0]), 2, widest);
     out->xfrag_capacity = xfrag_uint4s(gemm_row_tiles(max_rows), 2, widest);
-    out->xfrag_act_units = out->gate_up_swiglu_inside ? xfrag_uint4s(gemm_row_tiles(rows[0]), 2, cfg->d_ffn) : 0;
-    out->xfrag_act_capacity = xfrag_uint4s(gemm_row_tiles(max_rows), 2, std::max(cfg->d_model, cfg->d_ffn));
+    out->xfrag_act_units = act_frag_units(*cfg, rows[0], cu_count);
+    out->xfrag_act_capacity = act_frag_capacity(*cfg, max_rows);
     int kmax = 0;
     for (int b = 0; b < seqs[0]; ++b) kmax = ks.k[b] > kmax ? ks.k[b] : kmax;
     const CacheGeom g = make_cache_geom(*cfg);

@@ -49,11 +49,21 @@ def _check_invariants(shape, cfg, look, p, paged):
         n_pad = (n_out[i] + 15) // 16 * 16
         assert p.gemm_partial_floats[i] == s * p.pass_rows[0] * n_pad <= p.gemm_partial_capacity
         tiles_per_wg = nt * p.gemm_col_groups[i]
-        assert p.gemm_workgroups[i] == -(-(n_pad // 16) // tiles_per_wg) * s
-    # operand fragments fit their buffers; SwiGLU inside the GEMM only up to four row tiles
-    assert p.xfrag_units <= p.xfrag_capacity and p.xfrag_act_units <= p.xfrag_act_capacity
-    if p.gate_up_swiglu_inside:
-        assert p.gemm_row_tiles[2] <= 4 and p.xfrag_act_units > 0
+        # from 14 row tiles on two row blocks of eight, ten or twelve tiles; at eight row tiles one, for wide matrices
+        ring = p.gemm_ring >> i & 1
+        assert ring == (mt >= 14 or (mt == 8 and nt == 4 and p.gemm_col_groups[i] == 4))
+        assert p.gemm_workgroups[i] == -(-(n_pad // 16) // tiles_per_wg) * s * (2 if mt >= 14 else 1)
+    # operand fragments fit their buffers; SwiGLU inside the GEMM up to four row tiles, and from 14 on with one K range
+    mt = p.gemm_row_tiles[2]
+    units = lambda k: (k // 32 + 4) * 2 * mt * 64
+    assert p.xfrag_units == units(max(shape.d_model, dq, shape.d_ffn)) <= p.xfrag_capacity
+    if mt >= 14:
+        assert p.gate_up_swiglu_inside == (p.gemm_k_ranges[2] == 1)
+    elif p.gate_up_swiglu_inside:
+        assert mt <= 4
+    # the second buffer: the normalised residual of few rows, or SwiGLU's result where the product writes it
+    assert p.xfrag_act_units == (units(shape.d_model) if mt == 1 else units(shape.d_ffn) if p.gate_up_swiglu_inside else 0)
+    assert p.xfrag_act_units <= p.xfrag_act_capacity
     # attention of the first pass
     group = shape.n_q_heads // shape.n_kv_heads
     window = max(look[:p.pass_seqs[0]]) + 1
@@ -134,6 +144,21 @@ def test_plans_of_the_named_configurations():
     assert p.rows == sum(k + 1 for k in w.lookahead) and p.n_passes == 1
     assert list(p.gemm_row_tiles) == [10] * 5 and list(p.gemm_row_parts) == [2] * 5
     assert (p.attn_kv_share, p.attn_small, p.attn_chunks, p.attn_wavefronts) == (1, 0, 1, 1)
+
+
+def test_plan_of_the_many_row_step():
+    # 7B shape, 352 rows: two row blocks of twelve row tiles; gate/up in one K range, with SwiGLU and the second buffer
+    cfg, p = _plan(wl.SEVEN_B, [10] * 32, 32, 4107, 10)
+    assert p.rows == 352 and list(p.gemm_row_tiles) == [22] * 5 and p.gemm_ring == 0b11111
+    assert list(p.gemm_workgroups) == [256, 256, 230, 256, 250] and list(p.gemm_k_ranges) == [2, 4, 1, 8, 1]
+    assert p.gate_up_swiglu_inside == 1 and p.xfrag_act_units == (11008 // 32 + 4) * 2 * 22 * 64 <= p.xfrag_act_capacity
+    # 128 rows: the LM head alone, as one row block
+    cfg, p = _plan(wl.SEVEN_B, [15] * 8, 32, 4107, 15)
+    assert p.rows == 128 and p.gemm_ring == 0b10000 and p.gemm_workgroups[4] == 125 * p.gemm_k_ranges[4]
+    assert p.gate_up_swiglu_inside == 0 and p.xfrag_act_units == 0
+    # one row: the normalised residual
+    cfg, p = _plan(wl.ONE_B, [0], 1, 2048, 5)
+    assert p.gemm_ring == 0 and p.xfrag_act_units == (2048 // 32 + 4) * 2 * 64
 
 
 def test_steps_beyond_one_pass_and_beyond_64_rows_per_kv_head():
