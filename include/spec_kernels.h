@@ -44,7 +44,7 @@ int spec_k_gemm_bf16(const float* x, const void* w_packed, float* y, int32_t M, 
  * SPEC_ERR_SHAPE instead of writing past the workspace. */
 void spec_k_set_gemm_wg_target(int32_t workgroups);
 
-/* Tuning knob: launches of more than 112 rows whose twelve column tiles per workgroup would run as
+/* Tuning knob: launches of 97 to 192 rows whose twelve column tiles per workgroup would run as
  * three column groups of four tiles (six wavefronts) run as four groups of three tiles instead
  * (eight wavefronts, two on every SIMD); 1 = on (default), 0 = off.  Process-wide. */
 void spec_k_set_gemm_balance_groups(int32_t on);

@@ -1106,11 +1106,14 @@ static void plan_ring(GemmPlan& p, int n_tiles, int kb_total, int cu_count)
 {
     p.ring = p.mt <= 16 ? 8 : p.mt <= 20 ? 10 : 12;
     p.cg = RING_GROUPS;
+    auto may_cut = [&](int s) { return blocks_per_range(kb_total, s) >= 2 * WPACK_KG && ranges_have_work(kb_total, s); };
     double best = 0.0;
     for (int nt = 2; nt <= 4; ++nt)
         for (int s = 1; s <= 16; s *= 2) {
-            if (s > 1 && (blocks_per_range(kb_total, s) < 2 * WPACK_KG || !ranges_have_work(kb_total, s))) break;
+            if (s > 1 && !may_cut(s)) break;
             const int wgs = (n_tiles + RING_GROUPS * nt - 1) / (RING_GROUPS * nt) * 2 * s;
+            // a workgroup target that the caller set: the fewest ranges that reach it, or as many as the shape allows
+            if (g_wg_target > 0 && wgs < g_wg_target && s < 16 && may_cut(2 * s)) continue;
             const int rounds = (wgs + cu_count - 1) / cu_count;
             const double stage = 32.0 * p.ring * nt + 0.6 * 64.0 * (p.ring + nt);
             const double cost = rounds * blocks_per_range(kb_total, s) * stage + 0.0025 * s * p.mt * 16 * p.n_pad;
@@ -1119,6 +1122,7 @@ static void plan_ring(GemmPlan& p, int n_tiles, int kb_total, int cu_count)
                 p.nt = nt;
                 p.n_split = s;
             }
+            if (g_wg_target > 0) break;
         }
     p.kb_per_split = blocks_per_range(kb_total, p.n_split);
 }

@@ -161,6 +161,26 @@ def test_plan_of_the_many_row_step():
     assert p.gemm_ring == 0 and p.xfrag_act_units == (2048 // 32 + 4) * 2 * 64
 
 
+@pytest.mark.parametrize("rows", [6, 48, 128, 192, 208, 352])
+def test_workgroup_target_cuts_k(rows):
+    """The workgroups asked for decide the K ranges at every number of rows: the fewest ranges that reach them, and with a
+    target that no cut reaches as many as the shape allows."""
+    look, n = [15] * (rows // 16) or [rows - 1], []
+    try:
+        for target in (1, 300, 700, 100000):
+            sv.spec_k_set_gemm_wg_target(target)
+            _, p = _plan(wl.SEVEN_B, look, 32, 4107, 15)
+            n.append(list(p.gemm_k_ranges))
+            for i in range(sv.PLAN_PROJECTIONS):
+                s, wgs = p.gemm_k_ranges[i], p.gemm_workgroups[i]
+                assert wgs >= target or target == 100000 or s == 16
+                assert s == 1 or wgs // s * (s // 2) < target
+    finally:
+        sv.spec_k_set_gemm_wg_target(0)
+    assert n[0] == [1] * 5 and n[3] == [16] * 5
+    assert n[0][1] < n[1][1] <= n[2][1]     # (the output projection)
+
+
 def test_steps_beyond_one_pass_and_beyond_64_rows_per_kv_head():
     shape = wl.ModelShape(2, 256, 16, 2, 64, 512, 1000)          # 8 query heads per kv head
     cfg, p = _plan(shape, [15] * 40, 40, 400, 15)
