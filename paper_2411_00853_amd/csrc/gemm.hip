@@ -581,12 +581,16 @@ __global__ void __launch_bounds__(64 * RANGES) gemm_add_kernel(const u32x4* __re
 // ahead.  Stage i's products run while its last fragments and then stage i + 1's first ones are read: the barrier stands L tiles
 // before a stage's end, where all of stage i is in registers (its slot is free) and stage i + 1 has landed.  The
 // requests are not known to the compiler, which sees no load at all in this kernel; every wait is written here.
+// (m0 is none of the registers that the compiler hands out, about which it warns; it may set m0 for an instruction of its own.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <bool STREAM>
 __device__ __forceinline__ void fetch_to_lds(const char* base, uint32_t offset, uint32_t lds)   // 16 bytes per lane, to lds + 16 * lane
 {
-    if constexpr (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(offset), "s"(base) : "memory");
-    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
+    if constexpr (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(offset), "s"(base) : "memory", "m0");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 template <int N>
 __device__ __forceinline__ void wait_fetches()   // at most N requests of this wavefront still under way
 {

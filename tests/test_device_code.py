@@ -1,5 +1,5 @@
 """What the compiler made of the kernels, read from the built library's disassembly (no GPU).  Three things that no
-source line shows and that have gone wrong:
+source line shows and that have gone wrong, and one that the sources have to say:
 
 * The result of a matrix instruction may be read by a vector instruction only some wait states later, and the hardware
   does not hold the reader back.  The compiler counts them, but not along every path where branches meet: the
@@ -8,7 +8,8 @@ source line shows and that have gone wrong:
 * A register parked in the accumulation registers must not be fetched back where no lane is active: behind the exit of
   a loop that masks lanes off, before the mask is restored, the copy does nothing.
 * A kernel whose vector registers do not fit keeps some of them in memory.  The attention variants of eight wavefronts per
-  workgroup, two of which have to fit a SIMD, did when a request fetched more ahead than was left for it."""
+  workgroup, two of which have to fit a SIMD, did when a request fetched more ahead than was left for it.
+* Inline assembly that sets m0 says so to the compiler."""
 import os
 import re
 import shutil
@@ -170,6 +171,23 @@ def test_no_kernel_keeps_vector_registers_in_memory(objects):
     assert [(n, count) for n, count in found if count != "0"] == []
 
 
+def undeclared_m0(text):
+    """Inline assembly that writes m0 without naming it among the registers it changes."""
+    found = []
+    for asm in re.findall(r"\basm\s+volatile\s*\((.*?)\)\s*;", text, re.S):
+        if re.search(r"\bs_\w+\s+m0\b", asm) and not re.search(r'"m0"', asm.rsplit(":", 1)[-1]):
+            found.append(asm)
+    return found
+
+
+def test_assembly_names_m0_where_it_sets_it():
+    # (nothing else in a kernel that fetches into LDS uses it today; a compiler that kept something there would lose it)
+    from paper_2411_00853_amd import build
+    sources = [os.path.join(build.CSRC, f) for f in sorted(os.listdir(build.CSRC))]
+    assert sum("s_mov_b32 m0" in open(f).read() for f in sources) > 0
+    assert [(f, a) for f in sources for a in undeclared_m0(open(f).read())] == []
+
+
 def _listing(lines):
     return Code("f", ["%s // %012X: 00000000%s" % (l, 0x100 + 8 * i, "" if to is None else " <f+0x%x>" % (8 * to))
                       for i, (l, to) in enumerate(lines)])
@@ -182,6 +200,8 @@ def test_the_checks_find_what_they_look_for():
     # the wait stands on the way through, not on the branch past it
     assert fewest_wait_states(_listing([mfma, ("s_cbranch_execnz 1", 3), nops, read, end]))[0] == 1
     assert fewest_wait_states(_listing([mfma, ("v_accvgpr_write_b32 a5, 0", None), read, end])) is None
+    assert undeclared_m0('asm volatile("s_mov_b32 m0, %0" ::"s"(x) : "memory");')
+    assert not undeclared_m0('asm volatile("s_mov_b32 m0, %0" ::"s"(x) : "memory", "m0");')
     save, skip = ("s_and_saveexec_b64 s[0:1], vcc", None), ("s_cbranch_execz 2", 3)
     restore, back = ("s_or_b64 exec, exec, s[0:1]", None), ("v_accvgpr_read_b32 v9, a1", None)
     assert copies_without_lanes(_listing([save, skip, nops, back, restore, end]))
