@@ -60,7 +60,7 @@ int forward_init(spec_handle* h, int max_rows)
         if (rc == SPEC_OK) rc = a.alloc(&h->xf, xf_bytes);
         if (rc == SPEC_OK && hipMemset(h->xf, 0, xf_bytes) != hipSuccess) rc = fail(SPEC_ERR_DEVICE, "hipMemset failed");
         // the gate/up GEMM reads h->xf while its early workgroups already write the down projection's
-        // operand, which therefore has a buffer of its own
+        // operand, which therefore has a buffer of its own (up to 16 rows the two change places)
         const size_t xa_bytes = act_frag_capacity(c, max_rows) * sizeof(uint4);
         if (rc == SPEC_OK) rc = a.alloc(&h->xf_act, xa_bytes);
         if (rc == SPEC_OK && hipMemset(h->xf_act, 0, xa_bytes) != hipSuccess) rc = fail(SPEC_ERR_DEVICE, "hipMemset failed");
@@ -125,7 +125,11 @@ size_t act_frag_units(const spec_model_cfg& c, int M, int cu_count)
 
 size_t act_frag_capacity(const spec_model_cfg& c, int max_rows)
 {
-    return xfrag_uint4s(gemm_row_tiles(max_rows), 2, std::max(c.d_model, c.d_ffn));
+    // (whatever the tuning knobs say: they may change after init.  From 65 to 192 rows SwiGLU is a kernel of its own.)
+    size_t n = xfrag_uint4s(1, 2, c.d_model);
+    if (max_rows > 16) n = std::max(n, xfrag_uint4s(gemm_row_tiles(std::min(max_rows, 64)), 2, c.d_ffn));
+    if (max_rows > 192) n = std::max(n, xfrag_uint4s(gemm_row_tiles(max_rows), 2, c.d_ffn));
+    return n;
 }
 
 void projection_shapes(const spec_model_cfg& c, int* n_out, int* n_in)

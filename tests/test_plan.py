@@ -181,6 +181,25 @@ def test_workgroup_target_cuts_k(rows):
     assert n[0][1] < n[1][1] <= n[2][1]     # (the output projection)
 
 
+@pytest.mark.parametrize("rows", [1, 16, 32, 48, 64, 80, 128, 192, 208, 352, 1008])
+def test_second_operand_buffer_holds_what_is_written_and_no_more(rows):
+    """The buffer has readers up to 16 rows (d_model wide), up to 64 and above 192 (d_ffn wide): what a handle of 65 to 192 rows
+    reserves is what its passes of up to 64 rows write."""
+    units = lambda tiles, k: (k // 32 + 4) * 2 * tiles * 64
+    for shape in (wl.SEVEN_B, wl.ONE_B, wl.ModelShape(1, 2048, 16, 16, 64, 512, 1000)):
+        cfg = sv.make_cfg(shape, -(-rows // 16), 64, min(rows, 16) - 1)
+        plan = lambda n: sv.spec_k_plan_step(cfg, [15] * (n // 16) + [n % 16 - 1] * (n % 16 > 0), 256)
+        few, some = units(1, shape.d_model), units(min(-(-rows // 16), 4), shape.d_ffn)
+        many = units(plan(min(rows, 352)).gemm_row_tiles[0], shape.d_ffn)
+        want = few if rows <= 16 else max(few, some) if rows <= 192 else max(few, many)
+        assert plan(1).xfrag_act_capacity == want
+        try:
+            sv.spec_k_set_swiglu_min_wgs(1)      # SwiGLU inside wherever it may be
+            assert all(plan(n).xfrag_act_units <= want for n in range(1, rows + 1))
+        finally:
+            sv.spec_k_set_swiglu_min_wgs(0)
+
+
 def test_steps_beyond_one_pass_and_beyond_64_rows_per_kv_head():
     shape = wl.ModelShape(2, 256, 16, 2, 64, 512, 1000)          # 8 query heads per kv head
     cfg, p = _plan(shape, [15] * 40, 40, 400, 15)
