@@ -285,13 +285,13 @@ int launch_pack_x(const float* x, const float* gain, int M, int K, int mt_count,
                   hipStream_t s);
 void set_gemm_wg_target(int workgroups);
 // Gate/up projection that finishes SwiGLU itself and writes the down projection's operand fragments
-// (see gemm.hip); `fits` says whether the shape allows it.
+// (see gemm.hip; both operands have two planes); `fits` says whether the shape allows it.
 bool gemm_swiglu_fits(int M, int F, int cu_count);   // up to 4 row tiles
 bool gemm_ring_swiglu_fits(const GemmPlan& p);       // from 14 row tiles on
 void set_swiglu_min_wgs(int workgroups);
 void set_swiglu_column_groups(int groups);
-int launch_gemm_swiglu(const void* x_frags, int planes, const void* w_gate_up, int M, int F, int K, const double2* ssq,
-                       int n_ssq, int d, float eps, void* act_frags, int act_mt, int act_planes, int cu_count, hipStream_t s,
+int launch_gemm_swiglu(const void* x_frags, const void* w_gate_up, int M, int F, int K, const double2* ssq, int n_ssq, int d,
+                       float eps, void* act_frags, int act_mt, int cu_count, hipStream_t s,
                        const SsqTiles* tiles = nullptr);
 // fp32: y = x * W^T (F32_STORE), y += x * W^T (F32_ADD), or y[m][n] = silu(gate) * up with W = N gate rows then N up
 // rows (F32_SWIGLU).  gain != NULL: x is normalised first (RMSNorm over its K columns, times gain).

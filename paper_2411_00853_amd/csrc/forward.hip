@@ -229,13 +229,13 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
     };
     const int n_ssq = ssq_pairs(z.d);
     const int mt = bf16 ? gemm_row_tiles(M) : 0;
-    const int planes = h->split_act ? 2 : 1;
+    const int planes = 2;   // activations go to the matrix cores as bf16 head + remainder
     const XOut to_xf{bf16 ? h->xf : nullptr, mt, planes, nullptr};            // operand of the next GEMM
     const NormScale scaled{h->ssq, n_ssq, z.d, c.rms_eps};
     // Up to 16 rows the output and down projections finish the residual stream themselves (launch_gemm_add): the normalised
     // residual stays in the second fragment buffer, the attention's and SwiGLU's results in the first, and the sums of
     // squares of x come by column tile.
-    const GemmPlan plan_o = plan_gemm(M, z.d, z.dq, h->cu_count, h->split_act), plan_down = plan_gemm(M, z.d, z.F, h->cu_count, h->split_act);
+    const GemmPlan plan_o = plan_gemm(M, z.d, z.dq, h->cu_count, true), plan_down = plan_gemm(M, z.d, z.F, h->cu_count, true);
     const bool few = bf16 && mt == 1;
     const bool add_o = few && gemm_add_fits(plan_o, z.dq), add_down = few && gemm_add_fits(plan_down, z.F);
     void* const xn = few ? h->xf_act : h->xf;
@@ -243,7 +243,7 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
     const SsqTiles tiles{h->ssq_parts, h->ssq, z.d / ADD_COLS};
     const SsqTiles* by_tile = nullptr;   // where the last x was written that way
     auto gemm = [&](int cls, const void* w, int N, int K, Out* o, const void* in_frags, const SsqTiles* sums) -> int {
-        const GemmPlan p = plan_gemm(M, N, K, h->cu_count, h->split_act);
+        const GemmPlan p = plan_gemm(M, N, K, h->cu_count, true);
         // the plan follows process-wide tuning knobs; the buffer was sized with those in force at init
         if (gemm_partial_elems(p, M) > h->partial_cap)
             return fail(SPEC_ERR_SHAPE, "this step's GEMM plan (%d K ranges) needs %zu partial sums, the handle holds %zu: "
@@ -317,8 +317,8 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
         if (swiglu_in_gemm) {
             // the gate/up GEMM applies the norm's row scale and SwiGLU itself and writes the down
             // projection's operand (into the fragment buffer that it is not reading)
-            RUN(SPEC_PROF_GEMM_GATE_UP, launch_gemm_swiglu(xn, planes, w.w_gate_up, M, z.F, z.d, h->ssq, n_ssq, z.d, c.rms_eps,
-                                                   act, mt, planes, h->cu_count, s, by_tile));
+            RUN(SPEC_PROF_GEMM_GATE_UP, launch_gemm_swiglu(xn, w.w_gate_up, M, z.F, z.d, h->ssq, n_ssq, z.d, c.rms_eps,
+                                                   act, mt, h->cu_count, s, by_tile));
         } else {
             rc = gemm(SPEC_PROF_GEMM_GATE_UP, w.w_gate_up, 2 * z.F, z.d, &o, xn, by_tile);
             if (rc) return rc;

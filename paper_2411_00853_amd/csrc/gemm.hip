@@ -443,11 +443,12 @@ __global__ void __launch_bounds__(64 * CG * RS) gemm_skinny_kernel(const u32x4* 
 // 302 -> 291, decoding round 2217 -> 2184.
 // The row's whole sum of squares spans all workgroups: it leaves as one fp64 sum per row and workgroup, and the next
 // product adds those up (ssq_group_sums).
-template <int RANGES, int PLANES>
+template <int RANGES>
 __global__ void __launch_bounds__(64 * RANGES) gemm_add_kernel(const u32x4* __restrict__ Xf, const u32x4* __restrict__ Wp, float* __restrict__ x,
                                                                const float* __restrict__ gain, int M, int n_tiles, int kb_total,
                                                                int kb_per_range, uint16_t* __restrict__ frags, double* __restrict__ parts)
 {
+    constexpr int PLANES = 2;
     constexpr int DEPTH = RANGES > 8 ? 1 : 3;   // register buffers (128 registers a wavefront with sixteen of them, 256 with eight)
     static_assert(RANGES >= 4, "a thread for every element");
     __shared__ float red[RANGES][16 * ADD_COLS];
@@ -508,7 +509,6 @@ __global__ void __launch_bounds__(64 * RANGES) gemm_add_kernel(const u32x4* __re
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
-    using I3 = std::integral_constant<int, 3>;
     using ID = std::integral_constant<int, DEPTH>;
     if (n >= DEPTH) {
         start(ID{});
@@ -521,9 +521,8 @@ __global__ void __launch_bounds__(64 * RANGES) gemm_add_kernel(const u32x4* __re
             }
         switch (n - i - DEPTH) {
         case 0: finish(i, ID{}, I0{}); break;
-        case 1: finish(i, ID{}, I1{}); break;
-        case 2: if constexpr (DEPTH > 2) finish(i, ID{}, I2{}); break;
-        default: if constexpr (DEPTH > 3) finish(i, ID{}, I3{}); break;
+        case 1: if constexpr (DEPTH > 1) finish(i, ID{}, I1{}); break;
+        default: if constexpr (DEPTH > 2) finish(i, ID{}, I2{}); break;
         }
     } else if (n == 1) {
         start(I1{});
@@ -531,9 +530,6 @@ __global__ void __launch_bounds__(64 * RANGES) gemm_add_kernel(const u32x4* __re
     } else if (DEPTH > 2 && n == 2) {
         start(I2{});
         finish(0, I2{}, I0{});
-    } else if (DEPTH > 3 && n == 3) {
-        start(I3{});
-        finish(0, I3{}, I0{});
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) red[wave][(4 * g + r) * ADD_COLS + c] = acc[r];
@@ -551,7 +547,7 @@ __global__ void __launch_bounds__(64 * RANGES) gemm_add_kernel(const u32x4* __re
         const float o = v * gn;
         const __bf16 head = static_cast<__bf16>(o);
         *f = __builtin_bit_cast(uint16_t, head);
-        if constexpr (PLANES == 2) f[64 * 8] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(o - static_cast<float>(head)));
+        f[64 * 8] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(o - static_cast<float>(head)));
     }
     double ss = (double)v * v;
 #pragma unroll
@@ -1027,7 +1023,8 @@ int launch_variant(const GemmPlan& p, const void* xf, const void* w, int M, int 
     if constexpr (MT <= 4 && NT == 2) {
         if (p.cg == 2) return launch_groups<MT, NT, KC, RS, 2>(p, xf, w, M, K, n_tiles, partial, s, job, n_ssq);
     }
-    return launch_groups<MT, NT, KC, RS, 4>(p, xf, w, M, K, n_tiles, partial, s, job, n_ssq);
+    if constexpr (MT == 8 && NT == 4) return fail(SPEC_ERR_SHAPE, "eight row tiles by four column tiles in four groups: gemm_ring_kernel's");
+    else return launch_groups<MT, NT, KC, RS, 4>(p, xf, w, M, K, n_tiles, partial, s, job, n_ssq);
 }
 
 template <int MT, int NT, bool STREAM>
@@ -1036,7 +1033,7 @@ int launch_ring(const GemmPlan& p, const void* xf, const void* w, int M, int K, 
     const int row_blocks = gemm_row_blocks(p), n_blocks = (n_tiles + RING_GROUPS * NT - 1) / (RING_GROUPS * NT);
     int grid = n_blocks * p.n_split;
     if (p.n_split < 8) grid = (n_blocks + (8 / p.n_split) - 1) / (8 / p.n_split) * 8;   // (a multiple of eight either way)
-    auto* k = swiglu ? p.planes == 2 ? gemm_ring_kernel<MT, NT, 2, false, true> : gemm_ring_kernel<MT, NT, 1, false, true>
+    auto* k = swiglu ? gemm_ring_kernel<MT, NT, 2, false, true>
                      : p.planes == 2 ? gemm_ring_kernel<MT, NT, 2, STREAM, false> : gemm_ring_kernel<MT, NT, 1, STREAM, false>;
     hipLaunchKernelGGL(k, dim3(grid * row_blocks), dim3(512), 0, s, (const char*)xf, (const char*)w, partial, M, p.mt, n_tiles, K / 32,
                        p.kb_per_split, p.n_split, row_blocks, n_blocks, swiglu ? *swiglu : SwigluOut{});
@@ -1299,7 +1296,7 @@ int launch_gemm_bf16(const GemmPlan& p, const void* x_frags, const void* w_packe
 // (K: see the kernel; widths of 512 to 4096 measured, none slower)
 bool gemm_add_fits(const GemmPlan& p, int K)
 {
-    return K <= 6144 && p.mt == 1 && p.n_pad % 32 == 0 && (p.n_split == 4 || p.n_split == 8 || p.n_split == 16);
+    return K <= 6144 && p.mt == 1 && p.planes == 2 && p.n_pad % 32 == 0 && (p.n_split == 4 || p.n_split == 8 || p.n_split == 16);
 }
 
 int launch_gemm_add(const GemmPlan& p, const void* x_frags, const void* w_packed, int M, int d, int K, float* x, const float* gain,
@@ -1309,9 +1306,8 @@ int launch_gemm_add(const GemmPlan& p, const void* x_frags, const void* w_packed
         return fail(SPEC_ERR_SHAPE, "no residual GEMM for %d rows of %d x %d", M, d, K);
 #define SPECV_ADD(R_)                                                                                                          \
     if (p.n_split == R_) {                                                                                                     \
-        auto* k = p.planes == 2 ? gemm_add_kernel<R_, 2> : gemm_add_kernel<R_, 1>;                                             \
-        hipLaunchKernelGGL(k, dim3(d / ADD_COLS), dim3(64 * R_), 0, s, (const u32x4*)x_frags, (const u32x4*)w_packed, x, gain, M, \
-                           d / 16, K / 32, p.kb_per_split, (uint16_t*)out_frags, parts);                                       \
+        hipLaunchKernelGGL(gemm_add_kernel<R_>, dim3(d / ADD_COLS), dim3(64 * R_), 0, s, (const u32x4*)x_frags, (const u32x4*)w_packed, \
+                           x, gain, M, d / 16, K / 32, p.kb_per_split, (uint16_t*)out_frags, parts);                           \
     }
     SPECV_ADD(4)
     SPECV_ADD(8)
@@ -1343,18 +1339,14 @@ bool gemm_swiglu_fits(int M, int F, int cu_count)
 bool gemm_ring_swiglu_fits(const GemmPlan& p) { return p.ring && p.mt >= 14 && p.n_split == 1; }
 
 template <int MT, int KC, int CG>
-static int launch_swiglu_cg(int planes, const void* xf, const void* w, int M, int K, int n_tiles, const SwigluOut& so,
+static int launch_swiglu_cg(const void* xf, const void* w, int M, int K, int n_tiles, const SwigluOut& so,
                             hipStream_t s)
 {
     const int n_blocks = (n_tiles + 2 * CG - 1) / (2 * CG);
     const int grid = (n_blocks + 7) / 8 * 8;       // map_block deals workgroups to the 8 XCDs
     const int kb = K / 32;
-    if (planes == 2)
-        hipLaunchKernelGGL((gemm_skinny_kernel<MT, 2, KC, 2, 1, 1, CG>), dim3(grid), dim3(64 * CG), 0, s, (const u32x4*)xf,
-                           (const u32x4*)w, nullptr, M, n_tiles, kb, (kb + WPACK_KG - 1) / WPACK_KG * WPACK_KG, 1, n_blocks, so);
-    else
-        hipLaunchKernelGGL((gemm_skinny_kernel<MT, 2, KC, 1, 1, 1, CG>), dim3(grid), dim3(64 * CG), 0, s, (const u32x4*)xf,
-                           (const u32x4*)w, nullptr, M, n_tiles, kb, (kb + WPACK_KG - 1) / WPACK_KG * WPACK_KG, 1, n_blocks, so);
+    hipLaunchKernelGGL((gemm_skinny_kernel<MT, 2, KC, 2, 1, 1, CG>), dim3(grid), dim3(64 * CG), 0, s, (const u32x4*)xf,
+                       (const u32x4*)w, nullptr, M, n_tiles, kb, (kb + WPACK_KG - 1) / WPACK_KG * WPACK_KG, 1, n_blocks, so);
     SPECV_LAUNCH_CHECK("gemm_skinny_kernel (SwiGLU)");
     return SPEC_OK;
 }
@@ -1370,32 +1362,32 @@ static int swiglu_column_groups(int n_tiles, int cu_count)
 }
 
 template <int MT, int KC>
-static int launch_swiglu_variant(int planes, const void* xf, const void* w, int M, int K, int n_tiles, const SwigluOut& so,
+static int launch_swiglu_variant(const void* xf, const void* w, int M, int K, int n_tiles, const SwigluOut& so,
                                  int cu_count, hipStream_t s)
 {
     switch (g_swiglu_cg > 0 ? g_swiglu_cg : swiglu_column_groups(n_tiles, cu_count)) {
-    case 2: return launch_swiglu_cg<MT, KC, 2>(planes, xf, w, M, K, n_tiles, so, s);
-    case 3: return launch_swiglu_cg<MT, KC, 3>(planes, xf, w, M, K, n_tiles, so, s);
-    default: return launch_swiglu_cg<MT, KC, 4>(planes, xf, w, M, K, n_tiles, so, s);
+    case 2: return launch_swiglu_cg<MT, KC, 2>(xf, w, M, K, n_tiles, so, s);
+    case 3: return launch_swiglu_cg<MT, KC, 3>(xf, w, M, K, n_tiles, so, s);
+    default: return launch_swiglu_cg<MT, KC, 4>(xf, w, M, K, n_tiles, so, s);
     }
 }
 
-int launch_gemm_swiglu(const void* x_frags, int planes, const void* w_gate_up, int M, int F, int K, const double2* ssq,
-                       int n_ssq, int d, float eps, void* act_frags, int act_mt, int act_planes, int cu_count, hipStream_t s,
+int launch_gemm_swiglu(const void* x_frags, const void* w_gate_up, int M, int F, int K, const double2* ssq, int n_ssq, int d,
+                       float eps, void* act_frags, int act_mt, int cu_count, hipStream_t s,
                        const SsqTiles* tiles)
 {
     if (tiles && gemm_row_tiles(M) != 1) return fail(SPEC_ERR_SHAPE, "row sums by column tiles are for one row tile, got %d rows", M);
     if (K % 32 || F % 16) return fail(SPEC_ERR_SHAPE, "SwiGLU GEMM needs K %% 32 == 0 and F %% 16 == 0");
-    const SwigluOut so{ssq, n_ssq, d, eps, static_cast<uint4*>(act_frags), act_mt, act_planes, tiles ? *tiles : SsqTiles{}};
+    const SwigluOut so{ssq, n_ssq, d, eps, static_cast<uint4*>(act_frags), act_mt, 2, tiles ? *tiles : SsqTiles{}};
     const int n_tiles = 2 * F / 16;
     switch (gemm_row_tiles(M)) {
-    case 1: return launch_swiglu_variant<1, 4>(planes, x_frags, w_gate_up, M, K, n_tiles, so, cu_count, s);
-    case 2: return launch_swiglu_variant<2, 4>(planes, x_frags, w_gate_up, M, K, n_tiles, so, cu_count, s);
-    case 3: return launch_swiglu_variant<3, 4>(planes, x_frags, w_gate_up, M, K, n_tiles, so, cu_count, s);
-    case 4: return launch_swiglu_variant<4, 2>(planes, x_frags, w_gate_up, M, K, n_tiles, so, cu_count, s);
+    case 1: return launch_swiglu_variant<1, 4>(x_frags, w_gate_up, M, K, n_tiles, so, cu_count, s);
+    case 2: return launch_swiglu_variant<2, 4>(x_frags, w_gate_up, M, K, n_tiles, so, cu_count, s);
+    case 3: return launch_swiglu_variant<3, 4>(x_frags, w_gate_up, M, K, n_tiles, so, cu_count, s);
+    case 4: return launch_swiglu_variant<4, 2>(x_frags, w_gate_up, M, K, n_tiles, so, cu_count, s);
     default: break;
     }
-    const GemmPlan p = plan_gemm(M, 2 * F, K, cu_count, planes == 2);
+    const GemmPlan p = plan_gemm(M, 2 * F, K, cu_count, true);
     if (!gemm_ring_swiglu_fits(p)) return fail(SPEC_ERR_SHAPE, "no SwiGLU GEMM variant for %d rows", M);
     return launch_ring_plan(p, x_frags, w_gate_up, M, 2 * F, K, nullptr, s, &so);
 }

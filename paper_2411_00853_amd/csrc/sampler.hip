@@ -894,7 +894,6 @@ __global__ void __launch_bounds__(TPB) final_draw_kernel(const int32_t* accepted
 // ---------------------------------------------------------------------------------------------
 constexpr int DRAW_TPB = 1024, DRAW_WAVES = DRAW_TPB / 64, DRAW_MAX_RUNS = 8;
 constexpr int DRAW_MAX = DRAW_WAVES * 256 * DRAW_MAX_RUNS;   // 32768
-static_assert(STAT_CHUNK % (256 * DRAW_MAX_RUNS) == 0, "a wavefront's ids lie in one statistics chunk");
 static_assert(DRAW_WAVES == 16, "the wavefronts' sums are scanned by 16 lanes");
 constexpr int STATS_MAX = 2048;                              // a row in a wavefront's registers
 inline int draw_runs(int V) { return V <= 4096 ? 1 : V <= 8192 ? 2 : V <= 16384 ? 4 : 8; }
