@@ -1,5 +1,6 @@
 """The many-row projections: both row blocks of every size, ragged rows and columns, K ranges of one to many stages (fewer than
-the ring has slots, odd numbers, a last range that is short or empty), and the LM head's launch at eight row tiles."""
+the ring has slots, odd numbers, a last range that is short or empty), and the LM head's launch at eight row tiles (one row block)
+beside the shapes that the plan does not send there."""
 import pytest
 import torch
 
@@ -19,10 +20,32 @@ def test_many_rows_head_plane_only(M):
     _check(M, 720, 736, False)
 
 
+def _ring_at(M, N, K):
+    """Whether the plan runs an LM head of N rows by K columns as gemm_ring_kernel"""
+    from paper_2411_00853_amd import binding as sv
+    look = [15] * (M // 16) + [M % 16 - 1] * (M % 16 > 0)
+    return sv.spec_k_plan_step(sv.make_cfg(wl.ModelShape(1, K, 2, 2, 64, 64, N), len(look), 64, 15), look, 256).gemm_ring >> 4 & 1
+
+
 @pytest.mark.parametrize("N,K", [(16000, 64), (16008, 416), (32003, 1024)])
 @pytest.mark.parametrize("M", [97, 113, 128])
 def test_wide_matrices_at_eight_row_tiles(M, N, K):
+    assert not _ring_at(M, N, K)
     _check(M, N, K, True)
+
+
+# two K ranges and one, stages from fewer than the ring has slots on, an odd number, last column blocks of one and of all tiles
+@pytest.mark.parametrize("N,K", [(32000, 2048), (32003, 4096), (31989, 2080), (50257, 1024), (50257, 96), (128256, 32)])
+@pytest.mark.parametrize("M", [97, 112, 113, 128])
+def test_one_row_block(M, N, K):
+    assert _ring_at(M, N, K)
+    _check(M, N, K, True)
+
+
+@pytest.mark.parametrize("M", [100, 128])
+def test_one_row_block_head_plane_only(M):
+    assert _ring_at(M, 50257, 736)
+    _check(M, 50257, 736, False)
 
 
 def _check(M, N, K, split):
