@@ -9,9 +9,10 @@ from paper_2411_00853_amd import workload as wl
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d,F", [(64, 32), (96, 480), (416, 11008), (1056, 8192)])
+# (two, three and four column tiles per wavefront; of four the last column block whole and partial)
+@pytest.mark.parametrize("d,F,tiles", [(64, 32, 2), (96, 480, 2), (416, 11008, 3), (1056, 8192, 2), (3136, 12544, 4), (512, 12512, 4)])
 @pytest.mark.parametrize("rows", [200, 225, 256, 260, 312, 320, 330, 352])
-def test_swiglu_by_way_of_lds(d, F, rows):
+def test_swiglu_by_way_of_lds(d, F, tiles, rows):
     from paper_2411_00853_amd import binding as sv
     from test_gpu_forward import Rig
     V = 131
@@ -22,7 +23,8 @@ def test_swiglu_by_way_of_lds(d, F, rows):
     w["layers"][0]["w_o"].zero_()
     w["layers"][0]["ffn_norm"] = 1 + wl.Rng(5, "cpu").normal(2, (d,), 0.2)
     rig = Rig(shape, B, 64, k, w_cpu=w)
-    assert sv.spec_k_plan_step(rig.cfg, [k] * B).gemm_k_ranges[2] == 1
+    plan = sv.spec_k_plan_step(rig.cfg, [k] * B)
+    assert plan.gate_up_swiglu_inside == 1 and plan.gemm_k_ranges[2] == 1 and plan.gemm_col_tiles[2] == tiles
     rng = wl.Rng(7, "cpu")
     t0, toks = rng.randint(3, (B,), V), rng.randint(4, (B, k), V)
     got, _, _ = rig.step(list(range(B)), t0.tolist(), [k] * B, toks, torch.zeros((B, k, V)), torch.zeros((B, k + 1)), 1.0)
