@@ -134,8 +134,10 @@ typedef struct {
     uint64_t gemm_partial_capacity;   /* what spec_verify_init would allocate for them */
     int32_t gate_up_swiglu_inside;    /* 1: the gate/up projection finishes SwiGLU itself (one K range) */
     /* bit i: projection i fetches both operands straight into LDS, eight wavefronts as four column groups by two row
-     * halves; from 14 row tiles on as two row blocks per column block, which gemm_workgroups counts */
-    int32_t gemm_ring;
+     * halves; from 14 row tiles on as two row blocks per column block, which gemm_workgroups counts.
+     * bit 8 + i: projection i (output, down) adds its product to the residual stream itself, a workgroup for every 16
+     * columns whose wavefronts take the K ranges (not what gemm_col_tiles, gemm_col_groups and gemm_workgroups say) */
+    int32_t gemm_kernels;
     /* operand-fragment buffers, in 16-byte units: what the first pass writes and what init allocates;
      * the second pair holds the normalised residual up to 16 rows, beyond that the down projection's operand when
      * SwiGLU is finished inside the GEMM */

@@ -91,7 +91,7 @@ class spec_step_plan(C.Structure):
                                                             "gemm_k_blocks_per_range", "gemm_row_parts",
                                                             "gemm_col_groups", "gemm_workgroups")] + \
                [("gemm_partial_floats", C.c_uint64 * PLAN_PROJECTIONS), ("gemm_partial_capacity", C.c_uint64),
-                ("gate_up_swiglu_inside", C.c_int32), ("gemm_ring", C.c_int32), ("xfrag_units", C.c_uint64),
+                ("gate_up_swiglu_inside", C.c_int32), ("gemm_kernels", C.c_int32), ("xfrag_units", C.c_uint64),
                 ("xfrag_capacity", C.c_uint64), ("xfrag_act_units", C.c_uint64), ("xfrag_act_capacity", C.c_uint64)] + \
                [(n, C.c_int32) for n in ("attn_kv_share", "attn_small", "attn_chunks", "attn_chunk_keys",
                                          "attn_row_tiles", "attn_wavefronts", "attn_fused")] + \

@@ -276,9 +276,10 @@ inline int gemm_row_blocks(const GemmPlan& p) { return p.ring ? (p.mt + p.ring -
 // job != NULL (one row tile): the launch also adds up job's sums of squares into job->ssq_out ([M][n_ssq])
 int launch_gemm_bf16(const GemmPlan& p, const void* x_frags, const void* w_packed, int M, int N, int K,
                      float* partial, hipStream_t s, const SsqTiles* job = nullptr, int n_ssq = 0);
-// Up to 16 rows and K 6144: x += X * W^T, the new x times gain as fragments (one row tile), its sums of squares by ADD_COLS columns into
+// Up to 16 rows: x += X * W^T, the new x times gain as fragments (one row tile), its sums of squares by ADD_COLS columns into
 // parts [M][d / ADD_COLS].  out_frags is not the buffer of x_frags.
-bool gemm_add_fits(const GemmPlan& p, int K);
+// sums_again: the next product finishes SwiGLU, i.e. every workgroup of it adds the tiles' sums up.
+bool gemm_add_fits(const GemmPlan& p, int M, int K, int cu_count, bool sums_again);
 int launch_gemm_add(const GemmPlan& p, const void* x_frags, const void* w_packed, int M, int d, int K, float* x, const float* gain,
                     void* out_frags, double* parts, hipStream_t s);
 int launch_pack_x(const float* x, const float* gain, int M, int K, int mt_count, int planes, void* x_frags,

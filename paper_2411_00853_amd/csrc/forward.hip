@@ -232,12 +232,14 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
     const int planes = 2;   // activations go to the matrix cores as bf16 head + remainder
     const XOut to_xf{bf16 ? h->xf : nullptr, mt, planes, nullptr};            // operand of the next GEMM
     const NormScale scaled{h->ssq, n_ssq, z.d, c.rms_eps};
-    // Up to 16 rows the output and down projections finish the residual stream themselves (launch_gemm_add): the normalised
+    // Up to 16 rows the output and down projections may finish the residual stream themselves (launch_gemm_add): the normalised
     // residual stays in the second fragment buffer, the attention's and SwiGLU's results in the first, and the sums of
     // squares of x come by column tile.
     const GemmPlan plan_o = plan_gemm(M, z.d, z.dq, h->cu_count, true), plan_down = plan_gemm(M, z.d, z.F, h->cu_count, true);
     const bool few = bf16 && mt == 1;
-    const bool add_o = few && gemm_add_fits(plan_o, z.dq), add_down = few && gemm_add_fits(plan_down, z.F);
+    const bool swiglu_in_gemm = bf16 && swiglu_inside(c, M, h->cu_count);
+    const bool add_o = few && gemm_add_fits(plan_o, M, z.dq, h->cu_count, swiglu_in_gemm);
+    const bool add_down = few && gemm_add_fits(plan_down, M, z.F, h->cu_count, false);
     void* const xn = few ? h->xf_act : h->xf;
     const XOut to_xn{bf16 ? xn : nullptr, mt, planes, nullptr};
     const SsqTiles tiles{h->ssq_parts, h->ssq, z.d / ADD_COLS};
@@ -292,7 +294,6 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
         return mul(SPEC_PROF_GEMM_LM_HEAD, h->x, h->lm_head, z.V, z.d, logits_out, F32_STORE, h->final_norm);
     }
     Out o;
-    const bool swiglu_in_gemm = swiglu_inside(c, M, h->cu_count);
     const bool fuse = h->fuse_rope && attention_takes_qkv(h->geom, c.n_q_heads, ks, B, c.max_kv_len, h->cu_count);
     for (int l = 0; l < c.n_layers; ++l) {
         const spec_layer_weights& w = h->layers[l];

@@ -1293,16 +1293,32 @@ int launch_gemm_bf16(const GemmPlan& p, const void* x_frags, const void* w_packe
     return fail(SPEC_ERR_SHAPE, "no GEMM variant for %d rows (%d row tiles, %d column tiles per wave)", M, p.mt, p.nt);
 }
 
-// (K: see the kernel; widths of 512 to 4096 measured, none slower)
-bool gemm_add_fits(const GemmPlan& p, int K)
+// Where the residual product is the faster route, from steps of six and eight layers with and without it: widths 512 to 8192, K
+// 1024 to 6144, 1 to 16 rows.  What tells against it:
+//  * The reads of X, which every workgroup makes, grow with K.  Up to eight rows they take one 128-byte line per 8 columns of K and
+//    plane, from nine on two.
+//  * More than four ranges means a narrow matrix: few workgroups (a column tile each), each with a long stream to read.
+//  * In front of the product that finishes SwiGLU (sums_again) the row sums are added up by every workgroup of it.
+//  * More workgroups than compute units: steps of 5120 wide models 0.6 to 3.1 % slower, of 6144 by 6144 2.5 to 9 %.
+// Gain of the step at the longest K taken, and at the next one measured (in brackets):
+//                 up to 8 rows                                          9 to 16 rows
+//   4 ranges      6144 +4..+5.5 % (not measured beyond)                 6144 0..+0.6
+//   8             6144 +0.2..+0.9                                       3072 +1.2..+2.2 (4096 -0.3..-1.1, 5504 -1.8)
+//   16            6144 -0.3..+0.5                                       4096 -0.1..+1.6 (6144 -5)
+//   sums_again, 4 6144 +1..+2.2                                         3072 +0.3..+0.9 (4096 -0.4..-0.8)
+//   8 and 16      4096 +0.6..+1.8 (5120 -0.9..-1.3, 6144 -0.8..-2.7)    2048 +0.6..+1.5 (3072 -0.7..+0.5)
+bool gemm_add_fits(const GemmPlan& p, int M, int K, int cu_count, bool sums_again)
 {
-    return K <= 6144 && p.mt == 1 && p.planes == 2 && p.n_pad % 32 == 0 && (p.n_split == 4 || p.n_split == 8 || p.n_split == 16);
+    if (p.mt != 1 || p.planes != 2 || p.n_pad % 32 || p.n_pad / ADD_COLS > cu_count) return false;
+    if (p.n_split != 4 && p.n_split != 8 && p.n_split != 16) return false;
+    if (sums_again) return K <= (p.n_split == 4 ? 6144 : 4096) / (M <= 8 ? 1 : 2);
+    return K <= (M <= 8 || p.n_split == 4 ? 6144 : p.n_split == 8 ? 3072 : 4096);
 }
 
 int launch_gemm_add(const GemmPlan& p, const void* x_frags, const void* w_packed, int M, int d, int K, float* x, const float* gain,
                     void* out_frags, double* parts, hipStream_t s)
 {
-    if (!gemm_add_fits(p, K) || M < 1 || M > 16 || d != p.n_pad || K % 32 || K < 32)
+    if (!gemm_add_fits(p, M, K, d / ADD_COLS, false) || M < 1 || M > 16 || d != p.n_pad || K % 32 || K < 32)
         return fail(SPEC_ERR_SHAPE, "no residual GEMM for %d rows of %d x %d", M, d, K);
 #define SPECV_ADD(R_)                                                                                                          \
     if (p.n_split == R_) {                                                                                                     \

@@ -578,6 +578,7 @@ extern "C" int spec_k_plan_step(const spec_model_cfg* cfg, int32_t batch, const 
     const int max_rows = std::min(cfg->max_batch * (cfg->max_lookahead + 1), GEMM_MAX_ROWS);
     int n_out[SPEC_PLAN_PROJECTIONS], n_in[SPEC_PLAN_PROJECTIONS];
     projection_shapes(*cfg, n_out, n_in);
+    out->gate_up_swiglu_inside = swiglu_inside(*cfg, rows[0], cu_count) ? 1 : 0;
     for (int i = 0; i < SPEC_PLAN_PROJECTIONS; ++i) {
         const GemmPlan p = plan_gemm(rows[0], n_out[i], n_in[i], cu_count, true);
         out->gemm_row_tiles[i] = p.mt;
@@ -588,12 +589,12 @@ extern "C" int spec_k_plan_step(const spec_model_cfg* cfg, int32_t batch, const 
         out->gemm_col_groups[i] = p.cg;
         const int n_tiles = p.n_pad / 16;
         out->gemm_workgroups[i] = (n_tiles + p.cg * p.nt - 1) / (p.cg * p.nt) * gemm_row_blocks(p) * p.n_split;
-        if (p.ring) out->gemm_ring |= 1 << i;
+        if (p.ring) out->gemm_kernels |= 1 << i;
+        if ((i == 1 || i == 3) && gemm_add_fits(p, rows[0], n_in[i], cu_count, i == 1 && out->gate_up_swiglu_inside)) out->gemm_kernels |= 256 << i;
         out->gemm_partial_floats[i] = gemm_partial_elems(p, rows[0]);
     }
     out->gemm_partial_capacity = gemm_partial_capacity(*cfg, max_rows, cu_count);
     const int widest = std::max(std::max(cfg->d_model, cfg->n_q_heads * cfg->head_dim), cfg->d_ffn);
-    out->gate_up_swiglu_inside = swiglu_inside(*cfg, rows[0], cu_count) ? 1 : 0;
     out->xfrag_units = xfrag_uint4s(gemm_row_tiles(rows[0]), 2, widest);
     out->xfrag_capacity = xfrag_uint4s(gemm_row_tiles(max_rows), 2, widest);
     out->xfrag_act_units = act_frag_units(*cfg, rows[0], cu_count);

@@ -28,24 +28,28 @@ def test_steps_of_few_rows(d, heads, hd, F, look):
     assert (got - want).abs().max().item() <= 5e-3     # the bound of the other small bf16 models (test_gpu_row_scale)
 
 
-# 16 rows take the launches of few rows, 17 product and residual kernel: the rows they share come out alike bit for bit
-@pytest.mark.parametrize("d,heads,hd,F,ranges", [(4096, 16, 128, 2048, 4), (2048, 17, 128, 6144, 8), (1024, 16, 64, 5632, 16),
-                                                 (2080, 32, 64, 2144, 8), (1056, 8, 64, 4128, 8), (160, 2, 64, 2048, 8), (512, 4, 64, 5664, 16)])
-def test_few_rows_keep_the_bits_of_the_two_launches(d, heads, hd, F, ranges):
+# Steps of up to 16 rows against one of 17, which takes product and residual kernel: the rows they share come out alike bit for
+# bit.  `inside`: which of output and down projection (bits 1 and 3) add to the residual stream themselves.
+@pytest.mark.parametrize("looks", [([7, 7], [7, 8]), ([3, 3], [3, 12])])
+@pytest.mark.parametrize("d,heads,hd,F,ranges,inside", [
+    (4096, 16, 128, 2048, (4, 4), (0b1010, 0b1010)), (2720, 34, 64, 4128, (4, 4), (0b1010, 0b1010)), (2048, 17, 128, 4096, (4, 8), (0b0010, 0b1010)),
+    (1024, 16, 64, 2048, (4, 8), (0b1010, 0b1010)), (2080, 32, 64, 2144, (8, 4), (0b1010, 0b1010)), (1056, 8, 64, 4064, (2, 16), (0b1000, 0b1000)),
+    (512, 32, 64, 1568, (8, 4), (0b1010, 0b1010)), (1024, 16, 64, 5632, (4, 16), (0b0010, 0b1010))])
+def test_few_rows_keep_the_bits_of_the_two_launches(d, heads, hd, F, ranges, inside, looks):
     from paper_2411_00853_amd import binding as sv
     from test_gpu_forward import Rig
-    V, looks = 131, ([7, 7], [7, 8])
+    V, n = 131, sum(looks[0]) + 2
     shape = wl.ModelShape(2, d, heads, heads, hd, F, V, dtype="bf16")
-    rig = Rig(shape, 2, 64, 8, seed=d + F, std=0.5 / d ** 0.5)
+    rig = Rig(shape, 2, 64, 12, seed=d + F, std=0.5 / d ** 0.5)
     few, more = (sv.spec_k_plan_step(rig.cfg, look) for look in looks)
-    assert list(few.gemm_row_tiles) == [1] * 5 and list(more.gemm_row_tiles) == [2] * 5
-    assert list(few.gemm_k_ranges) == list(more.gemm_k_ranges) and ranges in (few.gemm_k_ranges[1], few.gemm_k_ranges[3])
+    assert list(few.gemm_k_ranges) == list(more.gemm_k_ranges) and (few.gemm_k_ranges[1], few.gemm_k_ranges[3]) == ranges
+    assert few.gemm_kernels >> 8 == inside[n == 8] and more.gemm_kernels == 0
     rng = wl.Rng(F, "cpu")
-    t0, toks = rng.randint(1, (2,), V).tolist(), rng.randint(2, (2, 8), V)
+    t0, toks = rng.randint(1, (2,), V).tolist(), rng.randint(2, (2, 12), V)
     got = []
     for look in looks:
         for s in range(2):
             rig.caches[s][:, :, :, :20 + 11 * s] = wl.Rng(5, "cpu").normal(20 + s, (2, 2, heads, 20 + 11 * s, hd), 0.5)
             rig.set_cache(s, 20 + 11 * s)
-        got.append(rig.step([0, 1], t0, look, toks, rng.normal(3, (2, 8, V), 1.0), rng.uniform(4, (2, 9)), 1.0)[0])
-    assert torch.equal(got[0], got[1][:16])
+        got.append(rig.step([0, 1], t0, look, toks, rng.normal(3, (2, 12, V), 1.0), rng.uniform(4, (2, 13)), 1.0)[0])
+    assert torch.equal(got[0], got[1][:n])

@@ -24,7 +24,7 @@ def _ring_at(M, N, K):
     """Whether the plan runs an LM head of N rows by K columns as gemm_ring_kernel"""
     from paper_2411_00853_amd import binding as sv
     look = [15] * (M // 16) + [M % 16 - 1] * (M % 16 > 0)
-    return sv.spec_k_plan_step(sv.make_cfg(wl.ModelShape(1, K, 2, 2, 64, 64, N), len(look), 64, 15), look, 256).gemm_ring >> 4 & 1
+    return sv.spec_k_plan_step(sv.make_cfg(wl.ModelShape(1, K, 2, 2, 64, 64, N), len(look), 64, 15), look, 256).gemm_kernels >> 4 & 1
 
 
 @pytest.mark.parametrize("N,K", [(16000, 64), (16008, 416), (32003, 1024)])

@@ -15,7 +15,7 @@ def _plan(shape, look, max_batch=None, max_kv_len=2048, kmax=None, cu=256, paged
     return cfg, sv.spec_k_plan_step(cfg, look, cu, paged)
 
 
-def _check_invariants(shape, cfg, look, p, paged):
+def _check_invariants(shape, cfg, look, p, paged, cu):
     B, rows = len(look), sum(k + 1 for k in look)
     # passes: consecutive sequences, all rows, none beyond what one launch of the projections takes
     assert p.rows == rows and 1 <= p.n_passes <= sv.PLAN_MAX_PASSES
@@ -50,9 +50,19 @@ def _check_invariants(shape, cfg, look, p, paged):
         assert p.gemm_partial_floats[i] == s * p.pass_rows[0] * n_pad <= p.gemm_partial_capacity
         tiles_per_wg = nt * p.gemm_col_groups[i]
         # from 14 row tiles on two row blocks of eight, ten or twelve tiles; at eight row tiles one, for wide matrices
-        ring = p.gemm_ring >> i & 1
+        ring = p.gemm_kernels >> i & 1
         assert ring == (mt >= 14 or (mt == 8 and nt == 4 and p.gemm_col_groups[i] == 4))
         assert p.gemm_workgroups[i] == -(-(n_pad // 16) // tiles_per_wg) * s * (2 if mt >= 14 else 1)
+    # the residual inside output and down projection: few rows, a K that suits their number and the ranges, a round of workgroups
+    few = p.pass_rows[0] <= 8
+    for i in range(sv.PLAN_PROJECTIONS):
+        s = p.gemm_k_ranges[i]
+        if i == 1 and p.gate_up_swiglu_inside:
+            longest = {4: 6144 if few else 3072, 8: 4096 if few else 2048, 16: 4096 if few else 2048}
+        else:
+            longest = {4: 6144, 8: 6144 if few else 3072, 16: 6144 if few else 4096}
+        assert (p.gemm_kernels >> 8 + i & 1) == (i in (1, 3) and p.pass_rows[0] <= 16 and n_in[i] <= longest.get(s, 0)
+                                                 and shape.d_model <= 16 * cu)
     # operand fragments fit their buffers; SwiGLU inside the GEMM up to four row tiles, and from 14 on with one K range
     mt = p.gemm_row_tiles[2]
     units = lambda k: (k // 32 + 4) * 2 * mt * 64
@@ -106,7 +116,7 @@ def test_plans_respect_every_limit(seed):
         cu = r.choice([256, 256, 64, 304])
         cfg = sv.make_cfg(shape, max_batch, max_kv_len, kmax)
         p = sv.spec_k_plan_step(cfg, look, cu, paged)
-        _check_invariants(shape, cfg, look, p, paged)
+        _check_invariants(shape, cfg, look, p, paged, cu)
 
 
 def test_capacity_holds_for_every_batch_and_row_count():
@@ -137,6 +147,7 @@ def test_plans_of_the_named_configurations():
     w = wl.workload_1b()
     cfg, p = _plan(w.shape, list(w.lookahead), w.batch, w.max_kv_len, w.max_lookahead)
     assert p.rows == 6 and list(p.gemm_row_tiles) == [1] * 5
+    assert p.gemm_kernels == 1 << 8 + 1     # the output projection adds to the residual stream; the down projection's K is 8192
     # a small launch: every query head a work item of its own, four chunks merged in the workgroup
     assert (p.attn_kv_share, p.attn_small, p.attn_chunks, p.attn_wavefronts, p.attn_fused) == (4, 1, 4, 4, 1)
     w = wl.workload_dyn()
@@ -149,16 +160,30 @@ def test_plans_of_the_named_configurations():
 def test_plan_of_the_many_row_step():
     # 7B shape, 352 rows: two row blocks of twelve row tiles; gate/up in one K range, with SwiGLU and the second buffer
     cfg, p = _plan(wl.SEVEN_B, [10] * 32, 32, 4107, 10)
-    assert p.rows == 352 and list(p.gemm_row_tiles) == [22] * 5 and p.gemm_ring == 0b11111
+    assert p.rows == 352 and list(p.gemm_row_tiles) == [22] * 5 and p.gemm_kernels == 0b11111
     assert list(p.gemm_workgroups) == [256, 256, 230, 256, 250] and list(p.gemm_k_ranges) == [2, 4, 1, 8, 1]
     assert p.gate_up_swiglu_inside == 1 and p.xfrag_act_units == (11008 // 32 + 4) * 2 * 22 * 64 <= p.xfrag_act_capacity
     # 128 rows: the LM head alone, as one row block
     cfg, p = _plan(wl.SEVEN_B, [15] * 8, 32, 4107, 15)
-    assert p.rows == 128 and p.gemm_ring == 0b10000 and p.gemm_workgroups[4] == 125 * p.gemm_k_ranges[4]
+    assert p.rows == 128 and p.gemm_kernels == 0b10000 and p.gemm_workgroups[4] == 125 * p.gemm_k_ranges[4]
     assert p.gate_up_swiglu_inside == 0 and p.xfrag_act_units == 0
     # one row: the normalised residual
     cfg, p = _plan(wl.ONE_B, [0], 1, 2048, 5)
-    assert p.gemm_ring == 0 and p.xfrag_act_units == (2048 // 32 + 4) * 2 * 64
+    assert p.gemm_kernels == 1 << 8 + 1 and p.xfrag_act_units == (2048 // 32 + 4) * 2 * 64
+
+
+@pytest.mark.parametrize("d,dq,F,rows,want", [
+    # gate/up and SwiGLU as two launches, then as one (F from 5472 on), narrow to wide
+    (512, 1024, 2048, 16, 0b1010), (1024, 4096, 4096, 16, 0b1010), (1024, 4608, 4608, 9, 0), (1024, 6144, 4608, 8, 0b1010),
+    (2048, 3072, 3072, 16, 0b1010), (2048, 4096, 4096, 9, 0), (2048, 5120, 4608, 8, 0b1010), (3072, 6144, 5120, 16, 0b1010),
+    (1024, 2048, 5504, 16, 0b0010), (1024, 3072, 5504, 9, 0), (1024, 4096, 6144, 8, 0b1010), (1024, 4608, 6176, 8, 0),
+    (2048, 2048, 5504, 8, 0b1010), (2048, 5120, 5504, 8, 0b1000), (3072, 3072, 8192, 16, 0b0010), (3072, 6144, 8192, 8, 0b0010),
+    (4096, 4096, 11008, 8, 0b0010), (4096, 4096, 11008, 9, 0), (5120, 5120, 13824, 1, 0), (8192, 2048, 4096, 1, 0)])
+def test_residual_inside_the_product_where_it_is_faster(d, dq, F, rows, want):
+    """Each line is a measured boundary: K by rows and ranges, widths by compute units."""
+    shape = wl.ModelShape(1, d, dq // 128, 4, 128, F, 1000)
+    look = [rows - 1] if rows < 16 else [15]
+    assert _plan(shape, look)[1].gemm_kernels >> 8 == want
 
 
 @pytest.mark.parametrize("rows", [6, 48, 128, 192, 208, 352])
