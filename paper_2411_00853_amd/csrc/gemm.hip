@@ -556,9 +556,10 @@ __global__ void __launch_bounds__(64 * RANGES) gemm_add_kernel(const u32x4* __re
 }
 
 // ---- many rows ---------------------------------------------------------------------------------------------
-// The product for more than 192 rows (and the widest matrices at 113..128): a tile of 128..192 rows x 128..256 columns per
-// workgroup, both operands fetched straight into LDS (global_load_lds: no registers on the way, so the accumulators of
-// that many tiles fit eight wavefronts, two on every SIMD) through a ring of stages of one K block.
+// The product for more than 192 rows (and, at 97..128 rows, of matrices wide enough for four column tiles per wavefront, e.g. the
+// LM head): a tile of 128..192 rows x 128..256 columns per workgroup, both operands fetched straight into LDS
+// (global_load_lds: no registers on the way, so the accumulators of that many tiles fit eight wavefronts, two on every
+// SIMD) through a ring of stages of one K block.
 //
 // What bounds it is the matrix instruction's rate together with the LDS reads that feed it: an X fragment read feeds NT
 // products, and the two overlap only as far as the other wavefront of the SIMD has something to do.  The kernel above
@@ -567,7 +568,9 @@ __global__ void __launch_bounds__(64 * RANGES) gemm_add_kernel(const u32x4* __re
 // take three or four, with W fetched twice.  7B shape, us per launch (QKV, gate/up, output, down, LM head), before and now:
 //   256 rows  59.9 109.5 23.1 46.9 122.6    50.3  90.7 22.4 43.6 109.4
 //   320       73.5 136.3 27.9 57.3 151.2    60.6 109.1 27.9 55.4 142.2
-//   352       84.8 157.6 31.2 65.8 173.7    67.9 121.9 30.0 58.6 151.9   (0.95 PFLOP/s of issued products at QKV)
+//   352       84.8 157.6 31.2 65.8 173.7    67.9 121.9 30.0 58.6 151.9   (1.04 PFLOP/s of issued products at QKV, 1.14 with the
+//             padded row tiles: 24 are multiplied for 22)
+// (launches repeated; means of a trace of nine single steps of 352 rows, QKV and gate/up: 91.4 170.3 before, 74.2 137.6 now)
 // Tried: four wavefronts with 32x32x16 products (one per SIMD: fetching, LDS reads and products add up instead of overlapping,
 // 85 and 158 us at 352 rows); fetching on two wavefronts of their own; from 65 to 192 rows, where W from memory is half of the
 // time, this kernel and the one above are within 5 % of each other either way, except for the LM head at eight row tiles
