@@ -90,15 +90,17 @@ enum {
     SPEC_PROF_GEMM = 0,          /* projection GEMMs (QKV, O, gate/up, down, LM head) */
     SPEC_PROF_ATTENTION = 1,     /* windowed-causal attention, position-chunk pass */
     SPEC_PROF_ATTN_MERGE = 2,    /* merge of the chunk results */
-    SPEC_PROF_GLUE = 3,          /* embedding, norms, rotary + KV append, SiLU gating, partial sums */
-    SPEC_PROF_SAMPLER_STATS = 4, /* softmax statistics over all target and draft rows */
-    SPEC_PROF_SAMPLER_DRAW = 5,  /* accept scan, residual mass, final draw, KV length update */
+    SPEC_PROF_GLUE = 3,          /* embedding, norms, rotary + KV append, SiLU gating, partial sums (the LM head's: greedy
+                                  * steps and steps of several passes only) */
+    SPEC_PROF_SAMPLER_STATS = 4, /* softmax statistics over all target and draft rows, with the LM head's partial sums */
+    SPEC_PROF_SAMPLER_DRAW = 5,  /* accept scan, residual mass, final draw, KV length update; a plain draw's
+                                  * partial sums and statistics, and those of rows of up to 2048 logits, where they share its launch */
     SPEC_PROF_PREPARE = 6,       /* row bookkeeping */
     /* the projection GEMMs one by one (each is also counted in SPEC_PROF_GEMM) */
     SPEC_PROF_GEMM_QKV = 7,
-    SPEC_PROF_GEMM_O = 8,
+    SPEC_PROF_GEMM_O = 8,        /* with the residual addition where the GEMM does it itself (some steps of up to 16 rows) */
     SPEC_PROF_GEMM_GATE_UP = 9,  /* with SwiGLU where the GEMM finishes it itself */
-    SPEC_PROF_GEMM_DOWN = 10,
+    SPEC_PROF_GEMM_DOWN = 10,    /* with the residual addition likewise */
     SPEC_PROF_GEMM_LM_HEAD = 11,
     SPEC_PROF_COUNT = 12
 };
