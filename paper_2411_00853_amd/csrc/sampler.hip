@@ -944,7 +944,6 @@ __device__ __forceinline__ void draw_store(float* row, int V, int id0, const flo
 
 struct DrawLds {
     double tot[DRAW_WAVES];
-    int last[DRAW_WAVES];
     int tok;
 };
 
