@@ -557,7 +557,7 @@ __global__ void __launch_bounds__(64 * RANGES) gemm_add_kernel(const u32x4* __re
 
 // ---- many rows ---------------------------------------------------------------------------------------------
 // The product for more than 192 rows (and, at 97..128 rows, of matrices wide enough for four column tiles per wavefront, e.g. the
-// LM head): a tile of 128..192 rows x 128..256 columns per workgroup, both operands fetched straight into LDS
+// LM head): a tile of 112..176 rows x 128..256 columns per workgroup, both operands fetched straight into LDS
 // (global_load_lds: no registers on the way, so the accumulators of that many tiles fit eight wavefronts, two on every
 // SIMD) through a ring of stages of one K block.
 //
@@ -568,9 +568,14 @@ __global__ void __launch_bounds__(64 * RANGES) gemm_add_kernel(const u32x4* __re
 // take three or four, with W fetched twice.  7B shape, us per launch (QKV, gate/up, output, down, LM head), before and now:
 //   256 rows  59.9 109.5 23.1 46.9 122.6    50.3  90.7 22.4 43.6 109.4
 //   320       73.5 136.3 27.9 57.3 151.2    60.6 109.1 27.9 55.4 142.2
-//   352       84.8 157.6 31.2 65.8 173.7    67.9 121.9 30.0 58.6 151.9   (1.04 PFLOP/s of issued products at QKV, 1.14 with the
-//             padded row tiles: 24 are multiplied for 22)
-// (launches repeated; means of a trace of nine single steps of 352 rows, QKV and gate/up: 91.4 170.3 before, 74.2 137.6 now)
+//   352       84.8 157.6 31.2 65.8 173.7    67.9 121.9 30.0 58.6 151.9   (1.04 PFLOP/s of issued products at QKV)
+// (launches repeated, row blocks of 8, 10 and 12 tiles; means of a trace of nine single steps of 352 rows, QKV and gate/up: 91.4
+// 170.3 before, 74.2 137.6 now)
+// Row blocks of an odd number of tiles (7, 9, 11: the halves of a workgroup differ by one, and every SIMD gets one of each) are
+// no longer multiplied as the next even one.  Steps of four layers, 208, 272, 288 and 352 rows: 7B shape 1124 -> 1102 us, 1307 ->
+// 1276, 1348 -> 1294, 1519 -> 1490, 1B shape 632 -> 596, 721 -> 678, 742 -> 688, 804 -> 748.  Less than the products saved:
+// at 352 rows a stage takes 1600-1700 cycles of which its products are 1060, the rest waiting for the slowest wavefront at the
+// barrier, and a launch spends 14 us before the first stage and after the last (counters in a copy of the kernel).
 // Tried: four wavefronts with 32x32x16 products (one per SIMD: fetching, LDS reads and products add up instead of overlapping,
 // 85 and 158 us at 352 rows); fetching on two wavefronts of their own; from 65 to 192 rows, where W from memory is half of the
 // time, this kernel and the one above are within 5 % of each other either way, except for the LM head at eight row tiles
@@ -644,13 +649,15 @@ __global__ void __launch_bounds__(512, 1) gemm_ring_kernel(const char* __restric
                                                            int row_blocks, int n_blocks, SwigluOut so)
 {
     constexpr int XT = PLANES * MT, ST = XT + RING_GROUPS * NT, U = (ST + 7) / 8;   // KiB tiles per stage; requests per wavefront
-    constexpr int S = ring_stages(MT, NT, PLANES), G = MT / 2, L = 2;                // row tiles of a wavefront; read ahead
-    static_assert(MT % 2 == 0 && G > L && S >= 3, "tile shape");
-    constexpr int GP = (G + 1) / 2, COLS = RING_GROUPS * NT * 16, LD = COLS + 4;   // SwiGLU: row tiles of a pass; its sums in LDS
+    constexpr int S = ring_stages(MT, NT, PLANES), L = 2;                            // read ahead, row tiles
+    constexpr int G0 = (MT + 1) / 2, G1 = MT / 2;                                    // row tiles of the two halves
+    static_assert(G1 > L && S >= 3, "tile shape");
+    constexpr int GP = (G0 + 1) / 2, COLS = RING_GROUPS * NT * 16, LD = COLS + 4;   // SwiGLU: row tiles of a pass; its sums in LDS
     static_assert((2 * GP * 16 * LD + MT * 16) * 4 <= S * ST * 1024 && MT * 16 <= 512, "the sums of a pass fit the ring");
     __shared__ u32x4 lds[S * ST * 64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int a0 = (wave & 1) * G, group = wave >> 1;
+    // Wavefronts i and i + 4 share a SIMD: they take different halves, so that an odd number of row tiles loads all SIMDs alike.
+    const int half = (MT % 2 ? wave ^ (wave >> 2) : wave) & 1, a0 = half * G0, group = wave >> 1;
     // row blocks of the same columns follow each other on one XCD (map_block's order otherwise): the second reads W from its L2
     const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
     int split, nblk;
@@ -676,7 +683,7 @@ __global__ void __launch_bounds__(512, 1) gemm_ring_kernel(const char* __restric
         const int tile = u * 8 + wave;
         if (u * 8 + 8 <= XT || (u * 8 < XT && tile < XT)) fetch_to_lds<false>(xbase, offset[u], to);
         else if (u * 8 + 8 <= ST || tile < ST) fetch_to_lds<STREAM>(wbase, offset[u], to);
-        else fetch_to_lds<false>(xbase, offset[0], to - u * 8192u);   // (its first tile again: every wavefront counts U a stage)
+        else fetch_to_lds<false>(wave < XT ? xbase : wbase, offset[0], to - u * 8192u);   // (its first tile again: every wavefront counts U a stage)
     };
     auto advance = [&]() {
         xbase += (size_t)PLANES * mt * 1024;
@@ -688,123 +695,128 @@ __global__ void __launch_bounds__(512, 1) gemm_ring_kernel(const char* __restric
         if (requested - 1 - stage >= S - 2) wait_fetches<(S - 2) * U>();
         else wait_fetches<0>();
     };
-    floatx4 acc[G][NT];
+    auto run = [&](auto tiles_of_half) {
+        constexpr int G = decltype(tiles_of_half)::value;
+        floatx4 acc[G][NT];
 #pragma unroll
-    for (int a = 0; a < G; ++a)
+        for (int a = 0; a < G; ++a)
 #pragma unroll
-        for (int i = 0; i < NT; ++i) acc[a][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < NT; ++i) acc[a][i] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    const u32x4* xl = lds + a0 * 64 + lane;
-    const u32x4* wl = lds + (XT + group * NT) * 64 + lane;
-    constexpr int R = 4;   // ring of X fragments in registers: tile g of a stage at g % R
-    bf16x8 xh[R], xr[R], wf[2][NT];
-    auto read_x = [&](int slot, int g, int at) {
-        xh[at] = __builtin_bit_cast(bf16x8, xl[(slot * ST + g) * 64]);
-        if constexpr (PLANES == 2) xr[at] = __builtin_bit_cast(bf16x8, xl[(slot * ST + MT + g) * 64]);
-    };
-    auto read_w = [&](int slot, int i) { return __builtin_bit_cast(bf16x8, wl[(slot * ST + i) * 64]); };
-    float scale = 0.f;   // SwiGLU: of row threadIdx.x
-    if (n > 0) {
-        for (int i = min(n, S - 1); i > 0; --i) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) request(u);
-            advance();
-        }
-        // (behind the first requests, so that the wait for it costs nothing)
-        if constexpr (SWIGLU) scale = row_inv_rms(so.ssq, so.n_ssq, min(t0 * 16 + (int)threadIdx.x, M - 1), so.d, so.eps);
-        landed(0);
-        workgroup_barrier();
-        int stage = 0, slot = 0;
-#pragma unroll
-        for (int i = 0; i < NT; ++i) wf[0][i] = wf[1][i] = read_w(0, i);
-#pragma unroll
-        for (int g = 0; g < L; ++g) read_x(0, g, g);
-        auto step = [&](auto set) {   // which of the two sets of W fragments the stage is in
-            constexpr int cur = decltype(set)::value;
-            const bool more = requested < n;
-            const int next = slot + 1 == S ? 0 : slot + 1;
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                if (g == G - L) {
-                    if (more) advance();
-                    wait_lds_reads();
-                    landed(min(stage + 1, n - 1));
-                    workgroup_barrier();
-#pragma unroll
-                    for (int i = 0; i < NT; ++i) wf[cur ^ 1][i] = read_w(next, i);   // (after the last stage: never used)
-                }
-                if (g + L < G) read_x(slot, g + L, (g + L) % R);
-                else read_x(next, g + L - G, (g + L) % R);
-                if (g < G - L && more) {
-#pragma unroll
-                    for (int u = g; u < U; u += G - L) request(u);
-                }
-#pragma unroll
-                for (int i = 0; i < NT; ++i) acc[g][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh[g % R], wf[cur][i], acc[g][i], 0, 0, 0);
-                if constexpr (PLANES == 2) {
-#pragma unroll
-                    for (int i = 0; i < NT; ++i) acc[g][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xr[g % R], wf[cur][i], acc[g][i], 0, 0, 0);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if constexpr (G % R != 0) {   // the next stage's first fragments to where it looks for them
-                bf16x8 h[L], r[L];
-#pragma unroll
-                for (int g = 0; g < L; ++g) { h[g] = xh[(G + g) % R]; r[g] = xr[(G + g) % R]; }
-#pragma unroll
-                for (int g = 0; g < L; ++g) { xh[g] = h[g]; xr[g] = r[g]; }
-            }
-            slot = next;
-            ++stage;
+        const u32x4* xl = lds + a0 * 64 + lane;
+        const u32x4* wl = lds + (XT + group * NT) * 64 + lane;
+        constexpr int R = 4;   // ring of X fragments in registers: tile g of a stage at g % R
+        bf16x8 xh[R], xr[R], wf[2][NT];
+        auto read_x = [&](int slot, int g, int at) {
+            xh[at] = __builtin_bit_cast(bf16x8, xl[(slot * ST + g) * 64]);
+            if constexpr (PLANES == 2) xr[at] = __builtin_bit_cast(bf16x8, xl[(slot * ST + MT + g) * 64]);
         };
-        if (n & 1) step(std::integral_constant<int, 1>{});   // (both sets hold stage 0)
-        while (stage < n) {
-            step(std::integral_constant<int, 0>{});
-            step(std::integral_constant<int, 1>{});
-        }
-        wait_lds_reads();
-        wait_fetches<0>();
-    }
-    if constexpr (SWIGLU) {
-        float* sums = reinterpret_cast<float*>(lds);
-        float* scales = sums + 2 * GP * 16 * LD;
-        const int g = lane >> 4, c = lane & 15;
+        auto read_w = [&](int slot, int i) { return __builtin_bit_cast(bf16x8, wl[(slot * ST + i) * 64]); };
+        float scale = 0.f;   // SwiGLU: of row threadIdx.x
+        if (n > 0) {
+            for (int i = min(n, S - 1); i > 0; --i) {
 #pragma unroll
-        for (int p0 = 0; p0 < G; p0 += GP) {
-            __syncthreads();   // everyone is done with the ring, and with the pass before
-            if (p0 == 0 && (int)threadIdx.x < MT * 16) scales[threadIdx.x] = scale;
+                for (int u = 0; u < U; ++u) request(u);
+                advance();
+            }
+            // (behind the first requests, so that the wait for it costs nothing)
+            if constexpr (SWIGLU) scale = row_inv_rms(so.ssq, so.n_ssq, min(t0 * 16 + (int)threadIdx.x, M - 1), so.d, so.eps);
+            landed(0);
+            workgroup_barrier();
+            int stage = 0, slot = 0;
 #pragma unroll
-            for (int a = 0; a < GP; ++a)
-                if (p0 + a < G) {
+            for (int i = 0; i < NT; ++i) wf[0][i] = wf[1][i] = read_w(0, i);
 #pragma unroll
-                    for (int i = 0; i < NT; ++i)
+            for (int g = 0; g < L; ++g) read_x(0, g, g);
+            auto step = [&](auto set) {   // which of the two sets of W fragments the stage is in
+                constexpr int cur = decltype(set)::value;
+                const bool more = requested < n;
+                const int next = slot + 1 == S ? 0 : slot + 1;
 #pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            sums[(((wave & 1) * GP + a) * 16 + 4 * g + r) * LD + (group * NT + i) * 16 + c] = acc[p0 + a][i][r];
+                for (int g = 0; g < G; ++g) {
+                    if (g == G - L) {
+                        if (more) advance();
+                        wait_lds_reads();
+                        landed(min(stage + 1, n - 1));
+                        workgroup_barrier();
+#pragma unroll
+                        for (int i = 0; i < NT; ++i) wf[cur ^ 1][i] = read_w(next, i);   // (after the last stage: never used)
+                    }
+                    if (g + L < G) read_x(slot, g + L, (g + L) % R);
+                    else read_x(next, g + L - G, (g + L) % R);
+                    if (g < G - L && more) {
+#pragma unroll
+                        for (int u = g; u < U; u += G - L) request(u);
+                    }
+#pragma unroll
+                    for (int i = 0; i < NT; ++i) acc[g][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh[g % R], wf[cur][i], acc[g][i], 0, 0, 0);
+                    if constexpr (PLANES == 2) {
+#pragma unroll
+                        for (int i = 0; i < NT; ++i) acc[g][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xr[g % R], wf[cur][i], acc[g][i], 0, 0, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-            __syncthreads();
-            swiglu_from_lds(sums, LD, scales, 2 * GP, COLS, nblk * (COLS / 2), n_tiles * 8, t0 * 16, M, wave, 8, lane, so, [&](int t) {
-                const int a = p0 + t % GP;
-                return a < G ? (t / GP) * G + a : -1;
-            });
+                if constexpr (G % R != 0) {   // the next stage's first fragments to where it looks for them
+                    bf16x8 h[L], r[L];
+#pragma unroll
+                    for (int g = 0; g < L; ++g) { h[g] = xh[(G + g) % R]; r[g] = xr[(G + g) % R]; }
+#pragma unroll
+                    for (int g = 0; g < L; ++g) { xh[g] = h[g]; xr[g] = r[g]; }
+                }
+                slot = next;
+                ++stage;
+            };
+            if (n & 1) step(std::integral_constant<int, 1>{});   // (both sets hold stage 0)
+            while (stage < n) {
+                step(std::integral_constant<int, 0>{});
+                step(std::integral_constant<int, 1>{});
+            }
+            wait_lds_reads();
+            wait_fetches<0>();
         }
-        return;
-    }
-    const int n_pad = n_tiles * 16, g4 = lane >> 4, c16 = lane & 15;
-    float* out = partial + (size_t)split * M * n_pad;
+        if constexpr (SWIGLU) {
+            float* sums = reinterpret_cast<float*>(lds);
+            float* scales = sums + 2 * GP * 16 * LD;
+            const int g = lane >> 4, c = lane & 15;
 #pragma unroll
-    for (int a = 0; a < G; ++a)
+            for (int p0 = 0; p0 < G0; p0 += GP) {   // (as many for either half)
+                __syncthreads();   // everyone is done with the ring, and with the pass before
+                if (p0 == 0 && (int)threadIdx.x < MT * 16) scales[threadIdx.x] = scale;
 #pragma unroll
-        for (int i = 0; i < NT; ++i) {
-            const int tile = c0 + group * NT + i;
-            if (tile < n_tiles) {
+                for (int a = 0; a < GP; ++a)
+                    if (p0 + a < G) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int m = (t0 + a0 + a) * 16 + 4 * g4 + r;
-                    if (m < M) out[(size_t)m * n_pad + tile * 16 + c16] = acc[a][i][r];
+                        for (int i = 0; i < NT; ++i)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r)
+                                sums[((half * GP + a) * 16 + 4 * g + r) * LD + (group * NT + i) * 16 + c] = acc[p0 + a][i][r];
+                    }
+                __syncthreads();
+                swiglu_from_lds(sums, LD, scales, 2 * GP, COLS, nblk * (COLS / 2), n_tiles * 8, t0 * 16, M, wave, 8, lane, so, [&](int t) {
+                    const int a = p0 + t % GP;
+                    return a < (t < GP ? G0 : G1) ? (t / GP) * G0 + a : -1;
+                });
+            }
+            return;
+        }
+        const int n_pad = n_tiles * 16, g4 = lane >> 4, c16 = lane & 15;
+        float* out = partial + (size_t)split * M * n_pad;
+#pragma unroll
+        for (int a = 0; a < G; ++a)
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                const int tile = c0 + group * NT + i;
+                if (tile < n_tiles) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int m = (t0 + a0 + a) * 16 + 4 * g4 + r;
+                        if (m < M) out[(size_t)m * n_pad + tile * 16 + c16] = acc[a][i][r];
+                    }
                 }
             }
-        }
+    };
+    if (G0 == G1 || half == 0) run(std::integral_constant<int, G0>{});
+    else run(std::integral_constant<int, G1>{});
 }
 
 // zero a fragment buffer (a kernel rather than a memset node, so that the call can be captured in a graph)
@@ -1100,7 +1112,7 @@ static bool ranges_have_work(int kb_total, int n)
     return (kb_total + per - 1) / per * 8 >= n * 7;
 }
 
-// Launch shape of gemm_ring_kernel: two row blocks of 8, 10 or 12 row tiles; column tiles per wavefront and K ranges by the
+// Launch shape of gemm_ring_kernel: two row blocks of half the row tiles each; column tiles per wavefront and K ranges by the
 // cheapest of what fits, counted in cycles: rounds of workgroups over the chip x stages x a stage's time -- its matrix
 // instructions (32 cycles per pair of tiles and SIMD) plus 0.6 of its LDS reads -- plus, per range, writing the partial sums and
 // reading them back.  (By row tiles, not rows: the space for the partial sums is reserved by row tiles.)  Calibrated on the 7B, 1B and 2048-wide shapes at 256, 320 and 352 rows, where it picks the best of
@@ -1108,7 +1120,7 @@ static bool ranges_have_work(int kb_total, int n)
 // and one (230), output two and four, down (K = 11008) four and eight, LM head four and one (250).
 static void plan_ring(GemmPlan& p, int n_tiles, int kb_total, int cu_count)
 {
-    p.ring = p.mt <= 16 ? 8 : p.mt <= 20 ? 10 : 12;
+    p.ring = p.mt / 2;
     p.cg = RING_GROUPS;
     auto may_cut = [&](int s) { return blocks_per_range(kb_total, s) >= 2 * WPACK_KG && ranges_have_work(kb_total, s); };
     double best = 0.0;
@@ -1245,15 +1257,21 @@ static int launch_ring_plan(const GemmPlan& p, const void* x_frags, const void* 
 #define SPECV_RING(MT_, NT_, STREAM_)                                                                              \
     if (p.ring == MT_ && p.nt == NT_ && (p.mt <= MT_) == STREAM_) return launch_ring<MT_, NT_, STREAM_>(p, x_frags, w_packed, M, K, n_tiles, partial, s, swiglu)
     SPECV_RING(8, 4, true);
+    SPECV_RING(7, 2, false);
+    SPECV_RING(7, 3, false);
+    SPECV_RING(7, 4, false);
     SPECV_RING(8, 2, false);
     SPECV_RING(8, 3, false);
     SPECV_RING(8, 4, false);
+    SPECV_RING(9, 2, false);
+    SPECV_RING(9, 3, false);
+    SPECV_RING(9, 4, false);
     SPECV_RING(10, 2, false);
     SPECV_RING(10, 3, false);
     SPECV_RING(10, 4, false);
-    SPECV_RING(12, 2, false);
-    SPECV_RING(12, 3, false);
-    SPECV_RING(12, 4, false);
+    SPECV_RING(11, 2, false);
+    SPECV_RING(11, 3, false);
+    SPECV_RING(11, 4, false);
 #undef SPECV_RING
     return fail(SPEC_ERR_SHAPE, "no GEMM variant for %d rows (%d row tiles, %d column tiles per wave)", M, p.mt, p.nt);
 }
