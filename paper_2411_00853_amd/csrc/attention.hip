@@ -323,10 +323,13 @@ static int merge_width(int hd, int rt, int max_chunks, int n_pairs, int cu_count
 // of one kv head then read the same blocks and most of the traffic stays in L2; with one head per kv
 // head every workgroup streams from HBM through a single compute unit, and the plan loses (7B-shape,
 // 32 x 128-dim kv heads, batch 1 at 1024 positions: 3.35 -> 3.44 ms, at 2048 3.47 -> 3.73, batch 3 4.04 -> 4.07).
+constexpr int BRIEF_POSITIONS = 512;    // capacity of a slot, in positions of 128-dim heads, up to which workgroups always merge
+constexpr int FUSED_MIN_KEYS = 192;   // fewest positions per chunk for the attention to put queries, keys and values together itself
 struct AttnLaunchPlan {
     int share;
     AttnPlan p;
     bool small;
+    bool brief;   // merged inside the workgroup however few pairs there are
 };
 static AttnLaunchPlan plan_launch(const CacheGeom& g, bool paged, int n_q_heads, int kmax, int B, int max_kv_len,
                                   int cu_count)
@@ -363,6 +366,37 @@ static AttnLaunchPlan plan_launch(const CacheGeom& g, bool paged, int n_q_heads,
         lp.p.chunk_keys = ((max_kv_len + few - 1) / few + 31) / 32 * 32;
         lp.p.max_chunks = (max_kv_len + lp.p.chunk_keys - 1) / lp.p.chunk_keys;
     }
+    const int rt = ((kmax + 1) * (group / lp.share) + 15) / 16;
+    const long pairs = (long)B * g.n_kv_heads * lp.share;
+    const bool own = !g_max_chunks_set && g_merge_min_pairs == 0 && g_items_per_cu == 0;   // (no knob set)
+    auto cut = [&](int keys) {
+        lp.p.chunk_keys = keys;
+        lp.p.max_chunks = (max_kv_len + keys - 1) / keys;
+    };
+    // Short slots: a few wavefronts of one compute unit stream them in less time than chunk results through memory and the merge
+    // kernel take, however few pairs there are.  Up to four chunks, merged in the workgroup; steps of four layers, 1 to 8
+    // sequences, up to 127 pairs, before -> with this: 40 to 360 positions of 128-dim heads -2..-8 % (7B shape 382 -> 370 us, 8 heads of
+    // a 1024 wide model 159 -> 146), of 64-dim heads -5..-8, 700 of them -2..-4.  At 700 positions of 128-dim heads -1.5..+11 %, at
+    // 1100 0..+10, 1800 of 64-dim heads +1.5..+5: a compute unit's share of the stream decides, so the limit counts bytes.
+    lp.brief = lp.small;
+    if (own && (long)max_kv_len * g.head_dim <= 128L * BRIEF_POSITIONS) {
+        lp.brief = true;
+        const int keys = std::max(FUSED_MIN_KEYS, ((max_kv_len + 3) / 4 + 31) / 32 * 32);
+        if (lp.p.chunk_keys < keys && merge_width(g.head_dim, rt, (max_kv_len + keys - 1) / keys, (int)pairs, cu_count, true) > 0) cut(keys);
+    }
+    // Chunks shorter than FUSED_MIN_KEYS would have the separate rotary/append kernel in front.  Fewer, longer chunks that do
+    // without it are the faster choice (same steps, without the rule above):
+    //  * 64-dim heads, a block of which is half as long to stream: 250 to 900 positions -2..-6 %, 1400 to 2500 -4..-9; short
+    //    slots of the small-launch plan -3..-5
+    //  * beyond 1024 positions, 128-dim heads too (9 to 16 chunks of 128 before): 1400 positions -3..-4.5 % at the 7B shape, -6..-9 with
+    //    8 heads of a 1024 wide model, 2500 positions -2..-5
+    //  * up to 384 positions with single rows, or where one or two chunks still give a quarter of the compute units a
+    //    workgroup: 7B shape 8 x 300 positions -2.5 %, 32 x 48 -2; 32 prompts of 64, 352 rows -2.2 (one chunk per pair: no
+    //    wavefront repeats another's queries, the kernel in front took 20 us a layer)
+    // Between 384 and 1024 positions of 128-dim heads it loses (8 heads, one sequence at 550: +2.5..+6 %) and is not made.
+    if (own && lp.p.chunk_keys < FUSED_MIN_KEYS && fused_fits(g.head_dim, rt)
+        && (g.head_dim == 64 || lp.small || max_kv_len > 1024 || (max_kv_len <= 2 * FUSED_MIN_KEYS && (kmax == 0 || 4 * pairs >= cu_count))))
+        cut(FUSED_MIN_KEYS);
     // Two blocks: measured over 0..128 positions, 7B-shape paged step 5.04 -> 4.95 ms, decoding round 6.69 -> 6.62 ms,
     // contiguous 7B-shape, tree and long-context steps 0.2-0.7 % shorter, nothing longer (32 and 96 positions, an
     // odd number of blocks with two buffers, were slower than none).  With the window attended to from LDS: a draft model's
@@ -384,9 +418,9 @@ AttnDescription describe_attention(const CacheGeom& g, bool paged, int n_q_heads
     d.chunk_keys = lp.p.chunk_keys;
     d.row_tiles = ((kmax + 1) * group + 15) / 16;
     d.wavefronts = d.row_tiles >= 1 && d.row_tiles <= 4
-                       ? merge_width(g.head_dim, d.row_tiles, lp.p.max_chunks, B * g.n_kv_heads * lp.share, cu_count, lp.small)
+                       ? merge_width(g.head_dim, d.row_tiles, lp.p.max_chunks, B * g.n_kv_heads * lp.share, cu_count, lp.brief)
                        : 0;
-    d.fused = fused_fits(g.head_dim, d.row_tiles) && lp.p.chunk_keys >= 192 ? 1 : 0;
+    d.fused = fused_fits(g.head_dim, d.row_tiles) && lp.p.chunk_keys >= FUSED_MIN_KEYS ? 1 : 0;
     d.partial_floats = (size_t)B * g.n_kv_heads * lp.share * lp.p.max_chunks * group * max_window * g.head_dim;
     return d;
 }
@@ -402,7 +436,7 @@ bool attention_takes_qkv(const CacheGeom& g, int n_q_heads, const LookaheadPack&
     // Every wavefront of a (sequence, kv head) puts the queries together again: with short chunks
     // (few sequences, many chunks each) that costs more than the separate kernel it replaces
     // (measured: batch 1 at 1B-shape, 128-position chunks, 2 % slower; 256-position chunks faster).
-    return lp.p.chunk_keys >= 192;
+    return lp.p.chunk_keys >= FUSED_MIN_KEYS;
 }
 
 int launch_attention(int max_kv_len, int cu_count, const StepTables& t, const LookaheadPack& ks, int B, int M, const CacheGeom& g,
@@ -451,7 +485,7 @@ int launch_attention(int max_kv_len, int cu_count, const StepTables& t, const Lo
     const dim3 grid(p.max_chunks, n_items_kv, B), wg_grid(n_items_kv, B);
     const float sl2 = scale * 1.4426950408889634f;
     if (hd != 64 && hd != 128) return fail(SPEC_ERR_SHAPE, "bf16 attention needs head_dim 64 or 128");
-    const int cw = rt >= 1 && rt <= 4 ? merge_width(hd, rt, p.max_chunks, B * n_items_kv, cu_count, lp.small) : 0;
+    const int cw = rt >= 1 && rt <= 4 ? merge_width(hd, rt, p.max_chunks, B * n_items_kv, cu_count, lp.brief) : 0;
     int rc;
     {
         ProfScope ps(prof, SPEC_PROF_ATTENTION, s);
