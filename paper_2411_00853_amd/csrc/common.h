@@ -140,9 +140,29 @@ struct SamplerWorkspace {
     int32_t* part_idx;    // [stat rows][stat chunks] greedy rule: lowest id holding the chunk maximum
 };
 
+// Where a producer puts a GEMM operand: fragment buffer (bf16 path) and/or plain fp32 rows.
+struct XOut {
+    void* frags;        // NULL on the fp32 path
+    int mt, planes;
+    float* plain;       // NULL on the bf16 path
+};
+// x = E[token] of every window row: the residual stream, its sums of squares (NULL: none) and x * gain as the first product's operand.
+struct EmbedTo {
+    const void* E;
+    int dtype, d;
+    float* x;
+    double2* ssq;
+    const float* gain;
+    XOut xo;
+};
+int launch_embed(const EmbedTo& e, const int32_t* row_tok, int M, hipStream_t s);
+
+// embed != NULL (steps of M <= EMBED_MAX_ROWS window rows): the same launch embeds the rows
+constexpr int EMBED_MAX_ROWS = SPEC_MAX_STEP_ROWS;
 int launch_prepare(const StepTables& t, const LookaheadPack& ks, int B, int Kmax, int V, int max_batch,
                    int max_kv_len, bool has_cache, const int32_t* seq_slot, const int32_t* last_token,
-                   const int32_t* draft_tokens, const int32_t* kv_len, int32_t* flag, hipStream_t s);
+                   const int32_t* draft_tokens, const int32_t* kv_len, int32_t* flag, hipStream_t s,
+                   const EmbedTo* embed = nullptr);
 
 // Temperature 0: keep a proposal iff it is the target row's most likely token (lowest id among equal
 // maxima); the final token is the most likely token of the first mismatching row, or of row K_b.
@@ -180,7 +200,7 @@ int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const Lookahe
 int launch_prepare_tree(const StepTables& t, const LookaheadPack& ks, int B, int Kmax, int V, int max_batch,
                         int max_kv_len, bool has_cache, const int32_t* seq_slot, const int32_t* last_token,
                         const int32_t* parent, const int32_t* tokens, const int32_t* kv_len, int32_t* flag,
-                        hipStream_t s);
+                        hipStream_t s, const EmbedTo* embed = nullptr);
 int launch_tree_sampler(const StepTables& t, const SamplerWorkspace& w, const LookaheadPack& ks, int B, int Kmax,
                         int V, int n_stat_rows, const float* target_logits, const float* draft_logits,
                         const int32_t* parent, const int32_t* tokens, const float* uniforms, float temperature,
@@ -225,14 +245,6 @@ struct CacheGeom {
 
 CacheGeom make_cache_geom(const spec_model_cfg& c);
 
-// Where a producer puts a GEMM operand: fragment buffer (bf16 path) and/or plain fp32 rows.
-struct XOut {
-    void* frags;        // NULL on the fp32 path
-    int mt, planes;
-    float* plain;       // NULL on the bf16 path
-};
-int launch_embed(int dtype, const void* tok_embed, const int32_t* row_tok, int M, int d, float* x, double2* ssq,
-                 const float* gain, const XOut& xo, hipStream_t s);
 // x[m] += sum of the n_split partial ranges ([n_split][M][ld], added in index order); ssq updated;
 // x * gain written as the next GEMM's operand
 int launch_resid(const float* partial, int n_split, size_t split_stride, int ld, int M, int d, float* x, double2* ssq,

@@ -290,11 +290,13 @@ extern "C" int spec_decode_round(spec_decoder* d, const spec_round_args* args, v
             if (i == 0)
                 for (int b = 0; b < B; ++b) ks.k[b] = 1;
             const int rows = (i == 0 ? 2 : 1) * B;
+            EmbedTo embed;
+            const bool embeds = forward_embeds(dr, rows, &embed);
             rc = launch_prepare(dr->tables, ks, B, d->Kd, V, dr->cfg.max_batch, dr->cfg.max_kv_len, true, d->seq_slot,
-                                i == 0 ? d->prev_tok : d->cur_tok, d->win, dr->kv_len, dr->flag, s);
+                                i == 0 ? d->prev_tok : d->cur_tok, d->win, dr->kv_len, dr->flag, s, embeds ? &embed : nullptr);
             if (rc) return rc;
             LogitsSrc src{};
-            rc = forward_run_grouped(dr, ks, B, rows, dr->logits, s, greedy ? nullptr : &src);
+            rc = forward_run_grouped(dr, ks, B, rows, dr->logits, s, greedy ? nullptr : &src, embeds);
             if (rc) return rc;
             DrawEmit em{};
             em.tokens = d->draft_tokens;
@@ -324,11 +326,13 @@ extern "C" int spec_decode_round(spec_decoder* d, const spec_round_args* args, v
         M += kb + 1;
         n_stat += 2 * kb + 1;
     }
+    EmbedTo embed;
+    const bool embeds = forward_embeds(tg, M, &embed);
     rc = launch_prepare(tg->tables, ks, B, Kt, V, tg->cfg.max_batch, tg->cfg.max_kv_len, true, d->seq_slot, d->last_tok,
-                        d->draft_tokens, tg->kv_len, tg->flag, s);
+                        d->draft_tokens, tg->kv_len, tg->flag, s, embeds ? &embed : nullptr);
     if (rc) return rc;
     LogitsSrc src{};
-    rc = forward_run_grouped(tg, ks, B, M, tg->logits, s, greedy ? nullptr : &src);
+    rc = forward_run_grouped(tg, ks, B, M, tg->logits, s, greedy ? nullptr : &src, embeds);
     if (rc) return rc;
     if (greedy)
         rc = launch_greedy(tg->tables, tg->sampler, ks, B, Kt, V, M, tg->logits, d->draft_tokens, 1, tg->kv_len,

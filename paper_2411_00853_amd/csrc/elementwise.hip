@@ -3,6 +3,7 @@
 // pass: embedding + RMSNorm, residual add + RMSNorm, SiLU gating, rotary embedding + KV append.
 #include "cache_layout.h"
 #include "common.h"
+#include "embed.h"
 #include "frag.h"
 #include "splits.h"
 
@@ -11,58 +12,46 @@ namespace {
 
 constexpr int TPB = 256;
 
-// Emit 8 consecutive values of a row as the next GEMM's operand: x * gain, as fragments (the fp32 path has none:
-// its GEMM takes the plain rows).
-__device__ __forceinline__ void emit_operand(const XOut& xo, int m, int k8, const float (&v)[8], const float* __restrict__ gain)
+// x = E[token], one wavefront per (row, SSQ_CHUNK columns)
+template <typename T>
+__global__ void __launch_bounds__(64) embed_kernel(const T* __restrict__ E, const int32_t* __restrict__ row_tok, float* __restrict__ x,
+                                                   const float* __restrict__ gain, double2* __restrict__ ssq, int d, XOut xo)
 {
-    if (!xo.frags) return;
-    float g[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) g[e] = v[e] * (gain ? gain[k8 * 8 + e] : 1.f);
-    store_x_unit(static_cast<uint4*>(xo.frags), xo.mt, xo.planes, m, k8, g);
+    const int m = blockIdx.y;
+    EmbedRow<T> row;
+    row.load(E, row_tok[m], blockIdx.x, d);
+    embed_chunk(row, m, blockIdx.x, gridDim.x, d, x, gain, xo, ssq);
 }
 
-// One wavefront per (row, SSQ_CHUNK columns), 8 columns per lane: x = E[token] (or x += partial sums);
+// One wavefront per (row, SSQ_CHUNK columns), 8 columns per lane: x += partial sums;
 // ssq[m][chunk] = sum x^2 over the chunk; x * gain goes out as the next GEMM's operand.  d is a multiple of 8.
 // Latency up to a hundred rows, then the partial sums and the fragment stores (16 bytes into a line each); single
 // wavefronts spread best over the chip: 352 rows of 4096 with eight ranges 12.1 us as workgroups of two, 10.1
 // as single ones; a wavefront per 16 rows x 32 columns, whose stores are contiguous, 10.9 (and slower at 48 rows).
-template <typename T, bool EMBED>
 __global__ void __launch_bounds__(64) resid_kernel(const float* __restrict__ partial, float* __restrict__ x, size_t split_stride,
                                                    int n_split, int ld, int d, int xmt, void* frags, const float* __restrict__ gain,
-                                                   double2* __restrict__ ssq, int planes, const T* __restrict__ E,
-                                                   const int32_t* __restrict__ row_tok)
+                                                   double2* __restrict__ ssq, int planes)
 {
-    // (ssq == NULL, the fp32 path's embedding: its GEMM sums the squares itself)
     const int m = blockIdx.y, k8 = blockIdx.x * 64 + threadIdx.x;
     double ss = 0.0;
     if (k8 * 8 < d) {
         float v[8];
         float* xp = x + (size_t)m * d + k8 * 8;
-        if constexpr (EMBED) {
-            const T* e = E + (size_t)row_tok[m] * d + k8 * 8;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = static_cast<float>(e[i]);
-        } else {
-            const float4 a = *reinterpret_cast<const float4*>(xp), b = *reinterpret_cast<const float4*>(xp + 4);
-            const float* pp = partial + (size_t)m * ld + k8 * 8;
-            const float* cols[2] = {pp, pp + 4};
-            float4 sums[2];
-            sum_ranges(cols, n_split, split_stride, sums);   // up to 8 ranges in one round trip
-            const float4 pa = sums[0], pb = sums[1];
-            v[0] = a.x + pa.x; v[1] = a.y + pa.y; v[2] = a.z + pa.z; v[3] = a.w + pa.w;
-            v[4] = b.x + pb.x; v[5] = b.y + pb.y; v[6] = b.z + pb.z; v[7] = b.w + pb.w;
-        }
+        const float4 a = *reinterpret_cast<const float4*>(xp), b = *reinterpret_cast<const float4*>(xp + 4);
+        const float* pp = partial + (size_t)m * ld + k8 * 8;
+        const float* cols[2] = {pp, pp + 4};
+        float4 sums[2];
+        sum_ranges(cols, n_split, split_stride, sums);   // up to 8 ranges in one round trip
+        const float4 pa = sums[0], pb = sums[1];
+        v[0] = a.x + pa.x; v[1] = a.y + pa.y; v[2] = a.z + pa.z; v[3] = a.w + pa.w;
+        v[4] = b.x + pb.x; v[5] = b.y + pb.y; v[6] = b.z + pb.z; v[7] = b.w + pb.w;
         *reinterpret_cast<float4*>(xp) = make_float4(v[0], v[1], v[2], v[3]);
         *reinterpret_cast<float4*>(xp + 4) = make_float4(v[4], v[5], v[6], v[7]);
 #pragma unroll
         for (int i = 0; i < 8; ++i) ss += (double)v[i] * v[i];
         emit_operand(XOut{frags, xmt, planes, nullptr}, m, k8, v, gain);
     }
-    if (!ssq) return;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-    if (threadIdx.x == 0) reinterpret_cast<double*>(ssq)[(size_t)m * gridDim.x + blockIdx.x] = ss;
+    store_ssq(ssq, m, gridDim.x, blockIdx.x, ss);
 }
 
 // act[m][f] = silu(gate) * up for 8 consecutive f per thread, gate and up first scaled by the row's
@@ -389,18 +378,15 @@ CacheGeom make_cache_geom(const spec_model_cfg& c)
     return g;
 }
 
-int launch_embed(int dtype, const void* tok_embed, const int32_t* row_tok, int M, int d, float* x, double2* ssq,
-                 const float* gain, const XOut& xo, hipStream_t s)
+int launch_embed(const EmbedTo& e, const int32_t* row_tok, int M, hipStream_t s)
 {
-    if (d % 8) return fail(SPEC_ERR_SHAPE, "d_model must be a multiple of 8");
-    const dim3 grid(2 * ssq_pairs(d), M);
-    if (dtype == SPEC_DTYPE_BF16)
-        hipLaunchKernelGGL((resid_kernel<__bf16, true>), grid, dim3(64), 0, s, nullptr, x, 0, 0, 0, d, xo.mt, xo.frags, gain, ssq,
-                           xo.planes, (const __bf16*)tok_embed, row_tok);
+    if (e.d % 8) return fail(SPEC_ERR_SHAPE, "d_model must be a multiple of 8");
+    const dim3 grid(2 * ssq_pairs(e.d), M);
+    if (e.dtype == SPEC_DTYPE_BF16)
+        hipLaunchKernelGGL(embed_kernel<__bf16>, grid, dim3(64), 0, s, (const __bf16*)e.E, row_tok, e.x, e.gain, e.ssq, e.d, e.xo);
     else
-        hipLaunchKernelGGL((resid_kernel<float, true>), grid, dim3(64), 0, s, nullptr, x, 0, 0, 0, d, xo.mt, xo.frags, gain, ssq,
-                           xo.planes, (const float*)tok_embed, row_tok);
-    SPECV_LAUNCH_CHECK("resid_kernel<embed>");
+        hipLaunchKernelGGL(embed_kernel<float>, grid, dim3(64), 0, s, (const float*)e.E, row_tok, e.x, e.gain, e.ssq, e.d, e.xo);
+    SPECV_LAUNCH_CHECK("embed_kernel");
     return SPEC_OK;
 }
 
@@ -409,8 +395,7 @@ int launch_resid(const float* partial, int n_split, size_t split_stride, int ld,
 {
     if (d % 8 || ld % 4 || split_stride % 4) return fail(SPEC_ERR_SHAPE, "residual rows must be multiples of 8 wide");
     const dim3 grid(2 * ssq_pairs(d), M);
-    hipLaunchKernelGGL((resid_kernel<float, false>), grid, dim3(64), 0, s, partial, x, split_stride, n_split, ld, d, xo.mt, xo.frags,
-                       gain, ssq, xo.planes, nullptr, nullptr);
+    hipLaunchKernelGGL(resid_kernel, grid, dim3(64), 0, s, partial, x, split_stride, n_split, ld, d, xo.mt, xo.frags, gain, ssq, xo.planes);
     SPECV_LAUNCH_CHECK("resid_kernel");
     return SPEC_OK;
 }

@@ -175,10 +175,28 @@ int plan_passes(const LookaheadPack& ks, int B, int M, int cap, int* pass_seqs, 
     return fill(limit, true);
 }
 
-int forward_run_grouped(spec_handle* h, const LookaheadPack& ks, int B, int M, float* logits_out, hipStream_t s, LogitsSrc* last)
+// where a pass of M rows embeds them
+static EmbedTo embed_to(const spec_handle* h, int M)
+{
+    const spec_model_cfg& c = h->cfg;
+    const bool bf16 = c.dtype == SPEC_DTYPE_BF16;
+    const int mt = bf16 ? gemm_row_tiles(M) : 0;
+    return EmbedTo{h->tok_embed, c.dtype, c.d_model, h->x, h->ssq, bf16 ? h->layers[0].attn_norm : nullptr,
+                   XOut{bf16 ? (mt == 1 ? h->xf_act : h->xf) : nullptr, mt, 2, nullptr}};
+}
+
+bool forward_embeds(const spec_handle* h, int M, EmbedTo* e)
+{
+    if (M < 1 || M > h->row_cap || M > EMBED_MAX_ROWS || h->cfg.d_model % 8) return false;
+    *e = embed_to(h, M);
+    return true;
+}
+
+int forward_run_grouped(spec_handle* h, const LookaheadPack& ks, int B, int M, float* logits_out, hipStream_t s, LogitsSrc* last,
+                        bool embedded)
 {
     if (last) *last = LogitsSrc{};
-    if (M <= h->row_cap) return forward_run(h, h->tables, ks, B, M, logits_out, s, last);
+    if (M <= h->row_cap) return forward_run(h, h->tables, ks, B, M, logits_out, s, last, embedded);
     if (!h->group_tables.seq_row0) return fail(SPEC_ERR_SHAPE, "%d window rows exceed the %d the handle takes", M, h->row_cap);
     int pass_seqs[SPEC_PLAN_MAX_PASSES], pass_rows[SPEC_PLAN_MAX_PASSES];
     const int n_passes = plan_passes(ks, B, M, h->row_cap, pass_seqs, pass_rows, SPEC_PLAN_MAX_PASSES);
@@ -202,7 +220,7 @@ int forward_run_grouped(spec_handle* h, const LookaheadPack& ks, int B, int M, f
 }
 
 int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, int B, int M, float* logits_out, hipStream_t s,
-                LogitsSrc* last)
+                LogitsSrc* last, bool embedded)
 {
     const spec_model_cfg& c = h->cfg;
     const Dims z = dims_of(c);
@@ -271,8 +289,7 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
         return launch_resid(h->partial, r.n_split, r.stride, r.ld, M, z.d, h->x, h->ssq, gain, to_xn, s);
     };
 
-    RUN(SPEC_PROF_GLUE, launch_embed(c.dtype, h->tok_embed, t.row_tok, M, z.d, h->x, h->ssq, bf16 ? h->layers[0].attn_norm : nullptr,
-                                     to_xn, s));
+    if (!embedded) RUN(SPEC_PROF_GLUE, launch_embed(embed_to(h, M), t.row_tok, M, s));
     if (!bf16) {
         if (z.F % 8) return fail(SPEC_ERR_SHAPE, "d_ffn must be a multiple of 8");
         auto mul = [&](int cls, const float* in, const void* w, int N, int K, float* out, int mode, const float* gain) -> int {

@@ -64,12 +64,16 @@ namespace specv {
 int forward_init(spec_handle* h, int max_rows);
 // one decoder pass over the B sequences (M <= row_cap window rows) that t describes
 // last != NULL (bf16): the logits stay partial sums, *last says where; else they are written to logits_out
+// embedded: the row bookkeeping's launch has embedded the rows (forward_embeds)
 int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, int B, int M, float* logits_out, hipStream_t s,
-                LogitsSrc* last = nullptr);
+                LogitsSrc* last = nullptr, bool embedded = false);
 // the same for any M: sequences are taken in groups of at most row_cap rows, one pass each (t = h->tables)
 // (last->partial == NULL where the logits are written after all: fp32 models, several passes)
 int forward_run_grouped(spec_handle* h, const LookaheadPack& ks, int B, int M, float* logits_out, hipStream_t s,
-                        LogitsSrc* last = nullptr);
+                        LogitsSrc* last = nullptr, bool embedded = false);
+// Whether a step of M window rows is embedded beside its row bookkeeping (launch_prepare with e), which a step of several
+// passes is not: its passes use the same buffers.
+bool forward_embeds(const spec_handle* h, int M, EmbedTo* e);
 // host logic behind the two (no device work): see forward.hip
 size_t gemm_partial_capacity(const spec_model_cfg& c, int max_rows, int cu_count);
 bool swiglu_inside(const spec_model_cfg& c, int M, int cu_count);

@@ -13,6 +13,7 @@
 // fixed order (no floating-point atomics), so results are reproducible bit for bit.
 #include "cache_layout.h"
 #include "common.h"
+#include "embed.h"
 #include "frag.h"
 
 #include <algorithm>
@@ -1405,16 +1406,14 @@ __global__ void __launch_bounds__(64) tree_greedy_kernel(StepTables t, Lookahead
 // Token trees.  Window slot 0 is the sequence's last token (the root), slot i+1 is node i; the
 // nodes come in topological order with parent[i] = -1 (child of the root) or an index < i.
 // ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(TPB) prepare_tree_kernel(StepTables t, LookaheadPack ks, int B, int Kmax, int V,
-                                                           int max_batch, int max_kv_len, int has_cache,
-                                                           const int32_t* __restrict__ seq_slot,
-                                                           const int32_t* __restrict__ last_token,
-                                                           const int32_t* __restrict__ parent,
-                                                           const int32_t* __restrict__ tokens,
-                                                           const int32_t* __restrict__ kv_len, int32_t* flag)
+typedef uint16_t TreeMasks[SPEC_MAX_LOOKAHEAD + 1][TPB];
+// (a workgroup of TPB threads, all of them calling)
+__device__ __forceinline__ void prepare_tree_rows(const StepTables& t, const LookaheadPack& ks, int B, int Kmax, int V, int max_batch,
+                                                  int max_kv_len, int has_cache, const int32_t* __restrict__ seq_slot,
+                                                  const int32_t* __restrict__ last_token, const int32_t* __restrict__ parent,
+                                                  const int32_t* __restrict__ tokens, const int32_t* __restrict__ kv_len, int32_t* flag,
+                                                  PrepLds& l, TreeMasks& s_mask)
 {
-    __shared__ uint16_t s_mask[SPEC_MAX_LOOKAHEAD + 1][TPB];
-    __shared__ PrepLds l;
     const int b = threadIdx.x;
     const int N = b < B ? ks.k[b] : 0;
     int ok = 1, slot = 0, n = 0;
@@ -1484,6 +1483,92 @@ __global__ void __launch_bounds__(TPB) prepare_tree_kernel(StepTables t, Lookahe
             }
         }
     }
+}
+
+__global__ void __launch_bounds__(TPB) prepare_tree_kernel(StepTables t, LookaheadPack ks, int B, int Kmax, int V,
+                                                           int max_batch, int max_kv_len, int has_cache,
+                                                           const int32_t* __restrict__ seq_slot,
+                                                           const int32_t* __restrict__ last_token,
+                                                           const int32_t* __restrict__ parent,
+                                                           const int32_t* __restrict__ tokens,
+                                                           const int32_t* __restrict__ kv_len, int32_t* flag)
+{
+    __shared__ TreeMasks s_mask;
+    __shared__ PrepLds l;
+    prepare_tree_rows(t, ks, B, Kmax, V, max_batch, max_kv_len, has_cache, seq_slot, last_token, parent, tokens, kv_len, flag, l, s_mask);
+}
+
+// ---------------------------------------------------------------------------------------------
+// The row bookkeeping and the embedding in one launch: the first workgroup does the one, a wavefront per (row, SSQ_CHUNK
+// columns) of the others the other, which has no need of the tables.  The embedding of a few rows and the bookkeeping take a
+// launch and two or three round trips each, one behind the other before (a step of the fp32 configuration 65.9 -> 63.8 us, draft
+// decode of 8 rows 289.3 -> 288.1, 1B shape, 32 sequences 514 -> 510, decoding round 2177 -> 2167, 7B shape, 352 rows 1460 -> 1455).
+// A row of a sequence that the bookkeeping skips embeds token 0, as from the tables, so every wavefront looks at its
+// sequence for itself: slot, cached length, tokens, parents.  (A page pool that runs dry is only seen by the
+// bookkeeping: those rows embed their tokens, and nothing reads what becomes of them.)
+// ---------------------------------------------------------------------------------------------
+struct RowPack {
+    uint16_t r[EMBED_MAX_ROWS];   // 16 * sequence + place in its window
+};
+static_assert(SPEC_MAX_LOOKAHEAD < 16 && SPEC_MAX_BATCH <= 4096, "a row's sequence and place in 16 bits");
+
+template <typename T, bool TREE>
+__global__ void __launch_bounds__(TPB) prepare_embed_kernel(const T* __restrict__ E, const int32_t* __restrict__ seq_slot,
+                                                            const int32_t* __restrict__ last_token, const int32_t* __restrict__ parent,
+                                                            const int32_t* __restrict__ tokens, const int32_t* __restrict__ kv_len,
+                                                            int32_t* flag, int B, int Kmax, int V, int max_batch, int max_kv_len, int M,
+                                                            int chunks, EmbedTo e, StepTables t, LookaheadPack ks, RowPack rows)
+{
+    __shared__ TreeMasks s_mask;
+    __shared__ PrepLds l;
+    if (blockIdx.x == 0) {
+        if constexpr (TREE) prepare_tree_rows(t, ks, B, Kmax, V, max_batch, max_kv_len, 1, seq_slot, last_token, parent, tokens, kv_len, flag, l, s_mask);
+        else prepare_rows(t, ks, B, Kmax, V, max_batch, max_kv_len, 1, seq_slot, last_token, tokens, kv_len, flag, l);
+        return;
+    }
+    const int item = (blockIdx.x - 1) * (TPB / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int m = item / chunks;
+    if (m >= M) return;
+    const int at = rows.r[m], b = at >> 4, j = at & 15, K = ks.k[b], lane = threadIdx.x & 63;
+    const int slot = seq_slot[b], first = last_token[b];
+    int tok = 0, par = -1;
+    if (lane < K) {
+        tok = tokens[b * Kmax + lane];
+        if (TREE) par = parent[b * Kmax + lane];
+    }
+    const int own = j == 0 ? first : __builtin_amdgcn_readlane(tok, j - 1);
+    EmbedRow<T> row;   // (asked for before the cached length has arrived)
+    row.load(E, own >= 0 && own < V ? own : 0, item % chunks, e.d);
+    bool bad = first < 0 || first >= V || tok < 0 || tok >= V || par < -1 || (par >= lane && lane < K);
+    for (int i = lane; i < b; i += 64) bad |= seq_slot[i] == slot;   // two sequences of a step must not share a slot
+    const int n = kv_len[slot >= 0 && slot < max_batch ? slot : 0];
+    bad |= slot < 0 || slot >= max_batch || n < 0 || n + K + 1 > max_kv_len;
+    if (__ballot(bad)) row.load(E, 0, item % chunks, e.d);
+    embed_chunk(row, m, item % chunks, chunks, e.d, e.x, e.gain, e.xo, e.ssq);
+}
+
+template <bool TREE>
+int launch_prepare_embed(const EmbedTo& e, const StepTables& t, const LookaheadPack& ks, int B, int Kmax, int V, int max_batch, int max_kv_len,
+                         const int32_t* seq_slot, const int32_t* last_token, const int32_t* parent, const int32_t* tokens,
+                         const int32_t* kv_len, int32_t* flag, hipStream_t s)
+{
+    RowPack rows;
+    int M = 0;
+    for (int b = 0; b < B; ++b)
+        for (int j = 0; j <= ks.k[b]; ++j) {
+            if (M == EMBED_MAX_ROWS) return fail(SPEC_ERR_SHAPE, "more than %d rows embedded beside their bookkeeping", EMBED_MAX_ROWS);
+            rows.r[M++] = (uint16_t)(16 * b + j);
+        }
+    const int chunks = 2 * ssq_pairs(e.d);
+    const dim3 grid(1 + (M * chunks + TPB / 64 - 1) / (TPB / 64));
+    if (e.dtype == SPEC_DTYPE_BF16)
+        hipLaunchKernelGGL((prepare_embed_kernel<__bf16, TREE>), grid, dim3(TPB), 0, s, (const __bf16*)e.E, seq_slot, last_token, parent,
+                           tokens, kv_len, flag, B, Kmax, V, max_batch, max_kv_len, M, chunks, e, t, ks, rows);
+    else
+        hipLaunchKernelGGL((prepare_embed_kernel<float, TREE>), grid, dim3(TPB), 0, s, (const float*)e.E, seq_slot, last_token, parent,
+                           tokens, kv_len, flag, B, Kmax, V, max_batch, max_kv_len, M, chunks, e, t, ks, rows);
+    SPECV_LAUNCH_CHECK("prepare_embed_kernel");
+    return SPEC_OK;
 }
 
 constexpr int TREE_TPB = 1024;   // the walk is one workgroup per sequence: make it a big one
@@ -1998,8 +2083,11 @@ __global__ void pool_cover_kernel(PagePool pool, int slot, int pos0, int pos1, i
 
 int launch_prepare(const StepTables& t, const LookaheadPack& ks, int B, int Kmax, int V, int max_batch,
                    int max_kv_len, bool has_cache, const int32_t* seq_slot, const int32_t* last_token,
-                   const int32_t* draft_tokens, const int32_t* kv_len, int32_t* flag, hipStream_t s)
+                   const int32_t* draft_tokens, const int32_t* kv_len, int32_t* flag, hipStream_t s, const EmbedTo* embed)
 {
+    if (embed)
+        return launch_prepare_embed<false>(*embed, t, ks, B, Kmax, V, max_batch, max_kv_len, seq_slot, last_token, nullptr, draft_tokens,
+                                           kv_len, flag, s);
     hipLaunchKernelGGL(prepare_kernel, dim3(1), dim3(TPB), 0, s, t, ks, B, Kmax, V, max_batch, max_kv_len,
                        has_cache ? 1 : 0, seq_slot, last_token, draft_tokens, kv_len, flag);
     SPECV_LAUNCH_CHECK("prepare_kernel");
@@ -2048,8 +2136,11 @@ int launch_tree_greedy(const StepTables& t, const SamplerWorkspace& w, const Loo
 int launch_prepare_tree(const StepTables& t, const LookaheadPack& ks, int B, int Kmax, int V, int max_batch,
                         int max_kv_len, bool has_cache, const int32_t* seq_slot, const int32_t* last_token,
                         const int32_t* parent, const int32_t* tokens, const int32_t* kv_len, int32_t* flag,
-                        hipStream_t s)
+                        hipStream_t s, const EmbedTo* embed)
 {
+    if (embed)
+        return launch_prepare_embed<true>(*embed, t, ks, B, Kmax, V, max_batch, max_kv_len, seq_slot, last_token, parent, tokens, kv_len,
+                                          flag, s);
     hipLaunchKernelGGL(prepare_tree_kernel, dim3(1), dim3(TPB), 0, s, t, ks, B, Kmax, V, max_batch, max_kv_len,
                        has_cache ? 1 : 0, seq_slot, last_token, parent, tokens, kv_len, flag);
     SPECV_LAUNCH_CHECK("prepare_tree_kernel");

@@ -377,17 +377,20 @@ extern "C" int spec_verify_step(spec_handle* h, const spec_step_args* args, cons
     // without a decoder pass nothing needs the row tables before the sampler's second kernel: its first
     // one fills them (the greedy rule's kernels read them from the start)
     const bool prepare_in_sampler = !run_model && !greedy;
+    EmbedTo embed;
+    const bool embeds = run_model && forward_embeds(h, M, &embed);
     if (!prepare_in_sampler) {
         ProfScope ps(&h->prof, SPEC_PROF_PREPARE, s);
         rc = launch_prepare(h->tables, ks, B, Kmax, c.vocab, c.max_batch, c.max_kv_len, run_model, args->seq_slot,
-                            run_model ? args->last_token : nullptr, args->draft_tokens, h->kv_len, h->flag, s);
+                            run_model ? args->last_token : nullptr, args->draft_tokens, h->kv_len, h->flag, s,
+                            embeds ? &embed : nullptr);
         if (rc) return rc;
     }
     const float* logits = args->target_logits_in;
     LogitsSrc src{};
     if (run_model) {
         float* dst = out->logits_out ? out->logits_out : h->logits;
-        rc = forward_run_grouped(h, ks, B, M, dst, s, greedy ? nullptr : &src);
+        rc = forward_run_grouped(h, ks, B, M, dst, s, greedy ? nullptr : &src, embeds);
         if (rc) return rc;
         logits = dst;
     } else if (out->logits_out) {
@@ -437,18 +440,20 @@ extern "C" int spec_verify_tree_step(spec_handle* h, const spec_tree_args* args,
     hipStream_t s = (hipStream_t)stream;
     int rc;
     h->tables.tree = 1;
+    EmbedTo embed;
+    const bool embeds = run_model && forward_embeds(h, M, &embed);
     {
         ProfScope ps(&h->prof, SPEC_PROF_PREPARE, s);
         rc = launch_prepare_tree(h->tables, ks, B, Kmax, c.vocab, c.max_batch, c.max_kv_len, run_model, args->seq_slot,
                                  run_model ? args->last_token : nullptr, args->parent, args->draft_tokens, h->kv_len,
-                                 h->flag, s);
+                                 h->flag, s, embeds ? &embed : nullptr);
     }
     if (rc) return rc;
     const float* logits = args->target_logits_in;
     LogitsSrc src{};
     if (run_model) {
         float* dst = out->logits_out ? out->logits_out : h->logits;
-        rc = forward_run_grouped(h, ks, B, M, dst, s, greedy ? nullptr : &src);
+        rc = forward_run_grouped(h, ks, B, M, dst, s, greedy ? nullptr : &src, embeds);
         if (rc) return rc;
         logits = dst;
     } else if (out->logits_out) {
