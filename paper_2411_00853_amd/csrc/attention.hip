@@ -103,36 +103,40 @@ __global__ void __launch_bounds__(64) attn_merge_kernel(StepTables t, LookaheadP
     store_x_unit(static_cast<uint4*>(xo.frags), xo.mt, xo.planes, m, unit, v);
 }
 
-// Plain fp32 attention for fp32 caches: one workgroup per (row, query head).  LP lanes share a position (four
-// dims each), so keys and values are read in contiguous runs, four positions per group in flight, whose sums over
-// the lanes go step by step side by side.  Latency: round trips to memory and across lanes.  Per launch of 20 (row,
-// head) pairs of 64 dims, at 133 and 1029 positions: 7.2 and 29.6 us; a thread per key, and one per dim walking all values,
-// 9.4 and 80; the number of lanes a run-time value, each sum over the lanes a rolled loop of its own, 10.8 and 41.
+// Plain fp32 attention for fp32 caches: one workgroup per (row, query head).  It takes the QKV projection as it is: the query
+// is rotated here, and so are the keys of the window, which every row that sees them rotates for itself; the workgroup of a kv
+// head's first query head puts its own row's key and value into the cache, which this launch reads below the window only.
+// LP lanes share a position (four dims each), so keys and values are read in contiguous runs, U positions per group in flight, whose
+// sums over the lanes go step by step side by side; the first U values and the window are requested with the keys.  Latency: round
+// trips to memory and across lanes.  With a rotary/append kernel in front (2.8 us), four positions in flight and the values only
+// after the softmax: steps of two layers, four 64-dim heads, one sequence of 128 positions and five rows 61.9 -> 56.8 us, 1000
+// positions and one row 86.1 -> 76.1, six of 1024 and 48 rows 141.7 -> 126.8.
+// (That kernel, per launch of 20 (row, head) pairs at 133 and 1029 positions: 7.2 and 29.6 us; a thread per key, and one per dim
+// walking all values, 9.4 and 80; the number of lanes a run-time value, each sum over the lanes a rolled loop of its own, 10.8 and 41.)
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 template <int LP>
-__global__ void __launch_bounds__(256) attn_f32_kernel(StepTables t, CacheGeom g, int n_q_heads, int layer,
-                                                       const float* __restrict__ cache, const float* __restrict__ q,
-                                                       float scale, float* __restrict__ out)
+__global__ void __launch_bounds__(256) attn_f32_kernel(const float* __restrict__ qkv, const float* __restrict__ cos_sin, float* cache,
+                                                       float* __restrict__ out, int n_q_heads, int layer, int ld, float scale,
+                                                       StepTables t, CacheGeom g)
 {
     extern __shared__ float4 dyn[];
     __shared__ float red[4];
     float* osum = reinterpret_cast<float*>(dyn);   // [4][4 * LP] outputs of the wavefronts
     float* sc = osum + 16 * LP;                    // [n_keys] scores
     const int m = blockIdx.x, hq = blockIdx.y;
-    const int hd = g.head_dim;
-    const int pos = t.row_pos[m];
+    const int hd = g.head_dim, half = hd >> 1;
+    const int pos = t.row_pos[m], b = t.row_seq[m];
+    const uint32_t wmask = t.tree ? t.row_mask[m] : 0xffffffffu;   // chains: n_keys = pos + 1 is the whole rule
+    const int n_cached = t.seq_n[b], slot = t.seq_slot[b], row0 = t.seq_row0[b];
     float* dst = out + ((size_t)m * n_q_heads + hq) * hd;
     if (pos < 0) {
         for (int i = threadIdx.x; i < hd; i += 256) dst[i] = 0.f;
         return;
     }
-    const int n_keys = pos + 1;
-    const int n_cached = t.seq_n[t.row_seq[m]];
-    const uint32_t wmask = t.tree ? t.row_mask[m] : 0xffffffffu;   // chains: n_keys = pos + 1 is the whole rule
-    const int slot = t.seq_slot[t.row_seq[m]];
-    const int hkv = hq / (n_q_heads / g.n_kv_heads);
-    const float* kbase = cache + cache_head_base(g, layer, slot, hkv) + plain_offset(g, 0, 0, 0);
-    const float* vbase = cache + cache_head_base(g, layer, slot, hkv) + plain_offset(g, 1, 0, 0);
+    const int n_keys = pos + 1, window = n_keys - n_cached;   // the row's own place in the window is the last
+    const int group = n_q_heads / g.n_kv_heads, hkv = hq / group;
+    float* kbase = cache + cache_head_base(g, layer, slot, hkv) + plain_offset(g, 0, 0, 0);
+    float* vbase = cache + cache_head_base(g, layer, slot, hkv) + plain_offset(g, 1, 0, 0);
     static_assert((LP & (LP - 1)) == 0 && LP <= 64, "a group of lanes lies within a wavefront");   // 4 * LP >= hd
     constexpr int n_grp = 256 / LP;
     const int sub = threadIdx.x & (LP - 1), grp = threadIdx.x / LP;
@@ -145,30 +149,107 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(StepTables t, CacheGeom g
         }
         return make_float4(d0 < hd ? row[d0] : 0.f, d0 + 1 < hd ? row[d0 + 1] : 0.f, d0 + 2 < hd ? row[d0 + 2] : 0.f, 0.f);
     };
-    const float4 qv = load4(q + ((size_t)m * n_q_heads + hq) * hd);
-    constexpr int U = 4;   // positions per group and trip, requested together (past the end: the last one again)
+    // the same four dims of a head turned to position p
+    auto turned4 = [&](const float* row, int p) -> float4 {
+        const float* cs = cos_sin + (size_t)p * hd;   // [half][2]
+        float r[4], ra, rb;
+        if ((hd & 7) == 0 && d0 < hd) {
+            const bool lower = d0 < half;
+            const int i0 = lower ? d0 : d0 - half;
+            const f32x4u a = *reinterpret_cast<const f32x4u*>(row + i0), bb = *reinterpret_cast<const f32x4u*>(row + i0 + half);
+            const f32x4u c0 = *reinterpret_cast<const f32x4u*>(cs + 2 * i0), c1 = *reinterpret_cast<const f32x4u*>(cs + 2 * i0 + 4);
+            const float co[4] = {c0.x, c0.z, c1.x, c1.z}, si[4] = {c0.y, c0.w, c1.y, c1.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                rotate_pair(a[e], bb[e], co[e], si[e], ra, rb);
+                r[e] = lower ? ra : rb;
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int d = d0 + e;
+                r[e] = 0.f;
+                if (d < hd) {
+                    const int i = d < half ? d : d - half;
+                    rotate_pair(row[i], row[i + half], cs[2 * i], cs[2 * i + 1], ra, rb);
+                    r[e] = d < half ? ra : rb;
+                }
+            }
+        }
+        return make_float4(r[0], r[1], r[2], r[3]);
+    };
+    auto turn_of = [&](int w) { return t.tree ? t.row_rope[row0 + w] : n_cached + w; };   // depth in the window, not the slot
+    constexpr int U = 8;   // positions per group and trip, requested together (past the end: the last one again)
+    float4 v0[U];
+    const int last = max(n_cached - 1, 0);
+    const float4 qv = turned4(qkv + (size_t)m * ld + hq * hd, turn_of(window - 1));
+    // the window's positions of this group (position k belongs to group k % n_grp), in registers from here on
+    constexpr int WN = (SPEC_MAX_LOOKAHEAD + n_grp) / n_grp;
+    const int w0 = (grp - n_cached) & (n_grp - 1);
+    float4 kw[WN], vw[WN];
+#pragma unroll
+    for (int i = 0; i < WN; ++i) {
+        const int w = min(w0 + i * n_grp, window - 1);
+        const float* row = qkv + (size_t)(row0 + w) * ld + (n_q_heads + hkv) * hd;
+        kw[i] = turned4(row, turn_of(w));
+        vw[i] = load4(row + g.n_kv_heads * hd);
+    }
     float mx = -INFINITY;
-    for (int k0 = grp; k0 < n_keys; k0 += U * n_grp) {
+    auto score = [&](int k, float a, bool on) {
+        if (on) {
+            if (sub == 0) sc[k] = a;
+            mx = fmaxf(mx, a);
+        }
+    };
+    auto dot = [&](const float4& k) { return fmaf(qv.x, k.x, fmaf(qv.y, k.y, fmaf(qv.z, k.z, qv.w * k.w))); };
+    auto scores_from = [&](int k0, bool first) {
         float4 kv[U];
 #pragma unroll
-        for (int i = 0; i < U; ++i) kv[i] = load4(kbase + (size_t)min(k0 + i * n_grp, n_keys - 1) * hd);
+        for (int i = 0; i < U; ++i) kv[i] = load4(kbase + (size_t)min(k0 + i * n_grp, last) * hd);
+        if (first) {
+#pragma unroll
+            for (int i = 0; i < U; ++i) v0[i] = load4(vbase + (size_t)min(k0 + i * n_grp, last) * hd);
+        }
         float a[U];
 #pragma unroll
-        for (int i = 0; i < U; ++i) a[i] = fmaf(qv.x, kv[i].x, fmaf(qv.y, kv[i].y, fmaf(qv.z, kv[i].z, qv.w * kv[i].w)));
+        for (int i = 0; i < U; ++i) a[i] = dot(kv[i]);
 #pragma unroll
         for (int o = LP >> 1; o > 0; o >>= 1)   // the positions' sums step by step, side by side
 #pragma unroll
             for (int i = 0; i < U; ++i) a[i] += __shfl_xor(a[i], o);
 #pragma unroll
-        for (int i = 0; i < U; ++i) {
-            const int k = k0 + i * n_grp;
-            if (k < n_keys) {
-                a[i] *= scale;
-                if (k >= n_cached && !((wmask >> (k - n_cached)) & 1u)) a[i] = -INFINITY;   // window slot not on this row's path
-                if (sub == 0) sc[k] = a[i];
-                mx = fmaxf(mx, a[i]);
-            }
+        for (int i = 0; i < U; ++i) score(k0 + i * n_grp, a[i] * scale, k0 + i * n_grp < n_cached);
+    };
+    scores_from(grp, true);   // (all groups: a barrier-free trip whose surplus positions count for nothing)
+    for (int k0 = grp + U * n_grp; k0 < n_cached; k0 += U * n_grp) scores_from(k0, false);
+    {
+        float a[WN];
+#pragma unroll
+        for (int i = 0; i < WN; ++i) a[i] = dot(kw[i]);
+#pragma unroll
+        for (int o = LP >> 1; o > 0; o >>= 1)
+#pragma unroll
+            for (int i = 0; i < WN; ++i) a[i] += __shfl_xor(a[i], o);
+#pragma unroll
+        for (int i = 0; i < WN; ++i) {   // (a window slot that is not on this row's path: -inf)
+            const int w = w0 + i * n_grp;
+            score(n_cached + w, (wmask >> (w & 31)) & 1u ? a[i] * scale : -INFINITY, w < window);
         }
+    }
+    if (hq % group == 0) {   // this row's entry of the cache
+#pragma unroll
+        for (int i = 0; i < WN; ++i)
+            if (w0 + i * n_grp == window - 1) {
+                float* kc = kbase + (size_t)pos * hd;
+                float* vc = vbase + (size_t)pos * hd;
+                const float ke[4] = {kw[i].x, kw[i].y, kw[i].z, kw[i].w}, ve[4] = {vw[i].x, vw[i].y, vw[i].z, vw[i].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (d0 + e < hd) {
+                        kc[d0 + e] = ke[e];
+                        vc[d0 + e] = ve[e];
+                    }
+            }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
@@ -188,25 +269,30 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(StepTables t, CacheGeom g
     __syncthreads();
     z = (red[0] + red[1]) + (red[2] + red[3]);
     float4 o4 = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int k0 = grp; k0 < n_keys; k0 += U * n_grp) {
+    // (a position that takes no part has weight zero; its value, which may be anything, is left out)
+    auto add = [&](float p, const float4& v) {
+        const bool on = p != 0.f;
+        o4.x = on ? fmaf(p, v.x, o4.x) : o4.x;
+        o4.y = on ? fmaf(p, v.y, o4.y) : o4.y;
+        o4.z = on ? fmaf(p, v.z, o4.z) : o4.z;
+        o4.w = on ? fmaf(p, v.w, o4.w) : o4.w;
+    };
+#pragma unroll
+    for (int i = 0; i < U; ++i) add(grp + i * n_grp < n_cached ? sc[grp + i * n_grp] : 0.f, v0[i]);
+    for (int k0 = grp + U * n_grp; k0 < n_cached; k0 += U * n_grp) {
         float4 vv[U];
         float p[U];
 #pragma unroll
         for (int i = 0; i < U; ++i) {
             const int k = k0 + i * n_grp;
-            vv[i] = load4(vbase + (size_t)min(k, n_keys - 1) * hd);
-            p[i] = k < n_keys ? sc[k] : 0.f;
+            vv[i] = load4(vbase + (size_t)min(k, last) * hd);
+            p[i] = k < n_cached ? sc[k] : 0.f;
         }
 #pragma unroll
-        for (int i = 0; i < U; ++i) {
-            // (a position that takes no part has weight zero; its value, which may be anything, is left out)
-            const bool on = p[i] != 0.f;
-            o4.x = on ? fmaf(p[i], vv[i].x, o4.x) : o4.x;
-            o4.y = on ? fmaf(p[i], vv[i].y, o4.y) : o4.y;
-            o4.z = on ? fmaf(p[i], vv[i].z, o4.z) : o4.z;
-            o4.w = on ? fmaf(p[i], vv[i].w, o4.w) : o4.w;
-        }
+        for (int i = 0; i < U; ++i) add(p[i], vv[i]);
     }
+#pragma unroll
+    for (int i = 0; i < WN; ++i) add(w0 + i * n_grp < window ? sc[n_cached + w0 + i * n_grp] : 0.f, vw[i]);
 #pragma unroll
     for (int o = LP; o < 64; o <<= 1) {
         o4.x += __shfl_xor(o4.x, o);
@@ -449,12 +535,13 @@ int launch_attention(int max_kv_len, int cu_count, const StepTables& t, const Lo
     const int hd = g.head_dim;
     const float scale = 1.0f / sqrtf((float)hd);
     if (g.dtype != SPEC_DTYPE_BF16) {
+        if (!src.partial || src.n_split != 1 || src.ns.ssq || !cache_w) return fail(SPEC_ERR_SHAPE, "fp32 attention takes whole, normalised projections");
         // scores for one row live in LDS: positions * 4 bytes
         if ((size_t)(hd + g.t_pad) * sizeof(float) > 60 * 1024) return fail(SPEC_ERR_SHAPE, "fp32 attention supports max_kv_len up to ~15000");
         ProfScope ps(prof, SPEC_PROF_ATTENTION, s);
 #define SPECV_ATTN_F32(LP)                                                                                         \
-    hipLaunchKernelGGL(attn_f32_kernel<LP>, dim3(M, n_q_heads), dim3(256), (size_t)(16 * LP + g.t_pad) * sizeof(float), s, t, g, \
-                       n_q_heads, layer, (const float*)cache, q, scale, xo.plain)
+    hipLaunchKernelGGL(attn_f32_kernel<LP>, dim3(M, n_q_heads), dim3(256), (size_t)(16 * LP + g.t_pad) * sizeof(float), s, src.partial, \
+                       src.cos_sin, (float*)cache_w, xo.plain, n_q_heads, layer, src.ld, scale, t, g)
         if (hd <= 4) SPECV_ATTN_F32(1);
         else if (hd <= 8) SPECV_ATTN_F32(2);
         else if (hd <= 16) SPECV_ATTN_F32(4);

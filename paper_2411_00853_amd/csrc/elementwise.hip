@@ -157,44 +157,6 @@ __global__ void __launch_bounds__(TPB) rope_append_tiled_kernel(const float* __r
     }
 }
 
-// The same for fp32 caches, any even head size: one 64-lane workgroup per (row, head of the q|k|v projection).
-__global__ void __launch_bounds__(64) rope_append_kernel(const float* __restrict__ partial, int ld, StepTables t, CacheGeom g,
-                                                         int n_q_heads, int layer, const float* __restrict__ cos_sin,
-                                                         float* cache, float* __restrict__ q_out)
-{
-    const int m = blockIdx.x, head = blockIdx.y;
-    const int pos = t.row_pos[m];
-    const int rope_pos = t.tree ? t.row_rope[m] : pos;   // loaded alongside pos, not after the branch below
-    const int hd = g.head_dim, half = hd >> 1;
-    const int dq = n_q_heads * hd;
-    const float* row = partial + (size_t)m * ld + head * hd;
-    if (pos < 0) {   // row of a skipped sequence: defined output, no cache write
-        if (head < n_q_heads)
-            for (int i = threadIdx.x; i < hd; i += 64) q_out[(size_t)m * dq + head * hd + i] = 0.f;
-        return;
-    }
-    const int slot = t.seq_slot[t.row_seq[m]];
-    if (head < n_q_heads + g.n_kv_heads) {
-        const float* cs = cos_sin + (size_t)rope_pos * hd;   // [half][2]; depth in the window, not the slot
-        for (int i = threadIdx.x; i < half; i += 64) {
-            const float a = row[i], b = row[i + half];
-            float ra, rb;
-            rotate_pair(a, b, cs[2 * i], cs[2 * i + 1], ra, rb);
-            if (head < n_q_heads) {
-                q_out[(size_t)m * dq + head * hd + i] = ra;
-                q_out[(size_t)m * dq + head * hd + i + half] = rb;
-            } else {
-                const size_t base = cache_head_base(g, layer, slot, head - n_q_heads);
-                cache[base + plain_offset(g, 0, pos, i)] = ra;
-                cache[base + plain_offset(g, 0, pos, i + half)] = rb;
-            }
-        }
-    } else {
-        const size_t base = cache_head_base(g, layer, slot, head - n_q_heads - g.n_kv_heads);
-        for (int i = threadIdx.x; i < hd; i += 64) cache[base + plain_offset(g, 1, pos, i)] = row[i];
-    }
-}
-
 // out[m][n] = sum of the ranges * the row's 1/rms; four columns per thread (rows of out start at any 4-byte address)
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 __global__ void __launch_bounds__(TPB) reduce_splits_kernel(const float* __restrict__ partial, int n_split,
@@ -415,18 +377,12 @@ int launch_rope_append(const float* partial, int n_split, size_t split_stride, i
                        const CacheGeom& g, int n_q_heads, int layer, const float* cos_sin, const NormScale& ns,
                        void* cache, float* q_out, hipStream_t s)
 {
-    const int heads = n_q_heads + 2 * g.n_kv_heads;
-    if (g.dtype == SPEC_DTYPE_BF16) {
-        if (ld % 4 || split_stride % 4) return fail(SPEC_ERR_SHAPE, "QKV rows must be multiples of 4 wide");
-        const int per_wg = 4 * (TPB / 64);   // units of 16 values
-        hipLaunchKernelGGL(rope_append_tiled_kernel, dim3((heads * (g.head_dim / 16) + per_wg - 1) / per_wg, (M + 15) / 16), dim3(TPB), 0, s,
-                           partial, n_split, split_stride, ld, t, g, n_q_heads, M, layer, cos_sin, ns, (uint16_t*)cache, q_out);
-    } else {
-        if (n_split != 1 || ns.ssq) return fail(SPEC_ERR_SHAPE, "fp32 rotation takes whole, normalised projections");
-        hipLaunchKernelGGL(rope_append_kernel, dim3(M, heads), dim3(64), 0, s, partial, ld, t, g, n_q_heads, layer, cos_sin,
-                           (float*)cache, q_out);
-    }
-    SPECV_LAUNCH_CHECK("rope_append_kernel");
+    if (g.dtype != SPEC_DTYPE_BF16) return fail(SPEC_ERR_SHAPE, "fp32 rotation is the attention's");
+    if (ld % 4 || split_stride % 4) return fail(SPEC_ERR_SHAPE, "QKV rows must be multiples of 4 wide");
+    const int units = (n_q_heads + 2 * g.n_kv_heads) * (g.head_dim / 16), per_wg = 4 * (TPB / 64);   // units of 16 values
+    hipLaunchKernelGGL(rope_append_tiled_kernel, dim3((units + per_wg - 1) / per_wg, (M + 15) / 16), dim3(TPB), 0, s, partial, n_split,
+                       split_stride, ld, t, g, n_q_heads, M, layer, cos_sin, ns, (uint16_t*)cache, q_out);
+    SPECV_LAUNCH_CHECK("rope_append_tiled_kernel");
     return SPEC_OK;
 }
 

@@ -47,7 +47,7 @@ int forward_init(spec_handle* h, int max_rows)
         if (rc == SPEC_OK) rc = a.alloc(reinterpret_cast<void**>(p), count * sizeof(float));
     };
     A(&h->x, (size_t)max_rows * z.d);
-    A(&h->q, (size_t)max_rows * z.dq);
+    if (c.dtype == SPEC_DTYPE_BF16) A(&h->q, (size_t)max_rows * z.dq);
     A(&h->logits, (size_t)all_rows * z.V);
     A(&h->cos_sin, (size_t)c.max_kv_len * c.head_dim);
     size_t part = 0;
@@ -299,10 +299,9 @@ int forward_run(spec_handle* h, const StepTables& t, const LookaheadPack& ks, in
         for (int l = 0; l < c.n_layers; ++l) {
             const spec_layer_weights& w = h->layers[l];
             if ((rc = mul(SPEC_PROF_GEMM_QKV, h->x, w.w_qkv, z.nqkv, z.d, h->partial, F32_STORE, w.attn_norm))) return rc;
-            RUN(SPEC_PROF_GLUE, launch_rope_append(h->partial, 1, 0, z.nqkv, t, M, h->geom, c.n_q_heads, l, h->cos_sin,
-                                                   NormScale{nullptr, 0, 0, 0.f}, h->kv_cache, h->q, s));
-            rc = launch_attention(c.max_kv_len, h->cu_count, t, ks, B, M, h->geom, c.n_q_heads, l, h->kv_cache, h->q, nullptr,
-                                  nullptr, 0, XOut{nullptr, 0, 0, h->att}, c.max_lookahead + 1, &h->prof, s);
+            const QkvSrc qkv{h->partial, 1, 0, z.nqkv, NormScale{nullptr, 0, 0, 0.f}, h->cos_sin};
+            rc = launch_attention(c.max_kv_len, h->cu_count, t, ks, B, M, h->geom, c.n_q_heads, l, h->kv_cache, nullptr, nullptr,
+                                  nullptr, 0, XOut{nullptr, 0, 0, h->att}, c.max_lookahead + 1, &h->prof, s, &qkv, h->kv_cache);
             if (rc) return rc;
             if ((rc = mul(SPEC_PROF_GEMM_O, h->att, w.w_o, z.d, z.dq, h->x, F32_ADD, nullptr))) return rc;
             if ((rc = mul(SPEC_PROF_GEMM_GATE_UP, h->x, w.w_gate_up, z.F, z.d, h->act, F32_SWIGLU, w.ffn_norm))) return rc;
