@@ -218,9 +218,19 @@ __global__ void __launch_bounds__(TPB) kv_copy_kernel(CacheGeom g, void* cache, 
 // positions of one dim, so values are turned around in LDS.  Element by element (the kernel above) every
 // 2-byte access to the cache touched a line of its own: 699 MB read and written (7B-shape, 1333 positions) took
 // 1039 us in and 935 us out; by blocks 264 us each way (5.3 TB/s; a plain copy reaches 4.8-5.2).
+// STREAM: 16-byte stores non-temporal as well, for copies that the 256 MB memory-side cache cannot hold (KV_STREAM_BYTES): an import
+// and an export of 699 MB each 525 -> 482 us, of 407 MB 330 -> 292, of 537 MB on the page pool 474 -> 420.  Below, what was written is
+// read again out of that cache, and streaming stores cost 5 to 25 % (67 MB 45 -> 57 us, 201 MB 126 -> 142, 268 MB 170 -> 181).
 typedef unsigned int kv_unit __attribute__((ext_vector_type(4)));
+constexpr size_t KV_STREAM_BYTES = (size_t)384 << 20;
+template <bool STREAM>
+__device__ __forceinline__ void kv_store(const kv_unit& v, kv_unit* p)
+{
+    if constexpr (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
 
-template <int HD, bool TO_CACHE>
+template <int HD, bool TO_CACHE, bool STREAM>
 __global__ void __launch_bounds__(TPB) kv_block_kernel(CacheGeom g, uint16_t* cache, int slot, int pos0, int n_pos,
                                                        uint16_t* plain, int blk0, int n_blk)
 {
@@ -270,7 +280,7 @@ __global__ void __launch_bounds__(TPB) kv_block_kernel(CacheGeom g, uint16_t* ca
             if (inside(v_row(i))) *unit(rows + v_row(i) * LD + v_col(i)) = v[i];
 #pragma unroll
         for (int i = 0; i < PER; ++i)
-            if (inside(kt[i])) *k_cache(i) = k[i];
+            if (inside(kt[i])) kv_store<STREAM>(k[i], k_cache(i));
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
@@ -280,7 +290,7 @@ __global__ void __launch_bounds__(TPB) kv_block_kernel(CacheGeom g, uint16_t* ca
             if (lo == 0 && hi == 32) {
                 kv_unit u;
                 __builtin_memcpy(&u, e8, 16);
-                *v_cache(i) = u;
+                kv_store<STREAM>(u, v_cache(i));
             } else {   // the block's other positions may hold entries: only these are written
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
@@ -302,11 +312,11 @@ __global__ void __launch_bounds__(TPB) kv_block_kernel(CacheGeom g, uint16_t* ca
         }
 #pragma unroll
         for (int i = 0; i < PER; ++i)
-            if (inside(kt[i])) *k_plain(i) = k[i];
+            if (inside(kt[i])) kv_store<STREAM>(k[i], k_plain(i));
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < PER; ++i)
-            if (inside(v_row(i))) *unit(vp + (ptrdiff_t)v_row(i) * HD + v_col(i)) = *unit(rows + v_row(i) * LD + v_col(i));
+            if (inside(v_row(i))) kv_store<STREAM>(*unit(rows + v_row(i) * LD + v_col(i)), unit(vp + (ptrdiff_t)v_row(i) * HD + v_col(i)));
     }
 }
 
@@ -456,9 +466,12 @@ int launch_kv_copy(const CacheGeom& g, void* cache, int slot, int pos0, int n_po
         const size_t groups = (size_t)g.n_layers * n_blk * g.n_kv_heads;
         if (groups <= 0x7fffffff) {
             const dim3 grid((unsigned)groups);
-#define SPECV_KV_BLOCK(HD, IN)                                                                                    \
-    hipLaunchKernelGGL((kv_block_kernel<HD, IN>), grid, dim3(TPB), 0, s, g, (uint16_t*)cache, slot, pos0, n_pos, \
-                       (uint16_t*)plain, blk0, n_blk)
+            const bool stream = (size_t)g.n_layers * 2 * g.n_kv_heads * n_pos * g.head_dim * sizeof(uint16_t) >= KV_STREAM_BYTES;
+#define SPECV_KV_BLOCK(HD, IN)                                                                                                   \
+    do {                                                                                                                         \
+        auto* k = stream ? kv_block_kernel<HD, IN, true> : kv_block_kernel<HD, IN, false>;                                       \
+        hipLaunchKernelGGL(k, grid, dim3(TPB), 0, s, g, (uint16_t*)cache, slot, pos0, n_pos, (uint16_t*)plain, blk0, n_blk);     \
+    } while (0)
             if (g.head_dim == 128) {
                 if (to_cache) SPECV_KV_BLOCK(128, true);
                 else SPECV_KV_BLOCK(128, false);
