@@ -146,6 +146,16 @@ __global__ void __launch_bounds__(64 * CG * RS) gemm_skinny_kernel(const u32x4* 
     int xoff[UPT];
 #pragma unroll
     for (int u = 0; u < UPT; ++u) xoff[u] = min(u * TPBK + (int)threadIdx.x, CHUNK_U4 - 1);   // surplus threads repeat
+    // Two row tiles: X through a buffer descriptor, whose bound makes rows past the last fetch nothing (their zeros are never
+    // stored).  Steps of four layers, 17 to 24 rows: 7B shape -2.0..-2.2 %, 3072 wide -2.3..-2.5, 1B shape -1.5..-1.8, 1536 and 1024 wide
+    // -0.9 and -0.1..-0.4; 32 rows -1.1, -0.9 and 0.  One row tile within 0.5 % either way, three +4 % at 48 rows, four mixed.
+    constexpr bool X_BUFFER = MT == 2;
+    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4*>(Xf), 0, (kb_total + XFRAG_PAD_KB) * PLANES * MT * 1024, 0x00027000);
+    uint32_t xbyte[UPT];
+    if constexpr (X_BUFFER) {
+#pragma unroll
+        for (int u = 0; u < UPT; ++u) xbyte[u] = ((xoff[u] >> 6) % MT) * 16 + (xoff[u] & 15) < M ? xoff[u] * 16u : 0x40000000u;
+    }
 
     // W tile order: [K group of 4 blocks][column tile][block in group][lane] -- the chunk a workgroup
     // reads in one step (its 4*NT tiles, KC blocks) is one contiguous run, and workgroups of
@@ -188,9 +198,15 @@ __global__ void __launch_bounds__(64 * CG * RS) gemm_skinny_kernel(const u32x4* 
     auto load_x = [&](int kbase) {
         // fragment buffers carry XFRAG_PAD_KB zeroed blocks past kb_total, so the last chunk of the
         // last range may overhang
-        const u32x4* src = Xf + (size_t)min(kbase, kb1 - 1) * (PLANES * MT * 64);
+        const int kb = min(kbase, kb1 - 1);
+        if constexpr (X_BUFFER) {
 #pragma unroll
-        for (int u = 0; u < UPT; ++u) xr[u] = src[xoff[u]];
+            for (int u = 0; u < UPT; ++u) xr[u] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, xbyte[u], kb * (PLANES * MT * 1024), 0);
+        } else {
+            const u32x4* src = Xf + (size_t)kb * (PLANES * MT * 64);
+#pragma unroll
+            for (int u = 0; u < UPT; ++u) xr[u] = src[xoff[u]];
+        }
     };
     auto store_x = [&](int buf) {
 #pragma unroll
