@@ -5,6 +5,8 @@
 #include <stdint.h>
 #include <stddef.h>
 
+#include <algorithm>
+
 #include "../../include/spec_verify.h"
 #include "../../include/spec_kernels.h"
 
@@ -128,15 +130,15 @@ struct LogitsSrc {
 
 // ---- sampler (sampler.hip) ---------------------------------------------------------------------
 constexpr int STAT_CHUNK = 16384;   // logits per workgroup in the statistics pass
-constexpr int RES_CHUNK = 4096;    // logits per workgroup in the residual pass / final scan
+constexpr int RES_CHUNK = 4096;    // logits per workgroup in the residual pass of many sequences (2048 for few)
+
+constexpr int ARRIVED_STRIDE = 32;   // a line per count: one after the other in a line, the counts of all sequences queue up there
 
 struct SamplerWorkspace {
     float* part_max;      // [stat rows][stat chunks] chunk maxima of raw logits
     double* part_sum;     // [stat rows][stat chunks] sum exp((l - chunk max)/T)
-    double* chunk_mass;   // [B][res chunks] mass of the final-draw distribution per chunk
-    int32_t* accepted;    // [B] a_b
-    double* row_inv_z;    // [B][2] 1/Z of the two rows the final draw reads (p, q)
-    float* row_max;       // [B][2] their maxima
+    double* slice_mass;   // [slice_masses(B, V)] mass of the final-draw distribution per sequence and slice of the vocabulary
+    int32_t* arrived;     // [B][ARRIVED_STRIDE] how many of a sequence's slices are done: zero between launches
     int32_t* part_idx;    // [stat rows][stat chunks] greedy rule: lowest id holding the chunk maximum
 };
 
@@ -159,6 +161,9 @@ int launch_embed(const EmbedTo& e, const int32_t* row_tok, int M, hipStream_t s)
 
 // embed != NULL (steps of M <= EMBED_MAX_ROWS window rows): the same launch embeds the rows
 constexpr int EMBED_MAX_ROWS = SPEC_MAX_STEP_ROWS;
+// slices of RES_CHUNK, or of half of that while a launch has up to 1024 of them
+inline size_t slice_masses(int B, int V) { return std::max((size_t)B * ((V + RES_CHUNK - 1) / RES_CHUNK), (size_t)1024); }
+
 int launch_prepare(const StepTables& t, const LookaheadPack& ks, int B, int Kmax, int V, int max_batch,
                    int max_kv_len, bool has_cache, const int32_t* seq_slot, const int32_t* last_token,
                    const int32_t* draft_tokens, const int32_t* kv_len, int32_t* flag, hipStream_t s,

@@ -581,313 +581,6 @@ __device__ __forceinline__ void combine_rows(const float* part_max, const double
 }
 
 // ---------------------------------------------------------------------------------------------
-// Pass 2: accept scan (every workgroup of a sequence repeats it: a handful of scalars) and the
-// mass of the final-draw distribution inside this workgroup's chunk of the vocabulary.
-// Two rows of logits stream through it, but what it waits for is the chain in front of them: statistics, test, and
-// only then the address of the rows (64 sequences x 32 chunks of a 128256 vocabulary: 18.5 us of which 10 are the
-// bytes; 20.5 with one thread per row combining the statistics and the proposals' logits requested after that).
-// ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(TPB) accept_mass_kernel(const int32_t* seq_stat0, const int32_t* seq_row0,
-                                                          const int32_t* __restrict__ draft_tokens,
-                                                          const float* __restrict__ part_max,
-                                                          const double* __restrict__ part_sum, int Kmax, int V,
-                                                          int n_stat_chunks, int u_stride,
-                                                          const float* __restrict__ uniforms,
-                                                          const float* __restrict__ target,
-                                                          const float* __restrict__ draft, int n_res_chunks, float inv_T_f,
-                                                          LookaheadPack ks, SamplerWorkspace w)
-{
-    __shared__ float row_m[2 * SPEC_MAX_LOOKAHEAD + 2];
-    __shared__ double row_z[2 * SPEC_MAX_LOOKAHEAD + 2];
-    __shared__ int s_a;
-    __shared__ double ssum[TPB / 64];
-    const int b = blockIdx.y;
-    const int chunk = blockIdx.x;
-    const int K = ks.k[b];
-    const double inv_T = (double)inv_T_f;
-    const int st0 = seq_stat0[b];
-    const float* trow0 = target + (size_t)seq_row0[b] * V;
-    const float* drow0 = draft + (size_t)b * Kmax * V;
-    // lane i tests proposal i (all positions at once: the tests are independent, only the first
-    // failure matters); padding lanes repeat the last proposal and are masked out.  Its logits are requested
-    // before the statistics are put together: that is one chain of memory round trips less in a row.
-    const int i = min((int)threadIdx.x, max(K - 1, 0));
-    float lp_x = 0.f, lq_x = 0.f;
-    double u = 0.0;
-    if (threadIdx.x < 64 && K > 0) {
-        const int x = draft_tokens[b * Kmax + i];
-        const bool xin = x >= 0 && x < V;   // out-of-range ids were flagged by prepare; stay in bounds
-        u = (double)uniforms[b * u_stride + i];
-        lp_x = xin ? trow0[(size_t)i * V + x] : 0.f;
-        lq_x = xin ? drow0[(size_t)i * V + x] : 0.f;
-    }
-    __shared__ CombineLds comb;
-    combine_rows<TPB>(part_max, part_sum, st0, 2 * K + 1, n_stat_chunks, inv_T, row_m, row_z, comb);
-    if (threadIdx.x < 64) {
-        bool keep = true;
-        if (K > 0) {
-            const double ep = exp((double)(lp_x - row_m[i]) * inv_T);
-            const double eq = exp((double)(lq_x - row_m[K + 1 + i]) * inv_T);
-            // keep iff u * q(x) < p(x)  <=>  u * eq * Zp < ep * Zq
-            keep = u * eq * row_z[i] < ep * row_z[K + 1 + i];
-        }
-        const unsigned long long failed = __ballot(!keep && (int)threadIdx.x < K);
-        if (threadIdx.x == 0) s_a = failed ? __builtin_ctzll(failed) : K;
-    }
-    __syncthreads();
-    const int a = s_a;
-    const bool residual = a < K;
-    const float* prow = trow0 + (size_t)a * V;            // a == K: the extra-token row
-    const float* qrow = drow0 + (size_t)(residual ? a : 0) * V;
-    const float mp = row_m[a];
-    const double izp = 1.0 / row_z[a];
-    const float mq = residual ? row_m[K + 1 + a] : 0.f;
-    const double izq = residual ? 1.0 / row_z[K + 1 + a] : 0.0;
-
-    const int base = chunk * RES_CHUNK;
-    const int lim = min(RES_CHUNK, V - base);
-    // all of a lane's logits are requested before the first is used (indices past the end clamped,
-    // their terms dropped): one memory round trip instead of one per element
-    constexpr int PER = RES_CHUNK / TPB;
-    float lp[PER], lq[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) lp[k] = prow[base + min((int)threadIdx.x + k * TPB, lim - 1)];
-    if (residual) {
-#pragma unroll
-        for (int k = 0; k < PER; ++k) lq[k] = qrow[base + min((int)threadIdx.x + k * TPB, lim - 1)];
-    }
-    double acc = 0.0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        double pv = (double)__expf((lp[k] - mp) * inv_T_f) * izp;
-        if (residual) {
-            double qv = (double)__expf((lq[k] - mq) * inv_T_f) * izq;
-            pv = pv > qv ? pv - qv : 0.0;
-        }
-        if ((int)threadIdx.x + k * TPB < lim) acc += pv;
-    }
-    acc = wave_sum(acc);
-    if ((threadIdx.x & 63) == 0) ssum[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        w.chunk_mass[(size_t)b * n_res_chunks + chunk] = (ssum[0] + ssum[1]) + (ssum[2] + ssum[3]);
-        if (chunk == 0) {
-            w.accepted[b] = a;
-            w.row_max[2 * b] = mp;
-            w.row_max[2 * b + 1] = mq;
-            w.row_inv_z[2 * b] = izp;
-            w.row_inv_z[2 * b + 1] = izq;
-        }
-    }
-}
-
-// Of the lanes of a wavefront whose running sum inc (own share loc, of PER ids with the masses x) passes the target, the first one
-// that has mass: which of its ids the target falls on, the first whose running sum passes it (rounding between that sum and inc: the
-// last id with mass).  -1 for the other lanes.  The lanes add up in different orders, so neighbours' ranges [inc - loc, inc) may
-// leave a gap or overlap by rounding: a lane is not asked whether the target lies in its range.
-template <int PER>
-__device__ __forceinline__ int lowest_crossing(const double* x, double loc, double inc, double target)
-{
-    const unsigned long long over = __ballot(loc > 0.0 && inc > target);
-    if (!over || (int)(threadIdx.x & 63) != __ffsll((long long)over) - 1) return -1;
-    double cdf = inc - loc;
-    int first = -1, last = -1;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        cdf += x[i];
-        if (first < 0 && x[i] > 0.0 && cdf > target) first = i;
-        if (x[i] > 0.0) last = i;
-    }
-    return first >= 0 ? first : last;
-}
-
-// ---------------------------------------------------------------------------------------------
-// Pass 3: locate u*S among the chunk masses, scan that chunk in ascending token id, emit.
-// Latency only, one workgroup per sequence (11 -> 9.3 us at 64 sequences: the masses walked eight at a time, padding
-// between the lanes' ids in LDS, where 128 bytes from lane to lane put all of them on one bank).
-// ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(TPB) final_draw_kernel(const int32_t* accepted, const double* chunk_mass, const int32_t* seq_row0,
-                                                         const float* __restrict__ uniforms, int u_stride, int n_res_chunks,
-                                                         int Kmax, int V, const float* row_max, float inv_T_f,
-                                                         const double* row_inv_z, const float* __restrict__ target,
-                                                         const float* __restrict__ draft,
-                                                         const int32_t* __restrict__ draft_tokens, int auto_rollback,
-                                                         int32_t* kv_len, int32_t* __restrict__ n_accepted,
-                                                         int32_t* __restrict__ out_tokens, StepTables t, LookaheadPack ks,
-                                                         DrawEmit emit)
-{
-    __shared__ double r[RES_CHUNK + RES_CHUNK / 16];   // 16 consecutive ids per lane, a word of padding between lanes
-    __shared__ double wave_tot[TPB / 64];
-    __shared__ int s_chunk, s_tok;
-    __shared__ double s_before, s_target;
-    const int b = blockIdx.x;
-    const int K = ks.k[b];
-    if (!t.seq_ok[b]) {
-        if (emit.tokens) {   // plain draw: an invalid id makes whoever consumes it skip the sequence too
-            if (threadIdx.x == 0) {
-                emit.tokens[b * emit.stride + emit.offset] = -1;
-                emit.next_token[b] = -1;
-            }
-            return;
-        }
-        if (threadIdx.x == 0) n_accepted[b] = -1;
-        for (int i = threadIdx.x; i <= Kmax; i += TPB) out_tokens[b * (Kmax + 1) + i] = -1;
-        return;
-    }
-    // everything that does not depend on the chunk is requested at once, the chunk masses by as many lanes
-    const int a = accepted[b];
-    const int row0 = seq_row0[b];
-    const float mp = row_max[2 * b], mq = row_max[2 * b + 1];
-    const double izp = row_inv_z[2 * b], izq = row_inv_z[2 * b + 1];
-    const double u = (double)uniforms[b * u_stride + K];
-    bool residual = a < K;
-    __shared__ double s_mass[TPB];
-    const double* mass = chunk_mass + (size_t)b * n_res_chunks;
-    const bool in_lds = n_res_chunks <= TPB;
-    if (in_lds) s_mass[threadIdx.x] = (int)threadIdx.x < n_res_chunks ? mass[threadIdx.x] : 0.0;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        // one lane walks the masses in chunk order, eight at a time (past the end: zeros, which change nothing)
-        auto eight = [&](int c, double(&v)[8]) {
-            if (in_lds) {
-#pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] = s_mass[min(c + k, TPB - 1)];
-            } else {
-#pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] = mass[min(c + k, n_res_chunks - 1)];
-            }
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = c + k < n_res_chunks ? v[k] : 0.0;
-        };
-        double S = 0.0;
-        for (int c = 0; c < n_res_chunks; c += 8) {
-            double v[8];
-            eight(c, v);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) S += v[k];
-        }
-        // S > 0 always holds for the extra-token row; for a residual it holds in exact arithmetic
-        // (a rejection means p(x) < q(x), so p exceeds q elsewhere).  S <= 0 falls back to p_a below.
-        s_before = S;
-        s_chunk = -1;
-        if (S > 0.0) {
-            const double target_mass = u * S;
-            double c0 = 0.0;
-            int pick = -1, last_pos = -1;
-            double last_before = 0.0;
-            for (int c = 0; c < n_res_chunks && pick < 0; c += 8) {
-                double v[8];
-                eight(c, v);
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    if (pick < 0) {
-                        if (v[k] > 0.0) { last_pos = c + k; last_before = c0; }
-                        if (c0 + v[k] > target_mass) pick = c + k;
-                        else c0 += v[k];
-                    }
-                }
-            }
-            if (pick < 0) { pick = last_pos; c0 = last_before; }
-            s_chunk = pick;
-            s_before = c0;
-            s_target = target_mass;
-        }
-    }
-    __syncthreads();
-    const float* prow = target + (size_t)(row0 + a) * V;
-    const float* qrow = draft + ((size_t)b * Kmax + (residual ? a : 0)) * V;
-    int c_lo = s_chunk, c_hi = s_chunk + 1;
-    double before = s_before, target_mass = s_target;
-    if (s_chunk < 0) {   // degenerate residual: draw from p_a over the whole vocabulary, chunk by chunk
-        residual = false;
-        c_lo = 0;
-        c_hi = n_res_chunks;
-        before = 0.0;
-        target_mass = u;   // p_a sums to 1
-    }
-    if (threadIdx.x == 0) s_tok = V;   // none yet
-    int last_positive = -1;
-    constexpr int PER = RES_CHUNK / TPB;   // 16 consecutive ids per lane
-    for (int c = c_lo; c < c_hi; ++c) {
-        const int base = c * RES_CHUNK;
-        const int lim = min(RES_CHUNK, V - base);
-        __syncthreads();
-        {
-            // all loads first (clamped), then the arithmetic: one memory round trip per chunk
-            float lp[PER], lq[PER];
-#pragma unroll
-            for (int k = 0; k < PER; ++k) lp[k] = prow[base + min((int)threadIdx.x + k * TPB, lim - 1)];
-            if (residual) {
-#pragma unroll
-                for (int k = 0; k < PER; ++k) lq[k] = qrow[base + min((int)threadIdx.x + k * TPB, lim - 1)];
-            }
-#pragma unroll
-            for (int k = 0; k < PER; ++k) {
-                const int i = threadIdx.x + k * TPB;
-                double pv = (double)__expf((lp[k] - mp) * inv_T_f) * izp;
-                if (residual) {
-                    double qv = (double)__expf((lq[k] - mq) * inv_T_f) * izq;
-                    pv = pv > qv ? pv - qv : 0.0;
-                }
-                r[i + i / PER] = i < lim ? pv : 0.0;
-            }
-        }
-        __syncthreads();
-        // lane-local sums of 16 consecutive ids, then an inclusive scan over the 256 lanes
-        double loc = 0.0;
-        int my_last = -1;
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            double x = r[threadIdx.x * (PER + 1) + i];
-            loc += x;
-            if (x > 0.0) my_last = base + threadIdx.x * PER + i;
-        }
-        double inc = wave_scan(loc);
-        if ((threadIdx.x & 63) == 63) wave_tot[threadIdx.x >> 6] = inc;
-        __syncthreads();
-        double off = before;
-        for (int wv = 0; wv < (int)(threadIdx.x >> 6); ++wv) off += wave_tot[wv];
-        inc += off;
-        // the first lane with mass whose running sum passes the target walks its ids (see lowest_crossing)
-        const int tok = lowest_crossing<PER>(r + threadIdx.x * (PER + 1), loc, inc, target_mass);
-        if (tok >= 0) atomicMin(&s_tok, base + threadIdx.x * PER + tok);
-        // remember the last id with positive mass in case rounding leaves no crossing at all
-        int wl = my_last;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) wl = max(wl, __shfl_xor(wl, o));
-        last_positive = max(last_positive, wl);
-        __syncthreads();
-        if (s_tok < V) break;
-        before += (wave_tot[0] + wave_tot[1]) + (wave_tot[2] + wave_tot[3]);
-    }
-    __syncthreads();
-    // cross-wave maximum of last_positive through LDS (reuse wave_tot storage as ints is not safe; use r)
-    int* scratch = reinterpret_cast<int*>(r);
-    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = last_positive;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int y = s_tok;
-        if (y >= V) y = max(max(scratch[0], scratch[1]), max(scratch[2], scratch[3]));
-        if (y < 0) y = 0;
-        if (emit.tokens) {
-            emit.tokens[b * emit.stride + emit.offset] = y;
-            emit.next_token[b] = y;
-            if (emit.kv_len) emit.kv_len[t.seq_slot[b]] = t.seq_n[b] + emit.kv_add;
-            return;
-        }
-        n_accepted[b] = a;
-        int32_t* o = out_tokens + b * (Kmax + 1);
-        for (int i = 0; i < a; ++i) o[i] = draft_tokens[b * Kmax + i];
-        o[a] = y;
-        for (int i = a + 1; i <= Kmax; ++i) o[i] = -1;
-        if (kv_len) {
-            kv_len[t.seq_slot[b]] = t.seq_n[b] + (auto_rollback ? a : K) + 1;
-            pool_trim(t.pool, t.seq_slot[b], t.seq_n[b] + (auto_rollback ? a : K) + 1);
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------------------------
 // Vocabularies of up to DRAW_MAX: one workgroup per sequence keeps the row (or the two rows) of the draw in registers, so
 // what the two passes above do -- and for a plain draw the statistics in front of them -- is one launch, without a second
 // read of the rows.  RUNS runs of 256 ids per wavefront: wavefront w holds ids [256 RUNS w, 256 RUNS (w + 1)), lane l of it
@@ -895,16 +588,25 @@ __global__ void __launch_bounds__(TPB) final_draw_kernel(const int32_t* accepted
 // ---------------------------------------------------------------------------------------------
 constexpr int DRAW_TPB = 1024, DRAW_WAVES = DRAW_TPB / 64, DRAW_MAX_RUNS = 8;
 constexpr int DRAW_MAX = DRAW_WAVES * 256 * DRAW_MAX_RUNS;   // 32768
-static_assert(DRAW_WAVES == 16, "the wavefronts' sums are scanned by 16 lanes");
+static_assert(DRAW_WAVES <= 16, "the wavefronts' sums are scanned by 16 lanes");
+constexpr int SLICE_MIN = 16384;   // accept_slice_kernel beyond: 16000 and two sequences 13.5 us in one workgroup each, 13.9 shared out, 20000 and 64 29.2 and 26.9
 constexpr int STATS_MAX = 2048;                              // a row in a wavefront's registers
 inline int draw_runs(int V) { return V <= 4096 ? 1 : V <= 8192 ? 2 : V <= 16384 ? 4 : 8; }
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // global memory takes 16-byte accesses at any 4-byte address
 
-// four ids from id0 on of each of N runs of a row of V logits; past the end -inf
-template <int N>
+// four ids from id0 on of each of N runs of a row of V logits; past the end -inf.  WHOLE: where all of the wavefront's ids exist (id0 is
+// its first id plus four times the lane) nothing is shifted, which is a seventh of a mass's arithmetic (64 sequences of 100000 25.3 ->
+// 24.6 us); the tree's draw, whose registers are full, is better off without (a step of 88 rows 854 -> 868 us with it).
+template <bool WHOLE = true, int N>
 __device__ __forceinline__ void draw_load(const float* row, int V, int id0, floatx4 (&v)[N])
 {
-    if (V >= 4) {   // every lane loads four ids that exist, the row's last ones shifted into place
+    if (WHOLE && __builtin_amdgcn_readfirstlane(id0) + 256 * N <= V) {   // (lane 0 has the wavefront's first ids) all of them exist
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const f32x4u x = *reinterpret_cast<const f32x4u*>(row + id0 + 256 * j);
+            v[j] = floatx4{x.x, x.y, x.z, x.w};
+        }
+    } else if (V >= 4) {   // every lane loads four ids that exist, the row's last ones shifted into place
         f32x4u x[N];
 #pragma unroll
         for (int j = 0; j < N; ++j) x[j] = *reinterpret_cast<const f32x4u*>(row + min(id0 + 256 * j, V - 4));
@@ -949,11 +651,12 @@ struct DrawLds {
 };
 
 // The id at which the running sum of the masses (never negative) first exceeds u times the whole (absolute: u itself), ids
-// ascending; if rounding leaves no crossing, the last id with mass of the stretch looked at.  run: this thread's sums of
+// ascending; if rounding leaves no crossing, the last id with mass of the stretch looked at.  PART: the workgroup holds a part of
+// the row, below is the mass of what lies before it.  run: this thread's sums of
 // its four ids of every run; four(j, x): those ids' masses again.  Returns false if there is no mass (nothing drawn).  All
 // threads call; the result is in l.tok for all of them.
-template <int RUNS, typename F>
-__device__ __forceinline__ bool draw_locate(double (&run)[RUNS], F four, double u, bool absolute, DrawLds& l)
+template <int RUNS, int WAVES, bool PART = false, typename F>
+__device__ __forceinline__ bool draw_locate(double (&run)[RUNS], F four, double u, bool absolute, DrawLds& l, double below = 0.0)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     double t = 0.0;
@@ -963,15 +666,15 @@ __device__ __forceinline__ bool draw_locate(double (&run)[RUNS], F four, double 
     if (lane == 0) l.tot[wave] = t;
     __syncthreads();
     // lane w takes wavefront w's sum: the first of them whose running sum passes the target
-    const double tw = lane < DRAW_WAVES ? l.tot[lane] : 0.0;
-    const double upto = row_scan(tw), S = read_lane(upto, DRAW_WAVES - 1);
+    const double tw = lane < WAVES ? l.tot[lane] : 0.0;
+    const double upto = PART ? below + row_scan(tw) : row_scan(tw), S = read_lane(upto, WAVES - 1);
     if (!absolute && !(S > 0.0)) return false;
     const double target = absolute ? u : u * S;
     // Only what has mass is picked, at each of the three levels below: lanes add the running sums up in different orders, so behind
     // the last mass before the target one may stand above it by its last bit (two halves alike and u = 0.5: an excluded id in 8 % of the draws).
     const unsigned long long over = __ballot(tw > 0.0 && upto > target), some = __ballot(tw > 0.0);   // (lanes past the wavefronts: 0)
     const int pick = over ? __ffsll((long long)over) - 1 : some ? 63 - __clzll((long long)some) : 0;
-    const double before = pick > 0 ? read_lane(upto, pick - 1) : 0.0;
+    const double before = pick > 0 ? read_lane(upto, pick - 1) : PART ? below : 0.0;
     if (wave == pick) {   // the only wavefront that looks closer: which run, which lane, which id
         int at = -1, last_run = 0;
         double c0 = before, at_before = before, last_before = before;
@@ -1007,7 +710,7 @@ __device__ __forceinline__ bool draw_locate(double (&run)[RUNS], F four, double 
     return true;
 }
 
-// what a draw leaves behind, as final_draw_kernel does it; the first wavefront calls.  x: lane i holds proposal i.
+// What a draw leaves behind; the first wavefront calls.  x: lane i holds proposal i.
 __device__ __forceinline__ void draw_emit(const StepTables& t, const DrawEmit& emit, int b, int slot, int n, int K, int Kmax, int a,
                                           int y, int x, int auto_rollback, int32_t* kv_len, int32_t* n_accepted, int32_t* out_tokens)
 {
@@ -1046,8 +749,8 @@ __device__ __forceinline__ void draw_skip(const DrawEmit& emit, int b, int Kmax,
     if (i <= Kmax) out_tokens[b * (Kmax + 1) + i] = -1;
 }
 
-// After the statistics: accept scan, mass of the final draw's distribution, the draw, the results.
-// (accept_mass_kernel and final_draw_kernel in one.)  STATS: the statistics as well, a wavefront per row -- at most 31 rows of
+// After the statistics: accept scan, mass of the final draw's distribution, the draw, the results.  Rows of up to SLICE_MIN
+// logits; longer ones are shared out (accept_slice_kernel).  STATS: the statistics as well, a wavefront per row -- at most 31 rows of
 // STATS_MAX logits, which one compute unit reads in the time that a launch takes (fp32 model of vocabulary 1024, one sequence of
 // five rows: 4.3 + 5.9 us as two launches, 7.8 as one).
 template <int RUNS, bool STATS>
@@ -1073,7 +776,7 @@ __global__ void __launch_bounds__(DRAW_TPB) accept_draw_kernel(const int32_t* se
     const double inv_T = (double)inv_T_f;
     const float* trow0 = target + (size_t)row0 * V;
     const float* drow0 = draft + (size_t)b * Kmax * V;
-    const int i = min((int)threadIdx.x, max(K - 1, 0));   // lane i tests proposal i, see accept_mass_kernel
+    const int i = min((int)threadIdx.x, max(K - 1, 0));   // lane i tests proposal i, all positions at once
     float lp_x = 0.f, lq_x = 0.f;
     double u = 0.0;
     int x = 0;
@@ -1155,14 +858,14 @@ __global__ void __launch_bounds__(DRAW_TPB) accept_draw_kernel(const int32_t* se
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[e] = mass(p[0][e], q[0][e]);
     };
-    if (!draw_locate(run, four, u_draw, false, l)) {   // no mass left (impossible in exact arithmetic): draw from p_a, which sums to 1
+    if (!draw_locate<RUNS, DRAW_WAVES>(run, four, u_draw, false, l)) {   // no mass left (impossible in exact arithmetic): draw from p_a, which sums to 1
         __syncthreads();
         auto plain = [&](float lp) { return (double)__expf((lp - mp) * inv_T_f) * izp; };
         floatx4 p[RUNS];
         draw_load(prow, V, draw_id0<RUNS>(), p);
 #pragma unroll
         for (int j = 0; j < RUNS; ++j) run[j] = (plain(p[j].x) + plain(p[j].y)) + (plain(p[j].z) + plain(p[j].w));
-        draw_locate(run, [&](int j, double (&x)[4]) {
+        draw_locate<RUNS, DRAW_WAVES>(run, [&](int j, double (&x)[4]) {
             floatx4 p1[1];
             draw_load(prow, V, draw_id0<RUNS>() + 256 * j, p1);
 #pragma unroll
@@ -1170,6 +873,170 @@ __global__ void __launch_bounds__(DRAW_TPB) accept_draw_kernel(const int32_t* se
         }, u_draw, true, l);
     }
     if (threadIdx.x < 64) draw_emit(t, DrawEmit{}, b, slot, n, K, Kmax, a, l.tok, x, auto_rollback, kv_len, n_accepted, out_tokens);
+}
+
+// The same for longer rows: a workgroup per sequence and slice of 1024 RUNS ids.  Every workgroup repeats the accept scan (a handful
+// of scalars) and sums the mass of its slice; whichever of a sequence's workgroups comes last finds the slice that the
+// target falls on, reads it again and draws.  The mass of an id is two exponentials and a few fp64 operations, 84 issue
+// cycles for a wavefront's 64: a row of 32000 in one workgroup of 1024 threads spent 4 to 5 us on them alone, and two
+// launches (masses, then draw) a launch and another chain of round trips.  The sampling part alone, us before and now: 4
+// sequences of 32003 16.4 -> 14.1, 8 of 32000 17.7 -> 14.2, 32 of 32000 19.7 -> 17.0, one of 128256 18.5 -> 13.9, 16 of 128256 29.0
+// -> 24.7, 64 of 128256 109.0 -> 107.9.  128 of 128256 stay where they were, 200 of 65536 lose 2 %.
+//
+// No workgroup waits for another: each stores its mass with an atomic store at device scope, waits until that has arrived, and then
+// counts itself; the one that counts last sees all masses, and leaves the count at zero for the next launch.
+template <int RUNS>
+__global__ void __launch_bounds__(TPB) accept_slice_kernel(const int32_t* seq_stat0, const int32_t* seq_row0,
+                                                           const int32_t* __restrict__ draft_tokens,
+                                                           const float* __restrict__ part_max,
+                                                           const double* __restrict__ part_sum, int Kmax, int V,
+                                                           int n_stat_chunks, int u_stride,
+                                                           const float* __restrict__ uniforms,
+                                                           const float* __restrict__ target,
+                                                           const float* __restrict__ draft, float inv_T_f, int auto_rollback,
+                                                           int32_t* kv_len, int32_t* __restrict__ n_accepted,
+                                                           int32_t* __restrict__ out_tokens, double* slice_mass, int32_t* arrived,
+                                                           StepTables t, DrawEmit emit, LookaheadPack ks)
+{
+    constexpr int WAVES = TPB / 64, SLICE = TPB * 4 * RUNS;
+    __shared__ float row_m[2 * SPEC_MAX_LOOKAHEAD + 2];
+    __shared__ double row_z[2 * SPEC_MAX_LOOKAHEAD + 2];
+    __shared__ int s_a, s_last;
+    __shared__ double s_iz[2];
+    __shared__ DrawLds l;
+    __shared__ CombineLds comb;
+    const int b = blockIdx.y, slice = blockIdx.x, n_slices = gridDim.x, lane = threadIdx.x & 63;
+    const int st0 = seq_stat0[b], row0 = seq_row0[b], ok = t.seq_ok[b], slot = t.seq_slot[b], n = t.seq_n[b];
+    const int K = ks.k[b];
+    const double inv_T = (double)inv_T_f;
+    const float* trow0 = target + (size_t)row0 * V;
+    const float* drow0 = draft + (size_t)b * Kmax * V;
+    // lane i tests proposal i (all positions at once: only the first failure matters); padding lanes repeat the last
+    // proposal and are masked out.  Its logits are requested before the statistics are put together.
+    const int i = min((int)threadIdx.x, max(K - 1, 0));
+    float lp_x = 0.f, lq_x = 0.f;
+    double u = 0.0;
+    int x = 0;
+    if (threadIdx.x < 64 && K > 0) {
+        x = draft_tokens[b * Kmax + i];
+        const bool xin = x >= 0 && x < V;   // out-of-range ids were flagged by prepare; stay in bounds
+        u = (double)uniforms[b * u_stride + i];
+        lp_x = xin ? trow0[(size_t)i * V + x] : 0.f;
+        lq_x = xin ? drow0[(size_t)i * V + x] : 0.f;
+    }
+    const double u_draw = (double)uniforms[b * u_stride + K];
+    if (!ok) {
+        if (slice == 0) draw_skip(emit, b, Kmax, n_accepted, out_tokens);
+        return;
+    }
+    combine_rows<TPB>(part_max, part_sum, st0, 2 * K + 1, n_stat_chunks, inv_T, row_m, row_z, comb);
+    if (threadIdx.x < 64) {
+        bool keep = true;
+        if (K > 0) {
+            const double ep = exp((double)(lp_x - row_m[i]) * inv_T);
+            const double eq = exp((double)(lq_x - row_m[K + 1 + i]) * inv_T);
+            keep = u * eq * row_z[i] < ep * row_z[K + 1 + i];   // u * q(x) < p(x)
+        }
+        const unsigned long long failed = __ballot(!keep && (int)threadIdx.x < K);
+        const int first = failed ? __builtin_ctzll(failed) : K;
+        if (threadIdx.x < 2) s_iz[threadIdx.x] = 1.0 / row_z[threadIdx.x == 0 ? first : first < K ? K + 1 + first : 0];
+        if (threadIdx.x == 0) s_a = first;
+    }
+    __syncthreads();
+    const int a = s_a;
+    const bool residual = a < K;
+    const float mp = row_m[a], mq = residual ? row_m[K + 1 + a] : 0.f;
+    const double izp = s_iz[0], izq = s_iz[1];
+    const float* prow = trow0 + (size_t)a * V;            // a == K: the extra-token row
+    const float* qrow = drow0 + (size_t)(residual ? a : 0) * V;
+    auto mass = [&](float lp, float lq, bool with_q) {
+        const double pv = (double)__expf((lp - mp) * inv_T_f) * izp, qv = with_q ? (double)__expf((lq - mq) * inv_T_f) * izq : 0.0;
+        return pv > qv ? pv - qv : 0.0;
+    };
+    // a thread's sums of its four ids of every run of a slice
+    auto sums_of = [&](int c, bool with_q, double (&run)[RUNS]) {
+        floatx4 p[RUNS], q[RUNS];
+        const int id0 = c * SLICE + draw_id0<RUNS>();
+        draw_load(prow, V, id0, p);
+        if (with_q) draw_load(qrow, V, id0, q);
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j)
+            run[j] = (mass(p[j].x, q[j].x, with_q) + mass(p[j].y, q[j].y, with_q)) + (mass(p[j].z, q[j].z, with_q) + mass(p[j].w, q[j].w, with_q));
+    };
+    auto total = [&](const double (&run)[RUNS]) {   // of the workgroup, the same for all threads
+        double sum = 0.0;
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j) sum += run[j];
+        sum = wave_sum(sum);
+        if (lane == 0) l.tot[threadIdx.x >> 6] = sum;
+        __syncthreads();
+        static_assert(WAVES == 4, "four sums");
+        return (l.tot[0] + l.tot[1]) + (l.tot[2] + l.tot[3]);
+    };
+    double* masses = slice_mass + (size_t)b * n_slices;
+    double run[RUNS];
+    sums_of(slice, residual, run);
+    {
+        const double sum = total(run);
+        if (threadIdx.x == 0) {
+            __hip_atomic_store(masses + slice, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the mass has arrived before it is counted)
+            s_last = __hip_atomic_fetch_add(arrived + b * ARRIVED_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_slices - 1;
+        }
+        __syncthreads();
+        if (!s_last) return;
+        if (threadIdx.x == 0) __hip_atomic_store(arrived + b * ARRIVED_STRIDE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // The slice that the running sum passes u times the whole in, as draw_locate looks among wavefronts: every wavefront for
+    // itself, 64 slices at a time
+    auto mass_of = [&](int c) { return c < n_slices ? __hip_atomic_load(masses + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0; };
+    const double first64 = mass_of(lane);
+    double S = 0.0;
+    for (int c0 = 0; c0 < n_slices; c0 += 64) S += wave_sum(c0 == 0 ? first64 : mass_of(c0 + lane));
+    int pick = -1;
+    bool with_q = residual;
+    double below = 0.0, goal = u_draw * S;
+    if (S > 0.0) {
+        double before = 0.0;
+        for (int c0 = 0; c0 < n_slices; c0 += 64) {
+            const double m = c0 == 0 ? first64 : mass_of(c0 + lane), upto = before + wave_scan(m);
+            const unsigned long long over = __ballot(m > 0.0 && upto > goal), some = __ballot(m > 0.0);
+            if (over || some) {
+                const int at = over ? __ffsll((long long)over) - 1 : 63 - __clzll((long long)some);
+                pick = c0 + at;
+                below = at > 0 ? read_lane(upto, at - 1) : before;
+            }
+            if (over) break;
+            before = read_lane(upto, 63);
+        }
+    } else {   // no mass left (impossible in exact arithmetic): draw from p_a, which sums to 1, slice by slice
+        with_q = false;
+        goal = u_draw;
+        double before = 0.0;
+        for (int c = 0; c < n_slices; ++c) {
+            sums_of(c, false, run);
+            const double sum = total(run);
+            __syncthreads();
+            if (sum > 0.0 || pick < 0) {
+                pick = c;
+                below = before;
+            }
+            before += sum;
+            if (before > goal) break;
+        }
+    }
+    sums_of(pick, with_q, run);
+    __syncthreads();
+    // (ids of the slice; a row's end lies inside the last one)
+    draw_locate<RUNS, WAVES, true>(run, [&](int j, double (&m4)[4]) {
+        floatx4 p[1], q[1];
+        const int id0 = pick * SLICE + draw_id0<RUNS>() + 256 * j;
+        draw_load(prow, V, id0, p);
+        if (with_q) draw_load(qrow, V, id0, q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m4[e] = mass(p[0][e], q[0][e], with_q);
+    }, goal, true, l, below);
+    if (threadIdx.x < 64) draw_emit(t, emit, b, slot, n, K, Kmax, a, min(pick * SLICE + l.tok, V - 1), x, auto_rollback, kv_len, n_accepted, out_tokens);
 }
 
 // A plain draw (no proposals): maximum, weights and draw of one row per sequence, which comes whole or as the LM head's
@@ -1231,7 +1098,7 @@ __global__ void __launch_bounds__(DRAW_TPB) plain_draw_kernel(const int32_t* seq
         run[j] = ((double)v[j].x + (double)v[j].y) + ((double)v[j].z + (double)v[j].w);
     }
     // (no mass at all takes a row without a finite logit; the draw is then what rounding makes of it)
-    if (!draw_locate(run, [&](int j, double (&x)[4]) {
+    if (!draw_locate<RUNS, DRAW_WAVES>(run, [&](int j, double (&x)[4]) {
             floatx4 e4 = v[0];
 #pragma unroll
             for (int i = 1; i < RUNS; ++i)
@@ -1579,6 +1446,26 @@ struct TreeOut {
     int32_t* out_tokens;   // [B][Kmax+1]
     int32_t* path;         // [B][Kmax] kept node indices root-down, then -1
 };
+
+// Of the lanes of a wavefront whose running sum inc (own share loc, of PER ids with the masses x) passes the target, the first one
+// that has mass: which of its ids the target falls on, the first whose running sum passes it (rounding between that sum and inc: the
+// last id with mass).  -1 for the other lanes.  The lanes add up in different orders, so neighbours' ranges [inc - loc, inc) may
+// leave a gap or overlap by rounding: a lane is not asked whether the target lies in its range.
+template <int PER>
+__device__ __forceinline__ int lowest_crossing(const double* x, double loc, double inc, double target)
+{
+    const unsigned long long over = __ballot(loc > 0.0 && inc > target);
+    if (!over || (int)(threadIdx.x & 63) != __ffsll((long long)over) - 1) return -1;
+    double cdf = inc - loc;
+    int first = -1, last = -1;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        cdf += x[i];
+        if (first < 0 && x[i] > 0.0 && cdf > target) first = i;
+        if (x[i] > 0.0) last = i;
+    }
+    return first >= 0 ? first : last;
+}
 
 // The walk of one sequence's tree (one workgroup).  At the current node r starts as the target
 // distribution p; a child with token x is kept iff u * q(x) < r(x); every rejection replaces r by
@@ -1930,8 +1817,8 @@ __global__ void __launch_bounds__(DRAW_TPB) tree_draw_kernel(const int32_t* seq_
         const float mp = row_m[cur + 1], mq = row_m[N + 1 + cur + 1];
         // both rows under way together; q's weights leave the registers before p's values, twice as wide, fill them
         floatx4 p[RUNS], q[RUNS];
-        draw_load(qrow, V, draw_id0<RUNS>(), q);
-        draw_load(prow, V, draw_id0<RUNS>(), p);
+        draw_load<false>(qrow, V, draw_id0<RUNS>(), q);
+        draw_load<false>(prow, V, draw_id0<RUNS>(), p);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < RUNS; ++j) {
@@ -2024,7 +1911,7 @@ __global__ void __launch_bounds__(DRAW_TPB) tree_draw_kernel(const int32_t* seq_
     double run[RUNS];
 #pragma unroll
     for (int j = 0; j < RUNS; ++j) run[j] = (r[j][0] + r[j][1]) + (r[j][2] + r[j][3]);
-    if (!draw_locate(run, [&](int j, double (&x)[4]) {
+    if (!draw_locate<RUNS, DRAW_WAVES>(run, [&](int j, double (&x)[4]) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[e] = r[0][e];
 #pragma unroll
@@ -2216,6 +2103,10 @@ int launch_pool_cover(const PagePool& pool, int slot, int pos0, int pos1, int32_
     return SPEC_OK;
 }
 
+// Runs of 256 ids per wavefront of accept_slice_kernel: slices of 2048 ids while there are up to four workgroups per compute unit,
+// 4096 from there on (slice_masses has the room that this takes).
+static int slice_runs(int B, int V) { return (size_t)B * ((V + 2047) / 2048) <= 1024 ? 2 : 4; }
+
 int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const LookaheadPack& ks, int B, int Kmax,
                    int V, int n_stat_rows, const float* target_logits, const float* draft_logits,
                    const int32_t* draft_tokens, const float* uniforms, int u_stride, float temperature,
@@ -2223,7 +2114,6 @@ int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const Lookahe
                    const DrawEmit* emit, Profiler* prof, hipStream_t s, int32_t* prepare_flag, const LogitsSrc* src)
 {
     const int n_stat_chunks = (V + STAT_CHUNK - 1) / STAT_CHUNK;
-    const int n_res_chunks = (V + RES_CHUNK - 1) / RES_CHUNK;
     const float inv_T = 1.0f / temperature;
     PrepIn prep{};
     const int prep_on = prepare_flag ? 1 : 0;
@@ -2265,24 +2155,21 @@ int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const Lookahe
     SPECV_LAUNCH_CHECK("stats_kernel");
     }
     ProfScope ps(prof, SPEC_PROF_SAMPLER_DRAW, s);
-    if (V <= DRAW_MAX && !emit) {
+    if (V <= SLICE_MIN && !emit) {
         const int runs = draw_runs(V);
         auto* k = stats_inside ? accept_draw_kernel<1, true> : runs == 1 ? accept_draw_kernel<1, false> : runs == 2 ? accept_draw_kernel<2, false>
-                  : runs == 4 ? accept_draw_kernel<4, false> : accept_draw_kernel<8, false>;
+                                                              : accept_draw_kernel<4, false>;
         hipLaunchKernelGGL(k, dim3(B), dim3(DRAW_TPB), 0, s, t.seq_stat0, t.seq_row0, draft_tokens, w.part_max,
                            w.part_sum, Kmax, V, n_stat_chunks, u_stride, uniforms, target_logits, draft_logits, inv_T, auto_rollback,
                            kv_len, n_accepted, out_tokens, t, ks);
         SPECV_LAUNCH_CHECK("accept_draw_kernel");
         return SPEC_OK;
     }
-    hipLaunchKernelGGL(accept_mass_kernel, dim3(n_res_chunks, B), dim3(TPB), 0, s, t.seq_stat0, t.seq_row0, draft_tokens, w.part_max,
-                       w.part_sum, Kmax, V, n_stat_chunks, u_stride, uniforms, target_logits, draft_logits, n_res_chunks, inv_T,
-                       ks, w);
-    SPECV_LAUNCH_CHECK("accept_mass_kernel");
-    hipLaunchKernelGGL(final_draw_kernel, dim3(B), dim3(TPB), 0, s, w.accepted, w.chunk_mass, t.seq_row0, uniforms, u_stride,
-                       n_res_chunks, Kmax, V, w.row_max, inv_T, w.row_inv_z, target_logits, draft_logits, draft_tokens,
-                       auto_rollback, kv_len, n_accepted, out_tokens, t, ks, em);
-    SPECV_LAUNCH_CHECK("final_draw_kernel");
+    const int runs = slice_runs(B, V), slices = (V + 1024 * runs - 1) / (1024 * runs);
+    hipLaunchKernelGGL(runs == 2 ? accept_slice_kernel<2> : accept_slice_kernel<4>, dim3(slices, B), dim3(TPB), 0, s, t.seq_stat0, t.seq_row0,
+                       draft_tokens, w.part_max, w.part_sum, Kmax, V, n_stat_chunks, u_stride, uniforms, target_logits, draft_logits, inv_T,
+                       auto_rollback, kv_len, n_accepted, out_tokens, w.slice_mass, w.arrived, t, em, ks);
+    SPECV_LAUNCH_CHECK("accept_slice_kernel");
     return SPEC_OK;
 }
 
@@ -2305,12 +2192,10 @@ constexpr int NA_RES_CHUNKS = (NA_MAX_VOCAB + RES_CHUNK - 1) / RES_CHUNK;
 
 struct NoAllocScratch {
     double part_sum[(size_t)NA_MAX_STAT * NA_STAT_CHUNKS];
-    double chunk_mass[(size_t)NA_MAX_BATCH * NA_RES_CHUNKS];
-    double row_inv_z[2 * NA_MAX_BATCH];
+    double slice_mass[(size_t)NA_MAX_BATCH * NA_RES_CHUNKS];
     float part_max[(size_t)NA_MAX_STAT * NA_STAT_CHUNKS];
     int32_t part_idx[(size_t)NA_MAX_STAT * NA_STAT_CHUNKS];
-    float row_max[2 * NA_MAX_BATCH];
-    int32_t accepted[NA_MAX_BATCH];
+    int32_t arrived[NA_MAX_BATCH * ARRIVED_STRIDE];   // zero between calls
     int32_t seq_row0[NA_MAX_BATCH + 1], seq_stat0[NA_MAX_BATCH + 1];
     int32_t seq_n[NA_MAX_BATCH], seq_ok[NA_MAX_BATCH], seq_slot[NA_MAX_BATCH];
     int32_t row_seq[NA_MAX_ROWS], row_pos[NA_MAX_ROWS], row_tok[NA_MAX_ROWS], row_rope[NA_MAX_ROWS];
@@ -2400,10 +2285,8 @@ extern "C" int spec_sample_step_noalloc(int32_t vocab, int32_t max_lookahead, co
     SamplerWorkspace sw{};
     sw.part_max = w->part_max;
     sw.part_sum = w->part_sum;
-    sw.chunk_mass = w->chunk_mass;
-    sw.accepted = w->accepted;
-    sw.row_inv_z = w->row_inv_z;
-    sw.row_max = w->row_max;
+    sw.slice_mass = w->slice_mass;
+    sw.arrived = w->arrived;
     sw.part_idx = w->part_idx;
     if (greedy) {   // the greedy rule's kernels read the tables from the start
         rc = launch_prepare(t, ks, B, Kmax, vocab, NA_MAX_BATCH, 0, false, nullptr, nullptr, args->draft_tokens, nullptr,

@@ -191,7 +191,6 @@ static int init_common(const spec_model_cfg* cfg, const spec_weights* weights, v
     const int max_rows = B * (Kmax + 1);
     const int max_stat = B * (2 * Kmax + 2);   // a tree has a draft row for its root as well
     const int n_stat_chunks = (V + STAT_CHUNK - 1) / STAT_CHUNK;
-    const int n_res_chunks = (V + RES_CHUNK - 1) / RES_CHUNK;
     Arena& a = h->arena;
     rc = SPEC_OK;
     auto A = [&](auto** p, size_t count) {
@@ -226,10 +225,9 @@ static int init_common(const spec_model_cfg* cfg, const spec_weights* weights, v
     }
     A(&h->sampler.part_max, (size_t)max_stat * n_stat_chunks);
     A(&h->sampler.part_sum, (size_t)max_stat * n_stat_chunks);
-    A(&h->sampler.chunk_mass, (size_t)B * n_res_chunks);
-    A(&h->sampler.accepted, B);
-    A(&h->sampler.row_inv_z, 2 * (size_t)B);
-    A(&h->sampler.row_max, 2 * (size_t)B);
+    A(&h->sampler.slice_mass, slice_masses(B, cfg->vocab));
+    A(&h->sampler.arrived, B * ARRIVED_STRIDE);
+    if (rc == SPEC_OK && hipMemset(h->sampler.arrived, 0, (size_t)B * ARRIVED_STRIDE * sizeof(int32_t)) != hipSuccess) rc = fail(SPEC_ERR_DEVICE, "hipMemset failed");
     A(&h->sampler.part_idx, (size_t)max_stat * n_stat_chunks);
     if (rc == SPEC_OK && hipMemset(h->flag, 0, 16) != hipSuccess) rc = fail(SPEC_ERR_DEVICE, "hipMemset failed");
     if (rc == SPEC_OK && paged) {
