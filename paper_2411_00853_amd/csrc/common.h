@@ -161,8 +161,8 @@ int launch_embed(const EmbedTo& e, const int32_t* row_tok, int M, hipStream_t s)
 
 // embed != NULL (steps of M <= EMBED_MAX_ROWS window rows): the same launch embeds the rows
 constexpr int EMBED_MAX_ROWS = SPEC_MAX_STEP_ROWS;
-// slices of RES_CHUNK, or of half of that while a launch has up to 1024 of them
-inline size_t slice_masses(int B, int V) { return std::max((size_t)B * ((V + RES_CHUNK - 1) / RES_CHUNK), (size_t)1024); }
+// slices of RES_CHUNK, or of half of that while a launch has up to 1024 of them; two numbers for half a one in a plain draw
+inline size_t slice_masses(int B, int V) { return std::max((size_t)B * 4 * ((V + RES_CHUNK - 1) / RES_CHUNK), (size_t)1024); }
 
 int launch_prepare(const StepTables& t, const LookaheadPack& ks, int B, int Kmax, int V, int max_batch,
                    int max_kv_len, bool has_cache, const int32_t* seq_slot, const int32_t* last_token,

@@ -590,6 +590,7 @@ constexpr int DRAW_TPB = 1024, DRAW_WAVES = DRAW_TPB / 64, DRAW_MAX_RUNS = 8;
 constexpr int DRAW_MAX = DRAW_WAVES * 256 * DRAW_MAX_RUNS;   // 32768
 static_assert(DRAW_WAVES <= 16, "the wavefronts' sums are scanned by 16 lanes");
 constexpr int SLICE_MIN = 16384;   // accept_slice_kernel beyond: 16000 and two sequences 13.5 us in one workgroup each, 13.9 shared out, 20000 and 64 29.2 and 26.9
+constexpr int PLAIN_MIN = 16384, PLAIN_MAX = 64 * 2048;   // plain_slice_kernel: beyond the one, up to the other (a lane per slice)
 constexpr int STATS_MAX = 2048;                              // a row in a wavefront's registers
 inline int draw_runs(int V) { return V <= 4096 ? 1 : V <= 8192 ? 2 : V <= 16384 ? 4 : 8; }
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // global memory takes 16-byte accesses at any 4-byte address
@@ -1111,6 +1112,117 @@ __global__ void __launch_bounds__(DRAW_TPB) plain_draw_kernel(const int32_t* seq
         __syncthreads();
     }
     if (threadIdx.x < 64) draw_emit(t, emit, b, slot, n, 0, Kmax, 0, l.tok, 0, auto_rollback, kv_len, n_accepted, out_tokens);
+}
+
+// The same for rows of more than PLAIN_MIN ids, shared out as accept_slice_kernel shares them: a workgroup per sequence and 2048 ids
+// finishes and stores its part of the row and leaves that part's maximum and sum of weights; the last one brings the parts
+// to one maximum, finds the part that the target falls on, makes its logits again and draws.  In one workgroup the row's
+// partial sums, its stores (the logits and the draft's copy of them) and its exponentials were a compute unit's share of all three.
+// Steps of two layers, one row a sequence, 1, 8 and 48 sequences: vocabulary 20000 95.6 -> 91.2, 96.7 -> 92.3 and 139.8 -> 137.4 us,
+// 50257 (before: statistics, then accept_slice_kernel) 109.9 -> 100.5, 112.7 -> 101.7 and 159.4 -> 146.8, 128256 132.5 -> 125.9, 136.0 ->
+// 127.6 and 194.9 -> 175.6; 12000 0 to +0.6 %.  Draft decode of 8 rows 288.0 -> 284.5, decoding round 2165 -> 2146.
+template <bool SRC>
+__global__ void __launch_bounds__(TPB) plain_slice_kernel(const int32_t* seq_row0, const float* __restrict__ target,
+                                                          const float* __restrict__ uniforms, int u_stride, int V, int Kmax,
+                                                          float inv_T_f, int auto_rollback, int32_t* kv_len,
+                                                          int32_t* __restrict__ n_accepted, int32_t* __restrict__ out_tokens,
+                                                          double* slice_mass, int32_t* arrived, StepTables t, DrawEmit emit, LogitsSrc src)
+{
+    constexpr int RUNS = 2, WAVES = TPB / 64, SLICE = TPB * 4 * RUNS;
+    __shared__ float s_max[WAVES];
+    __shared__ int s_last;
+    __shared__ DrawLds l;
+    const int b = blockIdx.y, slice = blockIdx.x, n_slices = gridDim.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int m = seq_row0[b], ok = t.seq_ok[b], slot = t.seq_slot[b], n = t.seq_n[b];
+    const double u = (double)uniforms[b * u_stride];
+    float rs = 1.f;
+    if constexpr (SRC) rs = row_inv_rms(src.ns.ssq, src.ns.n_ssq, m, src.ns.d, src.ns.eps);
+    auto logits = [&](int first, floatx4 (&v)[RUNS]) {   // a thread's ids of a slice; past the end -inf
+        if constexpr (SRC) {
+            const float* p = src.partial + (size_t)m * src.ld;   // (a row has ld >= V columns, a multiple of 16, to read)
+            switch (src.n_split) {
+            case 1: logits_from<1>(p, src.stride, 256, src.ld, first, rs, v); break;
+            case 2: logits_from<2>(p, src.stride, 256, src.ld, first, rs, v); break;
+            case 4: logits_from<4>(p, src.stride, 256, src.ld, first, rs, v); break;
+            case 8: logits_from<8>(p, src.stride, 256, src.ld, first, rs, v); break;
+            default: logits_from<16>(p, src.stride, 256, src.ld, first, rs, v); break;
+            }
+#pragma unroll
+            for (int j = 0; j < RUNS; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (first + 256 * j + e >= V) v[j][e] = -INFINITY;
+        } else {
+            draw_load(target + (size_t)m * V, V, first, v);
+        }
+    };
+    floatx4 v[RUNS];
+    const int first = slice * SLICE + draw_id0<RUNS>();
+    logits(first, v);
+    if constexpr (SRC) draw_store(src.out + (size_t)m * V, V, first, v);
+    if (emit.logits_copy) draw_store(emit.logits_copy + (size_t)b * emit.copy_stride, V, first, v);
+    if (!ok) {
+        if (slice == 0) draw_skip(emit, b, Kmax, n_accepted, out_tokens);
+        return;
+    }
+    float mw = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < RUNS; ++j) mw = fmaxf(fmaxf(mw, fmaxf(v[j].x, v[j].y)), fmaxf(v[j].z, v[j].w));
+    mw = wave_max(mw);
+    if (lane == 0) s_max[wave] = mw;
+    __syncthreads();
+    // weights relative to the slice's own maximum (a slice without a finite logit: all of them zero)
+    auto weights = [&](float mp, double (&run)[RUNS], floatx4 (&x)[RUNS]) {
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[j][e] = mp == -INFINITY ? 0.f : __expf((x[j][e] - mp) * inv_T_f);
+            run[j] = ((double)x[j].x + (double)x[j].y) + ((double)x[j].z + (double)x[j].w);
+        }
+    };
+    double run[RUNS];
+    const float mp = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
+    weights(mp, run, v);
+    const double part = wave_sum(run[0] + run[1]);
+    static_assert(RUNS == 2 && WAVES == 4, "two runs, four wavefronts");
+    if (lane == 0) l.tot[wave] = part;
+    __syncthreads();
+    double* parts = slice_mass + (size_t)b * n_slices * 2;   // maximum and sum of every slice
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(parts + 2 * slice, (double)mp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(parts + 2 * slice + 1, (l.tot[0] + l.tot[1]) + (l.tot[2] + l.tot[3]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (they have arrived before they are counted)
+        s_last = __hip_atomic_fetch_add(arrived + b * ARRIVED_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_slices - 1;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    if (threadIdx.x == 0) __hip_atomic_store(arrived + b * ARRIVED_STRIDE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // (at most 64 slices: PLAIN_MAX)
+    const bool in = lane < n_slices;
+    const float mc = in ? (float)__hip_atomic_load(parts + 2 * lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -INFINITY;
+    const double sc = in ? __hip_atomic_load(parts + 2 * lane + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+    const float mx = wave_max(mc);
+    const double f = sc > 0.0 ? exp((double)(mc - mx) * (double)inv_T_f) : 0.0, mass = sc * f;   // to the row's maximum
+    const double upto = wave_scan(mass), goal = u * read_lane(upto, 63);
+    const unsigned long long over = __ballot(mass > 0.0 && upto > goal), some = __ballot(mass > 0.0);
+    int tok = 0;   // (no mass at all takes a row without a finite logit)
+    if (some) {
+        const int pick = over ? __ffsll((long long)over) - 1 : 63 - __clzll((long long)some);
+        const double below = pick > 0 ? read_lane(upto, pick - 1) : 0.0, scale = read_lane(f, pick);
+        const float mpick = __shfl(mc, pick);
+        floatx4 x[RUNS];
+        logits(pick * SLICE + draw_id0<RUNS>(), x);
+        weights(mpick, run, x);
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j) run[j] *= scale;
+        __syncthreads();
+        draw_locate<RUNS, WAVES, true>(run, [&](int j, double (&m4)[4]) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) m4[e] = (double)(j == 0 ? x[0][e] : x[1][e]) * scale;
+        }, goal, true, l, below);
+        tok = min(pick * SLICE + l.tok, V - 1);
+    }
+    if (threadIdx.x < 64) draw_emit(t, emit, b, slot, n, 0, Kmax, 0, tok, 0, auto_rollback, kv_len, n_accepted, out_tokens);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2132,13 +2244,18 @@ int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const Lookahe
                       && ((reinterpret_cast<uintptr_t>(draft_logits) & 15) == 0)
                       && ((reinterpret_cast<uintptr_t>(em.logits_copy) & 15) == 0) && (em.copy_stride % 4 == 0);
     const LogitsSrc from = src ? *src : LogitsSrc{};
-    if (n_stat_rows == B && V <= DRAW_MAX && !prepare_flag) {   // nothing to test: one launch
+    if (n_stat_rows == B && V <= PLAIN_MAX && !prepare_flag) {   // nothing to test: one launch
         ProfScope ps(prof, SPEC_PROF_SAMPLER_DRAW, s);
+        if (V > PLAIN_MIN) {
+            hipLaunchKernelGGL(from.partial ? plain_slice_kernel<true> : plain_slice_kernel<false>, dim3((V + 2047) / 2048, B), dim3(TPB), 0, s,
+                               t.seq_row0, target_logits, uniforms, u_stride, V, Kmax, inv_T, auto_rollback, kv_len, n_accepted,
+                               out_tokens, w.slice_mass, w.arrived, t, em, from);
+            SPECV_LAUNCH_CHECK("plain_slice_kernel");
+            return SPEC_OK;
+        }
         const int runs = draw_runs(V);
-        auto* k = from.partial ? (runs == 1 ? plain_draw_kernel<true, 1> : runs == 2 ? plain_draw_kernel<true, 2> :
-                                  runs == 4 ? plain_draw_kernel<true, 4> : plain_draw_kernel<true, 8>)
-                               : (runs == 1 ? plain_draw_kernel<false, 1> : runs == 2 ? plain_draw_kernel<false, 2> :
-                                  runs == 4 ? plain_draw_kernel<false, 4> : plain_draw_kernel<false, 8>);
+        auto* k = from.partial ? (runs == 1 ? plain_draw_kernel<true, 1> : runs == 2 ? plain_draw_kernel<true, 2> : plain_draw_kernel<true, 4>)
+                               : (runs == 1 ? plain_draw_kernel<false, 1> : runs == 2 ? plain_draw_kernel<false, 2> : plain_draw_kernel<false, 4>);
         hipLaunchKernelGGL(k, dim3(B), dim3(DRAW_TPB), 0, s, t.seq_row0, target_logits, uniforms, u_stride, V, Kmax, inv_T,
                            auto_rollback, kv_len, n_accepted, out_tokens, t, em, from);
         SPECV_LAUNCH_CHECK("plain_draw_kernel");
