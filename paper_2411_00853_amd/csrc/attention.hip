@@ -454,7 +454,13 @@ static AttnLaunchPlan plan_launch(const CacheGeom& g, bool paged, int n_q_heads,
     }
     const int rt = ((kmax + 1) * (group / lp.share) + 15) / 16;
     const long pairs = (long)B * g.n_kv_heads * lp.share;
-    const bool own = !g_max_chunks_set && g_merge_min_pairs == 0 && g_items_per_cu == 0;   // (no knob set)
+    // Both rules below are for few query rows: a wavefront finishes an item's queries and the window by itself, and where several
+    // items share a cache head each of them finishes the window's keys and values again.  Steps of two layers up to 330 positions,
+    // without this line: 64-dim heads, 52 rows an item +0.5..+5 %, 32 rows -2..-7; 128-dim heads, 16 rows of a shared head
+    // +4..+12 %, 26 and 52 rows +1..+7, 13 to 16 of a head of their own -3..+3.5, 12 rows -4..-1.
+    const int rows = (kmax + 1) * (group / lp.share);
+    const bool few_rows = g.head_dim == 64 ? rows <= (lp.share > 1 ? 16 : 32) : lp.share == 1 && rows <= 12;
+    const bool own = few_rows && !g_max_chunks_set && g_merge_min_pairs == 0 && g_items_per_cu == 0;   // (no knob set)
     auto cut = [&](int keys) {
         lp.p.chunk_keys = keys;
         lp.p.max_chunks = (max_kv_len + keys - 1) / keys;

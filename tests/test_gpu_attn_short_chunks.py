@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("hd,heads,kv_heads,capacity,B,k,small", [
     (64, 4, 4, 40, 3, 5, 0), (64, 4, 4, 193, 3, 5, 0), (64, 24, 24, 900, 3, 2, 0), (64, 8, 2, 191, 2, 6, 1), (64, 8, 2, 700, 2, 6, 1),
     (128, 2, 2, 384, 3, 0, 0), (128, 2, 2, 1025, 3, 7, 0), (128, 2, 1, 2400, 2, 3, 0), (128, 8, 8, 200, 12, 3, 0),
-    (64, 4, 4, 1024, 1, 6, 0), (64, 4, 4, 1060, 1, 6, 0), (128, 2, 2, 512, 3, 15, 0), (128, 4, 2, 500, 3, 11, 1)])
+    (64, 4, 4, 1024, 1, 6, 0), (64, 4, 4, 1060, 1, 6, 0), (128, 2, 2, 512, 3, 11, 0), (128, 4, 4, 500, 3, 11, 0)])
 def test_longer_chunks_and_no_kernel_in_front(hd, heads, kv_heads, capacity, B, k, small):
     from paper_2411_00853_amd import binding as sv
     from test_gpu_forward import Rig
