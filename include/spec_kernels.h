@@ -95,7 +95,7 @@ enum {
     SPEC_PROF_SAMPLER_STATS = 4, /* softmax statistics over all target and draft rows, with the LM head's partial sums */
     SPEC_PROF_SAMPLER_DRAW = 5,  /* accept scan, residual mass, final draw, KV length update; a plain draw's
                                   * partial sums and statistics, and those of rows of up to 2048 logits, where they share its launch */
-    SPEC_PROF_PREPARE = 6,       /* row bookkeeping */
+    SPEC_PROF_PREPARE = 6,       /* row bookkeeping, with the embedding of a step of one pass */
     /* the projection GEMMs one by one (each is also counted in SPEC_PROF_GEMM) */
     SPEC_PROF_GEMM_QKV = 7,
     SPEC_PROF_GEMM_O = 8,        /* with the residual addition where the GEMM does it itself (some steps of up to 16 rows) */
