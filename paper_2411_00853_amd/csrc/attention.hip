@@ -458,8 +458,9 @@ static AttnLaunchPlan plan_launch(const CacheGeom& g, bool paged, int n_q_heads,
     // items share a cache head each of them finishes the window's keys and values again.  Steps of two layers up to 330 positions,
     // without this line: 64-dim heads, 52 rows an item +0.5..+5 %, 32 rows -2..-7; 128-dim heads, 16 rows of a shared head
     // +4..+12 %, 26 and 52 rows +1..+7, 13 to 16 of a head of their own -3..+3.5, 12 rows -4..-1.
+    // And for 128-dim heads only while their wavefronts, one to a SIMD, are all resident: 1056 pairs 0..+1.4 %, 840 -3.5.
     const int rows = (kmax + 1) * (group / lp.share);
-    const bool few_rows = g.head_dim == 64 ? rows <= (lp.share > 1 ? 16 : 32) : lp.share == 1 && rows <= 12;
+    const bool few_rows = g.head_dim == 64 ? rows <= (lp.share > 1 ? 16 : 32) : lp.share == 1 && rows <= 12 && pairs <= 4L * cu_count;
     const bool own = few_rows && !g_max_chunks_set && g_merge_min_pairs == 0 && g_items_per_cu == 0;   // (no knob set)
     auto cut = [&](int keys) {
         lp.p.chunk_keys = keys;
