@@ -207,7 +207,7 @@ int spec_verify_step(spec_handle* h, const spec_step_args* args, const spec_step
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): the sampling part of spec_verify_step -- what that call
  * does on a sampler-only handle when target_logits_in is given -- without a handle.  The row tables,
- * chunk statistics, slice masses and the error flag, which a handle keeps in its workspace, live in
+ * chunk statistics, slice masses and counts and the error flag, which a handle keeps in its workspace, live in
  * one fixed device array inside the library (about 0.55 MiB, held by every GPU the library runs on
  * until the process ends), sized for
  *     batch <= SPEC_NOALLOC_MAX_BATCH, max_lookahead <= SPEC_MAX_LOOKAHEAD, vocab <= SPEC_NOALLOC_MAX_VOCAB;

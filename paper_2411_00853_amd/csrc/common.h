@@ -77,6 +77,8 @@ struct alignas(16) SeqDesc {
     int32_t slot, ok, pad[2];
 };
 
+constexpr int ARRIVED_STRIDE = 32;   // a line per count: one after the other in a line, the counts of all sequences queue up there
+
 struct StepTables {
     int32_t* seq_row0;   // [B+1] first target row of each sequence (prefix of K_b+1)
     int32_t* seq_stat0;  // [B+1] first statistics row of each sequence (prefix of 2K_b+1)
@@ -89,6 +91,7 @@ struct StepTables {
     int32_t* row_tok;    // [M] token id fed at this row
     int32_t* row_rope;   // [M] position the rotary embedding uses: n_b + depth of the row in its window
     uint32_t* row_mask;  // [M] bit i set: the row attends to window slot i (position n_b + i)
+    int32_t* arrived;    // [B][ARRIVED_STRIDE] how many slices of the sequence's draw are done: cleared by the bookkeeping of chains, counted by the sampler
     PagePool pool;       // the cache's page pool (table == NULL: contiguous cache)
     int tree;            // set by the host: 0 = the windows are chains (row_rope = row_pos, row_mask = slots
                          // 0..j, so the kernels need not load them), 1 = token trees
@@ -132,13 +135,10 @@ struct LogitsSrc {
 constexpr int STAT_CHUNK = 16384;   // logits per workgroup in the statistics pass
 constexpr int RES_CHUNK = 4096;    // logits per workgroup in the residual pass of many sequences (2048 for few)
 
-constexpr int ARRIVED_STRIDE = 32;   // a line per count: one after the other in a line, the counts of all sequences queue up there
-
 struct SamplerWorkspace {
     float* part_max;      // [stat rows][stat chunks] chunk maxima of raw logits
     double* part_sum;     // [stat rows][stat chunks] sum exp((l - chunk max)/T)
     double* slice_mass;   // [slice_masses(B, V)] mass of the final-draw distribution per sequence and slice of the vocabulary
-    int32_t* arrived;     // [B][ARRIVED_STRIDE] how many of a sequence's slices are done: zero between launches
     int32_t* part_idx;    // [stat rows][stat chunks] greedy rule: lowest id holding the chunk maximum
 };
 

@@ -213,6 +213,7 @@ extern "C" int spec_decode_init(spec_handle* target, spec_handle* draft, const s
             t->row_tok = draft->tables.row_tok;
             t->row_rope = draft->tables.row_rope;
             t->row_mask = draft->tables.row_mask;
+            t->arrived = draft->tables.arrived;
             t->pool = draft->tables.pool;
         }
     }

@@ -203,6 +203,7 @@ __device__ __forceinline__ void prepare_rows(const StepTables& t, const Lookahea
         if (has_cache) write_desc(t, rank, b, K, n, slot, ok, row0);
         t.seq_row0[b] = row0;
         t.seq_stat0[b] = 2 * row0 - b;
+        t.arrived[b * ARRIVED_STRIDE] = 0;   // (in every call, whatever an earlier one left behind)
         t.seq_n[b] = n;
         t.seq_ok[b] = ok;
         t.seq_slot[b] = slot;
@@ -885,7 +886,7 @@ __global__ void __launch_bounds__(DRAW_TPB) accept_draw_kernel(const int32_t* se
 // -> 24.7, 64 of 128256 109.0 -> 107.9.  128 of 128256 stay where they were, 200 of 65536 lose 2 %.
 //
 // No workgroup waits for another: each stores its mass with an atomic store at device scope, waits until that has arrived, and then
-// counts itself; the one that counts last sees all masses, and leaves the count at zero for the next launch.
+// counts itself; the one that counts last sees all masses.  The row bookkeeping in front has set the count to zero.
 template <int RUNS>
 __global__ void __launch_bounds__(TPB) accept_slice_kernel(const int32_t* seq_stat0, const int32_t* seq_row0,
                                                            const int32_t* __restrict__ draft_tokens,
@@ -896,7 +897,7 @@ __global__ void __launch_bounds__(TPB) accept_slice_kernel(const int32_t* seq_st
                                                            const float* __restrict__ target,
                                                            const float* __restrict__ draft, float inv_T_f, int auto_rollback,
                                                            int32_t* kv_len, int32_t* __restrict__ n_accepted,
-                                                           int32_t* __restrict__ out_tokens, double* slice_mass, int32_t* arrived,
+                                                           int32_t* __restrict__ out_tokens, double* slice_mass,
                                                            StepTables t, DrawEmit emit, LookaheadPack ks)
 {
     constexpr int WAVES = TPB / 64, SLICE = TPB * 4 * RUNS;
@@ -982,11 +983,10 @@ __global__ void __launch_bounds__(TPB) accept_slice_kernel(const int32_t* seq_st
         if (threadIdx.x == 0) {
             __hip_atomic_store(masses + slice, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the mass has arrived before it is counted)
-            s_last = __hip_atomic_fetch_add(arrived + b * ARRIVED_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_slices - 1;
+            s_last = __hip_atomic_fetch_add(t.arrived + b * ARRIVED_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_slices - 1;
         }
         __syncthreads();
         if (!s_last) return;
-        if (threadIdx.x == 0) __hip_atomic_store(arrived + b * ARRIVED_STRIDE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // The slice that the running sum passes u times the whole in, as draw_locate looks among wavefronts: every wavefront for
     // itself, 64 slices at a time
@@ -1126,7 +1126,7 @@ __global__ void __launch_bounds__(TPB) plain_slice_kernel(const int32_t* seq_row
                                                           const float* __restrict__ uniforms, int u_stride, int V, int Kmax,
                                                           float inv_T_f, int auto_rollback, int32_t* kv_len,
                                                           int32_t* __restrict__ n_accepted, int32_t* __restrict__ out_tokens,
-                                                          double* slice_mass, int32_t* arrived, StepTables t, DrawEmit emit, LogitsSrc src)
+                                                          double* slice_mass, StepTables t, DrawEmit emit, LogitsSrc src)
 {
     constexpr int RUNS = 2, WAVES = TPB / 64, SLICE = TPB * 4 * RUNS;
     __shared__ float s_max[WAVES];
@@ -1192,11 +1192,10 @@ __global__ void __launch_bounds__(TPB) plain_slice_kernel(const int32_t* seq_row
         __hip_atomic_store(parts + 2 * slice, (double)mp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(parts + 2 * slice + 1, (l.tot[0] + l.tot[1]) + (l.tot[2] + l.tot[3]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (they have arrived before they are counted)
-        s_last = __hip_atomic_fetch_add(arrived + b * ARRIVED_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_slices - 1;
+        s_last = __hip_atomic_fetch_add(t.arrived + b * ARRIVED_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_slices - 1;
     }
     __syncthreads();
     if (!s_last) return;
-    if (threadIdx.x == 0) __hip_atomic_store(arrived + b * ARRIVED_STRIDE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // (at most 64 slices: PLAIN_MAX)
     const bool in = lane < n_slices;
     const float mc = in ? (float)__hip_atomic_load(parts + 2 * lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -INFINITY;
@@ -2249,7 +2248,7 @@ int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const Lookahe
         if (V > PLAIN_MIN) {
             hipLaunchKernelGGL(from.partial ? plain_slice_kernel<true> : plain_slice_kernel<false>, dim3((V + 2047) / 2048, B), dim3(TPB), 0, s,
                                t.seq_row0, target_logits, uniforms, u_stride, V, Kmax, inv_T, auto_rollback, kv_len, n_accepted,
-                               out_tokens, w.slice_mass, w.arrived, t, em, from);
+                               out_tokens, w.slice_mass, t, em, from);
             SPECV_LAUNCH_CHECK("plain_slice_kernel");
             return SPEC_OK;
         }
@@ -2285,7 +2284,7 @@ int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const Lookahe
     const int runs = slice_runs(B, V), slices = (V + 1024 * runs - 1) / (1024 * runs);
     hipLaunchKernelGGL(runs == 2 ? accept_slice_kernel<2> : accept_slice_kernel<4>, dim3(slices, B), dim3(TPB), 0, s, t.seq_stat0, t.seq_row0,
                        draft_tokens, w.part_max, w.part_sum, Kmax, V, n_stat_chunks, u_stride, uniforms, target_logits, draft_logits, inv_T,
-                       auto_rollback, kv_len, n_accepted, out_tokens, w.slice_mass, w.arrived, t, em, ks);
+                       auto_rollback, kv_len, n_accepted, out_tokens, w.slice_mass, t, em, ks);
     SPECV_LAUNCH_CHECK("accept_slice_kernel");
     return SPEC_OK;
 }
@@ -2294,8 +2293,7 @@ int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const Lookahe
 
 // ---------------------------------------------------------------------------------------------
 // The sampling part of the verify step for callers that cannot allocate: no handle, no hipMalloc.
-// The row tables and the sampler's workspace (chunk statistics, chunk masses, per-sequence
-// scalars, the error flag) live in one device array of fixed size instead of a handle's arena.
+// The row tables and the sampler's workspace (chunk statistics, slice masses, the error flag) live in one device array of fixed size instead of a handle's arena.
 // ---------------------------------------------------------------------------------------------
 namespace specv {
 namespace {
@@ -2312,7 +2310,7 @@ struct NoAllocScratch {
     double slice_mass[(size_t)NA_MAX_BATCH * NA_RES_CHUNKS];
     float part_max[(size_t)NA_MAX_STAT * NA_STAT_CHUNKS];
     int32_t part_idx[(size_t)NA_MAX_STAT * NA_STAT_CHUNKS];
-    int32_t arrived[NA_MAX_BATCH * ARRIVED_STRIDE];   // zero between calls
+    int32_t arrived[NA_MAX_BATCH * ARRIVED_STRIDE];
     int32_t seq_row0[NA_MAX_BATCH + 1], seq_stat0[NA_MAX_BATCH + 1];
     int32_t seq_n[NA_MAX_BATCH], seq_ok[NA_MAX_BATCH], seq_slot[NA_MAX_BATCH];
     int32_t row_seq[NA_MAX_ROWS], row_pos[NA_MAX_ROWS], row_tok[NA_MAX_ROWS], row_rope[NA_MAX_ROWS];
@@ -2398,12 +2396,12 @@ extern "C" int spec_sample_step_noalloc(int32_t vocab, int32_t max_lookahead, co
     t.row_tok = w->row_tok;
     t.row_rope = w->row_rope;
     t.row_mask = w->row_mask;
+    t.arrived = w->arrived;
     t.tree = 0;
     SamplerWorkspace sw{};
     sw.part_max = w->part_max;
     sw.part_sum = w->part_sum;
     sw.slice_mass = w->slice_mass;
-    sw.arrived = w->arrived;
     sw.part_idx = w->part_idx;
     if (greedy) {   // the greedy rule's kernels read the tables from the start
         rc = launch_prepare(t, ks, B, Kmax, vocab, NA_MAX_BATCH, 0, false, nullptr, nullptr, args->draft_tokens, nullptr,

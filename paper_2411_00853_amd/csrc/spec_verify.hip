@@ -208,6 +208,7 @@ static int init_common(const spec_model_cfg* cfg, const spec_weights* weights, v
     A(&h->tables.row_tok, max_rows);
     A(&h->tables.row_rope, max_rows);
     A(&h->tables.row_mask, max_rows);
+    A(&h->tables.arrived, (size_t)B * ARRIVED_STRIDE);
     if (cfg->dtype == SPEC_DTYPE_BF16 && max_rows > GEMM_MAX_ROWS && weights) {
         // a step may need several decoder passes: tables for one pass's share
         StepTables& g = h->group_tables;
@@ -226,8 +227,6 @@ static int init_common(const spec_model_cfg* cfg, const spec_weights* weights, v
     A(&h->sampler.part_max, (size_t)max_stat * n_stat_chunks);
     A(&h->sampler.part_sum, (size_t)max_stat * n_stat_chunks);
     A(&h->sampler.slice_mass, slice_masses(B, cfg->vocab));
-    A(&h->sampler.arrived, B * ARRIVED_STRIDE);
-    if (rc == SPEC_OK && hipMemset(h->sampler.arrived, 0, (size_t)B * ARRIVED_STRIDE * sizeof(int32_t)) != hipSuccess) rc = fail(SPEC_ERR_DEVICE, "hipMemset failed");
     A(&h->sampler.part_idx, (size_t)max_stat * n_stat_chunks);
     if (rc == SPEC_OK && hipMemset(h->flag, 0, 16) != hipSuccess) rc = fail(SPEC_ERR_DEVICE, "hipMemset failed");
     if (rc == SPEC_OK && paged) {
