@@ -135,10 +135,18 @@ struct LogitsSrc {
 constexpr int STAT_CHUNK = 16384;   // logits per workgroup in the statistics pass
 constexpr int RES_CHUNK = 4096;    // logits per workgroup in the residual pass of many sequences (2048 for few)
 
+// What a sequence's accept scan leaves to the draw where that is a launch of its own
+struct DrawnRow {
+    double izp, izq;   // 1/Z of the two rows the draw reads (p, q)
+    float mp, mq;      // their maxima
+    int32_t a, pad;    // proposals kept
+};
+
 struct SamplerWorkspace {
     float* part_max;      // [stat rows][stat chunks] chunk maxima of raw logits
     double* part_sum;     // [stat rows][stat chunks] sum exp((l - chunk max)/T)
     double* slice_mass;   // [slice_masses(B, V)] mass of the final-draw distribution per sequence and slice of the vocabulary
+    DrawnRow* drawn;      // [B]
     int32_t* part_idx;    // [stat rows][stat chunks] greedy rule: lowest id holding the chunk maximum
 };
 

@@ -582,15 +582,15 @@ __device__ __forceinline__ void combine_rows(const float* part_max, const double
 }
 
 // ---------------------------------------------------------------------------------------------
-// Vocabularies of up to DRAW_MAX: one workgroup per sequence keeps the row (or the two rows) of the draw in registers, so
-// what the two passes above do -- and for a plain draw the statistics in front of them -- is one launch, without a second
-// read of the rows.  RUNS runs of 256 ids per wavefront: wavefront w holds ids [256 RUNS w, 256 RUNS (w + 1)), lane l of it
+// One workgroup per sequence keeps the row (or the two rows) of the draw in registers, so the accept scan, the mass and the draw -- for
+// a plain draw the statistics as well -- are one launch: plain draws of up to PLAIN_MIN ids, chains of up to SLICE_MIN and, in large
+// batches, DRAW_MAX (draw_route), trees of up to DRAW_MAX.  RUNS runs of 256 ids per wavefront: wavefront w holds ids [256 RUNS w, 256 RUNS (w + 1)), lane l of it
 // the ids 4 l .. 4 l + 3 of every run.
 // ---------------------------------------------------------------------------------------------
 constexpr int DRAW_TPB = 1024, DRAW_WAVES = DRAW_TPB / 64, DRAW_MAX_RUNS = 8;
 constexpr int DRAW_MAX = DRAW_WAVES * 256 * DRAW_MAX_RUNS;   // 32768
 static_assert(DRAW_WAVES <= 16, "the wavefronts' sums are scanned by 16 lanes");
-constexpr int SLICE_MIN = 16384;   // accept_slice_kernel beyond: 16000 and two sequences 13.5 us in one workgroup each, 13.9 shared out, 20000 and 64 29.2 and 26.9
+constexpr int SLICE_MIN = 16384;   // accept_slice_kernel beyond (draw_route): 16000 and two sequences 13.5 us in one workgroup each, 13.9 shared out, 20000 and 64 29.2 and 26.9
 constexpr int PLAIN_MIN = 16384, PLAIN_MAX = 64 * 2048;   // plain_slice_kernel: beyond the one, up to the other (a lane per slice)
 constexpr int STATS_MAX = 2048;                              // a row in a wavefront's registers
 inline int draw_runs(int V) { return V <= 4096 ? 1 : V <= 8192 ? 2 : V <= 16384 ? 4 : 8; }
@@ -598,7 +598,8 @@ typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // globa
 
 // four ids from id0 on of each of N runs of a row of V logits; past the end -inf.  WHOLE: where all of the wavefront's ids exist (id0 is
 // its first id plus four times the lane) nothing is shifted, which is a seventh of a mass's arithmetic (64 sequences of 100000 25.3 ->
-// 24.6 us); the tree's draw, whose registers are full, is better off without (a step of 88 rows 854 -> 868 us with it).
+// 24.6 us); the tree's draw, whose registers are full, is better off without (a step of 88 rows 854 -> 868 us with it), and rows in eight
+// runs have no use for it (128 registers for 95, the same time).
 template <bool WHOLE = true, int N>
 __device__ __forceinline__ void draw_load(const float* row, int V, int id0, floatx4 (&v)[N])
 {
@@ -752,7 +753,7 @@ __device__ __forceinline__ void draw_skip(const DrawEmit& emit, int b, int Kmax,
 }
 
 // After the statistics: accept scan, mass of the final draw's distribution, the draw, the results.  Rows of up to SLICE_MIN
-// logits; longer ones are shared out (accept_slice_kernel).  STATS: the statistics as well, a wavefront per row -- at most 31 rows of
+// logits, in large batches DRAW_MAX; others are shared out (accept_slice_kernel, draw_route).  STATS: the statistics as well, a wavefront per row -- at most 31 rows of
 // STATS_MAX logits, which one compute unit reads in the time that a launch takes (fp32 model of vocabulary 1024, one sequence of
 // five rows: 4.3 + 5.9 us as two launches, 7.8 as one).
 template <int RUNS, bool STATS>
@@ -799,7 +800,7 @@ __global__ void __launch_bounds__(DRAW_TPB) accept_draw_kernel(const int32_t* se
             const float* row = r <= K ? trow0 + (size_t)r * V : drow0 + (size_t)(r - K - 1) * V;
             constexpr int N = STATS_MAX / 256;
             floatx4 v[N];
-            draw_load(row, V, 4 * (threadIdx.x & 63), v);
+            draw_load<RUNS < 8>(row, V, 4 * (threadIdx.x & 63), v);
             float mx = -INFINITY;
 #pragma unroll
             for (int j = 0; j < N; ++j) mx = fmaxf(fmaxf(mx, fmaxf(v[j].x, v[j].y)), fmaxf(v[j].z, v[j].w));
@@ -847,16 +848,16 @@ __global__ void __launch_bounds__(DRAW_TPB) accept_draw_kernel(const int32_t* se
     double run[RUNS];
     {
         floatx4 p[RUNS], q[RUNS];
-        draw_load(prow, V, draw_id0<RUNS>(), p);
-        if (residual) draw_load(qrow, V, draw_id0<RUNS>(), q);
+        draw_load<RUNS < 8>(prow, V, draw_id0<RUNS>(), p);
+        if (residual) draw_load<RUNS < 8>(qrow, V, draw_id0<RUNS>(), q);
 #pragma unroll
         for (int j = 0; j < RUNS; ++j)
             run[j] = (mass(p[j].x, q[j].x) + mass(p[j].y, q[j].y)) + (mass(p[j].z, q[j].z) + mass(p[j].w, q[j].w));
     }
     auto four = [&](int j, double (&x)[4]) {   // (read again rather than kept: both rows are 64 registers)
         floatx4 p[1], q[1];
-        draw_load(prow, V, draw_id0<RUNS>() + 256 * j, p);
-        if (residual) draw_load(qrow, V, draw_id0<RUNS>() + 256 * j, q);
+        draw_load<RUNS < 8>(prow, V, draw_id0<RUNS>() + 256 * j, p);
+        if (residual) draw_load<RUNS < 8>(qrow, V, draw_id0<RUNS>() + 256 * j, q);
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[e] = mass(p[0][e], q[0][e]);
     };
@@ -864,12 +865,12 @@ __global__ void __launch_bounds__(DRAW_TPB) accept_draw_kernel(const int32_t* se
         __syncthreads();
         auto plain = [&](float lp) { return (double)__expf((lp - mp) * inv_T_f) * izp; };
         floatx4 p[RUNS];
-        draw_load(prow, V, draw_id0<RUNS>(), p);
+        draw_load<RUNS < 8>(prow, V, draw_id0<RUNS>(), p);
 #pragma unroll
         for (int j = 0; j < RUNS; ++j) run[j] = (plain(p[j].x) + plain(p[j].y)) + (plain(p[j].z) + plain(p[j].w));
         draw_locate<RUNS, DRAW_WAVES>(run, [&](int j, double (&x)[4]) {
             floatx4 p1[1];
-            draw_load(prow, V, draw_id0<RUNS>() + 256 * j, p1);
+            draw_load<RUNS < 8>(prow, V, draw_id0<RUNS>() + 256 * j, p1);
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[e] = plain(p1[0][e]);
         }, u_draw, true, l);
@@ -883,11 +884,110 @@ __global__ void __launch_bounds__(DRAW_TPB) accept_draw_kernel(const int32_t* se
 // cycles for a wavefront's 64: a row of 32000 in one workgroup of 1024 threads spent 4 to 5 us on them alone, and two
 // launches (masses, then draw) a launch and another chain of round trips.  The sampling part alone, us before and now: 4
 // sequences of 32003 16.4 -> 14.1, 8 of 32000 17.7 -> 14.2, 32 of 32000 19.7 -> 17.0, one of 128256 18.5 -> 13.9, 16 of 128256 29.0
-// -> 24.7, 64 of 128256 109.0 -> 107.9.  128 of 128256 stay where they were, 200 of 65536 lose 2 %.
+// -> 24.7, 64 of 128256 109.0 -> 107.9.
 //
 // No workgroup waits for another: each stores its mass with an atomic store at device scope, waits until that has arrived, and then
 // counts itself; the one that counts last sees all masses.  The row bookkeeping in front has set the count to zero.
+//
+// COUNTED = false: the masses only, slice_draw_kernel draws.  Where a launch has many workgroups per compute unit, the round trip of
+// the count is time that none of them can use (see draw_route).
+
+// The rows a draw takes its masses from, in slices of 1024 RUNS ids: p at temperature, less q where a proposal was rejected.
 template <int RUNS>
+struct SliceRows {
+    static constexpr int SLICE = TPB * 4 * RUNS;
+    const float *prow, *qrow;
+    double izp, izq;
+    float mp, mq, inv_T;
+    int V;
+
+    __device__ __forceinline__ double mass(float lp, float lq, bool with_q) const
+    {
+        const double pv = (double)__expf((lp - mp) * inv_T) * izp, qv = with_q ? (double)__expf((lq - mq) * inv_T) * izq : 0.0;
+        return pv > qv ? pv - qv : 0.0;
+    }
+    // a thread's sums of its four ids of every run of a slice
+    __device__ __forceinline__ void sums_of(int c, bool with_q, double (&run)[RUNS]) const
+    {
+        floatx4 p[RUNS], q[RUNS];
+        const int id0 = c * SLICE + draw_id0<RUNS>();
+        draw_load(prow, V, id0, p);
+        if (with_q) draw_load(qrow, V, id0, q);
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j)
+            run[j] = (mass(p[j].x, q[j].x, with_q) + mass(p[j].y, q[j].y, with_q)) + (mass(p[j].z, q[j].z, with_q) + mass(p[j].w, q[j].w, with_q));
+    }
+    __device__ __forceinline__ double total(const double (&run)[RUNS], DrawLds& l) const   // of the workgroup, the same for all threads
+    {
+        double sum = 0.0;
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j) sum += run[j];
+        sum = wave_sum(sum);
+        if ((threadIdx.x & 63) == 0) l.tot[threadIdx.x >> 6] = sum;
+        __syncthreads();
+        static_assert(TPB == 256, "four sums");
+        return (l.tot[0] + l.tot[1]) + (l.tot[2] + l.tot[3]);
+    }
+
+    // The id that u times the whole falls on, once the masses of all slices are there.  All threads of the workgroup call.
+    __device__ __forceinline__ int draw(const double* masses, int n_slices, bool residual, double u, DrawLds& l) const
+    {
+        const int lane = threadIdx.x & 63;
+        double run[RUNS];
+        // The slice that the running sum passes u times the whole in, as draw_locate looks among wavefronts: every wavefront for
+        // itself, 64 slices at a time
+        auto mass_of = [&](int c) { return c < n_slices ? __hip_atomic_load(masses + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0; };
+        const double first64 = mass_of(lane);
+        double S = 0.0;
+        for (int c0 = 0; c0 < n_slices; c0 += 64) S += wave_sum(c0 == 0 ? first64 : mass_of(c0 + lane));
+        int pick = -1;
+        bool with_q = residual;
+        double below = 0.0, goal = u * S;
+        if (S > 0.0) {
+            double before = 0.0;
+            for (int c0 = 0; c0 < n_slices; c0 += 64) {
+                const double m = c0 == 0 ? first64 : mass_of(c0 + lane), upto = before + wave_scan(m);
+                const unsigned long long over = __ballot(m > 0.0 && upto > goal), some = __ballot(m > 0.0);
+                if (over || some) {
+                    const int at = over ? __ffsll((long long)over) - 1 : 63 - __clzll((long long)some);
+                    pick = c0 + at;
+                    below = at > 0 ? read_lane(upto, at - 1) : before;
+                }
+                if (over) break;
+                before = read_lane(upto, 63);
+            }
+        } else {   // no mass left (impossible in exact arithmetic): draw from p_a, which sums to 1, slice by slice
+            with_q = false;
+            goal = u;
+            double before = 0.0;
+            for (int c = 0; c < n_slices; ++c) {
+                sums_of(c, false, run);
+                const double sum = total(run, l);
+                __syncthreads();
+                if (sum > 0.0 || pick < 0) {
+                    pick = c;
+                    below = before;
+                }
+                before += sum;
+                if (before > goal) break;
+            }
+        }
+        sums_of(pick, with_q, run);
+        __syncthreads();
+        // (ids of the slice; a row's end lies inside the last one)
+        draw_locate<RUNS, TPB / 64, true>(run, [&](int j, double (&m4)[4]) {
+            floatx4 p[1], q[1];
+            const int id0 = pick * SLICE + draw_id0<RUNS>() + 256 * j;
+            draw_load(prow, V, id0, p);
+            if (with_q) draw_load(qrow, V, id0, q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) m4[e] = mass(p[0][e], q[0][e], with_q);
+        }, goal, true, l, below);
+        return min(pick * SLICE + l.tok, V - 1);
+    }
+};
+
+template <int RUNS, bool COUNTED>
 __global__ void __launch_bounds__(TPB) accept_slice_kernel(const int32_t* seq_stat0, const int32_t* seq_row0,
                                                            const int32_t* __restrict__ draft_tokens,
                                                            const float* __restrict__ part_max,
@@ -897,17 +997,16 @@ __global__ void __launch_bounds__(TPB) accept_slice_kernel(const int32_t* seq_st
                                                            const float* __restrict__ target,
                                                            const float* __restrict__ draft, float inv_T_f, int auto_rollback,
                                                            int32_t* kv_len, int32_t* __restrict__ n_accepted,
-                                                           int32_t* __restrict__ out_tokens, double* slice_mass,
+                                                           int32_t* __restrict__ out_tokens, double* slice_mass, DrawnRow* drawn,
                                                            StepTables t, DrawEmit emit, LookaheadPack ks)
 {
-    constexpr int WAVES = TPB / 64, SLICE = TPB * 4 * RUNS;
     __shared__ float row_m[2 * SPEC_MAX_LOOKAHEAD + 2];
     __shared__ double row_z[2 * SPEC_MAX_LOOKAHEAD + 2];
     __shared__ int s_a, s_last;
     __shared__ double s_iz[2];
     __shared__ DrawLds l;
     __shared__ CombineLds comb;
-    const int b = blockIdx.y, slice = blockIdx.x, n_slices = gridDim.x, lane = threadIdx.x & 63;
+    const int b = blockIdx.y, slice = blockIdx.x, n_slices = gridDim.x;
     const int st0 = seq_stat0[b], row0 = seq_row0[b], ok = t.seq_ok[b], slot = t.seq_slot[b], n = t.seq_n[b];
     const int K = ks.k[b];
     const double inv_T = (double)inv_T_f;
@@ -926,9 +1025,9 @@ __global__ void __launch_bounds__(TPB) accept_slice_kernel(const int32_t* seq_st
         lp_x = xin ? trow0[(size_t)i * V + x] : 0.f;
         lq_x = xin ? drow0[(size_t)i * V + x] : 0.f;
     }
-    const double u_draw = (double)uniforms[b * u_stride + K];
+    const double u_draw = COUNTED ? (double)uniforms[b * u_stride + K] : 0.0;
     if (!ok) {
-        if (slice == 0) draw_skip(emit, b, Kmax, n_accepted, out_tokens);
+        if (COUNTED && slice == 0) draw_skip(emit, b, Kmax, n_accepted, out_tokens);
         return;
     }
     combine_rows<TPB>(part_max, part_sum, st0, 2 * K + 1, n_stat_chunks, inv_T, row_m, row_z, comb);
@@ -947,39 +1046,13 @@ __global__ void __launch_bounds__(TPB) accept_slice_kernel(const int32_t* seq_st
     __syncthreads();
     const int a = s_a;
     const bool residual = a < K;
-    const float mp = row_m[a], mq = residual ? row_m[K + 1 + a] : 0.f;
-    const double izp = s_iz[0], izq = s_iz[1];
-    const float* prow = trow0 + (size_t)a * V;            // a == K: the extra-token row
-    const float* qrow = drow0 + (size_t)(residual ? a : 0) * V;
-    auto mass = [&](float lp, float lq, bool with_q) {
-        const double pv = (double)__expf((lp - mp) * inv_T_f) * izp, qv = with_q ? (double)__expf((lq - mq) * inv_T_f) * izq : 0.0;
-        return pv > qv ? pv - qv : 0.0;
-    };
-    // a thread's sums of its four ids of every run of a slice
-    auto sums_of = [&](int c, bool with_q, double (&run)[RUNS]) {
-        floatx4 p[RUNS], q[RUNS];
-        const int id0 = c * SLICE + draw_id0<RUNS>();
-        draw_load(prow, V, id0, p);
-        if (with_q) draw_load(qrow, V, id0, q);
-#pragma unroll
-        for (int j = 0; j < RUNS; ++j)
-            run[j] = (mass(p[j].x, q[j].x, with_q) + mass(p[j].y, q[j].y, with_q)) + (mass(p[j].z, q[j].z, with_q) + mass(p[j].w, q[j].w, with_q));
-    };
-    auto total = [&](const double (&run)[RUNS]) {   // of the workgroup, the same for all threads
-        double sum = 0.0;
-#pragma unroll
-        for (int j = 0; j < RUNS; ++j) sum += run[j];
-        sum = wave_sum(sum);
-        if (lane == 0) l.tot[threadIdx.x >> 6] = sum;
-        __syncthreads();
-        static_assert(WAVES == 4, "four sums");
-        return (l.tot[0] + l.tot[1]) + (l.tot[2] + l.tot[3]);
-    };
+    const SliceRows<RUNS> rows{trow0 + (size_t)a * V,            // a == K: the extra-token row
+                               drow0 + (size_t)(residual ? a : 0) * V, s_iz[0], s_iz[1], row_m[a], residual ? row_m[K + 1 + a] : 0.f, inv_T_f, V};
     double* masses = slice_mass + (size_t)b * n_slices;
     double run[RUNS];
-    sums_of(slice, residual, run);
-    {
-        const double sum = total(run);
+    rows.sums_of(slice, residual, run);
+    const double sum = rows.total(run, l);
+    if constexpr (COUNTED) {
         if (threadIdx.x == 0) {
             __hip_atomic_store(masses + slice, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the mass has arrived before it is counted)
@@ -987,57 +1060,36 @@ __global__ void __launch_bounds__(TPB) accept_slice_kernel(const int32_t* seq_st
         }
         __syncthreads();
         if (!s_last) return;
+        const int y = rows.draw(masses, n_slices, residual, u_draw, l);
+        if (threadIdx.x < 64) draw_emit(t, emit, b, slot, n, K, Kmax, a, y, x, auto_rollback, kv_len, n_accepted, out_tokens);
+    } else if (threadIdx.x == 0) {
+        masses[slice] = sum;
+        if (slice == 0) drawn[b] = DrawnRow{rows.izp, rows.izq, rows.mp, rows.mq, a, 0};
     }
-    // The slice that the running sum passes u times the whole in, as draw_locate looks among wavefronts: every wavefront for
-    // itself, 64 slices at a time
-    auto mass_of = [&](int c) { return c < n_slices ? __hip_atomic_load(masses + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0; };
-    const double first64 = mass_of(lane);
-    double S = 0.0;
-    for (int c0 = 0; c0 < n_slices; c0 += 64) S += wave_sum(c0 == 0 ? first64 : mass_of(c0 + lane));
-    int pick = -1;
-    bool with_q = residual;
-    double below = 0.0, goal = u_draw * S;
-    if (S > 0.0) {
-        double before = 0.0;
-        for (int c0 = 0; c0 < n_slices; c0 += 64) {
-            const double m = c0 == 0 ? first64 : mass_of(c0 + lane), upto = before + wave_scan(m);
-            const unsigned long long over = __ballot(m > 0.0 && upto > goal), some = __ballot(m > 0.0);
-            if (over || some) {
-                const int at = over ? __ffsll((long long)over) - 1 : 63 - __clzll((long long)some);
-                pick = c0 + at;
-                below = at > 0 ? read_lane(upto, at - 1) : before;
-            }
-            if (over) break;
-            before = read_lane(upto, 63);
-        }
-    } else {   // no mass left (impossible in exact arithmetic): draw from p_a, which sums to 1, slice by slice
-        with_q = false;
-        goal = u_draw;
-        double before = 0.0;
-        for (int c = 0; c < n_slices; ++c) {
-            sums_of(c, false, run);
-            const double sum = total(run);
-            __syncthreads();
-            if (sum > 0.0 || pick < 0) {
-                pick = c;
-                below = before;
-            }
-            before += sum;
-            if (before > goal) break;
-        }
+}
+
+// The draw behind accept_slice_kernel<RUNS, false>: one workgroup per sequence, the bits of the other route.
+template <int RUNS>
+__global__ void __launch_bounds__(TPB) slice_draw_kernel(const int32_t* seq_row0, const double* slice_mass, const DrawnRow* drawn,
+                                                         const float* __restrict__ uniforms, int u_stride, int n_slices, int Kmax, int V,
+                                                         const float* __restrict__ target, const float* __restrict__ draft, float inv_T_f,
+                                                         int auto_rollback, int32_t* kv_len, const int32_t* __restrict__ draft_tokens,
+                                                         int32_t* __restrict__ n_accepted, int32_t* __restrict__ out_tokens, StepTables t,
+                                                         DrawEmit emit, LookaheadPack ks)
+{
+    __shared__ DrawLds l;
+    const int b = blockIdx.x, K = ks.k[b];
+    const int row0 = seq_row0[b], ok = t.seq_ok[b], slot = t.seq_slot[b], n = t.seq_n[b];
+    const int x = K > 0 ? draft_tokens[b * Kmax + min((int)threadIdx.x, K - 1)] : 0;
+    const double u = (double)uniforms[b * u_stride + K];
+    if (!ok) {
+        draw_skip(emit, b, Kmax, n_accepted, out_tokens);
+        return;
     }
-    sums_of(pick, with_q, run);
-    __syncthreads();
-    // (ids of the slice; a row's end lies inside the last one)
-    draw_locate<RUNS, WAVES, true>(run, [&](int j, double (&m4)[4]) {
-        floatx4 p[1], q[1];
-        const int id0 = pick * SLICE + draw_id0<RUNS>() + 256 * j;
-        draw_load(prow, V, id0, p);
-        if (with_q) draw_load(qrow, V, id0, q);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) m4[e] = mass(p[0][e], q[0][e], with_q);
-    }, goal, true, l, below);
-    if (threadIdx.x < 64) draw_emit(t, emit, b, slot, n, K, Kmax, a, min(pick * SLICE + l.tok, V - 1), x, auto_rollback, kv_len, n_accepted, out_tokens);
+    const DrawnRow d = drawn[b];
+    const SliceRows<RUNS> rows{target + (size_t)(row0 + d.a) * V, draft + ((size_t)b * Kmax + (d.a < K ? d.a : 0)) * V, d.izp, d.izq, d.mp, d.mq, inv_T_f, V};
+    const int y = rows.draw(slice_mass + (size_t)b * n_slices, n_slices, d.a < K, u, l);
+    if (threadIdx.x < 64) draw_emit(t, emit, b, slot, n, K, Kmax, d.a, y, x, auto_rollback, kv_len, n_accepted, out_tokens);
 }
 
 // A plain draw (no proposals): maximum, weights and draw of one row per sequence, which comes whole or as the LM head's
@@ -2214,9 +2266,31 @@ int launch_pool_cover(const PagePool& pool, int slot, int pos0, int pos1, int32_
     return SPEC_OK;
 }
 
-// Runs of 256 ids per wavefront of accept_slice_kernel: slices of 2048 ids while there are up to four workgroups per compute unit,
-// 4096 from there on (slice_masses has the room that this takes).
-static int slice_runs(int B, int V) { return (size_t)B * ((V + 2047) / 2048) <= 1024 ? 2 : 4; }
+// How a draw behind the statistics is launched.  Beyond SLICE_MIN ids by the workgroups that slices of 2048 ids would give, up to
+// four, five or eight per compute unit: from there on, a round trip for the count that every workgroup makes before it can leave costs more
+// than a launch.  The sampling part, us, as one workgroup per sequence, counted (slices of 2048, more than 1024 of them 4096) and
+// as two launches:
+//                                          no proposals           three proposals
+//    64 sequences of 32768 (1024 of 2048)  16.1  16.0  19.1       24.5  23.1  22.8
+//    80              32768 (1280)          16.5  16.8  20.1       27.2  28.0  26.5
+//   100              32768 (1600)          17.1  18.6  21.1       30.5  32.6  30.6
+//   256              32768 (4096)          25.4  32.1  29.2       55.7  63.2  59.8
+//    64              50257 (1600)           -    17.7  17.8        -    36.5  36.8
+//   100              40000 (2000)           -    20.1  21.2        -    36.3  36.4
+//   100              50257 (2500)           -    22.8  20.7        -    50.2  48.3
+//    24             128256 (1512)           -    16.6  16.0        -    29.5  29.0
+//    64             128256 (4032)           -    27.6  24.3        -    58.0  56.4
+//   256             128256 (16128)          -    89.0  63.0        -   203.5 182.4
+// (Two launches that combined the statistics in the first and walked the masses one by one in the second took 26.9 and 60.4 for 64
+// of 128256, 67.2 and 190.5 for 256.)
+enum DrawRoute { DRAW_ONE_WG, DRAW_COUNTED, DRAW_TWO_LAUNCHES };
+static DrawRoute draw_route(int B, int V, bool any_proposals)
+{
+    const long wgs = (long)B * ((V + 2047) / 2048);
+    if (V <= SLICE_MIN) return DRAW_ONE_WG;
+    if (V <= DRAW_MAX) return wgs < (any_proposals ? 1280 : 1024) ? DRAW_COUNTED : DRAW_ONE_WG;
+    return wgs < 2048 ? DRAW_COUNTED : DRAW_TWO_LAUNCHES;
+}
 
 int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const LookaheadPack& ks, int B, int Kmax,
                    int V, int n_stat_rows, const float* target_logits, const float* draft_logits,
@@ -2271,21 +2345,29 @@ int launch_sampler(const StepTables& t, const SamplerWorkspace& w, const Lookahe
     SPECV_LAUNCH_CHECK("stats_kernel");
     }
     ProfScope ps(prof, SPEC_PROF_SAMPLER_DRAW, s);
-    if (V <= SLICE_MIN && !emit) {
+    const int route = draw_route(B, V, n_stat_rows > B);
+    if (route == DRAW_ONE_WG && !emit) {
         const int runs = draw_runs(V);
         auto* k = stats_inside ? accept_draw_kernel<1, true> : runs == 1 ? accept_draw_kernel<1, false> : runs == 2 ? accept_draw_kernel<2, false>
-                                                              : accept_draw_kernel<4, false>;
+                  : runs == 4 ? accept_draw_kernel<4, false> : accept_draw_kernel<8, false>;
         hipLaunchKernelGGL(k, dim3(B), dim3(DRAW_TPB), 0, s, t.seq_stat0, t.seq_row0, draft_tokens, w.part_max,
                            w.part_sum, Kmax, V, n_stat_chunks, u_stride, uniforms, target_logits, draft_logits, inv_T, auto_rollback,
                            kv_len, n_accepted, out_tokens, t, ks);
         SPECV_LAUNCH_CHECK("accept_draw_kernel");
         return SPEC_OK;
     }
-    const int runs = slice_runs(B, V), slices = (V + 1024 * runs - 1) / (1024 * runs);
-    hipLaunchKernelGGL(runs == 2 ? accept_slice_kernel<2> : accept_slice_kernel<4>, dim3(slices, B), dim3(TPB), 0, s, t.seq_stat0, t.seq_row0,
-                       draft_tokens, w.part_max, w.part_sum, Kmax, V, n_stat_chunks, u_stride, uniforms, target_logits, draft_logits, inv_T,
-                       auto_rollback, kv_len, n_accepted, out_tokens, w.slice_mass, t, em, ks);
+    const bool counted = route == DRAW_COUNTED;
+    const int runs = counted && (long)B * ((V + 2047) / 2048) <= 1024 ? 2 : 4;   // (slice_masses has the room)
+    const int slices = (V + 1024 * runs - 1) / (1024 * runs);
+    auto* k = !counted ? accept_slice_kernel<4, false> : runs == 2 ? accept_slice_kernel<2, true> : accept_slice_kernel<4, true>;
+    hipLaunchKernelGGL(k, dim3(slices, B), dim3(TPB), 0, s, t.seq_stat0, t.seq_row0, draft_tokens, w.part_max, w.part_sum, Kmax, V,
+                       n_stat_chunks, u_stride, uniforms, target_logits, draft_logits, inv_T, auto_rollback, kv_len, n_accepted,
+                       out_tokens, w.slice_mass, w.drawn, t, em, ks);
     SPECV_LAUNCH_CHECK("accept_slice_kernel");
+    if (counted) return SPEC_OK;
+    hipLaunchKernelGGL(slice_draw_kernel<4>, dim3(B), dim3(TPB), 0, s, t.seq_row0, w.slice_mass, w.drawn, uniforms, u_stride, slices, Kmax, V,
+                       target_logits, draft_logits, inv_T, auto_rollback, kv_len, draft_tokens, n_accepted, out_tokens, t, em, ks);
+    SPECV_LAUNCH_CHECK("slice_draw_kernel");
     return SPEC_OK;
 }
 
@@ -2308,6 +2390,7 @@ constexpr int NA_RES_CHUNKS = (NA_MAX_VOCAB + RES_CHUNK - 1) / RES_CHUNK;
 struct NoAllocScratch {
     double part_sum[(size_t)NA_MAX_STAT * NA_STAT_CHUNKS];
     double slice_mass[(size_t)NA_MAX_BATCH * NA_RES_CHUNKS];
+    DrawnRow drawn[NA_MAX_BATCH];
     float part_max[(size_t)NA_MAX_STAT * NA_STAT_CHUNKS];
     int32_t part_idx[(size_t)NA_MAX_STAT * NA_STAT_CHUNKS];
     int32_t arrived[NA_MAX_BATCH * ARRIVED_STRIDE];
@@ -2402,6 +2485,7 @@ extern "C" int spec_sample_step_noalloc(int32_t vocab, int32_t max_lookahead, co
     sw.part_max = w->part_max;
     sw.part_sum = w->part_sum;
     sw.slice_mass = w->slice_mass;
+    sw.drawn = w->drawn;
     sw.part_idx = w->part_idx;
     if (greedy) {   // the greedy rule's kernels read the tables from the start
         rc = launch_prepare(t, ks, B, Kmax, vocab, NA_MAX_BATCH, 0, false, nullptr, nullptr, args->draft_tokens, nullptr,

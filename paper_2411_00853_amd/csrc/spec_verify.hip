@@ -227,6 +227,7 @@ static int init_common(const spec_model_cfg* cfg, const spec_weights* weights, v
     A(&h->sampler.part_max, (size_t)max_stat * n_stat_chunks);
     A(&h->sampler.part_sum, (size_t)max_stat * n_stat_chunks);
     A(&h->sampler.slice_mass, slice_masses(B, cfg->vocab));
+    A(&h->sampler.drawn, B);
     A(&h->sampler.part_idx, (size_t)max_stat * n_stat_chunks);
     if (rc == SPEC_OK && hipMemset(h->flag, 0, 16) != hipSuccess) rc = fail(SPEC_ERR_DEVICE, "hipMemset failed");
     if (rc == SPEC_OK && paged) {
