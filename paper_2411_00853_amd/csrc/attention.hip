@@ -107,17 +107,18 @@ __global__ void __launch_bounds__(64) attn_merge_kernel(StepTables t, LookaheadP
 // is rotated here, and so are the keys of the window, which every row that sees them rotates for itself; the workgroup of a kv
 // head's first query head puts its own row's key and value into the cache, which this launch reads below the window only.
 // LP lanes share a position (four dims each), so keys and values are read in contiguous runs, U positions per group in flight, whose
-// sums over the lanes go step by step side by side; the first U values and the window are requested with the keys.  Latency: round
-// trips to memory and across lanes.  With a rotary/append kernel in front (2.8 us), four positions in flight and the values only
-// after the softmax: steps of two layers, four 64-dim heads, one sequence of 128 positions and five rows 61.9 -> 56.8 us, 1000
-// positions and one row 86.1 -> 76.1, six of 1024 and 48 rows 141.7 -> 126.8.
+// sums over the lanes go step by step side by side; the window and (AHEAD) the first U values are requested with the keys.  Latency:
+// round trips to memory and across lanes, until a launch has more workgroups than fit (see f32_positions).  U = 8 and AHEAD against a
+// rotary/append kernel in front (2.8 us), four positions in flight and the values only after the softmax: steps of two layers, four
+// 64-dim heads, one sequence of 128 positions and five rows 61.9 -> 56.8 us, 1000 positions and one row 86.1 -> 76.1, six of 1024 and 48
+// rows 141.7 -> 126.8.
 // (That kernel, per launch of 20 (row, head) pairs at 133 and 1029 positions: 7.2 and 29.6 us; a thread per key, and one per dim
 // walking all values, 9.4 and 80; the number of lanes a run-time value, each sum over the lanes a rolled loop of its own, 10.8 and 41.)
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-template <int LP>
-__global__ void __launch_bounds__(256) attn_f32_kernel(const float* __restrict__ qkv, const float* __restrict__ cos_sin, float* cache,
-                                                       float* __restrict__ out, int n_q_heads, int layer, int ld, float scale,
-                                                       StepTables t, CacheGeom g)
+template <int LP, int U, bool AHEAD>
+__global__ void __launch_bounds__(256, U == 2 ? 8 : 1)   // (two positions are for eight workgroups on a compute unit)
+attn_f32_kernel(const float* __restrict__ qkv, const float* __restrict__ cos_sin, float* cache, float* __restrict__ out, int n_q_heads,
+                int layer, int ld, float scale, StepTables t, CacheGeom g)
 {
     extern __shared__ float4 dyn[];
     __shared__ float red[4];
@@ -179,8 +180,8 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(const float* __restrict__
         return make_float4(r[0], r[1], r[2], r[3]);
     };
     auto turn_of = [&](int w) { return t.tree ? t.row_rope[row0 + w] : n_cached + w; };   // depth in the window, not the slot
-    constexpr int U = 8;   // positions per group and trip, requested together (past the end: the last one again)
-    float4 v0[U];
+    // U positions per group and trip, requested together (past the end: the last one again)
+    float4 v0[AHEAD ? U : 1];
     const int last = max(n_cached - 1, 0);
     const float4 qv = turned4(qkv + (size_t)m * ld + hq * hd, turn_of(window - 1));
     // the window's positions of this group (position k belongs to group k % n_grp), in registers from here on
@@ -206,7 +207,7 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(const float* __restrict__
         float4 kv[U];
 #pragma unroll
         for (int i = 0; i < U; ++i) kv[i] = load4(kbase + (size_t)min(k0 + i * n_grp, last) * hd);
-        if (first) {
+        if (AHEAD && first) {
 #pragma unroll
             for (int i = 0; i < U; ++i) v0[i] = load4(vbase + (size_t)min(k0 + i * n_grp, last) * hd);
         }
@@ -277,9 +278,11 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(const float* __restrict__
         o4.z = on ? fmaf(p, v.z, o4.z) : o4.z;
         o4.w = on ? fmaf(p, v.w, o4.w) : o4.w;
     };
+    if constexpr (AHEAD) {
 #pragma unroll
-    for (int i = 0; i < U; ++i) add(grp + i * n_grp < n_cached ? sc[grp + i * n_grp] : 0.f, v0[i]);
-    for (int k0 = grp + U * n_grp; k0 < n_cached; k0 += U * n_grp) {
+        for (int i = 0; i < U; ++i) add(grp + i * n_grp < n_cached ? sc[grp + i * n_grp] : 0.f, v0[i]);
+    }
+    for (int k0 = AHEAD ? grp + U * n_grp : grp; k0 < n_cached; k0 += U * n_grp) {
         float4 vv[U];
         float p[U];
 #pragma unroll
@@ -532,6 +535,35 @@ bool attention_takes_qkv(const CacheGeom& g, int n_q_heads, const LookaheadPack&
     return lp.p.chunk_keys >= FUSED_MIN_KEYS;
 }
 
+// Lanes of attn_f32_kernel that share a position, four dims each (head_dim <= 256: spec_verify_init sees to it)
+static int f32_lanes(int hd)
+{
+    int lp = 1;
+    while (4 * lp < hd) lp *= 2;
+    return lp;
+}
+
+// Positions that a group of lanes of attn_f32_kernel requests together.  Eight, with the first values ahead, while four workgroups to a
+// compute unit are all there are: they take 113 registers (64-dim heads), and the scores of slots from some 8000 positions on leave room
+// for no more either.  Beyond, more workgroups resident: four positions, and two from 16 workgroups to a compute unit on.
+// Steps of two layers, us with a rotary/append kernel in front and four positions, with eight, four and two (1024 workgroups are four to
+// a compute unit):
+//   positions   4 heads of 64, 1024   8 of 64, 2 kv heads, 2048    the same, 8192 (4000: 4096)   2 of 128, 2048     2 of 256, 1024
+//       8         98   96   93   91       123 127 117 115            251  286  248  244          161 173 162 159    151 162 151 155
+//     100        104  101   98   99       128 128 122 123            271  294  269  271          187 192 184 183    173 193 172 181
+//     400        125  123  118  121       155 162 148 148            446  455  438  421          273 270 274 264    259 295 258 264
+//    1000        166  160  158  165       220 218 218 209            870  780  879  759          481 450 486 453    450 519 440 451
+//    4000         -                       676 629 719  -            1666 1333 1711 1284            -                  -
+// Between, two positions lose where the last few workgroups start alone: 8 heads of 64 dims, 2176 workgroups, 1000 and 2500 positions 311
+// 297 308 324 and 602 558 581 653; and four against eight where these come out even (2048 workgroups of long slots, up to 16 %).
+constexpr size_t LDS_BYTES = 160 * 1024;   // of a compute unit
+static int f32_positions(int hd, long wgs, size_t lds, int cu_count)
+{
+    const bool few = hd > 128 ? wgs <= 2L * cu_count : hd > 64 ? wgs < 4L * cu_count : wgs <= 4L * cu_count;
+    if (few || 5 * lds > LDS_BYTES) return 8;
+    return hd <= 128 && wgs >= 16L * cu_count && 8 * lds <= LDS_BYTES ? 2 : 4;
+}
+
 int launch_attention(int max_kv_len, int cu_count, const StepTables& t, const LookaheadPack& ks, int B, int M, const CacheGeom& g,
                      int n_q_heads, int layer, const void* cache, const float* q, float* part_o, float* part_ml,
                      size_t part_cap, const XOut& xo, int max_window, Profiler* prof, hipStream_t s, const QkvSrc* qkv,
@@ -546,16 +578,29 @@ int launch_attention(int max_kv_len, int cu_count, const StepTables& t, const Lo
         // scores for one row live in LDS: positions * 4 bytes
         if ((size_t)(hd + g.t_pad) * sizeof(float) > 60 * 1024) return fail(SPEC_ERR_SHAPE, "fp32 attention supports max_kv_len up to ~15000");
         ProfScope ps(prof, SPEC_PROF_ATTENTION, s);
-#define SPECV_ATTN_F32(LP)                                                                                         \
-    hipLaunchKernelGGL(attn_f32_kernel<LP>, dim3(M, n_q_heads), dim3(256), (size_t)(16 * LP + g.t_pad) * sizeof(float), s, src.partial, \
-                       src.cos_sin, (float*)cache_w, xo.plain, n_q_heads, layer, src.ld, scale, t, g)
-        if (hd <= 4) SPECV_ATTN_F32(1);
-        else if (hd <= 8) SPECV_ATTN_F32(2);
-        else if (hd <= 16) SPECV_ATTN_F32(4);
-        else if (hd <= 32) SPECV_ATTN_F32(8);
-        else if (hd <= 64) SPECV_ATTN_F32(16);
-        else if (hd <= 128) SPECV_ATTN_F32(32);
-        else SPECV_ATTN_F32(64);   // head_dim <= 256: spec_verify_init sees to it
+        const size_t lds = (size_t)(16 * f32_lanes(hd) + g.t_pad) * sizeof(float);
+        const int u = f32_positions(hd, (long)M * n_q_heads, lds, cu_count);
+#define SPECV_F32(LP, U)                                                                                                     \
+    hipLaunchKernelGGL((attn_f32_kernel<LP, U, U == 8>), dim3(M, n_q_heads), dim3(256), lds, s, src.partial, src.cos_sin,    \
+                       (float*)cache_w, xo.plain, n_q_heads, layer, src.ld, scale, t, g)
+#define SPECV_ATTN_F32(LP)                 \
+    case LP:                               \
+        if (u == 8) SPECV_F32(LP, 8);      \
+        else if (u == 4) SPECV_F32(LP, 4); \
+        else SPECV_F32(LP, 2);             \
+        break
+        switch (f32_lanes(hd)) {
+            SPECV_ATTN_F32(1);
+            SPECV_ATTN_F32(2);
+            SPECV_ATTN_F32(4);
+            SPECV_ATTN_F32(8);
+            SPECV_ATTN_F32(16);
+            SPECV_ATTN_F32(32);
+        default:
+            if (u == 8) SPECV_F32(64, 8);
+            else SPECV_F32(64, 4);
+        }
+#undef SPECV_F32
 #undef SPECV_ATTN_F32
         SPECV_LAUNCH_CHECK("attn_f32_kernel");
         return SPEC_OK;
