@@ -293,8 +293,11 @@ extern "C" int spec_decode_round(spec_decoder* d, const spec_round_args* args, v
             const int rows = (i == 0 ? 2 : 1) * B;
             EmbedTo embed;
             const bool embeds = forward_embeds(dr, rows, &embed);
-            rc = launch_prepare(dr->tables, ks, B, d->Kd, V, dr->cfg.max_batch, dr->cfg.max_kv_len, true, d->seq_slot,
-                                i == 0 ? d->prev_tok : d->cur_tok, d->win, dr->kv_len, dr->flag, s, embeds ? &embed : nullptr);
+            {
+                ProfScope ps(&dr->prof, SPEC_PROF_PREPARE, s);
+                rc = launch_prepare(dr->tables, ks, B, d->Kd, V, dr->cfg.max_batch, dr->cfg.max_kv_len, true, d->seq_slot,
+                                    i == 0 ? d->prev_tok : d->cur_tok, d->win, dr->kv_len, dr->flag, s, embeds ? &embed : nullptr);
+            }
             if (rc) return rc;
             LogitsSrc src{};
             rc = forward_run_grouped(dr, ks, B, rows, dr->logits, s, greedy ? nullptr : &src, embeds);
@@ -329,8 +332,11 @@ extern "C" int spec_decode_round(spec_decoder* d, const spec_round_args* args, v
     }
     EmbedTo embed;
     const bool embeds = forward_embeds(tg, M, &embed);
-    rc = launch_prepare(tg->tables, ks, B, Kt, V, tg->cfg.max_batch, tg->cfg.max_kv_len, true, d->seq_slot, d->last_tok,
-                        d->draft_tokens, tg->kv_len, tg->flag, s, embeds ? &embed : nullptr);
+    {
+        ProfScope ps(&tg->prof, SPEC_PROF_PREPARE, s);
+        rc = launch_prepare(tg->tables, ks, B, Kt, V, tg->cfg.max_batch, tg->cfg.max_kv_len, true, d->seq_slot, d->last_tok,
+                            d->draft_tokens, tg->kv_len, tg->flag, s, embeds ? &embed : nullptr);
+    }
     if (rc) return rc;
     LogitsSrc src{};
     rc = forward_run_grouped(tg, ks, B, M, tg->logits, s, greedy ? nullptr : &src, embeds);
