@@ -27,8 +27,8 @@
  *    per-sequence lookaheads and rollback lengths are host values and are frozen into the recording.
  *  - Host-checkable arguments are validated before anything is launched.  Conditions that depend
  *    on device data (kv_len + K + 1 > max_kv_len, token id >= vocab, rollback beyond the current
- *    length) make the affected sequence a no-op (its n_accepted is written as -1), raise a flag
- *    in the handle and are reported by spec_verify_poll.
+ *    length) make the affected sequence a no-op (its n_accepted is written as -1; what its rows of
+ *    logits_out hold is unspecified), raise a flag in the handle and are reported by spec_verify_poll.
  */
 #ifndef SPEC_VERIFY_H
 #define SPEC_VERIFY_H

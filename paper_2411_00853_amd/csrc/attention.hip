@@ -485,13 +485,15 @@ static AttnLaunchPlan plan_launch(const CacheGeom& g, bool paged, int n_q_heads,
     //  * 64-dim heads, a block of which is half as long to stream: 250 to 900 positions -2..-6 %, 1400 to 2500 -4..-9; short
     //    slots of the small-launch plan -3..-5
     //  * beyond 1024 positions, 128-dim heads too (9 to 16 chunks of 128 before): 1400 positions -3..-4.5 % at the 7B shape, -6..-9 with
-    //    8 heads of a 1024 wide model, 2500 positions -2..-5
+    //    8 heads of a 1024 wide model, 2500 positions -2..-5.  Up to 8 rows: 88 steps of four layers, 1 to 16 heads of their own, 1 to
+    //    23 sequences, -2.8 % on average, +2.4 at most; 9 to 12 rows, 72 of them, 0 on average, -5.6..+6.7 and most of the losses
+    //    at 1300 to 2400 positions (5 sequences of 7 heads, 10 rows, 1053 to 2106 positions: a step of one layer 90.0 -> 94.7 us)
     //  * up to 384 positions with single rows, or where one or two chunks still give a quarter of the compute units a
     //    workgroup: 7B shape 8 x 300 positions -2.5 %, 32 x 48 -2; 32 prompts of 64, 352 rows -2.2 (one chunk per pair: no
     //    wavefront repeats another's queries, the kernel in front took 20 us a layer)
     // Between 384 and 1024 positions of 128-dim heads it loses (8 heads, one sequence at 550: +2.5..+6 %) and is not made.
     if (own && lp.p.chunk_keys < FUSED_MIN_KEYS && fused_fits(g.head_dim, rt)
-        && (g.head_dim == 64 || lp.small || max_kv_len > 1024 || (max_kv_len <= 2 * FUSED_MIN_KEYS && (kmax == 0 || 4 * pairs >= cu_count))))
+        && (g.head_dim == 64 || lp.small || (max_kv_len > 1024 && rows <= 8) || (max_kv_len <= 2 * FUSED_MIN_KEYS && (kmax == 0 || 4 * pairs >= cu_count))))
         cut(FUSED_MIN_KEYS);
     // Two blocks: measured over 0..128 positions, 7B-shape paged step 5.04 -> 4.95 ms, decoding round 6.69 -> 6.62 ms,
     // contiguous 7B-shape, tree and long-context steps 0.2-0.7 % shorter, nothing longer (32 and 96 positions, an

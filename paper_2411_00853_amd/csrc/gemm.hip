@@ -673,6 +673,9 @@ __global__ void __launch_bounds__(512, 1) gemm_ring_kernel(const char* __restric
     __shared__ u32x4 lds[S * ST * 64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     // Wavefronts i and i + 4 share a SIMD: they take different halves, so that an odd number of row tiles loads all SIMDs alike.
+    // The halves of an odd number run two instantiations of `run` and meet in barriers of both: the hardware counts wavefronts, not
+    // places in the code, and either half comes to as many -- one before the first stage, one a stage, and with SWIGLU two for
+    // each of the ceil(G0 / GP) passes, also where the shorter half has no tile left.
     const int half = (MT % 2 ? wave ^ (wave >> 2) : wave) & 1, a0 = half * G0, group = wave >> 1;
     // row blocks of the same columns follow each other on one XCD (map_block's order otherwise): the second reads W from its L2
     const int x = blockIdx.x & 7, j = blockIdx.x >> 3;

@@ -884,10 +884,12 @@ __global__ void __launch_bounds__(DRAW_TPB) accept_draw_kernel(const int32_t* se
 // cycles for a wavefront's 64: a row of 32000 in one workgroup of 1024 threads spent 4 to 5 us on them alone, and two
 // launches (masses, then draw) a launch and another chain of round trips.  The sampling part alone, us before and now: 4
 // sequences of 32003 16.4 -> 14.1, 8 of 32000 17.7 -> 14.2, 32 of 32000 19.7 -> 17.0, one of 128256 18.5 -> 13.9, 16 of 128256 29.0
-// -> 24.7, 64 of 128256 109.0 -> 107.9.
+// -> 24.7.
 //
 // No workgroup waits for another: each stores its mass with an atomic store at device scope, waits until that has arrived, and then
-// counts itself; the one that counts last sees all masses.  The row bookkeeping in front has set the count to zero.
+// counts itself; the one that counts last sees all masses.  The row bookkeeping in front has set the count to zero.  The accesses are
+// relaxed (a release would write back the XCD's whole L2); what orders them is gfx950's own: vmcnt counts stores, which leave it
+// when they have arrived where they are visible, and accesses at device scope pass the XCD's L2 in both directions.
 //
 // COUNTED = false: the masses only, slice_draw_kernel draws.  Where a launch has many workgroups per compute unit, the round trip of
 // the count is time that none of them can use (see draw_route).
@@ -1055,7 +1057,7 @@ __global__ void __launch_bounds__(TPB) accept_slice_kernel(const int32_t* seq_st
     if constexpr (COUNTED) {
         if (threadIdx.x == 0) {
             __hip_atomic_store(masses + slice, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the mass has arrived before it is counted)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the mass has arrived before it is counted: see above)
             s_last = __hip_atomic_fetch_add(t.arrived + b * ARRIVED_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_slices - 1;
         }
         __syncthreads();
@@ -1243,7 +1245,7 @@ __global__ void __launch_bounds__(TPB) plain_slice_kernel(const int32_t* seq_row
     if (threadIdx.x == 0) {
         __hip_atomic_store(parts + 2 * slice, (double)mp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(parts + 2 * slice + 1, (l.tot[0] + l.tot[1]) + (l.tot[2] + l.tot[3]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (they have arrived before they are counted)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (they have arrived before they are counted: see accept_slice_kernel)
         s_last = __hip_atomic_fetch_add(t.arrived + b * ARRIVED_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_slices - 1;
     }
     __syncthreads();
@@ -1531,11 +1533,12 @@ __global__ void __launch_bounds__(TPB) prepare_tree_kernel(StepTables t, Lookahe
 // ---------------------------------------------------------------------------------------------
 // The row bookkeeping and the embedding in one launch: the first workgroup does the one, a wavefront per (row, SSQ_CHUNK
 // columns) of the others the other, which has no need of the tables.  The embedding of a few rows and the bookkeeping take a
-// launch and two or three round trips each, one behind the other before (a step of the fp32 configuration 65.9 -> 63.8 us, draft
-// decode of 8 rows 289.3 -> 288.1, 1B shape, 32 sequences 514 -> 510, decoding round 2177 -> 2167, 7B shape, 352 rows 1460 -> 1455).
+// launch and two or three round trips each, one behind the other before: a step of the fp32 configuration 65.9 -> 63.8 us, draft
+// decode of 8 rows 289.3 -> 288.1; the same 2 us or so of longer steps are less than their runs differ.
 // A row of a sequence that the bookkeeping skips embeds token 0, as from the tables, so every wavefront looks at its
 // sequence for itself: slot, cached length, tokens, parents.  (A page pool that runs dry is only seen by the
-// bookkeeping: those rows embed their tokens, and nothing reads what becomes of them.)
+// bookkeeping: those rows embed their tokens.  The caller may see what becomes of them in logits_out, where a skipped
+// sequence's rows are unspecified; nothing else reads it.)
 // ---------------------------------------------------------------------------------------------
 struct RowPack {
     uint16_t r[EMBED_MAX_ROWS];   // 16 * sequence + place in its window

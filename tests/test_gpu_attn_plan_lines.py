@@ -1,6 +1,7 @@
 """Where the attention's plan changes between longer chunks without a kernel in front and the general one: query rows per item (12 and 13
-of 128-dim heads, 32 and 33 of 64-dim heads, 16 and 18 where items share a head) and 128-dim pairs for four wavefronts per compute unit.
-The plan on both sides, and the logits of both sides against the oracle, contiguous and on a page pool."""
+of 128-dim heads, 8 and 9 beyond 1024 positions, 32 and 33 of 64-dim heads, 16 and 18 where items share a head) and 128-dim pairs for
+four wavefronts per compute unit.  The plan on both sides, and the logits of both sides against the oracle, contiguous and on a page
+pool."""
 import pytest
 import torch
 
@@ -8,7 +9,7 @@ from paper_2411_00853_amd import binding as sv
 from paper_2411_00853_amd import workload as wl
 
 # head_dim, query heads, kv heads, capacity, sequences, lookahead; inside the rule
-LINES = [(128, 2, 2, 300, 3, 11, 1), (128, 2, 2, 300, 3, 12, 0), (128, 2, 2, 1500, 3, 11, 1), (128, 2, 2, 1500, 3, 12, 0),
+LINES = [(128, 2, 2, 300, 3, 11, 1), (128, 2, 2, 300, 3, 12, 0), (128, 2, 2, 1500, 3, 7, 1), (128, 2, 2, 1500, 3, 8, 0),
          (64, 32, 8, 300, 5, 7, 1), (64, 33, 11, 300, 3, 10, 0), (64, 16, 2, 300, 9, 7, 1), (64, 16, 2, 300, 9, 8, 0),
          (128, 32, 32, 64, 32, 0, 1), (128, 32, 32, 64, 33, 0, 0)]
 V, D = 131, 256
