@@ -460,7 +460,8 @@ static AttnLaunchPlan plan_launch(const CacheGeom& g, bool paged, int n_q_heads,
     // Both rules below are for few query rows: a wavefront finishes an item's queries and the window by itself, and where several
     // items share a cache head each of them finishes the window's keys and values again.  Steps of two layers up to 330 positions,
     // without this line: 64-dim heads, 52 rows an item +0.5..+5 %, 32 rows -2..-7; 128-dim heads, 16 rows of a shared head
-    // +4..+12 %, 26 and 52 rows +1..+7, 13 to 16 of a head of their own -3..+3.5, 12 rows -4..-1.
+    // +4..+12 %, 26 and 52 rows +1..+7, 13 to 16 of a head of their own -3..+3.5, 9 to 12 rows (143 steps up to 550 positions) -8.5..+5.1,
+    // -0.7 on average, up to 8 (68 steps) -21..+1, -6.6 on average.
     // And for 128-dim heads only while their wavefronts, one to a SIMD, are all resident: 1056 pairs 0..+1.4 %, 840 -3.5.
     const int rows = (kmax + 1) * (group / lp.share);
     const bool few_rows = g.head_dim == 64 ? rows <= (lp.share > 1 ? 16 : 32) : lp.share == 1 && rows <= 12 && pairs <= 4L * cu_count;
