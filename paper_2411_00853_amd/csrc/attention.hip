@@ -180,7 +180,8 @@ attn_f32_kernel(const float* __restrict__ qkv, const float* __restrict__ cos_sin
         return make_float4(r[0], r[1], r[2], r[3]);
     };
     auto turn_of = [&](int w) { return t.tree ? t.row_rope[row0 + w] : n_cached + w; };   // depth in the window, not the slot
-    // U positions per group and trip, requested together (past the end: the last one again)
+    // U positions per group and trip, requested together (past the end: the last one again; of an empty cache the first entry, which
+    // another workgroup may be writing: nothing is made of what is read)
     float4 v0[AHEAD ? U : 1];
     const int last = max(n_cached - 1, 0);
     const float4 qv = turned4(qkv + (size_t)m * ld + hq * hd, turn_of(window - 1));
