@@ -38,3 +38,22 @@ def test_no_proposals(V, B, noalloc):
     # exponentials in fp32, 2 ulp each, sums in fp64: edges move by 3e-7 of the whole
     assert (own > 0).all() and (hi - own - 1e-6 <= at).all() and (at <= hi + 1e-6).all()
     if not noalloc: h.close()
+
+
+@pytest.mark.parametrize("B", [31, 32])
+def test_proposals_from_large_vocabularies(B):
+    """The draft's draws of a decoding round beyond the plain draw's longest row, counted (2015 slices) and as two launches (2080)."""
+    from test_gpu_decode import Pair
+    V, K = 131073, 2
+    shape = wl.ModelShape(1, 64, 1, 1, 64, 64, V, dtype="bf16")
+    rng = wl.Rng(B, "cpu")
+    pair = Pair(shape, shape, [rng.randint(b, (3 + b % 3,), V).tolist() for b in range(B)], 40, K, 20, std=0.1)
+    du, vu = rng.uniform(100, (B, K)), rng.uniform(101, (B, K + 1))
+    du[0, 0], du[1, 1] = 0.0, 1 - 2 ** -24
+    g = pair.round(K, du, vu, 1.0)
+    p = torch.softmax(g["draft_logits"].double(), 2)
+    cdf, y = p.cumsum(2), g["draft_tokens"].long().unsqueeze(2)
+    at, hi, own = du.double() * cdf[:, :, -1], cdf.gather(2, y)[:, :, 0], p.gather(2, y)[:, :, 0]
+    # exponentials in fp32, 2 ulp each, sums in fp64: edges move by 3e-7 of the whole
+    assert (own > 0).all() and (hi - own - 1e-6 <= at).all() and (at <= hi + 1e-6).all()
+    assert (g["n_accepted"] >= 0).all()
